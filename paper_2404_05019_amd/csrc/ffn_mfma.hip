@@ -89,6 +89,14 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   int nk = nk_all;                         // k-tiles of the current item
 
   // ---- per-lane source addresses of the direct-to-LDS loads -------------------------------
+  // First row of the tile that this wave's A load i fills (RPL rows): the first half of the
+  // loads covers the first halves of the wave tiles (rows 0 .. TM/2-1 of each), the second half
+  // the second halves.
+  auto a_block = [&](int i) {
+    constexpr int H = CFG::A_PER_WAVE / 2, HALF = CFG::TM / 2;
+    const int q = (wave * H + i % H) * CFG::RPL;                // row among the rows of that half
+    return (q / HALF) * CFG::TM + (i / H) * HALF + q % HALF;
+  };
   // OFF32 (both operands span less than 4 GiB, checked on the host): an address is a
   // wave-uniform 64-bit base plus a 32-bit per-lane offset, which the load takes as scalar
   // base + vector offset: one register per load and no vector address arithmetic between
@@ -111,7 +119,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     wbase = We;
 #pragma unroll
     for (int i = 0; i < CFG::A_PER_WAVE; ++i) {
-      const int row = (wave * CFG::A_PER_WAVE + i) * CFG::RPL + lane / CPR;
+      const int row = a_block(i) + lane / CPR;
       const int kc = (lane % CPR) ^ swz<CPR>(row);
       int m = row0 + row;
       if (m > row_end - 1) m = row_end - 1;      // rows past the segment re-read its last row
@@ -129,22 +137,29 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       else bptr[i] = We + static_cast<int64_t>(n) * ldw * 2 + kc * 16;
     }
   };
-  auto issue_loads = [&](int kt, int stage) {
-    unsigned char* sa = smem + stage * STAGE + wave * CFG::A_PER_WAVE * 1024;
-    unsigned char* sb = smem + stage * STAGE + A_BYTES + wave * CFG::B_PER_WAVE * 1024;
+  // The copies of a k-tile come in two groups: W and the first half of every wave tile's rows
+  // (W_A0), and the second half of those rows (A1).
+  constexpr int A1_LPW = CFG::A_PER_WAVE / 2;                   // loads per wave of the group A1
+  auto issue_a = [&](int kt, int stage, auto half_c) {
+    constexpr int h = decltype(half_c)::value;
     const unsigned char* ak = abase + static_cast<int64_t>(kt) * RB;
-    const unsigned char* wk = wbase + static_cast<int64_t>(kt) * RB;
-    if constexpr (OFF32) asm volatile("" : "+s"(ak), "+s"(wk));   // the scalar sums stay scalar
+    if constexpr (OFF32) asm volatile("" : "+s"(ak));           // the scalar sum stays scalar
 #pragma unroll
-    for (int i = 0; i < CFG::A_PER_WAVE; ++i) {
+    for (int i = h * A1_LPW; i < (h + 1) * A1_LPW; ++i) {
+      unsigned char* sa = smem + stage * STAGE + a_block(i) * RB;
       if constexpr (OFF32) {
         asm volatile("" : "+v"(aoff[i]));   // keeps the offset a 32-bit register of its own
-        __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(ak + aoff[i]), SCMOE_LDS_PTR(sa + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(ak + aoff[i]), SCMOE_LDS_PTR(sa), 16, 0, 0);
       } else {
         __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(aptr[i] + static_cast<int64_t>(kt) * RB),
-                                         SCMOE_LDS_PTR(sa + i * 1024), 16, 0, 0);
+                                         SCMOE_LDS_PTR(sa), 16, 0, 0);
       }
     }
+  };
+  auto issue_w = [&](int kt, int stage) {
+    unsigned char* sb = smem + stage * STAGE + A_BYTES + wave * CFG::B_PER_WAVE * 1024;
+    const unsigned char* wk = wbase + static_cast<int64_t>(kt) * RB;
+    if constexpr (OFF32) asm volatile("" : "+s"(wk));
 #pragma unroll
     for (int i = 0; i < CFG::B_PER_WAVE; ++i) {
       if constexpr (OFF32) {
@@ -156,10 +171,19 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       }
     }
   };
+  auto issue_wa0 = [&](int kt, int stage) {
+    issue_w(kt, stage);
+    issue_a(kt, stage, std::integral_constant<int, 0>{});
+  };
+  auto issue_a1 = [&](int kt, int stage) { issue_a(kt, stage, std::integral_constant<int, 1>{}); };
   auto issue_prologue = [&]() {
 #pragma unroll
-    for (int t = 0; t < NS; ++t)
-      if (t < nk) issue_loads(t, t);
+    for (int t = 0; t < NS; ++t) {
+      if (t < nk) {
+        issue_wa0(t, t);
+        issue_a1(t, t);
+      }
+    }
   };
   // wait until at most `tiles` of the newest k-tiles are still in flight (loads complete in
   // issue order, LPW loads per k-tile and wave)
@@ -168,10 +192,13 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     static_assert(n < 64, "vmcnt field");
     __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x0F70);
   };
-  auto wait_tiles = [&](int tiles) {
-    if (tiles >= 2) wait_vm(std::integral_constant<int, 2 * LPW>{});
-    else if (tiles == 1) wait_vm(std::integral_constant<int, LPW>{});
-    else wait_vm(std::integral_constant<int, 0>{});
+  // ... and `extra` more loads, at most
+  auto wait_tiles = [&](int tiles, auto extra_c) {
+    constexpr int x = decltype(extra_c)::value;
+    if (NS > 3 && tiles >= 3) wait_vm(std::integral_constant<int, 3 * LPW + x < 63 ? 3 * LPW + x : 63>{});
+    else if (NS > 2 && tiles >= 2) wait_vm(std::integral_constant<int, 2 * LPW + x < 63 ? 2 * LPW + x : 63>{});
+    else if (tiles >= 1) wait_vm(std::integral_constant<int, LPW + x>{});
+    else wait_vm(std::integral_constant<int, x>{});
   };
 
   // ---- fragment reads (the same for every tile) ---------------------------------------------
@@ -202,33 +229,35 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
                                 // uses buffer (R * KS32 + q) % 2, consecutive steps alternate
   bf16x8_t xf[2][MI / 2];       // activation fragments of a half-step, one buffer per half
   static_assert((NS * KS32) % 2 == 0, "the weight-fragment buffers alternate over the unrolled k loop");
-  // Reads for half-step hs of stage R.  Read order = order of first use.
+  // Half-step hs of a k-tile multiplies the weight fragments of 32-k step hs % KS32 with the
+  // activation fragments of that step of row-subtile half hs / KS32.  Reads for half-step hs of
+  // stage R, in the order of first use:
   auto load_frags = [&](int R, int hs) {
-    const int ks = hs >> 1, half = hs & 1, st = R * STAGE, wbuf = (R * KS32 + ks) & 1;
+    const int ks = hs % KS32, half = hs / KS32, st = R * STAGE, wbuf = (R * KS32 + ks) & 1, xbuf = hs & 1;
     if (half == 0) {
 #pragma unroll
       for (int t = 0; t < (MI / 2 > NJ ? MI / 2 : NJ); ++t) {
         if (t < NJ) wf[wbuf][t] = *reinterpret_cast<lds_frag_ptr>(static_cast<uintptr_t>(wb[ks] + st + t * 16 * RB));
-        if (t < MI / 2) xf[0][t] = *reinterpret_cast<lds_frag_ptr>(static_cast<uintptr_t>(xb[ks] + st + t * 16 * RB));
+        if (t < MI / 2) xf[xbuf][t] = *reinterpret_cast<lds_frag_ptr>(static_cast<uintptr_t>(xb[ks] + st + t * 16 * RB));
       }
     } else {
 #pragma unroll
       for (int t = 0; t < MI / 2; ++t)
-        xf[1][t] = *reinterpret_cast<lds_frag_ptr>(static_cast<uintptr_t>(xb[ks] + st + (MI / 2 + t) * 16 * RB));
+        xf[xbuf][t] = *reinterpret_cast<lds_frag_ptr>(static_cast<uintptr_t>(xb[ks] + st + (MI / 2 + t) * 16 * RB));
     }
   };
   auto mfma_step = [&](int R, int hs) {
-    const int ks = hs >> 1, half = hs & 1, wbuf = (R * KS32 + ks) & 1;
+    const int ks = hs % KS32, half = hs / KS32, wbuf = (R * KS32 + ks) & 1, xbuf = hs & 1;
 #pragma unroll
     for (int i = 0; i < MI / 2; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         acc[half * (MI / 2) + i][j] =
-            __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[wbuf][j], xf[half][i], acc[half * (MI / 2) + i][j], 0, 0, 0);
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[wbuf][j], xf[xbuf][i], acc[half * (MI / 2) + i][j], 0, 0, 0);
   };
   // issue order of one half-step: MFMA, ds_read, MFMA, ds_read, ... (the reads feed the NEXT one)
   auto interleave = [&](auto next_hs_c) {
-    constexpr int reads = (decltype(next_hs_c)::value & 1) ? MI / 2 : MI / 2 + NJ;
+    constexpr int reads = (decltype(next_hs_c)::value / KS32) ? MI / 2 : MI / 2 + NJ;
 #pragma unroll
     for (int q = 0; q < reads; ++q) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -281,43 +310,49 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     // One k-tile with its LDS stage known at compile time (the k loop is unrolled NS-fold),
     // so every LDS address is a loop-invariant register plus an immediate and no address
     // arithmetic has to share registers with fragments that are still in flight.
+    // Two barriers per k-tile.  When half-step KS32 - 1 begins, this wave holds every weight
+    // fragment of the k-tile and every activation fragment of the first row half in registers;
+    // behind the first barrier that is so for all waves, and W and the first halves of the rows
+    // (3/4 of the stage) are refilled with k-tile kt + NS while the second half is still being
+    // multiplied.  The second barrier, ahead of the last half-step, does the same for the second
+    // halves.  So a copy has NS - 1/2 k-tiles to arrive in, and a wait never drains the queue:
+    // LPW (NS - 1) newer copies stay in flight.
     auto k_tile = [&](auto stage_c, auto steady_c, int kt) {
       constexpr int stage = decltype(stage_c)::value;
       constexpr bool steady = decltype(steady_c)::value;   // k-tiles kt+1 .. kt+NS all exist
       constexpr int next = (stage + 1 == NS) ? 0 : stage + 1;
-      static_for<0, HS - 1>([&](auto hs_c) {
+      using X0 = std::integral_constant<int, 0>;
+      using XA1 = std::integral_constant<int, A1_LPW>;
+      static_for<0, HS>([&](auto hs_c) {
         constexpr int hs = decltype(hs_c)::value;
         __builtin_amdgcn_sched_barrier(0);
-        load_frags(stage, hs + 1);
-        mfma_step(stage, hs);
-        interleave(std::integral_constant<int, hs + 1>{});
-      });
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (steady) {
-        // No branches here: the compiler's counter bookkeeping merges conservatively at every
-        // join, and a full LDS wait ahead of the last step would idle the MFMA pipe while all
-        // waves fetch the next stage's first fragments at once.
-        wait_tiles(NS - 2);
-        lds_barrier();
-        issue_loads(kt + NS, stage);
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(next, 0);
-        mfma_step(stage, HS - 1);
-        interleave(std::integral_constant<int, 0>{});
-      } else {
-        if (kt + 1 < nk) {
-          // k-tiles kt+1 .. min(kt+NS-1, nk-1) are in flight; k-tile kt+1 must have landed.
-          // After the barrier it has for every wave, and every wave holds its last fragments
-          // of k-tile kt in registers, so this stage can be refilled with k-tile kt+NS.
-          const int later = nk - kt - 2;
-          wait_tiles(later < NS - 2 ? later : NS - 2);
+        if constexpr (hs == KS32 - 1) {
+          // the second row halves of this k-tile must have landed; in flight may be the k-tiles after it
+          if constexpr (steady) wait_tiles(NS - 1, X0{});
+          else wait_tiles(nk - 1 - kt < NS - 1 ? nk - 1 - kt : NS - 1, X0{});
           lds_barrier();
-          if (kt + NS < nk) issue_loads(kt + NS, stage);
-          load_frags(next, 0);
+          if (steady || kt + NS < nk) issue_wa0(kt + NS, stage);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step(stage, HS - 1);
-      }
+        if constexpr (hs == HS - 1) {
+          if (steady || kt + 1 < nk) {
+            // W and the first row halves of k-tile kt + 1 must have landed; in flight may be its
+            // second halves and the k-tiles after it, of k-tile kt + NS the first group only
+            if (steady || kt + NS < nk) wait_tiles(NS - 1, X0{});
+            else wait_tiles(nk - 2 - kt, XA1{});
+            lds_barrier();
+            if (steady || kt + NS < nk) issue_a1(kt + NS, stage);
+            __builtin_amdgcn_sched_barrier(0);
+            load_frags(next, 0);
+          }
+          mfma_step(stage, hs);
+          if constexpr (steady) interleave(std::integral_constant<int, 0>{});
+        } else {
+          load_frags(stage, hs + 1);
+          mfma_step(stage, hs);
+          interleave(std::integral_constant<int, hs + 1>{});
+        }
+      });
     };
     using std::integral_constant;
     using std::bool_constant;
