@@ -82,36 +82,38 @@ struct ScanChores {
 struct FfnArgs {
   const void* x; int64_t ldx;      // [rows, d] activations
   const int32_t* gather;           // row r reads x[gather[r]] (the dispatch permutation applied
-                                   // on load); nullptr = identity.  MFMA path only.
+                                   // on load); nullptr = identity
   int64_t x_rows;                  // with gather: rows of x that gather may name
-  const int32_t* offsets;          // [E + 1] segment starts, device
+  const int32_t* offsets;          // [E + 1] segment starts, device (direct kernel: nullptr = one segment of max_rows rows)
   int max_rows, E, d, F;
   const void* W1; int64_t ldw1; const float* b1;   // [E, F, d]
   const void* W2; int64_t ldw2; const float* b2;   // [E, d, F]
   void* hidden; int64_t ldh;       // [rows, F] scratch
   void* y; int64_t ldy;            // [rows, d]
   int gelu_mode;
-  // Fused output decode of the second GEMM (MFMA path only; all three pointers nullptr: off).
-  // With scatter (addend optional in the tiled kernel, required by the few-row one):
+  // Fused output decode of the second GEMM (all three pointers nullptr: off).
+  // With scatter (addend optional):
   //   y[scatter[r], :] = addend[scatter[r], :] + row_scale[scatter[r]] * (W2 . hidden[r] + b2)
-  // Without scatter (rows stay in place; tiled kernel only, not the few-row one), row_scale
-  // holding PAIRS of coefficients per row of which the first is used, either pointer optional:
+  // Without scatter (rows stay in place), row_scale holding PAIRS of coefficients per row of
+  // which the first is used, either pointer optional:
   //   y[r, :] = addend[r, :] + row_scale[2 r] * (W2 . hidden[r] + b2)
   const int32_t* scatter; const float* row_scale; const void* addend; int64_t ldadd;
-  // Scratch of the MFMA path (split-K of the last round of tiles); may be nullptr: no split.
+  // Scratch of the tiled path (split-K of the last round of tiles); may be nullptr: no split.
   void* scratch; size_t scratch_bytes;
   bool scratch_zeroed;             // the arrival counters at the start of scratch are zero already
-  // Event the stream waits for between the first and the second GEMM (nullptr: none).  MFMA path.
+  // Event the stream waits for between the first and the second GEMM (nullptr: none).
   hipEvent_t before_second;
 };
 
-int ffn_generic(const FfnArgs& a, int dtype, hipStream_t stream);
-
-// bf16 MFMA path.  Returns SCMOE_ERR_ARG when the shape is outside what the MFMA kernels
-// cover (the caller then uses ffn_generic).
-int ffn_mfma_bf16(const FfnArgs& a, hipStream_t stream);
-// shared expert `se` (one dense segment) and routed experts `rt` with their first GEMMs in one launch
-int ffn_mfma_bf16_pair(const FfnArgs& se, const FfnArgs& rt, hipStream_t stream);
+// The tiled bf16 kernel runs a call of this many packed rows over E segments (else: the direct one).
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E);
+// One expert-FFN call, whichever kernel it takes.
+int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream);
+// The shared expert `se` (one dense segment) and the routed experts `rt`.  Both tiled: their
+// first GEMMs share a launch, then the shared expert's second GEMM runs, then the routed
+// experts' (which may decode into the rows of the shared one).  Both direct: first GEMMs in one
+// launch, second GEMMs in one launch (no decode into the other's rows).
+int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_t stream);
 
 // Row stride the grouped GEMM likes for an operand of `width` columns: rows at a multiple
 // of 512 bytes get 128 bytes of padding.
@@ -120,8 +122,7 @@ inline int64_t padded_ld(int64_t width, int dtype) {
   return ((width * eb) % 512 == 0) ? width + 128 / eb : width;
 }
 bool ffn_mfma_supported(int d, int F);
-bool gemm_skinny_fits(int max_rows, int E);   // the MFMA path would take its few-row kernel for such a call
-size_t ffn_mfma_scratch_bytes();   // scratch the MFMA path can use (16-byte aligned)
+size_t ffn_mfma_scratch_bytes();   // scratch the tiled path can use (16-byte aligned)
 int ffn_mfma_counter_ints();       // ints at the start of that scratch that must be zero before a call
 
 // Compute units of the current device (256 on MI355X), cached per device.

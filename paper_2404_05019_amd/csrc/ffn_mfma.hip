@@ -825,18 +825,31 @@ static int wait_before_second(const FfnArgs& a, hipStream_t stream) {
   return e == hipSuccess ? SCMOE_OK : hip_fail(e);
 }
 
-int ffn_mfma_bf16(const FfnArgs& a, hipStream_t stream) {
-  if (!ffn_mfma_supported(a.d, a.F)) return SCMOE_ERR_ARG;
+// A call is one for the direct kernel if it has at most 64 rows in all, or if its segments
+// average 16 rows or fewer (then a 128- or 256-row tile would be mostly padding), and always in
+// fp32 or at widths that are no multiples of 64.
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E) {
+  if (dtype != SCMOE_BF16 || !ffn_mfma_supported(d, F)) return false;
+  return !(max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024));
+}
+
+static DirectJob direct_job(const GemmArgs& g, bool act, int max_rows) {
+  DirectJob j;
+  j.g = g;
+  j.act = act;
+  j.max_rows = max_rows;
+  return j;
+}
+
+int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
   if (a.max_rows <= 0) return SCMOE_OK;
-  if (gemm_skinny_fits(a.max_rows, a.E)) {
-    // a handful of rows per expert (a decode step): bound by streaming the weights, not by the matrix cores
-    if (a.scatter == nullptr && (a.row_scale != nullptr || a.addend != nullptr)) return SCMOE_ERR_ARG;
-    const SplitK none;
-    const int st1 = launch_gemm_skinny(first_gemm(a, none), true, a.max_rows, a.scratch, a.scratch_bytes, stream);
-    if (st1 != SCMOE_OK) return st1;
-    const int stw = wait_before_second(a, stream);
-    if (stw != SCMOE_OK) return stw;
-    return launch_gemm_skinny(second_gemm(a, none), false, a.max_rows, a.scratch, a.scratch_bytes, stream);
+  const SplitK none;
+  if (!ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E)) {
+    const DirectJob first = direct_job(first_gemm(a, none), true, a.max_rows);
+    const DirectJob second = direct_job(second_gemm(a, none), false, a.max_rows);
+    int st = launch_gemm_direct(&first, 1, dtype, stream);
+    if (st == SCMOE_OK) st = wait_before_second(a, stream);
+    return st == SCMOE_OK ? launch_gemm_direct(&second, 1, dtype, stream) : st;
   }
   SplitK sk;
   int st = prepare_splitk(a, sk, stream);
@@ -848,20 +861,21 @@ int ffn_mfma_bf16(const FfnArgs& a, hipStream_t stream) {
   return launch_variant<false>(second_gemm(a, sk), a.max_rows, a.max_rows, stream);
 }
 
-// The shared expert (one dense segment of se.max_rows rows, no gather) and the routed experts
-// in three launches instead of four: the first GEMMs of both run as one grouped GEMM with the
-// shared expert as an extra segment; the second GEMMs stay apart and in this order, because
-// the routed one may decode into the rows the shared one writes (rt.addend).
-int ffn_mfma_bf16_pair(const FfnArgs& se, const FfnArgs& rt, hipStream_t stream) {
-  if (!ffn_mfma_supported(rt.d, rt.F) || se.d != rt.d || se.F != rt.F || se.E != 1 || se.gather != nullptr ||
-      se.gelu_mode != rt.gelu_mode)
-    return SCMOE_ERR_ARG;
-  if (se.max_rows <= 0) return ffn_mfma_bf16(rt, stream);
-  if (rt.max_rows <= 0) return ffn_mfma_bf16(se, stream);
-  if (gemm_skinny_fits(se.max_rows, se.E) || gemm_skinny_fits(rt.max_rows, rt.E)) {
-    const int st0 = ffn_mfma_bf16(se, stream);      // the shared expert first: rt may add to its rows
-    if (st0 != SCMOE_OK) return st0;
-    return ffn_mfma_bf16(rt, stream);
+int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_t stream) {
+  if (se.d != rt.d || se.F != rt.F || se.E != 1 || se.gather != nullptr || se.gelu_mode != rt.gelu_mode) return SCMOE_ERR_ARG;
+  if (se.max_rows <= 0) return ffn_forward(rt, dtype, stream);
+  if (rt.max_rows <= 0) return ffn_forward(se, dtype, stream);
+  const bool ts = ffn_is_tiled(dtype, se.d, se.F, se.max_rows, se.E), tr = ffn_is_tiled(dtype, rt.d, rt.F, rt.max_rows, rt.E);
+  if (!ts && !tr && rt.addend == nullptr) {
+    const SplitK none;
+    const DirectJob first[2] = {direct_job(first_gemm(rt, none), true, rt.max_rows), direct_job(first_gemm(se, none), true, se.max_rows)};
+    const DirectJob second[2] = {direct_job(second_gemm(rt, none), false, rt.max_rows), direct_job(second_gemm(se, none), false, se.max_rows)};
+    const int st = launch_gemm_direct(first, 2, dtype, stream);
+    return st == SCMOE_OK ? launch_gemm_direct(second, 2, dtype, stream) : st;
+  }
+  if (!ts || !tr) {
+    const int st0 = ffn_forward(se, dtype, stream);      // the shared expert first: rt may add to its rows
+    return st0 == SCMOE_OK ? ffn_forward(rt, dtype, stream) : st0;
   }
   SplitK sks, skr;
   int st = prepare_splitk(se, sks, stream);

@@ -51,7 +51,7 @@ static int check_desc(const scmoe_desc* D, int kmin, int kmax) {
 struct LayerWs {
   int32_t* expert_idx; float* gate_w; int32_t* counts; int32_t* offsets; int32_t* dst_row;
   int32_t* src_token; int32_t* offsets_shared; int32_t* offsets_c; float* coef; float* gate_cg; void* disp_ws; size_t disp_bytes;
-  void* x_perm; void* hidden; void* y_perm; void* hidden_s; void* s;
+  void* hidden; void* y_perm; void* hidden_s; void* s;
   void* scratch_r; void* scratch_s; size_t scratch_bytes;   // GEMM scratch of the routed / shared chain
   int64_t ldh;   // row stride of hidden and hidden_s
   size_t total;
@@ -81,7 +81,6 @@ static LayerWs carve(const scmoe_desc* D, void* base, bool shared) {
   w.gate_cg = static_cast<float*>(take(D->cg_mode ? static_cast<size_t>(D->T) * 4 : 0));   // gate weight x routed coefficient
   w.disp_bytes = dispatch_ws_bytes(D->T, D->E, D->k);
   w.disp_ws = take(w.disp_bytes);
-  w.x_perm = take(rows * D->d * eb);
   w.ldh = padded_ld(D->F, D->dtype);
   w.hidden = take(rows * w.ldh * eb);
   w.y_perm = take(rows * D->d * eb);
@@ -120,19 +119,7 @@ __global__ void set_pair(int32_t* p, int a, int b) {
   }
 }
 
-// FFN over segments: MFMA path for bf16 shapes it covers, else the generic kernel.
-static int expert_ffn_any(const FfnArgs& a, int dtype, hipStream_t stream) {
-  if (a.max_rows <= 0) return SCMOE_OK;
-  if (dtype == SCMOE_BF16 && ffn_mfma_supported(a.d, a.F)) return ffn_mfma_bf16(a, stream);
-  if (a.gather != nullptr || a.scatter != nullptr) return SCMOE_ERR_ARG;  // packed rows in, packed rows out only
-  return ffn_generic(a, dtype, stream);
-}
-
 static inline int64_t ld_or(int64_t ld, int64_t dense) { return ld ? ld : dense; }
-
-static bool gather_on_load(const scmoe_desc* D) {
-  return D->dtype == SCMOE_BF16 && ffn_mfma_supported(D->d, D->F);
-}
 
 // Fork/join events of the two-stream layer call: one pair per host thread and device.
 struct EventPair { hipEvent_t fork = nullptr, join = nullptr; };
@@ -198,15 +185,14 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
                         bool nothing_below = false) {
   SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, stream));
-  const bool gol = gather_on_load(D);
+  // (no packed copy of the rows: the first GEMM gathers them on load)
   SCMOE_TRY(dispatch(x, ldx, D->dtype, w.expert_idx, D->T, D->d, D->E, D->k, D->capacity, w.counts,
-                     w.offsets, w.dst_row, w.src_token, gol ? nullptr : w.x_perm, D->d, w.disp_ws,
-                     w.disp_bytes, stream, chores));
+                     w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, stream, chores));
   const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
   FfnArgs a{};
-  a.x = gol ? x : w.x_perm;
-  a.ldx = gol ? ldx : D->d;
-  a.gather = gol ? w.src_token : nullptr;
+  a.x = x;
+  a.ldx = ldx;
+  a.gather = w.src_token;
   a.x_rows = D->T;
   a.offsets = w.offsets;
   a.max_rows = rows; a.E = D->E; a.d = D->d; a.F = D->F;
@@ -237,9 +223,9 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
   if (shared != nullptr) {
     FfnArgs se = *shared;
     se.scratch_zeroed = chores != nullptr && chores->nzero > 0 && chores->zero_b == se.scratch && se.scratch != nullptr;
-    return ffn_mfma_bf16_pair(se, a, stream);
+    return ffn_forward_pair(se, a, D->dtype, stream);
   }
-  return expert_ffn_any(a, D->dtype, stream);
+  return ffn_forward(a, D->dtype, stream);
 }
 
 }  // namespace scmoe
@@ -308,7 +294,7 @@ extern "C" int scmoe_expert_ffn(const void* x_perm, int64_t ld_perm, int32_t dty
     if (!aligned16(workspace)) return SCMOE_ERR_SHAPE;
     a.scratch = workspace; a.scratch_bytes = ws_bytes;
   }
-  return expert_ffn_any(a, dtype, static_cast<hipStream_t>(stream));
+  return ffn_forward(a, dtype, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int scmoe_expert_ffn_workspace_bytes(int32_t dtype, int32_t d, int32_t F, size_t* out) {
@@ -369,30 +355,33 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     e = hipStreamWaitEvent(sa, ev->fork, 0);
     if (e != hipSuccess) return hip_fail(e);
   }
-  // One stream and the MFMA path: the shared expert's first GEMM joins the routed experts'
-  // (one launch over E + 1 segments), and the dispatch scan also writes the shared expert's
-  // segment bounds and clears the split-K counters of both chains; otherwise the shared expert
-  // runs on its own, ahead of the routing, with kernels of its own for those chores.
-  const bool joint = !two && gather_on_load(D);
+  // One stream: the shared expert's first GEMM joins the routed experts' (one launch over E + 1
+  // segments, or one launch of two jobs of the direct kernel), and on the tiled path the
+  // dispatch scan also writes the shared expert's segment bounds and clears the split-K counters
+  // of both chains.  Two streams: the shared expert runs on its own, ahead of the routing.
+  const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
+  const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1), tiled_r = ffn_is_tiled(D->dtype, D->d, D->F, rows, D->E);
+  const bool joint = !two;
   ScanChores chores;
   if (joint) {
     chores.pair = w.offsets_shared;
     chores.pair_hi = D->T;
     chores.zero_a = static_cast<int*>(w.scratch_r);
     chores.zero_b = static_cast<int*>(w.scratch_s);
-    chores.nzero = w.scratch_bytes ? ffn_mfma_counter_ints() : 0;
-  } else {
+    chores.nzero = (w.scratch_bytes && (tiled_s || tiled_r)) ? ffn_mfma_counter_ints() : 0;
+  } else if (tiled_s) {
     // shared expert on the current-layer representation (Eq. (6)/(7)): independent of routing
     hipLaunchKernelGGL(set_pair, dim3(1), dim3(64), 0, s_shared, w.offsets_shared, 0, D->T);
     SCMOE_TRY(launch_status());
   }
-  // Fused output decode: for top-1 routing on the MFMA path, the shared expert writes y and the
-  // routed GEMM2 adds its gate-weighted rows into y[src_token[r]] (every row is written once,
-  // dropped tokens keep SE(x_cur)): no y_perm round trip and no combine kernel.  Needs y not
-  // to overlap the inputs, which are still being read when y is first written.  With a
-  // coefficient gate or a residual the shared expert's GEMM2 decodes too (in place: its rows
-  // times the shared coefficient, plus the residual rows), and the routed rows carry the
-  // routed coefficient in their factor; the few-row kernels do not have that form.
+  // Fused output decode: for top-1 routing, the shared expert writes y and the routed GEMM2 adds
+  // its gate-weighted rows into y[src_token[r]] (every row is written once, dropped tokens keep
+  // SE(x_cur)): no y_perm round trip and no combine kernel.  Needs y not to overlap the inputs,
+  // which are still being read when y is first written.  With a coefficient gate or a residual
+  // the shared expert's GEMM2 decodes too (in place: its rows times the shared coefficient, plus
+  // the residual rows), and the routed rows carry the routed coefficient in their factor.
+  // Not on one stream with both chains direct: there the two second GEMMs run in one launch,
+  // which is worth more than the combine kernel costs (few tiles each).
   const size_t eb = elem_bytes(D->dtype);
   auto overlaps = [&](const void* a, int64_t lda_, const void* b, int64_t ldb_) {
     const unsigned char* a0 = static_cast<const unsigned char*>(a);
@@ -401,13 +390,10 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     return a0 < b0 + bn && b0 < a0 + an;
   };
   const bool extras = D->cg_mode != SCMOE_CG_NONE || residual != nullptr;
-  const bool tiled = !gemm_skinny_fits(D->T, 1) &&
-                     !gemm_skinny_fits(static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity)), D->E);
-  const bool fused = D->k == 1 && gather_on_load(D) && !overlaps(y, ldy, x_prev, ld_prev) &&
-                     !overlaps(y, ldy, x_cur, ld_cur) &&
-                     (!extras || (tiled && (!residual || !overlaps(y, ldy, residual, ldres))));
+  const bool fused = D->k == 1 && !(joint && !tiled_s && !tiled_r) && !overlaps(y, ldy, x_prev, ld_prev) &&
+                     !overlaps(y, ldy, x_cur, ld_cur) && (!residual || !overlaps(y, ldy, residual, ldres));
   FfnArgs se{};
-  se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = w.offsets_shared;
+  se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = tiled_s ? w.offsets_shared : nullptr;
   se.max_rows = D->T; se.E = 1; se.d = D->d; se.F = D->F;
   se.W1 = W->W1s; se.ldw1 = ld_or(W->ld_w1, D->d); se.b1 = W->b1s;
   se.W2 = W->W2s; se.ldw2 = ld_or(W->ld_w2, D->F); se.b2 = W->b2s;
@@ -423,7 +409,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   }
   if (coef != nullptr)
     SCMOE_TRY(coef_gate(x_cur, ld_cur, D->dtype, W->W_cg, D->cg_mode, D->T, D->d, w.coef, s_shared));
-  if (!joint) SCMOE_TRY(expert_ffn_any(se, D->dtype, s_shared));
+  if (!joint) SCMOE_TRY(ffn_forward(se, D->dtype, s_shared));
   if (two) {
     hipError_t e = hipEventRecord(ev->join, sa);
     if (e != hipSuccess) return hip_fail(e);
@@ -529,10 +515,8 @@ extern "C" int scmoe_offload_begin(const scmoe_desc* D, const void* x_prev, int6
   //    migration below moves exactly the experts that will run (nothing is predicted).
   SCMOE_TRY(gate_topk(x_prev, ld_prev, D->dtype, W->W_g, W->bias, D->T, D->d, E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, sm));
-  const bool gol = gather_on_load(D);
   SCMOE_TRY(dispatch(x_prev, ld_prev, D->dtype, w.expert_idx, D->T, D->d, E, D->k, D->capacity, w.counts,
-                     w.offsets, w.dst_row, w.src_token, gol ? nullptr : w.x_perm, D->d, w.disp_ws,
-                     w.disp_bytes, sm, nullptr));
+                     w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, sm, nullptr));
   hipError_t he = hipMemcpyAsync(host_plan, w.counts, static_cast<size_t>(E) * 4, hipMemcpyDeviceToHost, sm);
   if (he != hipSuccess) return hip_fail(he);
   EventPair* ev = nullptr;
@@ -618,7 +602,7 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
   se.hidden = w.hidden_s; se.ldh = w.ldh; se.gelu_mode = D->gelu_mode;
   se.scratch = w.scratch_bytes ? w.scratch_s : nullptr; se.scratch_bytes = w.scratch_bytes;
   se.y = w.s; se.ldy = D->d;
-  SCMOE_TRY(expert_ffn_any(se, D->dtype, sm));
+  SCMOE_TRY(ffn_forward(se, D->dtype, sm));
   if (D->cg_mode != SCMOE_CG_NONE)
     SCMOE_TRY(coef_gate(x_cur, ld_cur, D->dtype, W->W_cg, D->cg_mode, D->T, D->d, w.coef, sm));
 
@@ -628,11 +612,10 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
     if (he != hipSuccess) return hip_fail(he);
   }
   if (m > 0) {
-    const bool gol = gather_on_load(D);
     FfnArgs a{};
-    a.x = gol ? x_prev : w.x_perm;
-    a.ldx = gol ? ld_prev : D->d;
-    a.gather = gol ? w.src_token : nullptr;
+    a.x = x_prev;
+    a.ldx = ld_prev;
+    a.gather = w.src_token;
     a.x_rows = D->T;
     a.offsets = w.offsets_c;
     a.max_rows = static_cast<int>(packed_rows(D->T, E, D->k, D->capacity));
@@ -641,7 +624,7 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
     a.W2 = pool.W2; a.ldw2 = D->F; a.b2 = W->b2 ? pool.b2 : nullptr;
     a.hidden = w.hidden; a.ldh = w.ldh; a.y = w.y_perm; a.ldy = D->d; a.gelu_mode = D->gelu_mode;
     a.scratch = w.scratch_bytes ? w.scratch_r : nullptr; a.scratch_bytes = w.scratch_bytes;
-    SCMOE_TRY(expert_ffn_any(a, D->dtype, sm));
+    SCMOE_TRY(ffn_forward(a, D->dtype, sm));
   }
   return combine(w.y_perm, D->d, D->dtype, w.dst_row, w.gate_w, D->T, D->d, D->k, w.s, D->d, nullptr, 0,
                  D->cg_mode != SCMOE_CG_NONE ? w.coef : nullptr, y, ldy, sm);
@@ -678,15 +661,14 @@ extern "C" int moe_topk_layer_forward(const scmoe_desc* D, const void* x, int64_
   const LayerWs w = carve(D, workspace, false);
   if (ws_bytes < w.total) return SCMOE_ERR_WORKSPACE;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  // Top-1 on the tiled MFMA path with y apart from x: the second GEMM decodes in its epilogue
+  // Top-1 with y apart from x: the second GEMM decodes in its epilogue
   // (y[src_token[r]] = gate weight x row; dropped tokens' rows are zeroed by a kernel of their
   // own), no y_perm round trip and no combine launch.
   const unsigned char* x0 = static_cast<const unsigned char*>(x);
   const unsigned char* y0 = static_cast<const unsigned char*>(y);
   const size_t eb = elem_bytes(D->dtype);
   const bool apart = x0 + static_cast<size_t>(D->T) * ldx * eb <= y0 || y0 + static_cast<size_t>(D->T) * ldy * eb <= x0;
-  const bool fused = D->k == 1 && gather_on_load(D) && apart &&
-                     !gemm_skinny_fits(static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity)), D->E);
+  const bool fused = D->k == 1 && apart;
   if (fused) {
     SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, y, ldy, nullptr, nullptr, nullptr, nullptr, true));
     return copy_routing(D, w, routing, sm);

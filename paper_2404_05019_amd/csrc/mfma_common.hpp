@@ -334,10 +334,14 @@ struct TileSchedule {
   }
 };
 
-// Grouped GEMM for calls of very few rows (ffn_skinny.hip): true if a call with this upper
-// bound on its packed rows is one for it.
-bool gemm_skinny_fits(int max_rows, int E);
-int launch_gemm_skinny(const GemmArgs& a, bool act, int max_rows, void* scratch, size_t scratch_bytes,
-                       hipStream_t stream);
+// One product of a launch of the direct grouped GEMM (ffn_direct.hip).  g.offsets == nullptr: one
+// dense segment of max_rows rows; otherwise max_rows bounds the packed rows.
+struct DirectJob {
+  GemmArgs g;
+  bool act;
+  int max_rows;
+};
+// One launch for one or two products (any width that is a multiple of 8, either storage type).
+int launch_gemm_direct(const DirectJob* jobs, int n, int dtype, hipStream_t stream);
 
 }  // namespace scmoe
