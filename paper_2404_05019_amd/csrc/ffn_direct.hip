@@ -46,18 +46,6 @@ struct DirectCfg {
   static_assert(LDS <= 64 * 1024, "static LDS");
 };
 
-template <bool F32>
-__device__ __forceinline__ f32x4_t direct_mfma(u32x4_t w, u32x4_t x, f32x4_t acc) {
-  if constexpr (F32) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[c]), __uint_as_float(x[c]), acc, 0, 0, 0);
-    return acc;
-  } else {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, x), acc, 0, 0, 0);
-  }
-}
-
 template <bool F32, int MI, int NJ, int WK>
 __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArgs args) {
   using CFG = DirectCfg<F32, MI, NJ, WK>;
@@ -109,44 +97,81 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   }
 
   // ---- operand rows of this lane (rows past the segment or past N re-read the last one) --------
-  const unsigned char* ap[MI];
-  const unsigned char* bp[NJ];
+  const unsigned char* const abase = p.A;
+  const unsigned char* const wbase = p.W + static_cast<int64_t>(e) * p.N * p.ldw * EB;
+  int64_t ao[MI], wo[NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     int r = row0 + i * 16 + l16;
     if (r > row_end - 1) r = row_end - 1;
     const int64_t src = p.gather ? p.gather[r] : r;
-    ap[i] = p.A + src * p.lda * EB + lq * 16;
+    ao[i] = src * p.lda * EB + lq * 16;
   }
-  const unsigned char* We = p.W + static_cast<int64_t>(e) * p.N * p.ldw * EB + lq * 16;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     int n = n0 + j * 16 + l16;
     if (n > p.N - 1) n = p.N - 1;
-    bp[j] = We + static_cast<int64_t>(n) * p.ldw * EB;
+    wo[j] = static_cast<int64_t>(n) * p.ldw * EB + lq * 16;
   }
-  // ---- this wave's share of the finished tile: fragments wave, wave + WK, ... -------------------
-  constexpr int FPW = (MI * NJ + WK - 1) / WK;
-  f32x4_t bias4[FPW];
-  int orow[FPW];                       // output row
-  float rscale[FPW];
-#pragma unroll
-  for (int f = 0; f < FPW; ++f) {
-    const int q = wave + f * WK, i = q / NJ, jj = q - i * NJ;
+  // ---- what the epilogue needs of fragment (i, j) of the tile ------------------------------------
+  struct Finish { f32x4_t bias; int orow; float rscale; };
+  auto finish_loads = [&](int i, int jj) {
+    Finish t;
     const int n = n0 + jj * 16 + 4 * lq;
     int r = row0 + i * 16 + l16;
     if (r > row_end - 1) r = row_end - 1;
-    bias4[f] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    if (p.bias != nullptr && n < p.N) bias4[f] = *reinterpret_cast<const f32x4_t*>(p.bias + static_cast<int64_t>(e) * p.N + n);
-    orow[f] = r;
-    rscale[f] = 1.0f;
+    t.bias = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    if (p.bias != nullptr && n < p.N) t.bias = *reinterpret_cast<const f32x4_t*>(p.bias + static_cast<int64_t>(e) * p.N + n);
+    t.orow = r;                                                 // output row
+    t.rscale = 1.0f;
     if (p.scatter != nullptr) {
-      orow[f] = p.scatter[r];
-      rscale[f] = p.row_scale[orow[f]];
+      t.orow = p.scatter[r];
+      t.rscale = p.row_scale[t.orow];
     } else if (p.row_scale != nullptr) {
-      rscale[f] = p.row_scale[2 * static_cast<int64_t>(r)];
+      t.rscale = p.row_scale[2 * static_cast<int64_t>(r)];
     }
-  }
+    return t;
+  };
+  // bias, activation, decode, store: v[c] = row l16 of subtile i, column 4 lq + c of column block jj
+  auto finish = [&](int i, int jj, f32x4_t v, const Finish& t) {
+    v += t.bias;
+    if (act) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if constexpr (F32) v[c] = gelu_f32(v[c], p.gelu_mode);
+        else v[c] = (p.gelu_mode == SCMOE_GELU_TANH) ? gelu_tanh_fast(v[c]) : gelu_erf_fast(v[c]);
+      }
+    }
+    v *= t.rscale;
+    const int r = row0 + i * 16 + l16, n = n0 + jj * 16 + 4 * lq;
+    if (r >= row_end || n >= p.N) return;
+    if (p.addend != nullptr) {
+      const unsigned char* ad = p.addend + (static_cast<int64_t>(t.orow) * p.ldadd + n) * EB;
+      if constexpr (F32) {
+        v += *reinterpret_cast<const f32x4_t*>(ad);
+      } else {
+        const uint2 q2 = *reinterpret_cast<const uint2*>(ad);
+        v[0] += __uint_as_float(q2.x << 16);
+        v[1] += __uint_as_float(q2.x & 0xffff0000u);
+        v[2] += __uint_as_float(q2.y << 16);
+        v[3] += __uint_as_float(q2.y & 0xffff0000u);
+      }
+    }
+    unsigned char* out = p.C + (static_cast<int64_t>(t.orow) * p.ldc + n) * EB;
+    if constexpr (F32) {
+      *reinterpret_cast<f32x4_t*>(out) = v;
+    } else {
+      uint2 o;
+      o.x = cvt_pk_bf16(v[0], v[1]);
+      o.y = cvt_pk_bf16(v[2], v[3]);
+      *reinterpret_cast<uint2*>(out) = o;
+    }
+  };
+  // split K: a wave finishes fragments wave, wave + WK, ... of the tile
+  constexpr int FPW = (MI * NJ + WK - 1) / WK;
+  Finish fin[FPW];
+#pragma unroll
+  for (int f = 0; f < FPW; ++f) fin[f] = finish_loads((wave + f * WK) / NJ, (wave + f * WK) % NJ);
 
   // ---- the sums over this wave's share of k ---------------------------------------------------
   const int pieces = p.Kd * EB / 16;                            // 16-byte pieces per row
@@ -157,55 +182,75 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   const int subs = (row_end - row0 + 15) >> 4;                  // subtiles that hold rows
   auto body = [&](auto ns_c) {
     constexpr int NS = decltype(ns_c)::value;
-    constexpr int PF = F32 ? (NS >= 4 ? 2 : 3) : (NS >= 4 ? 3 : NS == 2 ? 4 : 6);
+    constexpr int PF = NS >= 4 ? 3 : NS == 2 ? 4 : 6;
     f32x4_t acc[NS][NJ];
 #pragma unroll
     for (int i = 0; i < NS; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     u32x4_t ra[PF][NS], rb[PF][NJ];
-    const unsigned char* a[NS];
-    const unsigned char* w[NJ];
+    // The PF steps of a block are read from where `seek` has put the bases.  A wave starts in
+    // the middle of its share (another block for each tile) and wraps round: with row strides of
+    // a power of two, tiles that walk k in step would all be at the same few memory channels.
+    int n = s1 - s0;
+    const int nblk = n / PF;
+    int blk = nblk > 0 ? (b * 5 + wave) % nblk : 0;
+    const unsigned char* a = nullptr;
+    const unsigned char* w = nullptr;
+    auto seek = [&](int step) {
+      a = abase + static_cast<int64_t>(step) * 64;
+      w = wbase + static_cast<int64_t>(step) * 64;
+    };
+    auto next_block = [&](int left) {                             // left: steps that come after the block
+      if (left >= PF) {
+        blk = blk + 1 == nblk ? 0 : blk + 1;
+        seek(s0 + blk * PF);
+      } else {
+        seek(s0 + nblk * PF);
+      }
+    };
+    auto load = [&](int u) {                                      // step u of the block into ring slot u
 #pragma unroll
-    for (int i = 0; i < NS; ++i) a[i] = ap[i] + static_cast<int64_t>(s0) * 64;
+      for (int j = 0; j < NJ; ++j) rb[u][j] = *reinterpret_cast<const u32x4_t*>(w + wo[j] + u * 64);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) w[j] = bp[j] + static_cast<int64_t>(s0) * 64;
-    auto load = [&](int u) {                                    // step u from the pointers into ring slot u
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) rb[u][j] = *reinterpret_cast<const u32x4_t*>(w[j] + u * 64);
-#pragma unroll
-      for (int i = 0; i < NS; ++i) ra[u][i] = *reinterpret_cast<const u32x4_t*>(a[i] + u * 64);
+      for (int i = 0; i < NS; ++i) ra[u][i] = *reinterpret_cast<const u32x4_t*>(a + ao[i] + u * 64);
     };
     auto compute = [&](int u) {
+      // (fp32: element by element over all accumulators, so that no instruction waits for the
+      // one before it: a dependent one issues after 50 cycles, an independent one after 32)
 #pragma unroll
-      for (int i = 0; i < NS; ++i)
+      for (int c = 0; c < (F32 ? 4 : 1); ++c)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = direct_mfma<F32>(rb[u][j], ra[u][i], acc[i][j]);
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            if constexpr (F32)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(rb[u][j][c]), __uint_as_float(ra[u][i][c]), acc[i][j], 0, 0, 0);
+            else
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, rb[u][j]),
+                                                                  __builtin_bit_cast(bf16x8_t, ra[u][i]), acc[i][j], 0, 0, 0);
+          }
     };
-    auto advance = [&]() {
-#pragma unroll
-      for (int i = 0; i < NS; ++i) a[i] += PF * 64;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) w[j] += PF * 64;
-    };
-    int n = s1 - s0;
+    seek(s0 + blk * PF);
     if (n >= PF) {
 #pragma unroll
       for (int u = 0; u < PF; ++u) load(u);
-      advance();
       n -= PF;
+      next_block(n);
       for (; n >= PF; n -= PF) {
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
           compute(u);
           load(u);
+          if (F32) __builtin_amdgcn_sched_barrier(0);           // (or the compiler gathers the loads at the loop's end)
         }
-        advance();
+        next_block(n - PF);
       }
 #pragma unroll
       for (int u = 0; u < PF; ++u) {
         compute(u);
         if (u < n) load(u);                                     // (uniform)
+        if (F32) __builtin_amdgcn_sched_barrier(0);
       }
     } else {
 #pragma unroll
@@ -217,89 +262,52 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
       if (u < n) compute(u);
     if (has_tail) {                                             // pieces past the end of a row count as zeros
       const bool in = lq < tail;
-      const int64_t off = in ? static_cast<int64_t>(full) * 64 : 0;
       const u32x4_t zero = {0u, 0u, 0u, 0u};
+      const int64_t back = in ? 0 : lq * 16;        // (then: the step's first piece, unused)
+      seek(full);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(in ? bp[j] + off : bp[j] - lq * 16);
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(w + (wo[j] - back));
         rb[0][j] = in ? v : zero;
       }
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(in ? ap[i] + off : ap[i] - lq * 16);
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(a + (ao[i] - back));
         ra[0][i] = in ? v : zero;
       }
       compute(0);
     }
     // more than four waves: the upper half hands its sums to the lower half first
     constexpr int P = CFG::PARTS;
-    if constexpr (WK > P) {
-      if (wave >= P) {
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) red[wave - P][i * NJ + j][lane] = acc[i][j];
-      }
-      __syncthreads();
-      if (wave < P) {
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) red[wave][i * NJ + j][lane] += acc[i][j];   // (this lane's own slots)
-      }
-    } else {
+    if (WK > P && wave >= P) {
 #pragma unroll
       for (int i = 0; i < NS; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) red[wave][i * NJ + j][lane] = acc[i][j];
+        for (int j = 0; j < NJ; ++j) red[wave - P][i * NJ + j][lane] = acc[i][j];
+    }
+    if (WK > P) __syncthreads();
+    if (wave < P) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {                          // (this lane's own slots)
+          if (WK > P) red[wave][i * NJ + j][lane] += acc[i][j];
+          else red[wave][i * NJ + j][lane] = acc[i][j];
+        }
     }
   };
   if (subs <= 1) body(std::integral_constant<int, 1>{});
   else if (MI == 2 || subs == 2) body(std::integral_constant<int, 2>{});
   else body(std::integral_constant<int, MI>{});
   __syncthreads();
-
-  // ---- sum of the waves' parts, bias, activation, decode, store ---------------------------------
-  // acc[v] = output row l16 of its subtile, column 4 lq + v of its column block
 #pragma unroll
   for (int f = 0; f < FPW; ++f) {
     const int q = wave + f * WK, i = q / NJ, jj = q - i * NJ;
-    if (i >= subs || i >= MI) continue;                         // (wave-uniform)
+    if (i >= subs || i >= MI) continue;                           // (wave-uniform)
     f32x4_t v = red[0][q][lane];
 #pragma unroll
     for (int s = 1; s < CFG::PARTS; ++s) v += red[s][q][lane];
-    v += bias4[f];
-    if (act) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if constexpr (F32) v[c] = gelu_f32(v[c], p.gelu_mode);
-        else v[c] = (p.gelu_mode == SCMOE_GELU_TANH) ? gelu_tanh_fast(v[c]) : gelu_erf_fast(v[c]);
-      }
-    }
-    v *= rscale[f];
-    const int r = row0 + i * 16 + l16, n = n0 + jj * 16 + 4 * lq;
-    if (r >= row_end || n >= p.N) continue;
-    if (p.addend != nullptr) {
-      const unsigned char* ad = p.addend + (static_cast<int64_t>(orow[f]) * p.ldadd + n) * EB;
-      if constexpr (F32) {
-        v += *reinterpret_cast<const f32x4_t*>(ad);
-      } else {
-        const uint2 q2 = *reinterpret_cast<const uint2*>(ad);
-        v[0] += __uint_as_float(q2.x << 16);
-        v[1] += __uint_as_float(q2.x & 0xffff0000u);
-        v[2] += __uint_as_float(q2.y << 16);
-        v[3] += __uint_as_float(q2.y & 0xffff0000u);
-      }
-    }
-    unsigned char* out = p.C + (static_cast<int64_t>(orow[f]) * p.ldc + n) * EB;
-    if constexpr (F32) {
-      *reinterpret_cast<f32x4_t*>(out) = v;
-    } else {
-      uint2 o;
-      o.x = cvt_pk_bf16(v[0], v[1]);
-      o.y = cvt_pk_bf16(v[2], v[3]);
-      *reinterpret_cast<uint2*>(out) = o;
-    }
+    finish(i, jj, v, fin[f]);
   }
 }
 
@@ -311,32 +319,48 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
   DirectArgs a{};
   int64_t blocks[2] = {0, 0};
   for (int q = 0; q < n; ++q) {
-    a.j[q] = jobs[q].g;
-    a.j[q].nt = (a.j[q].N + CFG::BN - 1) / CFG::BN;
+    GemmArgs& g = a.j[q];
+    g = jobs[q].g;
+    g.nt = (g.N + CFG::BN - 1) / CFG::BN;
     a.rows[q] = jobs[q].max_rows;
     a.act[q] = jobs[q].act ? 1 : 0;
     // upper bound on row tiles: sum_e ceil(c_e / BM) <= rows / BM + (segments that can hold a row)
     const int64_t rows = jobs[q].max_rows;
-    const int64_t segs = a.j[q].offsets == nullptr ? 1 : (a.j[q].E < rows ? a.j[q].E : rows);
-    blocks[q] = (a.j[q].offsets == nullptr ? (rows + CFG::BM - 1) / CFG::BM : rows / CFG::BM + segs) * a.j[q].nt;
+    const int64_t segs = g.E < rows ? g.E : rows;
+    blocks[q] = (g.offsets == nullptr ? (rows + CFG::BM - 1) / CFG::BM : rows / CFG::BM + segs) * g.nt;
   }
   if (blocks[0] + blocks[1] > 0x7fffffffLL) return SCMOE_ERR_SHAPE;
   a.blocks0 = static_cast<int>(blocks[0]);
-  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ, WK>), dim3(static_cast<unsigned>(blocks[0] + blocks[1])),
-                     dim3(CFG::THREADS), 0, stream, a);
+  const dim3 grid(static_cast<unsigned>(blocks[0] + blocks[1])), block(CFG::THREADS);
+  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ, WK>), grid, block, 0, stream, a);
   return launch_status();
 }
 
+// Which tile, measured as a layer call's time (us) at d = 2048, F = 8192, E = 16 unless noted:
+//  * 64 x 64, four waves: when that gives every compute unit a tile and the segments average 32
+//    rows or more (fp32, 2048 tokens, d = 384: 165 against 190 with 32 x 32).
+//  * 32 x 32, four waves: everything smaller; weights are streamed (64 tokens: 251 against 261;
+//    fp32, 64 tokens, d = 1024: 126 against 155).
+//  * 32 x 16, eight waves: when those tiles would put fewer than 16 waves on a compute unit and K is
+//    long enough for eight (8 tokens, second GEMM alone: 48 against 64; d = 512: 33 against 29,
+//    hence the bound on K).
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
-  // 64 x 64 tiles; 32 x 32 when those would leave compute units idle
-  int64_t tiles = 0;
+  int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0;
+  int steps = 0;
   for (int q = 0; q < n; ++q) {
-    const int64_t rows = jobs[q].max_rows, segs = jobs[q].g.offsets == nullptr ? 1 : (jobs[q].g.E < rows ? jobs[q].g.E : rows);
-    tiles += ((rows + 63) / 64 + segs - 1) * ((jobs[q].g.N + 63) / 64);
+    const GemmArgs& g = jobs[q].g;
+    const int64_t r = jobs[q].max_rows, s = g.offsets == nullptr ? 1 : (g.E < r ? g.E : r);
+    tiles64 += (r / 64 + s) * ((g.N + 63) / 64);
+    tiles32 += (r / 32 + s) * ((g.N + 31) / 32);
+    rows += r;
+    segs += s;
+    const int st = g.Kd * (F32 ? 4 : 2) / 64;
+    if (st > steps) steps = st;
   }
-  if (tiles <= num_cus()) return launch_direct_cfg<F32, 2, 2, 8>(jobs, n, stream);
-  return launch_direct_cfg<F32, 4, 4, 4>(jobs, n, stream);
+  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4, 4>(jobs, n, stream);
+  if (tiles32 * 4 < 16 * num_cus() && steps >= 128) return launch_direct_cfg<F32, 2, 1, 8>(jobs, n, stream);
+  return launch_direct_cfg<F32, 2, 2, 4>(jobs, n, stream);
 }
 
 int launch_gemm_direct(const DirectJob* jobs, int n, int dtype, hipStream_t stream) {

@@ -833,20 +833,18 @@ bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E) {
   return !(max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024));
 }
 
-static DirectJob direct_job(const GemmArgs& g, bool act, int max_rows) {
-  DirectJob j;
-  j.g = g;
-  j.act = act;
-  j.max_rows = max_rows;
-  return j;
+// The two products of a call as jobs of the direct kernel.
+static DirectJob direct_first(const FfnArgs& a) {
+  return DirectJob{first_gemm(a, SplitK{}), true, a.max_rows};
+}
+static DirectJob direct_second(const FfnArgs& a) {
+  return DirectJob{second_gemm(a, SplitK{}), false, a.max_rows};
 }
 
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
   if (a.max_rows <= 0) return SCMOE_OK;
-  const SplitK none;
   if (!ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E)) {
-    const DirectJob first = direct_job(first_gemm(a, none), true, a.max_rows);
-    const DirectJob second = direct_job(second_gemm(a, none), false, a.max_rows);
+    const DirectJob first = direct_first(a), second = direct_second(a);
     int st = launch_gemm_direct(&first, 1, dtype, stream);
     if (st == SCMOE_OK) st = wait_before_second(a, stream);
     return st == SCMOE_OK ? launch_gemm_direct(&second, 1, dtype, stream) : st;
@@ -867,9 +865,7 @@ int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_
   if (rt.max_rows <= 0) return ffn_forward(se, dtype, stream);
   const bool ts = ffn_is_tiled(dtype, se.d, se.F, se.max_rows, se.E), tr = ffn_is_tiled(dtype, rt.d, rt.F, rt.max_rows, rt.E);
   if (!ts && !tr && rt.addend == nullptr) {
-    const SplitK none;
-    const DirectJob first[2] = {direct_job(first_gemm(rt, none), true, rt.max_rows), direct_job(first_gemm(se, none), true, se.max_rows)};
-    const DirectJob second[2] = {direct_job(second_gemm(rt, none), false, rt.max_rows), direct_job(second_gemm(se, none), false, se.max_rows)};
+    const DirectJob first[2] = {direct_first(rt), direct_first(se)}, second[2] = {direct_second(rt), direct_second(se)};
     const int st = launch_gemm_direct(first, 2, dtype, stream);
     return st == SCMOE_OK ? launch_gemm_direct(second, 2, dtype, stream) : st;
   }
