@@ -73,6 +73,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   constexpr int HS = 2 * KS32;                                  // half-steps per k-tile
   constexpr int LPW = CFG::A_PER_WAVE + CFG::B_PER_WAVE;        // direct loads per wave and k-tile
   constexpr bool XSEG = ACT, DECODE = DEC != 0;
+  constexpr bool ROTK = BM < 256;                               // (the large tiles are for calls it does not help)
   static_assert(!(ACT && DEC != 0) && DEC >= 0 && DEC <= 2, "the output decode belongs to second GEMMs");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -87,6 +88,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   int it = blockIdx.x >> 3;                // work item: a tile, one K-part of a tile of the last round, or a finish item
   if (it >= sched.ngemm + sched.nfin) return;
   int nk = nk_all;                         // k-tiles of the current item
+  int rot = 0;                             // the one it starts with (the walk wraps round)
 
   // ---- per-lane source addresses of the direct-to-LDS loads -------------------------------
   // First row of the tile that this wave's A load i fills (RPL rows): the first half of the
@@ -142,6 +144,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   constexpr int A1_LPW = CFG::A_PER_WAVE / 2;                   // loads per wave of the group A1
   auto issue_a = [&](int kt, int stage, auto half_c) {
     constexpr int h = decltype(half_c)::value;
+    if (ROTK && (kt += rot) >= nk) kt -= nk;
     const unsigned char* ak = abase + static_cast<int64_t>(kt) * RB;
     if constexpr (OFF32) asm volatile("" : "+s"(ak));           // the scalar sum stays scalar
 #pragma unroll
@@ -157,6 +160,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     }
   };
   auto issue_w = [&](int kt, int stage) {
+    if (ROTK && (kt += rot) >= nk) kt -= nk;
     unsigned char* sb = smem + stage * STAGE + A_BYTES + wave * CFG::B_PER_WAVE * 1024;
     const unsigned char* wk = wbase + static_cast<int64_t>(kt) * RB;
     if constexpr (OFF32) asm volatile("" : "+s"(wk));
@@ -277,6 +281,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       kb = part * nk_all / sched.S;
       nk = (part + 1) * nk_all / sched.S - kb;
     }
+    if (ROTK) rot = p.rotk ? static_cast<int>(static_cast<unsigned>(n0 / BN) * p.rotk % static_cast<unsigned>(nk)) : 0;
     set_ptrs(e, row0, row_end, n0, kb);
   };
   if (it < sched.ngemm) {
@@ -631,11 +636,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 
 using CfgA = TileCfg<256, 256, 64, 2, 4, 2>;   // 8 waves, 128 KiB LDS, one workgroup per CU
 using CfgB = TileCfg<256, 256, 32, 2, 4, 4>;   // 8 waves, 4 stages, 128 KiB LDS
-#ifndef SCMOE_SMALL_TILES
-#define SCMOE_SMALL_TILES 4      // in quarters of the CU count
-#endif
-using CfgS = TileCfg<128, 128, 32, 1, 2, 2>;   // 2 waves, 40 KiB LDS, four workgroups per CU: small problems
+using CfgS = TileCfg<128, 128, 32, 1, 2, 2>;   // 2 waves, 40 KiB LDS, four workgroups per CU
 using CfgT = TileCfg<128, 128, 64, 2, 2, 3>;   // 4 waves of 64 x 64, 104 KiB LDS, one workgroup per CU: fewer 128 x 128 tiles than CUs
+using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
 // Tile configuration in use: 0 unless scmoe_set_gemm_variant has set another.  The one piece of
 // process-wide state of the library: an atomic, read once per launch.
@@ -733,23 +736,30 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
     case 3: return launch_gemm<CfgT, ACT>(a, max_rows, a_rows, stream);
     default: break;
   }
-  // Variant 0 picks by size: a problem whose 256 x 256 tiles would not give every CU one is
-  // cut into 128 x 128 tiles instead (four small workgroups per CU).
-  const int64_t tiles = (static_cast<int64_t>(max_rows) / CfgA::BM + a.E + (a.xrows + CfgA::BM - 1) / CfgA::BM) *
-                        ((a.N + CfgA::BN - 1) / CfgA::BN);
-  if (tiles < SCMOE_SMALL_TILES * num_cus() / 4) {
-    // Not even one 128 x 128 tile per CU: every workgroup is alone on its CU and walks all of K,
-    // and what the launch lacks is waves.  Then a tile gets four waves of 64 x 64 (one per
-    // SIMD) and k-tiles 64 deep in three LDS stages (half as many barriers and waits for the
-    // same arithmetic).  Measured on the small workload's second GEMMs (192 tiles): 27.8 -> 18.4 us
-    // and 32.7 -> 21.0 us (two waves with 64-deep k-tiles: 24.1 and 28.1).  With more tiles than
-    // CUs the two-wave 32-deep form is faster, the first GEMM there by a factor of two.
-    const int64_t tiles_s = ((static_cast<int64_t>(max_rows) + CfgS::BM - 1) / CfgS::BM + a.E +
-                             (a.xrows + CfgS::BM - 1) / CfgS::BM) * ((a.N + CfgS::BN - 1) / CfgS::BN);
-    if (tiles_s <= num_cus()) return launch_gemm<CfgT, ACT>(a, max_rows, a_rows, stream);
-    return launch_gemm<CfgS, ACT>(a, max_rows, a_rows, stream);
-  }
-  return launch_gemm<CfgA, ACT>(a, max_rows, a_rows, stream);
+  // Variant 0 picks by size.
+  const int64_t segs = a.E + (a.xrows > 0 ? 1 : 0), rows = static_cast<int64_t>(max_rows) + a.xrows;
+  auto tiles_of = [&](int64_t edge) {     // upper bound on the tiles of that edge
+    return (max_rows / edge + a.E + (a.xrows + edge - 1) / edge) * ((a.N + edge - 1) / edge);
+  };
+  // Segments of 128 rows or fewer on average: the launch is bound by streaming the weights, and
+  // 256-row tiles would be mostly padding.  128 x 128 tiles, two workgroups per CU, and the
+  // column tiles start their walk over K at different places (rotk): in step, with rows a power
+  // of two apart, they would all be at the same few memory channels.  Measured, layer call at
+  // d = 2048, F = 8192, E = 16: 500 tokens 0.383 -> 0.331 ms, 1000 tokens 0.451 -> 0.364; at 2000
+  // tokens (125 rows per expert) equal to the large tiles, above that those win.
+  const bool few_rows = rows <= 128 * segs;
+  GemmArgs g = a;
+  g.rotk = few_rows ? 5 : 0;
+  if (tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
+  // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
+  // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
+  // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
+  // of layer time with two workgroups per CU, whose free slots would cut the tiles along K).
+  if (!ACT && tiles_of(CfgT::BM) <= num_cus()) return launch_gemm<CfgT, ACT>(g, max_rows, a_rows, stream);
+  // Otherwise two workgroups per CU, whose epilogues and waits fall on each other's arithmetic
+  // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500
+  // tokens, top-2, d = 768, E = 16: 86 -> 79; 3000 tokens, d = 1024, E = 32: 278 -> 245).
+  return launch_gemm<CfgU, ACT>(g, max_rows, a_rows, stream);
 }
 
 __global__ void zero_ints(int* p, int n) {
