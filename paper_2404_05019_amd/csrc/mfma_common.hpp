@@ -57,8 +57,8 @@ struct GemmArgs {
   int* splitk_count;             // SPLITK_PARTS arrival counters, zero between launches
   // Optional dense extra segment with operands of its own (xrows == 0: none): xC[r, :] =
   // act(xA[r, :] . xW^T + xbias) for r < xrows, same N and Kd.  Its tiles come first in the
-  // tile order and it has the segment id E.  (The shared expert riding in the launch of the
-  // routed experts' first GEMM.)  Not combined with scatter.
+  // tile order and it has the segment id E.  (The shared expert riding in the routed experts'
+  // launch.)  Not combined with the output decode.
   int xrows;
   const unsigned char* xA;
   int64_t xlda;
