@@ -28,34 +28,48 @@ constexpr int GATE_TOK = 64;            // tokens per workgroup (one per lane)
 constexpr int GATE_ROW_BYTES = 256;     // bytes of one token row staged per tile
 constexpr int GATE_ROW_STRIDE = 272;    // LDS row stride: +16 B keeps the row reads conflict-free
 
-// Top-k selection and gate weights of one token from its E logits `l` (Eq. (2)-(3)); also
-// returns the maximum and the sum of exp(l - max) for the caller's softmax output.
-__device__ __forceinline__ void route_token(const float* l, int E, int k, int normalize, bool write, int64_t t,
-                                            int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
-                                            float& m_out, float& sum_out) {
+// Top-k selection and gate weights of one token from its E <= NE logits `l` in LDS (Eq. (2)-(3));
+// also returns the maximum and the sum of exp(l - max) for the caller's softmax output.  One lane
+// walks a token's logits, so the walk is kept out of the LDS: all logits are read at once into
+// registers, and every pass over them is unrolled (reading them one after the other, each
+// compare waiting for its read, took 30 of the kernel's 48 us at 64 experts and top-2).
+template <int NE>
+__device__ __forceinline__ void route_token_n(const float* l, int E, int k, int normalize, bool write, int64_t t,
+                                              int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
+                                              float& m_out, float& sum_out) {
+  float v[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) v[e] = l[e < E ? e : E - 1];
   // the j-th choice: largest logit among the experts not chosen yet, lowest index among
   // equals, a NaN only if nothing else is left
   int sel[SCMOE_MAX_TOPK];
+  float sv[SCMOE_MAX_TOPK];
   unsigned long long taken = 0ull;
 #pragma unroll
   for (int j = 0; j < SCMOE_MAX_TOPK; ++j) {
     int best = -1;
+    float bv = 0.0f;
     if (j < k) {
-      for (int e = 0; e < E; ++e) {
-        if ((taken >> e) & 1ull) continue;
-        if (best < 0) { best = e; continue; }
-        const float v = l[e], b = l[best];
-        if (v > b || (b != b && v == v)) best = e;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const bool free = e < E && !((taken >> e) & 1ull);
+        const bool take = free && (best < 0 || v[e] > bv || (bv != bv && v[e] == v[e]));
+        best = take ? e : best;
+        bv = take ? v[e] : bv;
       }
       taken |= 1ull << best;
     }
     sel[j] = best;
+    sv[j] = bv;
   }
   float m = -INFINITY;
-  for (int e = 0; e < E; ++e)
-    if (l[e] > m) m = l[e];
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+    if (e < E && v[e] > m) m = v[e];
   float sum = 0.0f;
-  for (int e = 0; e < E; ++e) sum += expf(l[e] - m);
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+    if (e < E) sum += expf(v[e] - m);
   m_out = m;
   sum_out = sum;
   if (write) {
@@ -67,7 +81,7 @@ __device__ __forceinline__ void route_token(const float* l, int E, int k, int no
     for (int j = 0; j < SCMOE_MAX_TOPK; ++j) {
       z[j] = 0.0f;
       if (j < k) {
-        z[j] = (j == 0) ? 1.0f : expf(l[sel[j]] - l[sel[0]]);
+        z[j] = (j == 0) ? 1.0f : expf(sv[j] - sv[0]);
         zsum += z[j];
       }
     }
@@ -75,10 +89,22 @@ __device__ __forceinline__ void route_token(const float* l, int E, int k, int no
     for (int j = 0; j < SCMOE_MAX_TOPK; ++j) {
       if (j < k) {
         expert_idx[t * k + j] = sel[j];
-        gate_w[t * k + j] = normalize ? z[j] / zsum : expf(l[sel[j]] - m) / sum;
+        gate_w[t * k + j] = normalize ? z[j] / zsum : expf(sv[j] - m) / sum;
       }
     }
   }
+}
+
+// EMAX: the most experts the caller's kernel can have.
+template <int EMAX>
+__device__ __forceinline__ void route_token(const float* l, int E, int k, int normalize, bool write, int64_t t,
+                                            int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
+                                            float& m_out, float& sum_out) {
+  static_assert(SCMOE_MAX_EXPERTS == 64 && EMAX <= 64, "sizes below");
+  if (EMAX <= 8 || E <= 8) route_token_n<8>(l, E, k, normalize, write, t, expert_idx, gate_w, m_out, sum_out);
+  else if (EMAX <= 16 || E <= 16) route_token_n<16>(l, E, k, normalize, write, t, expert_idx, gate_w, m_out, sum_out);
+  else if (EMAX <= 32 || E <= 32) route_token_n<32>(l, E, k, normalize, write, t, expert_idx, gate_w, m_out, sum_out);
+  else route_token_n<64>(l, E, k, normalize, write, t, expert_idx, gate_w, m_out, sum_out);
 }
 
 // NW waves per workgroup, each owning EPL experts; a lane owns TPL tokens (lane, lane + 64),
@@ -249,7 +275,7 @@ __global__ __launch_bounds__(64 * NW) void gate_kernel(
 
   if (wave < TPL) {                                // wave w routes tokens 64 w .. 64 w + 63 of the workgroup
     const int tl = wave * GATE_TOK + lane;
-    route_token(lg + tl * LGS, E, k, normalize, t0 + tl < T, t0 + tl, expert_idx, gate_w, row_max[tl], row_sum[tl]);
+    route_token<EPAD>(lg + tl * LGS, E, k, normalize, t0 + tl < T, t0 + tl, expert_idx, gate_w, row_max[tl], row_sum[tl]);
   }
   if (probs != nullptr) {
     __syncthreads();
@@ -599,7 +625,7 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
   }
   __syncthreads();
   if (tid < TOK)
-    route_token(lg + tid * LGS, E, k, normalize, t0 + tid < T, t0 + tid, expert_idx, gate_w, row_max[tid], row_sum[tid]);
+    route_token<16 * EG>(lg + tid * LGS, E, k, normalize, t0 + tid < T, t0 + tid, expert_idx, gate_w, row_max[tid], row_sum[tid]);
   if (probs != nullptr) {
     __syncthreads();
     const int ntok = (T - t0 < TOK) ? T - t0 : TOK;
@@ -775,7 +801,7 @@ __global__ __launch_bounds__(256) void gate_small_kernel(
   __syncthreads();
   if (tid < tpw) {
     const int tt = blockIdx.x * tpw + tid;
-    if (tt < T) route_token(lg + tid * (epad + 1), E, k, normalize, true, tt, expert_idx, gate_w, row_max[tid], row_sum[tid]);
+    if (tt < T) route_token<SCMOE_MAX_EXPERTS>(lg + tid * (epad + 1), E, k, normalize, true, tt, expert_idx, gate_w, row_max[tid], row_sum[tid]);
   }
   if (probs != nullptr) {
     __syncthreads();
@@ -820,11 +846,14 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
   // against 43 us, E = 64: 75 against 80)
   const bool few_many = E > 16 && static_cast<int64_t>(T) * epad <= GATE_SMALL_LANES / 8;
   if (aligned16(Wg) && !few_many) {
-    // A wave takes 16 tokens.  Up to one wave per SIMD: one workgroup of four waves per CU (fewer
-    // waves per workgroup when that leaves CUs idle); beyond that eight waves.
+    // A wave takes 16 tokens.  Beyond one wave per SIMD eight waves per workgroup; below, four
+    // share the copying of W_g, also where that leaves CUs idle: a single wave cannot keep enough
+    // of W_g in flight to feed its chain (bf16, us, one wave per workgroup / four / eight: d = 2048,
+    // E = 16, 8 to 500 tokens 21 / 18 / 26; 4096 tokens, d = 1024, E = 32: 29.5 / 25.5 / 34).  Short
+    // rows have little of it: then as many waves as keep all CUs in use (d = 64: 3.1 / 3.8).
     const int64_t waves = (static_cast<int64_t>(T) + 15) / 16;
     const bool bf = dtype == SCMOE_BF16;
-    const int nw = waves > 4 * num_cus() ? 8 : waves > 2 * num_cus() ? 4 : waves > num_cus() ? 2 : 1;
+    const int nw = waves > 4 * num_cus() ? 8 : (waves > 2 * num_cus() || d >= 512) ? 4 : waves > num_cus() ? 2 : 1;
 #define SCMOE_GATE_MFMA(NW, EG)                                                                                    \
   return bf ? launch_gate_mfma<true, NW, EG>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)      \
             : launch_gate_mfma<false, NW, EG>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)
