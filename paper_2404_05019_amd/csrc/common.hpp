@@ -86,6 +86,7 @@ struct FfnArgs {
   int64_t x_rows;                  // with gather: rows of x that gather may name
   const int32_t* offsets;          // [E + 1] segment starts, device (direct kernel: nullptr = one segment of max_rows rows)
   int max_rows, E, d, F;
+  int64_t call_rows;               // mean rows of the expert products of the whole layer call; 0: max_rows
   const void* W1; int64_t ldw1; const float* b1;   // [E, F, d]
   const void* W2; int64_t ldw2; const float* b2;   // [E, d, F]
   void* hidden; int64_t ldh;       // [rows, F] scratch
@@ -105,8 +106,9 @@ struct FfnArgs {
   hipEvent_t before_second;
 };
 
-// The tiled bf16 kernel runs a call of this many packed rows over E segments (else: the direct one).
-bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E);
+// The tiled bf16 kernel runs a call of this many packed rows over E segments (else: the direct
+// one).  call_rows: FfnArgs::call_rows.
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows);
 // One expert-FFN call, whichever kernel it takes.
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream);
 // The shared expert `se` (one dense segment) and the routed experts `rt`.  Both tiled: their

@@ -780,6 +780,7 @@ int ffn_mfma_counter_ints() { return SPLITK_PARTS; }
 struct SplitK { float* parts = nullptr; int* counters = nullptr; };
 static int prepare_splitk(const FfnArgs& a, SplitK& sk, hipStream_t stream) {
   if (a.scratch == nullptr || a.scratch_bytes < SPLITK_WS_BYTES) return SCMOE_OK;
+  if (a.d < SPLITK_MIN_K && a.F < SPLITK_MIN_K) return SCMOE_OK;      // no product long enough to be cut
   sk.counters = static_cast<int*>(a.scratch);
   sk.parts = reinterpret_cast<float*>(static_cast<unsigned char*>(a.scratch) + SPLITK_COUNT_BYTES);
   if (a.scratch_zeroed) return SCMOE_OK;
@@ -841,12 +842,22 @@ static int wait_before_second(const FfnArgs& a, hipStream_t stream) {
   return e == hipSuccess ? SCMOE_OK : hip_fail(e);
 }
 
-// A call is one for the direct kernel if it has at most 64 rows in all, or if its segments
-// average 16 rows or fewer (then a 128- or 256-row tile would be mostly padding), and always in
-// fp32 or at widths that are no multiples of 64.
-bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E) {
+// A call is one for the direct kernel in fp32, at widths that are no multiples of 64, and
+//  * with at most 64 rows in all, or segments that average 16 rows or fewer (a 128- or 256-row
+//    tile would be mostly padding: 8 tokens at the large widths 173 -> 129 us of layer time), or
+//  * when its products are small, up to 5e8 multiply-adds each: then a launch is mostly the tiled
+//    kernel's start and end (us, tiled / direct; rows x d x F: 300 tokens, d = 256, 0.8e8 46 / 29;
+//    400, d = 512, 4.2e8 55 / 48; 200, d = 768, 4.7e8 66 / 64; 2000, d = 256, 5.2e8 52 / 54; 150,
+//    d = 1024, 6.3e8 68 / 75).  Both chains of a layer decide by their mean (call_rows), so that
+//    they can share launches.
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows) {
   if (dtype != SCMOE_BF16 || !ffn_mfma_supported(d, F)) return false;
-  return !(max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024));
+  if (max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024)) return false;
+  return static_cast<double>(call_rows) * d * F > 5e8;
+}
+
+static bool is_tiled(const FfnArgs& a, int dtype) {
+  return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.call_rows > 0 ? a.call_rows : a.max_rows);
 }
 
 // The two products of a call as jobs of the direct kernel.
@@ -859,7 +870,7 @@ static DirectJob direct_second(const FfnArgs& a) {
 
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
   if (a.max_rows <= 0) return SCMOE_OK;
-  if (!ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E)) {
+  if (!is_tiled(a, dtype)) {
     const DirectJob first = direct_first(a), second = direct_second(a);
     int st = launch_gemm_direct(&first, 1, dtype, stream);
     if (st == SCMOE_OK) st = wait_before_second(a, stream);
@@ -879,7 +890,7 @@ int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_
   if (se.d != rt.d || se.F != rt.F || se.E != 1 || se.gather != nullptr || se.gelu_mode != rt.gelu_mode) return SCMOE_ERR_ARG;
   if (se.max_rows <= 0) return ffn_forward(rt, dtype, stream);
   if (rt.max_rows <= 0) return ffn_forward(se, dtype, stream);
-  const bool ts = ffn_is_tiled(dtype, se.d, se.F, se.max_rows, se.E), tr = ffn_is_tiled(dtype, rt.d, rt.F, rt.max_rows, rt.E);
+  const bool ts = is_tiled(se, dtype), tr = is_tiled(rt, dtype);
   if (!ts && !tr && rt.addend == nullptr) {
     const DirectJob first[2] = {direct_first(rt), direct_first(se)}, second[2] = {direct_second(rt), direct_second(se)};
     const int st = launch_gemm_direct(first, 2, dtype, stream);

@@ -203,7 +203,7 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
                         const LayerWs& w, hipStream_t stream, void* fused_y = nullptr, int64_t ld_fused = 0,
                         hipEvent_t before_ffn = nullptr, const FfnArgs* shared = nullptr,
                         const ScanChores* chores = nullptr, const float* row_coef = nullptr,
-                        bool nothing_below = false) {
+                        bool nothing_below = false, int64_t call_rows = 0) {
   SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, stream));
   // (no packed copy of the rows: the first GEMM gathers them on load)
@@ -241,6 +241,7 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
       a.row_scale = w.gate_cg;
     }
   }
+  a.call_rows = call_rows;
   if (shared != nullptr) {
     FfnArgs se = *shared;
     se.scratch_zeroed = chores != nullptr && chores->nzero > 0 && chores->zero_b == se.scratch && se.scratch != nullptr;
@@ -381,7 +382,9 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // dispatch scan also writes the shared expert's segment bounds and clears the split-K counters
   // of both chains.  Two streams: the shared expert runs on its own, ahead of the routing.
   const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
-  const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1), tiled_r = ffn_is_tiled(D->dtype, D->d, D->F, rows, D->E);
+  const int64_t call_rows = (static_cast<int64_t>(D->T) + rows + 1) / 2;
+  const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1, call_rows);
+  const bool tiled_r = ffn_is_tiled(D->dtype, D->d, D->F, rows, D->E, call_rows);
   const bool joint = !two;
   ScanChores chores;
   if (joint) {
@@ -416,6 +419,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   FfnArgs se{};
   se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = tiled_s ? w.offsets_shared : nullptr;
   se.max_rows = D->T; se.E = 1; se.d = D->d; se.F = D->F;
+  se.call_rows = call_rows;
   se.W1 = W->W1s; se.ldw1 = ld_or(W->ld_w1, D->d); se.b1 = W->b1s;
   se.W2 = W->W2s; se.ldw2 = ld_or(W->ld_w2, D->F); se.b2 = W->b2s;
   se.hidden = w.hidden_s; se.ldh = w.ldh; se.gelu_mode = D->gelu_mode;
@@ -438,11 +442,11 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // routed experts on the preceding-layer representation
   if (fused) {
     SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, y, ldy, two ? ev->join : nullptr, joint ? &se : nullptr,
-                           joint ? &chores : nullptr, coef));
+                           joint ? &chores : nullptr, coef, false, call_rows));
     return copy_routing(D, w, routing, sm);
   }
   SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, nullptr, 0, nullptr, joint ? &se : nullptr,
-                         joint ? &chores : nullptr));
+                         joint ? &chores : nullptr, nullptr, false, call_rows));
   if (two) {
     hipError_t e = hipStreamWaitEvent(sm, ev->join, 0);
     if (e != hipSuccess) return hip_fail(e);
@@ -690,11 +694,14 @@ extern "C" int moe_topk_layer_forward(const scmoe_desc* D, const void* x, int64_
   const size_t eb = elem_bytes(D->dtype);
   const bool apart = x0 + static_cast<size_t>(D->T) * ldx * eb <= y0 || y0 + static_cast<size_t>(D->T) * ldy * eb <= x0;
   const bool fused = D->k == 1 && apart;
+  ScanChores chores;              // (the dispatch clears the split-K counters on the side)
+  chores.zero_a = static_cast<int*>(w.scratch_r);
+  chores.nzero = w.scratch_bytes ? ffn_mfma_counter_ints() : 0;
   if (fused) {
-    SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, y, ldy, nullptr, nullptr, nullptr, nullptr, true));
+    SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, y, ldy, nullptr, nullptr, &chores, nullptr, true));
     return copy_routing(D, w, routing, sm);
   }
-  SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm));
+  SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, nullptr, 0, nullptr, nullptr, &chores));
   SCMOE_TRY(combine(w.y_perm, D->d, D->dtype, w.dst_row, w.gate_w, D->T, D->d, D->k, nullptr, 0, nullptr, 0,
                     nullptr, y, ldy, sm));
   return copy_routing(D, w, routing, sm);
