@@ -404,8 +404,10 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // which are still being read when y is first written.  With a coefficient gate or a residual
   // the shared expert's GEMM2 decodes too (in place: its rows times the shared coefficient, plus
   // the residual rows), and the routed rows carry the routed coefficient in their factor.
-  // Not on one stream with both chains direct: there the two second GEMMs run in one launch,
-  // which is worth more than the combine kernel costs (few tiles each).
+  // Not on one stream with both chains direct, or with 65 to 128 rows per segment: there the two
+  // second GEMMs run in one launch, which is worth more than the combine kernel costs (layer us,
+  // two launches / one, d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens 501 / 496;
+  // at 500 tokens 328 / 342: too few tiles for two workgroups on every compute unit).
   const size_t eb = elem_bytes(D->dtype);
   auto overlaps = [&](const void* a, int64_t lda_, const void* b, int64_t ldb_) {
     const unsigned char* a0 = static_cast<const unsigned char*>(a);
@@ -414,7 +416,9 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     return a0 < b0 + bn && b0 < a0 + an;
   };
   const bool extras = D->cg_mode != SCMOE_CG_NONE || residual != nullptr;
-  const bool fused = D->k == 1 && !(joint && !tiled_s && !tiled_r) && !overlaps(y, ldy, x_prev, ld_prev) &&
+  const int64_t all_rows = static_cast<int64_t>(rows) + D->T, segs = static_cast<int64_t>(D->E) + 1;
+  const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || (all_rows > 64 * segs && all_rows <= 128 * segs));
+  const bool fused = D->k == 1 && !one_launch && !overlaps(y, ldy, x_prev, ld_prev) &&
                      !overlaps(y, ldy, x_cur, ld_cur) && (!residual || !overlaps(y, ldy, residual, ldres));
   FfnArgs se{};
   se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = tiled_s ? w.offsets_shared : nullptr;
