@@ -122,11 +122,12 @@ int scmoe_last_hip_error(void);
  * integer, read once per launch; no environment variable is consulted): tile configuration of
  * the bf16 grouped GEMM behind scmoe_expert_ffn and the layer calls.  Meant for benchmarks and
  * tests; a call that races with a change of the knob uses the old or the new value.
- * 0 (default) = chosen per launch: 256x256x64 tiles,
- * 8 waves, 2 LDS stages, or 128x128 tiles, 2 waves, when the larger tiles would not give
- * every compute unit one (128x128x32, or 128x128x64 with 4 waves and 3 stages when even those
- * are fewer than the compute units); 1 = always 256x256x32, 8 waves, 4 stages; 2 = always
- * 128x128x32; 3 = always 128x128x64.
+ * 0 (default) = chosen per launch: 256x256x64 tiles, 8 waves, 2 LDS stages; 128x128x64 tiles,
+ * 4 waves, for few rows per expert and for problems that the larger tiles would not spread over
+ * all compute units; small products take a kernel without tiles in LDS.  1 = always 256x256x32,
+ * 8 waves, 4 stages; 2 = always 128x128x32; 3 = always 128x128x64 with 3 stages (where the tiled
+ * kernel is used at all: not in fp32, at widths that are no multiples of 64, for at most 64 rows,
+ * or for at most 16 rows per expert and 1024 in all).
  * Results agree to bf16 rounding of the same fp32 sums; only speed differs.  Other values
  * give SCMOE_ERR_ARG. */
 int scmoe_set_gemm_variant(int32_t variant);
@@ -261,11 +262,10 @@ int scmoe_dispatch_static_max_bytes(size_t* out);
  * identical; they may differ in the last bit from a call without workspace).  NULL, or
  * fewer bytes than asked for: that round runs unsplit.  Calls that may overlap in time
  * need separate workspaces.
- * max_rows <= 64, or max_rows <= 16 E and max_rows <= 1024 (decode steps; bf16, d and F
- * multiples of 64): the call
- * is bound by reading the weights, and a weight-streaming kernel replaces the tiled one; up to
- * 64 rows and with a workspace it cuts K into parts so that the whole chip streams (parts
- * summed in a fixed order).
+ * max_rows <= 64, or max_rows <= 16 E and max_rows <= 1024 (decode steps: bound by reading the
+ * weights), products of at most 5e8 multiply-adds (max_rows d F), fp32, and widths that are no
+ * multiples of 64 take a kernel that feeds the matrix cores straight from global memory; it
+ * uses no workspace.
  * hidden with a row stride of scmoe_padded_ld(F) instead of F is worth about 15 % of the
  * first GEMM when F * 2 bytes is a large power of two.
  * With E = 1 and offsets = {0, T} this is the dense MLP used for the shared expert

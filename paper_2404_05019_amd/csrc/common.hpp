@@ -78,6 +78,7 @@ struct ScanChores {
 };
 
 // ---- entry points implemented in one source and used by the layer orchestration --------
+enum { FFN_AUTO = 0, FFN_TILED = 1, FFN_DIRECT = 2 };
 // One expert-FFN call over packed segments.  All strides in elements.
 struct FfnArgs {
   const void* x; int64_t ldx;      // [rows, d] activations
@@ -86,7 +87,7 @@ struct FfnArgs {
   int64_t x_rows;                  // with gather: rows of x that gather may name
   const int32_t* offsets;          // [E + 1] segment starts, device (direct kernel: nullptr = one segment of max_rows rows)
   int max_rows, E, d, F;
-  int64_t call_rows;               // mean rows of the expert products of the whole layer call; 0: max_rows
+  int path;                        // FFN_AUTO: by ffn_is_tiled; else the caller has decided
   const void* W1; int64_t ldw1; const float* b1;   // [E, F, d]
   const void* W2; int64_t ldw2; const float* b2;   // [E, d, F]
   void* hidden; int64_t ldh;       // [rows, F] scratch
@@ -107,7 +108,7 @@ struct FfnArgs {
 };
 
 // The tiled bf16 kernel runs a call of this many packed rows over E segments (else: the direct
-// one).  call_rows: FfnArgs::call_rows.
+// one).  call_rows: mean rows of the products of the whole call (a layer's two chains).
 bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows);
 // One expert-FFN call, whichever kernel it takes.
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream);

@@ -853,11 +853,13 @@ static int wait_before_second(const FfnArgs& a, hipStream_t stream) {
 bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows) {
   if (dtype != SCMOE_BF16 || !ffn_mfma_supported(d, F)) return false;
   if (max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024)) return false;
+  if (gemm_variant() != 0) return true;                 // a tile configuration has been asked for
   return static_cast<double>(call_rows) * d * F > 5e8;
 }
 
 static bool is_tiled(const FfnArgs& a, int dtype) {
-  return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.call_rows > 0 ? a.call_rows : a.max_rows);
+  if (a.path != FFN_AUTO) return a.path == FFN_TILED;
+  return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.max_rows);
 }
 
 // The two products of a call as jobs of the direct kernel.

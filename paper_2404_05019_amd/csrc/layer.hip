@@ -203,7 +203,7 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
                         const LayerWs& w, hipStream_t stream, void* fused_y = nullptr, int64_t ld_fused = 0,
                         hipEvent_t before_ffn = nullptr, const FfnArgs* shared = nullptr,
                         const ScanChores* chores = nullptr, const float* row_coef = nullptr,
-                        bool nothing_below = false, int64_t call_rows = 0) {
+                        bool nothing_below = false, int path = FFN_AUTO) {
   SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, stream));
   // (no packed copy of the rows: the first GEMM gathers them on load)
@@ -241,7 +241,7 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
       a.row_scale = w.gate_cg;
     }
   }
-  a.call_rows = call_rows;
+  a.path = path;
   if (shared != nullptr) {
     FfnArgs se = *shared;
     se.scratch_zeroed = chores != nullptr && chores->nzero > 0 && chores->zero_b == se.scratch && se.scratch != nullptr;
@@ -423,7 +423,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   FfnArgs se{};
   se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = tiled_s ? w.offsets_shared : nullptr;
   se.max_rows = D->T; se.E = 1; se.d = D->d; se.F = D->F;
-  se.call_rows = call_rows;
+  se.path = tiled_s ? FFN_TILED : FFN_DIRECT;
   se.W1 = W->W1s; se.ldw1 = ld_or(W->ld_w1, D->d); se.b1 = W->b1s;
   se.W2 = W->W2s; se.ldw2 = ld_or(W->ld_w2, D->F); se.b2 = W->b2s;
   se.hidden = w.hidden_s; se.ldh = w.ldh; se.gelu_mode = D->gelu_mode;
@@ -446,11 +446,11 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // routed experts on the preceding-layer representation
   if (fused) {
     SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, y, ldy, two ? ev->join : nullptr, joint ? &se : nullptr,
-                           joint ? &chores : nullptr, coef, false, call_rows));
+                           joint ? &chores : nullptr, coef, false, tiled_r ? FFN_TILED : FFN_DIRECT));
     return copy_routing(D, w, routing, sm);
   }
   SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, nullptr, 0, nullptr, joint ? &se : nullptr,
-                         joint ? &chores : nullptr, nullptr, false, call_rows));
+                         joint ? &chores : nullptr, nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
   if (two) {
     hipError_t e = hipStreamWaitEvent(sm, ev->join, 0);
     if (e != hipSuccess) return hip_fail(e);

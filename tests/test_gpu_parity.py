@@ -309,6 +309,74 @@ def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, work
     _ffn_case(oracle, E, lens, d, F, "bf16", biases, gelu_mode, extra_rows=0, pad=pad, workspace=workspace)
 
 
+@pytest.mark.parametrize("E,lens,d,F,dtype,biases,gelu_mode,pad", [
+    # one 16-byte piece, a step less / exactly / more than a whole number of 64-byte steps, shares
+    # of K that are empty for most waves
+    (1, [1], 8, 8, "f32", False, 0, False), (2, [15, 16], 8, 16, "bf16", True, 0, False),
+    (3, [17, 0, 31], 24, 40, "bf16", True, 1, True), (2, [32, 33], 56, 72, "f32", True, 1, False),
+    (4, [63, 64, 65, 1], 264, 200, "bf16", True, 0, False), (3, [48, 49, 130], 136, 520, "f32", False, 0, True),
+    # more segments than a wave has lanes, most of them empty
+    (70, [0, 3] * 35, 40, 24, "f32", True, 0, False), (130, [0] * 64 + [1] * 2 + [0] * 63 + [20], 64, 64, "bf16", True, 0, False),
+    # 64 x 64 tiles (every compute unit has one, 32 rows or more per segment), ragged in both directions
+    (3, [1100, 0, 937], 72, 1000, "f32", True, 0, False), (2, [900, 1201], 136, 776, "bf16", True, 1, False),
+    # 32 x 16 tiles with eight waves: few rows, long K
+    (4, [3, 0, 8, 5], 64, 4160, "bf16", True, 0, False), (2, [7, 9], 72, 2120, "f32", True, 0, False),
+    # small products at widths the tiled kernel has
+    (3, [300, 0, 129], 256, 448, "bf16", True, 0, True)])
+def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad):
+    """The kernel without LDS tiles: row subtiles and their remainders, K remainders, both types."""
+    _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=2, pad=pad)
+
+
+@pytest.mark.parametrize("E,lens,d,F", [
+    (4, [700, 1, 511, 129], 512, 1024),          # two workgroups of 128 x 128 tiles per compute unit; then one (three stages)
+    (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 512, 1088),   # few rows per expert: rotated walk over K, N tail
+    (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 448, 2112)])  # ... and a second GEMM whose tiles are cut along K
+@pytest.mark.parametrize("workspace", [False, True])
+def test_expert_ffn_medium_tiles(oracle, E, lens, d, F, workspace):
+    """Products above the direct kernel's limit with few 256-row tiles, every element compared."""
+    assert sum(lens) * d * F > 5e8
+    _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, workspace=workspace)
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams", [
+    (600, 512, 2048, 16, 1, 600, 0, False, False),     # 65-128 rows per segment: one second GEMM, then combine
+    (600, 512, 2048, 16, 1, 30, 2, True, False),       # ... with drops, a coefficient gate and the residual
+    (500, 640, 2048, 24, 1, 500, 0, False, True),      # fewer rows, two streams: fused decode behind 128-row tiles
+    (1400, 256, 2048, 4, 1, 320, 1, True, False),      # tiles cut along K with fused decodes
+    (1400, 256, 2048, 4, 1, 100000, 0, False, True),
+    (700, 384, 1536, 8, 2, 180, 0, False, False),      # two experts per token: shared second GEMM as the extra segment
+    (700, 384, 2112, 8, 3, 100000, 1, True, False)])   # ... whose last round of tiles may be cut along K
+def test_layer_medium_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
+    """Layers above the direct kernel's limit, through the launches that both chains share."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=700 + E + k, biases=True, cg_rows=cg, w_scale=0.03)
+    y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, True, int(k > 1), cg, 0, res, two_streams=two_streams)
+    assert_close(y, ref, "bf16")
+
+
+@pytest.mark.parametrize("dtype,d,F", [("f32", 72, 200), ("bf16", 128, 256), ("bf16", 512, 1024)])
+def test_non_finite_values_stay_in_their_rows(dtype, d, F):
+    """A NaN or an infinity in one row of x reaches that row of the output and no other."""
+    rng = np.random.default_rng(5)
+    rows, E = 1200, 2
+    x = inputs.quantize(rng.standard_normal((rows, d)), dtype)
+    W1, W2 = (inputs.quantize(0.05 * rng.standard_normal(s), dtype) for s in ((E, F, d), (E, d, F)))
+    offsets = torch.tensor([0, 500, rows], dtype=torch.int32, device=DEV)
+    out = []
+    for bad in (False, True):
+        gx = to_dev(x, dtype)
+        if bad:
+            gx[3, 5], gx[700, 0] = float("nan"), float("inf")
+        hidden, y = torch.zeros((rows, F), dtype=gx.dtype, device=DEV), torch.zeros((rows, d), dtype=gx.dtype, device=DEV)
+        B.scmoe_expert_ffn(gx, offsets, rows, to_dev(W1, dtype), None, to_dev(W2, dtype), None, hidden, y)
+        torch.cuda.synchronize()
+        out.append(to_host(y))
+    assert np.isnan(out[1][3]).all() and not np.isfinite(out[1][700]).any()
+    keep = np.ones(rows, bool)
+    keep[[3, 700]] = False
+    assert np.array_equal(out[0][keep], out[1][keep])
+
+
 @pytest.mark.parametrize("T,E,k,C_,shared,cg,res", [
     (8, 4, 1, 8, True, 0, False), (20, 8, 1, 3, True, 0, False), (1, 2, 1, 1, True, 0, False),
     (16, 4, 2, 32, False, 0, False), (10, 8, 3, 30, False, 0, False), (32, 16, 1, 32, True, 1, True),
