@@ -404,10 +404,14 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // which are still being read when y is first written.  With a coefficient gate or a residual
   // the shared expert's GEMM2 decodes too (in place: its rows times the shared coefficient, plus
   // the residual rows), and the routed rows carry the routed coefficient in their factor.
-  // Not on one stream with both chains direct, or with 65 to 128 rows per segment: there the two
-  // second GEMMs run in one launch, which is worth more than the combine kernel costs (layer us,
-  // two launches / one, d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens 501 / 496;
-  // at 500 tokens 328 / 342: too few tiles for two workgroups on every compute unit).
+  // Not on one stream where the two second GEMMs are better off in one launch, followed by the
+  // combine kernel (layer us, two launches / one):
+  //  * both chains direct (few tiles each);
+  //  * F < 2048 (tiles are not cut along K) and the 128 x 128 tiles of both fit two workgroups per
+  //    compute unit at once (8192 tokens, d = 384: 96 / 90.5; 4000, d = 256: 59 / 47; 2500, d = 640:
+  //    83 / 70; with more tiles 0.99 to 1.04);
+  //  * 65 to 128 rows per segment (d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens
+  //    501 / 496; at 500 tokens 328 / 342: the shared expert's tiles alone are cut along K).
   const size_t eb = elem_bytes(D->dtype);
   auto overlaps = [&](const void* a, int64_t lda_, const void* b, int64_t ldb_) {
     const unsigned char* a0 = static_cast<const unsigned char*>(a);
@@ -417,7 +421,9 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   };
   const bool extras = D->cg_mode != SCMOE_CG_NONE || residual != nullptr;
   const int64_t all_rows = static_cast<int64_t>(rows) + D->T, segs = static_cast<int64_t>(D->E) + 1;
-  const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || (all_rows > 64 * segs && all_rows <= 128 * segs));
+  const int64_t tiles = (all_rows / 128 + segs) * ((D->d + 127) / 128);
+  const bool one_round = D->F < 2048 && tiles <= 2 * num_cus();
+  const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || one_round || (all_rows > 64 * segs && all_rows <= 128 * segs));
   const bool fused = D->k == 1 && !one_launch && !overlaps(y, ldy, x_prev, ld_prev) &&
                      !overlaps(y, ldy, x_cur, ld_cur) && (!residual || !overlaps(y, ldy, residual, ldres));
   FfnArgs se{};
