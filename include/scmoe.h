@@ -320,12 +320,12 @@ int scmoe_workspace_bytes(const scmoe_desc* desc, size_t* out);
  * The shared expert depends on x_cur only and the routed chain on x_prev only (Sec. 3.2):
  * with stream_aux != NULL the shared expert's GEMMs are enqueued on stream_aux and the
  * routed chain on stream_main, forked and joined with events.  Where the output decode is fused
- * into the routed experts' second GEMM (bf16 MFMA path, k = 1, y apart from the inputs) the join
+ * into the routed experts' second GEMM (k = 1, y apart from the inputs) the join
  * sits in front of that second GEMM only: gate, encode and the routed first GEMM run beside the
  * shared expert; otherwise the whole routed chain does and the join sits in front of the
  * combine kernel.  With stream_aux == NULL
- * everything runs in order on stream_main (and, on the bf16 MFMA path, the first GEMMs of the
- * shared and the routed experts share one launch).  The result is ready on stream_main.
+ * everything runs in order on stream_main (and the first GEMMs of the shared and the routed
+ * experts share one launch, and so do the second ones where that is faster).  The result is ready on stream_main.
  * (Measured on one MI355X: kernels of a few thousand tokens and more fill the chip and a second
  * stream gains nothing; up to about 4096 tokens it saves 5-13 % of the call.)
  * desc->k = 1 is ScMoE; desc->k = 2 routes two experts per token on x_prev (ScMoE-2,

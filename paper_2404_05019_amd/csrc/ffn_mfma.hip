@@ -15,9 +15,10 @@
 //    lane, no VGPR staging).  Such a load writes 1 KiB of consecutive LDS per wave, so the
 //    bank-conflict swizzle is applied on the global side: the lane that fills LDS slot
 //    (row, c) fetches k-chunk  c ^ swz(row)  of that row.
-//  * N LDS stages and double-buffered register fragments: global loads run N-1 k-tiles
-//    ahead, LDS reads one half-step (16 MFMAs) ahead, issued one behind each MFMA; one
-//    workgroup barrier per k-tile, which orders LDS traffic only (lds_barrier).
+//  * N LDS stages and double-buffered register fragments: global loads run N - 1/2 k-tiles
+//    ahead (a stage is refilled in two groups, see k_tile), LDS reads one half-step (16 MFMAs)
+//    ahead, issued one behind each MFMA; two workgroup barriers per k-tile, which order LDS
+//    traffic only (lds_barrier).
 //  * The MFMA is issued with the weight fragment as its first operand, so a lane ends up
 //    holding 4 consecutive output columns of one row; the epilogue re-assembles rows in a
 //    small per-wave LDS patch and stores whole 128-byte lines.
@@ -305,8 +306,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     }
 
     // ---- main loop ---------------------------------------------------------------------------
-    // Global -> LDS runs NS-1 k-tiles ahead; LDS -> registers runs one half-step ahead, each
-    // ds_read slotted behind an MFMA; one workgroup barrier per k-tile.  After an epilogue
+    // LDS -> registers runs one half-step ahead, each ds_read slotted behind an MFMA.  After an epilogue
     // the stores of the previous tile share the counter with the loads, so everything is
     // waited for (the prologue loads had the whole epilogue to land).
     wait_vm(std::integral_constant<int, 0>{});
@@ -321,7 +321,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     // (3/4 of the stage) are refilled with k-tile kt + NS while the second half is still being
     // multiplied.  The second barrier, ahead of the last half-step, does the same for the second
     // halves.  So a copy has NS - 1/2 k-tiles to arrive in, and a wait never drains the queue:
-    // LPW (NS - 1) newer copies stay in flight.
+    // LPW (NS - 1) newer copies stay in flight.  (One group per k-tile, one k-tile of look-ahead and
+    // a drained queue before: layer 3.69 -> 3.61 ms at 32768 tokens, d = 2048, F = 8192, E = 16; 0.579
+    // -> 0.562 at 16384 tokens, d = 1024, F = 4096, E = 8.)
     auto k_tile = [&](auto stage_c, auto steady_c, int kt) {
       constexpr int stage = decltype(stage_c)::value;
       constexpr bool steady = decltype(steady_c)::value;   // k-tiles kt+1 .. kt+NS all exist

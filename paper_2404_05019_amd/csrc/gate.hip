@@ -31,8 +31,9 @@ constexpr int GATE_ROW_STRIDE = 272;    // LDS row stride: +16 B keeps the row r
 // Top-k selection and gate weights of one token from its E <= NE logits `l` in LDS (Eq. (2)-(3));
 // also returns the maximum and the sum of exp(l - max) for the caller's softmax output.  One lane
 // walks a token's logits, so the walk is kept out of the LDS: all logits are read at once into
-// registers, and every pass over them is unrolled (reading them one after the other, each
-// compare waiting for its read, took 30 of the kernel's 48 us at 64 experts and top-2).
+// registers, and every pass over them is unrolled (instead of reading them one after the other,
+// each compare waiting for its read: top-2, 4096 tokens, d = 1024, E = 64 47.6 -> 43.0 us, E = 32
+// 25.6 -> 23.4).
 template <int NE>
 __device__ __forceinline__ void route_token_n(const float* l, int E, int k, int normalize, bool write, int64_t t,
                                               int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
