@@ -121,20 +121,20 @@ __global__ void set_pair(int32_t* p, int a, int b) {
 
 static inline int64_t ld_or(int64_t ld, int64_t dense) { return ld ? ld : dense; }
 
-// Fork/join events of the two-stream layer call: one pair per host thread and device.
-struct EventPair { hipEvent_t fork = nullptr, join = nullptr; };
-static int get_events(EventPair** out) {
+// Events of the two-stream calls, per host thread and device: fork and join, and in between one
+// for the coefficients of the merge.
+struct StreamEvents { hipEvent_t fork = nullptr, coef = nullptr, join = nullptr; };
+static int get_events(StreamEvents** out) {
   constexpr int MAXDEV = 64;
-  static thread_local EventPair pairs[MAXDEV];
+  static thread_local StreamEvents events[MAXDEV];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
   if (dev < 0 || dev >= MAXDEV) return SCMOE_ERR_ARG;
-  EventPair& p = pairs[dev];
-  if (!p.fork) {
-    e = hipEventCreateWithFlags(&p.fork, hipEventDisableTiming);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipEventCreateWithFlags(&p.join, hipEventDisableTiming);
+  StreamEvents& p = events[dev];
+  for (hipEvent_t* ev : {&p.fork, &p.coef, &p.join}) {
+    if (*ev != nullptr) continue;
+    e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(e);
   }
   *out = &p;
@@ -196,14 +196,15 @@ static int copy_routing(const scmoe_desc* D, const LayerWs& w, const scmoe_routi
 // With shared != nullptr (MFMA path, same stream) the shared expert runs here too: its first
 // GEMM rides in the launch of the routed experts' first GEMM as one more segment.
 // With fused_y and row_coef != nullptr (coefficient gate, Eq. (14)-(17)) the decoded rows are
-// also scaled by the routed coefficient row_coef[2 t + 1] of their token.
+// also scaled by the routed coefficient row_coef[2 t + 1] of their token; `coef_ready` (optional:
+// the coefficient gate on another stream) is waited for before it is read.
 // With fused_y and nothing_below (standard top-1 layer: no shared expert has written fused_y)
 // the decoded rows are stored as they are and the rows of dropped tokens are set to zero.
 static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const scmoe_weights* W,
                         const LayerWs& w, hipStream_t stream, void* fused_y = nullptr, int64_t ld_fused = 0,
                         hipEvent_t before_ffn = nullptr, const FfnArgs* shared = nullptr,
                         const ScanChores* chores = nullptr, const float* row_coef = nullptr,
-                        bool nothing_below = false, int path = FFN_AUTO) {
+                        hipEvent_t coef_ready = nullptr, bool nothing_below = false, int path = FFN_AUTO) {
   SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, stream));
   // (no packed copy of the rows: the first GEMM gathers them on load)
@@ -236,6 +237,10 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
       SCMOE_TRY(launch_status());
     }
     if (row_coef != nullptr) {
+      if (coef_ready != nullptr) {
+        const hipError_t e = hipStreamWaitEvent(stream, coef_ready, 0);
+        if (e != hipSuccess) return hip_fail(e);
+      }
       hipLaunchKernelGGL(scale_gate, dim3((D->T + 255) / 256), dim3(256), 0, stream, w.gate_w, row_coef, w.gate_cg, D->T);
       SCMOE_TRY(launch_status());
       a.row_scale = w.gate_cg;
@@ -369,7 +374,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   hipStream_t sa = static_cast<hipStream_t>(stream_aux);
   const bool two = stream_aux != nullptr && sa != sm;
   hipStream_t s_shared = two ? sa : sm;
-  EventPair* ev = nullptr;
+  StreamEvents* ev = nullptr;
   if (two) {
     SCMOE_TRY(get_events(&ev));
     hipError_t e = hipEventRecord(ev->fork, sm);
@@ -442,8 +447,14 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     se.addend = residual;
     se.ldadd = ldres;
   }
-  if (coef != nullptr)
+  if (coef != nullptr) {
     SCMOE_TRY(coef_gate(x_cur, ld_cur, D->dtype, W->W_cg, D->cg_mode, D->T, D->d, w.coef, s_shared));
+    if (two && fused) {
+      // the fused decode reads the coefficients on the main stream, ahead of the join
+      hipError_t e = hipEventRecord(ev->coef, sa);
+      if (e != hipSuccess) return hip_fail(e);
+    }
+  }
   if (!joint) SCMOE_TRY(ffn_forward(se, D->dtype, s_shared));
   if (two) {
     hipError_t e = hipEventRecord(ev->join, sa);
@@ -452,11 +463,11 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // routed experts on the preceding-layer representation
   if (fused) {
     SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, y, ldy, two ? ev->join : nullptr, joint ? &se : nullptr,
-                           joint ? &chores : nullptr, coef, false, tiled_r ? FFN_TILED : FFN_DIRECT));
+                           joint ? &chores : nullptr, coef, two ? ev->coef : nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
     return copy_routing(D, w, routing, sm);
   }
   SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, nullptr, 0, nullptr, joint ? &se : nullptr,
-                         joint ? &chores : nullptr, nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
+                         joint ? &chores : nullptr, nullptr, nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
   if (two) {
     hipError_t e = hipStreamWaitEvent(sm, ev->join, 0);
     if (e != hipSuccess) return hip_fail(e);
@@ -554,7 +565,7 @@ extern "C" int scmoe_offload_begin(const scmoe_desc* D, const void* x_prev, int6
                      w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, sm, nullptr));
   hipError_t he = hipMemcpyAsync(host_plan, w.counts, static_cast<size_t>(E) * 4, hipMemcpyDeviceToHost, sm);
   if (he != hipSuccess) return hip_fail(he);
-  EventPair* ev = nullptr;
+  StreamEvents* ev = nullptr;
   if (async) {
     SCMOE_TRY(get_events(&ev));
     he = hipEventRecord(ev->fork, sm);          // everything that used the pool before is older than this
@@ -618,7 +629,7 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
   const int m = offload_plan(host_plan, E, pool_experts, slot_expert, nullptr);
   if (m < 0) return SCMOE_ERR_WORKSPACE;
   hipError_t he;
-  EventPair* ev = nullptr;
+  StreamEvents* ev = nullptr;
   if (async) {
     SCMOE_TRY(get_events(&ev));
     he = hipEventRecord(ev->join, sc);          // behind the copies that scmoe_offload_begin put on this stream
@@ -708,7 +719,7 @@ extern "C" int moe_topk_layer_forward(const scmoe_desc* D, const void* x, int64_
   chores.zero_a = static_cast<int*>(w.scratch_r);
   chores.nzero = w.scratch_bytes ? ffn_mfma_counter_ints() : 0;
   if (fused) {
-    SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, y, ldy, nullptr, nullptr, &chores, nullptr, true));
+    SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, y, ldy, nullptr, nullptr, &chores, nullptr, nullptr, true));
     return copy_routing(D, w, routing, sm);
   }
   SCMOE_TRY(routed_chain(D, x, ldx, W, w, sm, nullptr, 0, nullptr, nullptr, &chores));

@@ -566,6 +566,33 @@ def test_layer_tiles_cut_along_k(oracle, k, shared, C_, cg, res, two_streams):
         assert (r["dst_row"] < 0).any()
 
 
+@pytest.mark.parametrize("dtype,T,d,F,C_", [
+    ("f32", 300, 64, 256, 60), ("bf16", 300, 128, 256, 60),            # direct kernel, both types
+    ("bf16", 1400, 256, 2048, 320)])                                   # tiled kernel
+@pytest.mark.parametrize("cg", [1, 2])
+def test_layer_second_stream_runs_late(oracle, dtype, T, d, F, C_, cg):
+    """The second stream is busy with the caller's own work when the layer is called, and the
+    workspace holds NaNs: the result is the same, and complete for the main stream alone."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=4, dtype=dtype, seed=90 + T + cg, biases=True, cg_rows=cg, w_scale=0.03)
+    D = DevLayer(L, dtype)
+    desc = B.make_desc(T, d, F, 4, 1, C_, D.code, 0, 0, cg)
+    ws = torch.full((B.scmoe_workspace_bytes(desc),), 0xff, dtype=torch.uint8, device=DEV)
+    y = torch.full((T, d), float("nan"), dtype=D.tdtype, device=DEV)
+    busy = torch.randn((4096, 4096), device=DEV)
+    aux, main = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(aux):
+        for _ in range(8):
+            busy = busy @ busy * 1e-2
+    with torch.cuda.stream(main):
+        B.scmoe_layer_forward(desc, D.x_prev, D.x_cur, D.weights, y, ws, residual=D.x_cur, stream_main=main, stream_aux=aux)
+        out = y.clone()
+    main.synchronize()
+    ref, _ = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1, cg_mode=cg, add_residual=1)
+    assert_close(to_host(out), ref, dtype)
+    torch.cuda.synchronize()
+
+
 def test_scmoe2_two_routed_experts_plus_shared(oracle):
     """ScMoE-2: top-2 routing on x_prev with the shared expert on x_cur."""
     L = inputs.make_layer(T=600, d=128, F=256, E=8, dtype="bf16", seed=51, biases=True, w_scale=0.05)

@@ -1,0 +1,107 @@
+"""What the library enqueues, without a GPU: the calls go to tests/hip_recorder.c in place of the
+HIP runtime (in a child process), and the order that streams and events give the launches is
+worked out from what it wrote down."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MAIN, AUX = 0xa0, 0xb0                                 # streams; like every address here never dereferenced
+F32, BF16 = 0, 1
+
+
+def _child(recorder, library, calls):
+    rec = C.CDLL(recorder, mode=C.RTLD_GLOBAL)         # found before the runtime that the library is linked with
+    lib = C.CDLL(library)
+    rec.recorder_text.restype = C.c_char_p
+    P = lambda i: C.c_void_p(0x100000000000 + (i << 40))  # noqa: E731 (buffers far apart)
+    out = []
+    for c in calls:
+        rec.recorder_reset()
+        if c["what"] == "layer":
+            desc = (C.c_int32 * 10)(*[c[n] for n in ("T", "d", "F", "E", "k", "capacity", "dtype")], 0, 0, c["cg"])
+            w = (C.c_int64 * 13)(*[P(20 + i).value for i in range(11)], 0, 0)
+            size = C.c_size_t(0)
+            assert lib.scmoe_workspace_bytes(desc, C.byref(size)) == 0
+            st = lib.scmoe_layer_forward(desc, P(1), C.c_int64(c["d"]), P(2), C.c_int64(c["d"]), w, P(3) if c["res"] else None,
+                                         C.c_int64(c["d"]), P(4), C.c_int64(c["d"]), None, P(5), size, C.c_void_p(MAIN),
+                                         C.c_void_p(AUX) if c["two"] else None)
+        out.append([st, rec.recorder_text().decode()])
+    print(json.dumps(out))
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    """record(calls) -> for each call its status and the lines of the recorder, split into words."""
+    so = str(tmp_path_factory.mktemp("recorder") / "hip_recorder.so")
+    subprocess.check_call(["gcc", "-std=c11", "-O1", "-Wall", "-shared", "-fPIC", os.path.join(ROOT, "tests", "hip_recorder.c"),
+                           "-o", so])
+    library = os.path.join(ROOT, "paper_2404_05019_amd", "libscmoe.so")
+
+    def run(calls):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), so, library, json.dumps(calls)], stdout=subprocess.PIPE,
+                           stderr=subprocess.PIPE, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-3000:]
+        return [(st, [line.split(" ") for line in text.splitlines()]) for st, text in json.loads(r.stdout)]
+    return run
+
+
+def _order(lines):
+    """(kernels, after, end): for each launch its name, stream and the launches that are done before it
+    starts; the launches that are done before anything enqueued later on the main stream."""
+    kernels, done, events = [], {}, {}
+    for w in lines:
+        if w[0] == "kernel":
+            stream = int(w[1], 16)
+            kernels.append((w[2], stream, frozenset(done.get(stream, set()))))
+            done.setdefault(stream, set()).add(len(kernels) - 1)
+        elif w[0] == "record":
+            events[w[2]] = set(done.get(int(w[1], 16), set()))
+        elif w[0] == "wait":
+            done.setdefault(int(w[1], 16), set()).update(events.get(w[2], set()))
+    return kernels, done.get(MAIN, set())
+
+
+def _at(kernels, part):
+    return [i for i, k in enumerate(kernels) if part in k[0]]
+
+
+def _layers():
+    out = []
+    for dtype, T, d, F in [(F32, 256, 64, 256), (BF16, 8, 256, 512), (BF16, 4000, 512, 2048), (BF16, 300, 72, 200),
+                           (BF16, 64, 1024, 4096)]:
+        for k in (1, 2):
+            for cg in (0, 1, 2):
+                for res in (False, True):
+                    for capacity in (T * k, 10):
+                        out.append(dict(what="layer", T=T, d=d, F=F, E=8, k=k, capacity=capacity, dtype=dtype, cg=cg, res=res,
+                                        two=True))
+    return out
+
+
+def test_second_stream_of_a_layer_is_ordered_with_the_first(record):
+    """Both streams of a layer call: nothing of the call starts before what the main stream held, the
+    coefficients are written before they are read, the decode that adds to the shared expert's rows
+    comes after them, and at the end the main stream waits for everything."""
+    calls = _layers()
+    for c, (st, lines) in zip(calls, record(calls)):
+        assert st == 0, c
+        kernels, end = _order(lines)
+        assert {s for _, s, _ in kernels} == {MAIN, AUX}, c
+        assert end == set(range(len(kernels))), c
+        aux = {i for i, k in enumerate(kernels) if k[1] == AUX}
+        coef = _at(kernels, "coef_gate_kernel")
+        assert len(coef) == (1 if c["cg"] else 0)
+        for name in ("scale_gate", "combine_kernel"):
+            for i in _at(kernels, name):
+                assert set(coef) <= kernels[i][2], (c, name)
+        last = kernels[max(i for i, k in enumerate(kernels) if k[1] == MAIN)]
+        assert aux <= last[2], c
+
+
+if __name__ == "__main__":
+    _child(sys.argv[1], sys.argv[2], json.loads(sys.argv[3]))
