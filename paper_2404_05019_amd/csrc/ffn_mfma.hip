@@ -873,7 +873,7 @@ static DirectJob direct_second(const FfnArgs& a) {
 }
 
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
-  if (a.max_rows <= 0) return SCMOE_OK;
+  if (a.max_rows <= 0) return wait_before_second(a, stream);      // (nothing kept: the wait is the caller's join)
   if (!is_tiled(a, dtype)) {
     const DirectJob first = direct_first(a), second = direct_second(a);
     int st = launch_gemm_direct(&first, 1, dtype, stream);

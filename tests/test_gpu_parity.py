@@ -568,7 +568,8 @@ def test_layer_tiles_cut_along_k(oracle, k, shared, C_, cg, res, two_streams):
 
 @pytest.mark.parametrize("dtype,T,d,F,C_", [
     ("f32", 300, 64, 256, 60), ("bf16", 300, 128, 256, 60),            # direct kernel, both types
-    ("bf16", 1400, 256, 2048, 320)])                                   # tiled kernel
+    ("bf16", 1400, 256, 2048, 320),                                    # tiled kernel
+    ("f32", 300, 64, 256, 0), ("bf16", 1400, 256, 2048, 0)])           # nothing kept: the shared expert alone
 @pytest.mark.parametrize("cg", [1, 2])
 def test_layer_second_stream_runs_late(oracle, dtype, T, d, F, C_, cg):
     """The second stream is busy with the caller's own work when the layer is called, and the
