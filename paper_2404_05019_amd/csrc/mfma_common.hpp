@@ -3,6 +3,7 @@
 // the persistent tile schedule.
 #pragma once
 #include "common.hpp"
+#include "gelu.hpp"
 
 #include <type_traits>
 
@@ -81,26 +82,6 @@ constexpr int SPLITK_MAX = 8;    // most parts one tile is cut into
 // time, so it is memory traffic, not latency); below K = 2048 a tile is done sooner than that.
 // (Measured, layer step: small 0.129 -> 0.119 ms, medium 0.659 -> 0.647 ms with the limit.)
 constexpr int SPLITK_MIN_K = 2048;
-
-// erf-form GELU for the bf16 epilogue: v * Phi(v) with Phi(v) ~ 0.5 + v * Q(v^2), clamped to
-// [0, 1] (degree-8 minimax fit of v * Phi(v) on |v| <= 4.35 whose leading coefficient is
-// positive and which stays above Phi beyond, so the clamp saturates it the right way; |error of
-// GELU| < 3.5e-5, far below the bf16 rounding of the stored value).  11 VALU operations (the
-// clamp is an output modifier), no transcendental; +-inf and NaN come out as in v * Phi(v).
-// (A first GEMM's epilogue is bound by these: see gemm_bf16_kernel.)
-__device__ __forceinline__ float gelu_erf_fast(float v) {
-  const float u = v * v;
-  float p = 3.8724568690584604e-11f;
-  p = fmaf(p, u, -3.995667796630187e-09f);
-  p = fmaf(p, u, 1.820544497377341e-07f);
-  p = fmaf(p, u, -4.865358732786262e-06f);
-  p = fmaf(p, u, 8.571954822400585e-05f);
-  p = fmaf(p, u, -0.0010633631609380245f);
-  p = fmaf(p, u, 0.009669928811490536f);
-  p = fmaf(p, u, -0.06611771136522293f);
-  p = fmaf(p, u, 0.3987829089164734f);
-  return v * __builtin_amdgcn_fmed3f(fmaf(p, v, 0.5f), 0.0f, 1.0f);
-}
 
 // tanh-form GELU: 0.5 v (1 + tanh u) == v / (1 + exp(-2 u)) == v / (1 + 2^(v (c1 + c2 v^2))).
 // The reciprocal is the hardware's (1 ulp), like the exponential: both far below the bf16 rounding
