@@ -263,9 +263,9 @@ int scmoe_dispatch_static_max_bytes(size_t* out);
  * fewer bytes than asked for: that round runs unsplit.  Calls that may overlap in time
  * need separate workspaces.
  * max_rows <= 64, or max_rows <= 16 E and max_rows <= 1024 (decode steps: bound by reading the
- * weights), products of at most 5e8 multiply-adds (max_rows d F), fp32, and widths that are no
- * multiples of 64 take a kernel that feeds the matrix cores straight from global memory; it
- * uses no workspace.
+ * weights), small calls (at most 5e8 multiply-adds max_rows d F, and at most 2.2e6 outputs
+ * max_rows (d + F) unless d and F are 64), fp32, and widths that are no multiples of 64 take a
+ * kernel that feeds the matrix cores straight from global memory; it uses no workspace.
  * hidden with a row stride of scmoe_padded_ld(F) instead of F is worth about 15 % of the
  * first GEMM when F * 2 bytes is a large power of two.
  * With E = 1 and offsets = {0, T} this is the dense MLP used for the shared expert

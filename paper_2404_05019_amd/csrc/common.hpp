@@ -108,8 +108,8 @@ struct FfnArgs {
 };
 
 // The tiled bf16 kernel runs a call of this many packed rows over E segments (else: the direct
-// one).  call_rows: mean rows of the products of the whole call (a layer's two chains).
-bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows);
+// one).  mean_rows, all_rows: rows per chain and of all chains of the whole call (a layer has two).
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_rows, int64_t all_rows);
 // One expert-FFN call, whichever kernel it takes.
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream);
 // The shared expert `se` (one dense segment) and the routed experts `rt`.  Both tiled: their

@@ -758,7 +758,10 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   const bool few_rows = rows <= 128 * segs;
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;
-  if (tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
+  // At N <= 128 half of a 256-column tile would be padding (layer call, us, large tiles / two
+  // workgroups of 128 x 128: 32000 tokens, d = 64, F = 128, E = 8 50.7 / 39.5, E = 32 79 / 68; top-2 of
+  // 16 experts, d = 128, F = 1024 161 / 148).
+  if (a.N > CfgU::BN && tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
@@ -847,21 +850,26 @@ static int wait_before_second(const FfnArgs& a, hipStream_t stream) {
 // A call is one for the direct kernel in fp32, at widths that are no multiples of 64, and
 //  * with at most 64 rows in all, or segments that average 16 rows or fewer (a 128- or 256-row
 //    tile would be mostly padding: 8 tokens at the large widths 173 -> 129 us of layer time), or
-//  * when its products are small, up to 5e8 multiply-adds each: then a launch is mostly the tiled
-//    kernel's start and end (us, tiled / direct; rows x d x F: 300 tokens, d = 256, 0.8e8 46 / 29;
-//    400, d = 512, 4.2e8 55 / 48; 200, d = 768, 4.7e8 66 / 64; 2000, d = 256, 5.2e8 52 / 54; 150,
-//    d = 1024, 6.3e8 68 / 75).  Both chains of a layer decide by their mean (call_rows), so that
-//    they can share launches.
-bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t call_rows) {
+//  * when it is small: then a launch is mostly the tiled kernel's start and end.  Up to 5e8
+//    multiply-adds a product (us, tiled / direct, layer calls, rows x d x F: 300 tokens, d = 256,
+//    0.8e8 46 / 29; 400, d = 512, 4.2e8 55 / 48; 200, d = 768, 4.7e8 66 / 64; 150, d = 1024, 6.3e8
+//    68 / 75) and 2.2e6 outputs of all products together: the direct kernel needs a workgroup for
+//    64 x 64 outputs, however short K is (tokens, d, F: 4000, 64, 128 29.2 / 25.9; 16000 32.9 / 35.6;
+//    2000, 64, 512 32.6 / 31.5; 8000 39.9 / 49.1; 4000, 128, 128 31.0 / 29.4; 16000 36.0 / 43.3; 1000,
+//    256, 512 34.4 / 33.0; 2000 34.6 / 40.2; 1000, 384, 768 38.3 / 43.2).  Not counted where neither
+//    width fills a 128-column tile (32000, 64, 64 46.9 / 41.8).
+//    Both chains of a layer decide by their mean and their sum, so that they can share launches.
+bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_rows, int64_t all_rows) {
   if (dtype != SCMOE_BF16 || !ffn_mfma_supported(d, F)) return false;
   if (max_rows <= 64 || (max_rows <= 16 * static_cast<int64_t>(E) && max_rows <= 1024)) return false;
   if (gemm_variant() != 0) return true;                 // a tile configuration has been asked for
-  return static_cast<double>(call_rows) * d * F > 5e8;
+  if (static_cast<double>(mean_rows) * d * F > 5e8) return true;
+  return (d >= 128 || F >= 128) && static_cast<double>(all_rows) * (d + F) > 2.2e6;
 }
 
 static bool is_tiled(const FfnArgs& a, int dtype) {
   if (a.path != FFN_AUTO) return a.path == FFN_TILED;
-  return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.max_rows);
+  return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.max_rows, a.max_rows);
 }
 
 // The two products of a call as jobs of the direct kernel.

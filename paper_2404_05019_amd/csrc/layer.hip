@@ -387,9 +387,9 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // dispatch scan also writes the shared expert's segment bounds and clears the split-K counters
   // of both chains.  Two streams: the shared expert runs on its own, ahead of the routing.
   const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
-  const int64_t call_rows = (static_cast<int64_t>(D->T) + rows + 1) / 2;
-  const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1, call_rows);
-  const bool tiled_r = ffn_is_tiled(D->dtype, D->d, D->F, rows, D->E, call_rows);
+  const int64_t all_rows = static_cast<int64_t>(D->T) + rows, mean_rows = (all_rows + 1) / 2;
+  const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1, mean_rows, all_rows);
+  const bool tiled_r = ffn_is_tiled(D->dtype, D->d, D->F, rows, D->E, mean_rows, all_rows);
   const bool joint = !two;
   ScanChores chores;
   if (joint) {
@@ -425,7 +425,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     return a0 < b0 + bn && b0 < a0 + an;
   };
   const bool extras = D->cg_mode != SCMOE_CG_NONE || residual != nullptr;
-  const int64_t all_rows = static_cast<int64_t>(rows) + D->T, segs = static_cast<int64_t>(D->E) + 1;
+  const int64_t segs = static_cast<int64_t>(D->E) + 1;
   const int64_t tiles = (all_rows / 128 + segs) * ((D->d + 127) / 128);
   const bool one_round = D->F < 2048 && tiles <= 2 * num_cus();
   const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || one_round || (all_rows > 64 * segs && all_rows <= 128 * segs));

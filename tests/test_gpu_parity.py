@@ -331,11 +331,13 @@ def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad)
 @pytest.mark.parametrize("E,lens,d,F", [
     (4, [700, 1, 511, 129], 512, 1024),          # two workgroups of 128 x 128 tiles per compute unit; then one (three stages)
     (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 512, 1088),   # few rows per expert: rotated walk over K, N tail
-    (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 448, 2112)])  # ... and a second GEMM whose tiles are cut along K
+    (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 448, 2112),   # ... and a second GEMM whose tiles are cut along K
+    (3, [40000, 0, 26001], 64, 128),             # many rows, one column tile (half of one in the second GEMM), K of one k-tile
+    (2, [129, 1500], 64, 1344)])                 # products just above the outputs limit
 @pytest.mark.parametrize("workspace", [False, True])
 def test_expert_ffn_medium_tiles(oracle, E, lens, d, F, workspace):
     """Products above the direct kernel's limit with few 256-row tiles, every element compared."""
-    assert sum(lens) * d * F > 5e8
+    assert sum(lens) * d * F > 5e8 or sum(lens) * (d + F) > 2.2e6
     _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, workspace=workspace)
 
 

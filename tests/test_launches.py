@@ -30,6 +30,10 @@ def _child(recorder, library, calls):
             st = lib.scmoe_layer_forward(desc, P(1), C.c_int64(c["d"]), P(2), C.c_int64(c["d"]), w, P(3) if c["res"] else None,
                                          C.c_int64(c["d"]), P(4), C.c_int64(c["d"]), None, P(5), size, C.c_void_p(MAIN),
                                          C.c_void_p(AUX) if c["two"] else None)
+        elif c["what"] == "ffn":
+            n, d, F, code = c["T"], c["d"], c["F"], c["dtype"]
+            st = lib.scmoe_expert_ffn(P(1), C.c_int64(d), code, P(2), n, c["E"], d, F, P(3), C.c_int64(d), None, P(4), C.c_int64(F),
+                                      None, P(5), C.c_int64(F), P(6), C.c_int64(d), 0, None, C.c_size_t(0), C.c_void_p(MAIN))
         out.append([st, rec.recorder_text().decode()])
     print(json.dumps(out))
 
@@ -102,6 +106,24 @@ def test_second_stream_of_a_layer_is_ordered_with_the_first(record):
         if c["capacity"]:                              # (otherwise no decode: nothing is kept)
             last = kernels[max(i for i, k in enumerate(kernels) if k[1] == MAIN)]
             assert aux <= last[2], c
+
+
+def _layer(T, d, F, E=8, k=1, dtype=BF16, two=False):
+    return dict(what="layer", T=T, d=d, F=F, E=E, k=k, capacity=T * k, dtype=dtype, cg=0, res=False, two=two)
+
+
+def test_small_products_take_the_direct_kernel_and_many_rows_the_tiled_one(record):
+    """bf16: both limits of the rule (multiply-adds per product, outputs per call), and what it leaves out."""
+    ffn = dict(what="ffn", E=8, dtype=BF16)
+    direct = [_layer(256, 256, 1024), _layer(400, 512, 2048), _layer(4000, 64, 128), _layer(30000, 64, 64), dict(ffn, T=8000, d=64, F=192),
+              _layer(8, 2048, 8192, 16), _layer(2000, 256, 1024, dtype=F32)]
+    tiled = [_layer(30000, 64, 128), _layer(30000, 64, 256, two=True), _layer(2000, 256, 512), _layer(1000, 512, 2048),
+             dict(ffn, T=32768, d=64, F=192), dict(ffn, T=500, d=1024, F=1024)]
+    for want, calls in (("gemm_direct_kernel", direct), ("gemm_bf16_kernel", tiled)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            gemms = _at(kernels, "gemm_")
+            assert st == 0 and gemms and _at(kernels, want) == gemms, c
 
 
 if __name__ == "__main__":
