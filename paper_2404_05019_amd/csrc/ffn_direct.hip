@@ -39,6 +39,8 @@ struct DirectArgs {
   int act[2];
   int blocks0;         // workgroups of job 0; the others belong to job 1
 };
+constexpr int GRID_X = 1 << 16;   // workgroups per row of the grid (the runtime takes fewer than 2^32 work-items in x);
+                                  // those past the last tile find no row and leave
 
 template <bool F32, int MI, int NJ, int WK>
 struct DirectCfg {
@@ -58,7 +60,7 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
-  int b = blockIdx.x;
+  int b = blockIdx.y * GRID_X + blockIdx.x;
   const int which = b >= args.blocks0 ? 1 : 0;
   if (which) b -= args.blocks0;
   const GemmArgs& p = args.j[which];
@@ -333,9 +335,12 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
     const int64_t segs = g.E < rows ? g.E : rows;
     blocks[q] = (g.offsets == nullptr ? (rows + CFG::BM - 1) / CFG::BM : rows / CFG::BM + segs) * g.nt;
   }
-  if (blocks[0] + blocks[1] > 0x7fffffffLL) return SCMOE_ERR_SHAPE;
+  const int64_t total = blocks[0] + blocks[1];
+  if (total > 0x7fffffffLL - GRID_X) return SCMOE_ERR_SHAPE;
   a.blocks0 = static_cast<int>(blocks[0]);
-  const dim3 grid(static_cast<unsigned>(blocks[0] + blocks[1])), block(CFG::THREADS);
+  if (n == 1) a.j[1].nt = 1;                                    // (workgroups past the last tile: no rows there)
+  const dim3 grid(static_cast<unsigned>(total < GRID_X ? total : GRID_X), static_cast<unsigned>((total + GRID_X - 1) / GRID_X)),
+      block(CFG::THREADS);
   hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ, WK>), grid, block, 0, stream, a);
   return launch_status();
 }

@@ -322,7 +322,9 @@ def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, work
     # 32 x 16 tiles with eight waves: few rows, long K
     (4, [3, 0, 8, 5], 64, 4160, "bf16", True, 0, False), (2, [7, 9], 72, 2120, "f32", True, 0, False),
     # small products at widths the tiled kernel has
-    (3, [300, 0, 129], 256, 448, "bf16", True, 0, True)])
+    (3, [300, 0, 129], 256, 448, "bf16", True, 0, True),
+    # more workgroups than one row of the grid holds
+    (3, [21000, 0, 20010], 8, 6808, "bf16", True, 0, False)])
 def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad):
     """The kernel without LDS tiles: row subtiles and their remainders, K remainders, both types."""
     _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=2, pad=pad)

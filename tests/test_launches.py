@@ -126,5 +126,19 @@ def test_small_products_take_the_direct_kernel_and_many_rows_the_tiled_one(recor
             assert st == 0 and gemms and _at(kernels, want) == gemms, c
 
 
+def test_no_launch_passes_the_limit_on_work_items(record):
+    """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
+    workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
+    calls = [dict(what="ffn", E=E, T=T, d=d, F=F, dtype=BF16) for E, T, d, F in
+             [(1, 1100000, 8, 65544), (8, 1100000, 72, 65544), (1, 300, 72, 200), (2, 600000, 120120, 8)]]
+    for c, (st, lines) in zip(calls, record(calls)):
+        gemms = [w for w in lines if w[0] == "kernel" and "gemm_direct_kernel" in w[2]]
+        assert st == 0 and len(gemms) == 2, c
+        for w, width in zip(gemms, (c["F"], c["d"])):
+            gx, gy, gz, bx = (int(v) for v in w[3:7])
+            assert gx * bx < 2 ** 32 and gy < 65536 and gz == 1, (c, w)
+            assert gx * gy * 64 * 64 >= c["T"] * width, (c, w)
+
+
 if __name__ == "__main__":
     _child(sys.argv[1], sys.argv[2], json.loads(sys.argv[3]))
