@@ -256,6 +256,8 @@ int scmoe_dispatch_static_max_bytes(size_t* out);
  * b2 [E, d] fp32 or NULL.  hidden: caller scratch [max_rows, F] in `dtype`, row stride ldh.
  * All strides are in elements, multiples of 8, and at least the row width.
  * bf16: fp32 accumulation, hidden and y_perm rounded to bf16 (RNE) on store.
+ * fp32: K is summed in four parts, one after the other in an order that depends on the widths,
+ * the column and the segment: a row's bits do not depend on the other rows of the call.
  * workspace: optional device scratch of scmoe_expert_ffn_workspace_bytes bytes (16-byte
  * aligned).  With it the bf16 kernels cut the tiles of the last, partly filled round of
  * workgroups along K and add the parts up in a fixed order (results stay run-to-run

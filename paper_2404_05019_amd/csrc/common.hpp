@@ -88,6 +88,7 @@ struct FfnArgs {
   const int32_t* offsets;          // [E + 1] segment starts, device (direct kernel: nullptr = one segment of max_rows rows)
   int max_rows, E, d, F;
   int path;                        // FFN_AUTO: by ffn_is_tiled; else the caller has decided
+  bool slots;                      // segments are pool slots: which expert has which depends on the other rows
   const void* W1; int64_t ldw1; const float* b1;   // [E, F, d]
   const void* W2; int64_t ldw2; const float* b2;   // [E, d, F]
   void* hidden; int64_t ldh;       // [rows, F] scratch

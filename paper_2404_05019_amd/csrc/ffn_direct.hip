@@ -188,7 +188,7 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   const int subs = (row_end - row0 + 15) >> 4;                  // subtiles that hold rows
   auto body = [&](auto ns_c) {
     constexpr int NS = decltype(ns_c)::value;
-    constexpr int PF = NS >= 4 ? 3 : NS == 2 ? 4 : 6;
+    constexpr int PF = NS >= 4 ? 3 : NS == 2 ? (F32 ? 3 : 4) : 6;
     f32x4_t acc[NS][NJ];
 #pragma unroll
     for (int i = 0; i < NS; ++i)
@@ -198,9 +198,18 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
     // The PF steps of a block are read from where `seek` has put the bases.  A wave starts in
     // the middle of its share (another block for each tile) and wraps round: with row strides of
     // a power of two, tiles that walk k in step would all be at the same few memory channels.
+    // fp32: it starts at a multiple of 6 steps (whole blocks for every PF) that depends on the
+    // columns and the segment alone, and the steps past the last such multiple come last: the order
+    // of a row's sum, and so its bits, do not depend on the other rows of the call or on the tile
+    // shape.  (Layer us with the place depending on the tile, and any PF / so: 2048 tokens,
+    // d = 384, E = 8 158.6 / 160.8; 200 tokens, d = 1024, E = 16 216 / 221; 64, d = 2048, E = 8 364 / 340;
+    // 8, d = 2048, E = 16 233 / 224; by the columns alone the first is 164.8, not at all 162.6.)
     int n = s1 - s0;
-    const int nblk = n / PF;
-    int blk = nblk > 0 ? (b * 5 + wave) % nblk : 0;
+    const int all = n;
+    constexpr int UNIT = F32 ? 6 : PF;
+    static_assert(UNIT % PF == 0, "whole blocks");
+    const int starts = n / UNIT, nblk = starts * (UNIT / PF);     // blocks that take part in the rotation
+    int blk = starts > 0 ? ((F32 ? n0 / 64 * 5 + e * p.rotk : b * 5) + wave) % starts * (UNIT / PF) : 0;
     const unsigned char* a = nullptr;
     const unsigned char* w = nullptr;
     auto seek = [&](int step) {
@@ -208,11 +217,11 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
       w = wbase + static_cast<int64_t>(step) * 64;
     };
     auto next_block = [&](int left) {                             // left: steps that come after the block
-      if (left >= PF) {
+      if (all - left < nblk * PF) {
         blk = blk + 1 == nblk ? 0 : blk + 1;
         seek(s0 + blk * PF);
       } else {
-        seek(s0 + nblk * PF);
+        seek(s0 + (all - left));
       }
     };
     auto load = [&](int u) {                                      // step u of the block into ring slot u
@@ -352,7 +361,8 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 //    fp32, 64 tokens, d = 1024: 126 against 155).
 //  * 32 x 16, eight waves: when those tiles would put fewer than 16 waves on a compute unit and K is
 //    long enough for eight (8 tokens, second GEMM alone: 48 against 64; d = 512: 33 against 29,
-//    hence the bound on K).
+//    hence the bound on K).  fp32: four waves like the others, so that K is always summed in the same
+//    four parts (8 tokens 224 against 232 with eight).
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
   int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0;
@@ -368,7 +378,7 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     if (st > steps) steps = st;
   }
   if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4, 4>(jobs, n, stream);
-  if (tiles32 * 4 < 16 * num_cus() && steps >= 128) return launch_direct_cfg<F32, 2, 1, 8>(jobs, n, stream);
+  if (tiles32 * 4 < 16 * num_cus() && steps >= 128) return launch_direct_cfg<F32, 2, 1, F32 ? 4 : 8>(jobs, n, stream);
   return launch_direct_cfg<F32, 2, 2, 4>(jobs, n, stream);
 }
 

@@ -873,12 +873,12 @@ static bool is_tiled(const FfnArgs& a, int dtype) {
 }
 
 // The two products of a call as jobs of the direct kernel.
-static DirectJob direct_first(const FfnArgs& a) {
-  return DirectJob{first_gemm(a, SplitK{}), true, a.max_rows};
+static DirectJob direct_job(GemmArgs g, bool act, const FfnArgs& a) {
+  g.rotk = a.slots ? 0 : 3;
+  return DirectJob{g, act, a.max_rows};
 }
-static DirectJob direct_second(const FfnArgs& a) {
-  return DirectJob{second_gemm(a, SplitK{}), false, a.max_rows};
-}
+static DirectJob direct_first(const FfnArgs& a) { return direct_job(first_gemm(a, SplitK{}), true, a); }
+static DirectJob direct_second(const FfnArgs& a) { return direct_job(second_gemm(a, SplitK{}), false, a); }
 
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
   if (a.max_rows <= 0) return wait_before_second(a, stream);      // (nothing kept: the wait is the caller's join)

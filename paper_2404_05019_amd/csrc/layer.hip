@@ -666,6 +666,7 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
     a.offsets = w.offsets_c;
     a.max_rows = static_cast<int>(packed_rows(D->T, E, D->k, D->capacity));
     a.E = m; a.d = D->d; a.F = D->F;
+    a.slots = true;
     a.W1 = pool.W1; a.ldw1 = D->d; a.b1 = W->b1 ? pool.b1 : nullptr;
     a.W2 = pool.W2; a.ldw2 = D->F; a.b2 = W->b2 ? pool.b2 : nullptr;
     a.hidden = w.hidden; a.ldh = w.ldh; a.y = w.y_perm; a.ldy = D->d; a.gelu_mode = D->gelu_mode;

@@ -45,7 +45,8 @@ struct GemmArgs {
   int E, N, Kd;
   int nt;                   // column tiles
   int gelu_mode;
-  int rotk;                 // column tile c starts its walk over K at k-tile rotk * c (mod the k-tiles); 0: at the first
+  int rotk;                 // tiled: column tile c starts its walk over K at k-tile rotk * c (mod the k-tiles); 0: at the first.
+                            // direct, fp32: what the segment index adds to the place of the first step
   int stream_out;           // store C with the streaming (non-temporal) hint
   // Fused output decode (optional; scatter == nullptr stores C[r, :] as is).  Packed row r
   // is written to row t = scatter[r] of C as  addend[t, :] + row_scale[t] * (sum + bias).

@@ -330,6 +330,28 @@ def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad)
     _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=2, pad=pad)
 
 
+@pytest.mark.parametrize("d,F", [(520, 2120), (384, 1536), (1024, 2048)])
+def test_fp32_rows_do_not_depend_on_the_batch(d, F):
+    """fp32: a row of a segment has the same bits alone, among a few and among many rows, wherever
+    it lies (one to four row subtiles, all three tile shapes, with and without a K remainder)."""
+    g = torch.Generator(device=DEV).manual_seed(d)
+    E, probe = 3, torch.randn((7, d), generator=g, device=DEV)
+    W1, W2 = (0.05 * torch.randn(s, generator=g, device=DEV) for s in ((E, F, d), (E, d, F)))
+    b1, b2 = (torch.randn(s, generator=g, device=DEV) for s in ((E, F), (E, d)))
+    out = []
+    for lens, at in (([0, 7, 0], 0), ([3, 30, 1], 22), ([40, 50, 60], 33), ([2, 200, 9], 120), ([700, 1500, 800], 777)):
+        rows = sum(lens)
+        x = torch.randn((rows, d), generator=g, device=DEV)
+        x[lens[0] + at:lens[0] + at + 7] = probe
+        offsets = torch.tensor([0] + [sum(lens[:i + 1]) for i in range(E)], dtype=torch.int32, device=DEV)
+        hidden, y = torch.empty((rows, F), device=DEV), torch.empty((rows, d), device=DEV)
+        B.scmoe_expert_ffn(x, offsets, rows, W1, b1, W2, b2, hidden, y)
+        torch.cuda.synchronize()
+        out.append(to_host(y[lens[0] + at:lens[0] + at + 7]))
+    for y in out[1:]:
+        assert np.array_equal(y, out[0])
+
+
 @pytest.mark.parametrize("E,lens,d,F", [
     (4, [700, 1, 511, 129], 512, 1024),          # two workgroups of 128 x 128 tiles per compute unit; then one (three stages)
     (12, [128, 127, 0, 129, 64, 65, 90, 128, 1, 100, 77, 200], 512, 1088),   # few rows per expert: rotated walk over K, N tail
