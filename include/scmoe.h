@@ -401,7 +401,9 @@ int scmoe_layer_forward_offload(const scmoe_desc* desc, const void* x_prev, int6
  * experts from the pool, output decode and merge into y.  Must follow a scmoe_offload_begin
  * with the same desc, weights, pool, host_plan, workspace and streams; between the two calls
  * the caller must leave the workspace, the pool and host_plan alone (they carry the routing
- * and the migrating experts) and must enqueue nothing on stream_copy.  No host synchronisation.
+ * and the migrating experts) and must enqueue nothing on stream_copy; in bf16 with d and F
+ * multiples of 64 also x_prev, which the first GEMM reads again (otherwise its rows have been
+ * copied).  No host synchronisation.
  */
 int scmoe_offload_begin(const scmoe_desc* desc, const void* x_prev, int64_t ld_prev,
                         const scmoe_weights* w, void* expert_pool, int32_t pool_experts,

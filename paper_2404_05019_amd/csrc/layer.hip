@@ -119,6 +119,12 @@ __global__ void set_pair(int32_t* p, int a, int b) {
   }
 }
 
+// The offload calls pack the selected rows in scmoe_offload_begin, so that x_prev is free after it:
+// fp32 and widths that are no multiples of 64.  (The other calls read x_prev again in the first
+// GEMM of scmoe_offload_finish.)  The rows wait where the experts' outputs go later: the second GEMM
+// writes those when the first has read its input.
+static bool offload_packs(const scmoe_desc* D) { return D->dtype != SCMOE_BF16 || !ffn_mfma_supported(D->d, D->F); }
+
 static inline int64_t ld_or(int64_t ld, int64_t dense) { return ld ? ld : dense; }
 
 // Events of the two-stream calls, per host thread and device: fork and join, and in between one
@@ -562,7 +568,8 @@ extern "C" int scmoe_offload_begin(const scmoe_desc* D, const void* x_prev, int6
   SCMOE_TRY(gate_topk(x_prev, ld_prev, D->dtype, W->W_g, W->bias, D->T, D->d, E, D->k, D->normalize,
                       w.expert_idx, w.gate_w, nullptr, sm));
   SCMOE_TRY(dispatch(x_prev, ld_prev, D->dtype, w.expert_idx, D->T, D->d, E, D->k, D->capacity, w.counts,
-                     w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, sm, nullptr));
+                     w.offsets, w.dst_row, w.src_token, offload_packs(D) ? w.y_perm : nullptr, D->d, w.disp_ws,
+                     w.disp_bytes, sm, nullptr));
   hipError_t he = hipMemcpyAsync(host_plan, w.counts, static_cast<size_t>(E) * 4, hipMemcpyDeviceToHost, sm);
   if (he != hipSuccess) return hip_fail(he);
   StreamEvents* ev = nullptr;
@@ -659,9 +666,10 @@ extern "C" int scmoe_offload_finish(const scmoe_desc* D, const void* x_prev, int
   }
   if (m > 0) {
     FfnArgs a{};
-    a.x = x_prev;
-    a.ldx = ld_prev;
-    a.gather = w.src_token;
+    const bool packed = offload_packs(D);
+    a.x = packed ? w.y_perm : x_prev;
+    a.ldx = packed ? D->d : ld_prev;
+    a.gather = packed ? nullptr : w.src_token;
     a.x_rows = D->T;
     a.offsets = w.offsets_c;
     a.max_rows = static_cast<int>(packed_rows(D->T, E, D->k, D->capacity));

@@ -778,13 +778,13 @@ def test_layer_is_deterministic(oracle):
 
 # ------------------------------------------------------------------ expert offloading
 
-def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed):
+def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed, d=128, F=256, dtype="bf16"):
     """Routed experts in pinned host memory, migrated on demand: the same from call to call,
     the resident layer's numbers up to the rounding of a different tile schedule (which tiles
     of a GEMM fall into the split-K tail depends on what shares the launch), and within the
     bar of the oracle."""
-    L = inputs.make_layer(T=T, d=128, F=256, E=E, dtype="bf16", seed=seed, biases=True, w_scale=0.05)
-    D = DevLayer(L, "bf16")
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype=dtype, seed=seed, biases=True, w_scale=0.05)
+    D = DevLayer(L, dtype)
     desc = B.make_desc(T, D.d, D.F, E, k, C_, D.code)
     ws = torch.empty(B.scmoe_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
     # resident reference through the combine path (y in place of a copy of x_cur: no fused decode)
@@ -808,7 +808,7 @@ def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed):
         first = y.clone()
     ref, rr = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=k, capacity_=C_, shared=1,
                                    normalize=0)
-    assert relerr(to_host(y), ref) <= TOL["bf16"]
+    assert relerr(to_host(y), ref) <= TOL[dtype]
     assert np.array_equal(plan[:E].numpy(), rr["counts"])
     # The two halves as calls of their own, with work of the caller on the main stream in between
     # (the window the migration hides in): the same bits as the single call.
@@ -818,6 +818,8 @@ def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed):
     B.scmoe_offload_begin(desc, D.x_prev, wts, pool, pool_experts, plan, ws, async_copy=async_copy,
                           stream_copy=copy_stream)
     filler_b = filler_a @ filler_a
+    if dtype == "f32" or d % 64 or F % 64:               # the selected rows have been copied
+        D.x_prev.fill_(float("nan"))
     B.scmoe_offload_finish(desc, D.x_prev, D.x_cur, wts, pool, pool_experts, plan, y2, ws, async_copy=async_copy,
                            stream_copy=copy_stream)
     torch.cuda.synchronize()
@@ -829,6 +831,8 @@ def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed):
 def test_offload_matches_resident_layer(oracle, async_copy):
     _offload_case(oracle, 700, 4, 1, 300, 4, async_copy, seed=71)
     _offload_case(oracle, 600, 8, 2, 200, 8, async_copy, seed=72)          # ScMoE-2 routing
+    _offload_case(oracle, 300, 4, 1, 60, 4, async_copy, seed=75, d=64, dtype="f32")
+    _offload_case(oracle, 300, 4, 2, 100, 4, async_copy, seed=76, d=72, F=200)
 
 
 def test_offload_decode_step_migrates_only_selected_experts(oracle):
