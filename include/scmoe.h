@@ -125,9 +125,9 @@ int scmoe_last_hip_error(void);
  * 0 (default) = chosen per launch: 256x256x64 tiles, 8 waves, 2 LDS stages; 128x128x64 tiles,
  * 4 waves, for few rows per expert and for problems that the larger tiles would not spread over
  * all compute units; small products take a kernel without tiles in LDS.  1 = always 256x256x32,
- * 8 waves, 4 stages; 2 = always 128x128x32; 3 = always 128x128x64 with 3 stages (where the tiled
- * kernel is used at all: not in fp32, at widths that are no multiples of 64, for at most 64 rows,
- * or for at most 16 rows per expert and 1024 in all).
+ * 8 waves, 4 stages; 2 = always 128x128x64, 2 stages, two workgroups per compute unit; 3 = always
+ * 128x128x64 with 3 stages (where the tiled kernel is used at all: not in fp32, at widths that are
+ * no multiples of 64, for at most 64 rows, or for at most 16 rows per expert and 1024 in all).
  * Results agree to bf16 rounding of the same fp32 sums; only speed differs.  Other values
  * give SCMOE_ERR_ARG. */
 int scmoe_set_gemm_variant(int32_t variant);

@@ -638,7 +638,6 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 
 using CfgA = TileCfg<256, 256, 64, 2, 4, 2>;   // 8 waves, 128 KiB LDS, one workgroup per CU
 using CfgB = TileCfg<256, 256, 32, 2, 4, 4>;   // 8 waves, 4 stages, 128 KiB LDS
-using CfgS = TileCfg<128, 128, 32, 1, 2, 2>;   // 2 waves, 40 KiB LDS, four workgroups per CU
 using CfgT = TileCfg<128, 128, 64, 2, 2, 3>;   // 4 waves of 64 x 64, 104 KiB LDS, one workgroup per CU: fewer 128 x 128 tiles than CUs
 using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
@@ -740,7 +739,7 @@ template <bool ACT>
 static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipStream_t stream) {
   switch (gemm_variant()) {
     case 1: return launch_gemm<CfgB, ACT>(a, max_rows, a_rows, stream);
-    case 2: return launch_gemm<CfgS, ACT>(a, max_rows, a_rows, stream);
+    case 2: return launch_gemm<CfgU, ACT>(a, max_rows, a_rows, stream);
     case 3: return launch_gemm<CfgT, ACT>(a, max_rows, a_rows, stream);
     default: break;
   }

@@ -422,7 +422,7 @@ def test_layer_decode_batches(oracle, T, E, k, C_, shared, cg, res):
 def test_expert_ffn_random_segments(oracle, seed):
     """Seeded sweep of the MFMA grouped GEMM: 1-10 segments of 0-700 rows (empty ones
     included), widths in multiples of 64, dense or padded strides, with and without the
-    split-K workspace, both GELU forms, both tile variants."""
+    split-K workspace, both GELU forms, every tile variant."""
     rng = np.random.default_rng(9000 + seed)
     E = int(rng.integers(1, 11))
     lens = [int(v) for v in rng.integers(0, 701, E) * (rng.random(E) > 0.2)]
@@ -440,7 +440,7 @@ def test_expert_ffn_split_k_tail(oracle):
     """Tiles are cut along K from K = 2048 on, when a workspace is given and the last round of
     workgroups is partly filled.  Here both GEMMs have K = 2048 and 296 tiles of 256 x 256 (37
     per XCD on 32 workgroups: 32 whole tiles, then 5 tiles in 6 parts each, added up by finish
-    items at the end of the launch); with 128 x 128 tiles 144 per XCD on 128 workgroups.  Every
+    items at the end of the launch); with 128 x 128 tiles 144 per XCD on 64 or 32 workgroups.  Every
     element compared with the oracle, for every tile configuration; identical from run to run;
     the workspace may hold anything on entry; and close to the call without a workspace."""
     E, lens, d, F = 3, [4000, 300, 4700], 2048, 2048
