@@ -43,6 +43,19 @@ def assert_routing_equal(g, r, w_tol=1e-6):
     assert np.abs(g["w"].astype(np.float64) - r["w"].astype(np.float64)).max() <= w_tol
 
 
+def tiled_chains(T, d, F, E, k, C_, shared=True, dtype="bf16"):
+    """Which chains of a layer the tiled GEMM kernel runs: (shared expert, routed experts).  The
+    others take the kernel without LDS tiles.  Tests that are about one of them assert it."""
+    if dtype != "bf16" or d % 64 or F % 64:
+        return (False, False)
+    rows = min(T * k, E * C_)
+    total = rows + (T if shared else 0)
+    mean = (total + 1) // 2 if shared else rows
+    large = mean * d * F > 5e8 or (total * (d + F) > 2.2e6 and (d >= 128 or F >= 128))
+    few = lambda n, e: n <= 64 or (n <= 16 * e and n <= 1024)  # noqa: E731
+    return (shared and large and not few(T, 1), large and not few(rows, E))
+
+
 def stratified_tokens(rr, T, E, seed, block=128):
     """Tokens chosen so that every tile of both GEMM chains is compared: one seeded row out of
     every `block` consecutive token rows (the shared expert's row tiles) and out of every

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     from paper_2404_05019_amd import binding as B
     from gpu_util import (DEV, TOL, DevLayer, assert_close, assert_routing_equal, relerr, run_layer,
-                          stratified_tokens, to_dev, to_host)
+                          stratified_tokens, tiled_chains, to_dev, to_host)
 
 
 def _i32(n, fill=None):
@@ -294,18 +294,17 @@ def test_expert_ffn_many_tiles(oracle, E, lens, d, F, workspace):
     (2, [17, 15], 1024, 576, True, 0, False),               # two row subtiles, several k chunks
     (3, [16, 0, 16], 256, 1088, False, 0, True),
     (16, [2, 0, 0, 1, 0, 3, 0, 0, 1, 0, 0, 0, 0, 0, 0, 1], 512, 2048, True, 0, False),
-    (16, [100, 3, 0, 0, 17, 64, 1, 0, 0, 0, 0, 0, 0, 0, 0, 40], 256, 576, True, 0, False),   # 64-row blocks
+    (16, [100, 3, 0, 0, 17, 64, 1, 0, 0, 0, 0, 0, 0, 0, 0, 40], 256, 576, True, 0, False),   # segments of many lengths
     (8, [0, 65, 0, 0, 16, 33, 0, 14], 128, 320, True, 1, True),
     (64, [5] * 64, 64, 192, False, 0, False),
-    (2, [40, 24], 1024, 576, True, 0, False),               # 33-64 rows in all: 64-row blocks, cut along K
+    (2, [40, 24], 1024, 576, True, 0, False),               # 33-64 rows in all
     (1, [50], 256, 2048, True, 1, True),
-    # the widths of a decode step of the large workload: many parts along K, whose last one to
-    # arrive adds them up
+    # the widths of a decode step of the large workload
     (1, [33], 2048, 8192, True, 0, False), (1, [64], 2048, 8192, False, 0, False), (2, [20, 12], 2048, 4096, True, 0, False)])
 @pytest.mark.parametrize("workspace", [False, True])
 def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, workspace):
     """Calls of at most 64 rows, or of segments averaging at most 16 rows (decode steps), take
-    the weight-streaming kernel; with a workspace the small ones are cut along K."""
+    the kernel without LDS tiles, which uses no workspace: it may be there or not."""
     _ffn_case(oracle, E, lens, d, F, "bf16", biases, gelu_mode, extra_rows=0, pad=pad, workspace=workspace)
 
 
@@ -367,7 +366,10 @@ def test_expert_ffn_medium_tiles(oracle, E, lens, d, F, workspace):
 
 @pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams", [
     (600, 512, 2048, 16, 1, 600, 0, False, False),     # 65-128 rows per segment: one second GEMM, then combine
-    (600, 512, 2048, 16, 1, 30, 2, True, False),       # ... with drops, a coefficient gate and the residual
+    (600, 512, 2048, 16, 1, 34, 2, True, False),       # ... with drops, a coefficient gate and the residual
+    (1500, 512, 1536, 8, 1, 1500, 0, False, False),    # F < 2048 and few tiles: the same form
+    (1500, 512, 1536, 8, 1, 150, 1, True, False),      # ... with drops, a coefficient gate and the residual
+    (1500, 512, 1536, 8, 1, 150, 2, True, True),       # two streams: fused decodes, tiles not cut along K
     (500, 640, 2048, 24, 1, 500, 0, False, True),      # fewer rows, two streams: fused decode behind 128-row tiles
     (1400, 256, 2048, 4, 1, 320, 1, True, False),      # tiles cut along K with fused decodes
     (1400, 256, 2048, 4, 1, 100000, 0, False, True),
@@ -375,9 +377,14 @@ def test_expert_ffn_medium_tiles(oracle, E, lens, d, F, workspace):
     (700, 384, 2112, 8, 3, 100000, 1, True, False)])   # ... whose last round of tiles may be cut along K
 def test_layer_medium_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
     """Layers above the direct kernel's limit, through the launches that both chains share."""
+    assert tiled_chains(T, d, F, E, k, C_) == (True, True)
+    if E == 16:                                        # one second GEMM for both chains
+        assert 64 * (E + 1) < T + min(T * k, E * C_) <= 128 * (E + 1)
     L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=700 + E + k, biases=True, cg_rows=cg, w_scale=0.03)
     y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, True, int(k > 1), cg, 0, res, two_streams=two_streams)
     assert_close(y, ref, "bf16")
+    if C_ < T // E:
+        assert (r["dst_row"] < 0).any()
 
 
 @pytest.mark.parametrize("dtype,d,F", [("f32", 72, 200), ("bf16", 128, 256), ("bf16", 512, 1024)])
@@ -409,7 +416,8 @@ def test_non_finite_values_stay_in_their_rows(dtype, d, F):
     (12, 4, 2, 5, True, 2, False), (100, 8, 1, 100, True, 0, False), (64, 16, 2, 9, False, 0, False),
     (250, 16, 1, 250, True, 0, False), (48, 8, 1, 48, True, 0, False), (64, 4, 1, 20, True, 1, False)])
 def test_layer_decode_batches(oracle, T, E, k, C_, shared, cg, res):
-    """Layers of a few tokens (per-token decoding, Sec. 5.3): every GEMM has at most 32 rows."""
+    """Layers of a few tokens (per-token decoding, Sec. 5.3): the kernel without LDS tiles."""
+    assert not any(tiled_chains(T, 256, 512, E, k, C_, shared))
     L = inputs.make_layer(T=T, d=256, F=512, E=E, dtype="bf16", seed=300 + T, biases=True, cg_rows=cg,
                           w_scale=0.05)
     _layer_case(oracle, L, "bf16", E, k, C_, shared, normalize=int(k > 1), cg_mode=cg, residual=res)
@@ -487,6 +495,7 @@ def test_expert_ffn_tile_variants(oracle, variant):
     try:
         _ffn_case(oracle, 3, [300, 77, 517], 256, 384, "bf16", True, 0)
         _ffn_case(oracle, 1, [1000], 128, 512, "bf16", False, 0)
+        _ffn_case(oracle, 3, [900, 77, 1517], 256, 1024, "bf16", True, 0)       # tiled in variant 0 too
     finally:
         B.scmoe_set_gemm_variant(0)
 
@@ -553,15 +562,18 @@ def test_layer_tiny_config(oracle, two_streams):
     assert cfg["C"] == 80 and int(r["offsets"][-1]) == int((r["dst_row"] >= 0).sum())
 
 
+@pytest.mark.parametrize("T,d,F", [(700, 128, 256), (1000, 512, 2048)])       # direct, tiled
 @pytest.mark.parametrize("k,shared,C_,normalize,cg,res,gelu", [
     (1, True, 200, 0, 0, False, 0), (1, True, 100000, 0, 1, True, 0), (1, True, 150, 0, 2, False, 1),
     (2, False, 300, 1, 0, False, 0), (2, False, 100000, 0, 0, False, 0), (1, False, 0, 0, 0, False, 0),
     (1, True, 0, 1, 0, False, 0), (3, False, 450, 1, 0, False, 0), (3, False, 100000, 0, 0, False, 1),
     (4, False, 600, 1, 0, False, 0), (3, True, 450, 1, 1, False, 0)])
-def test_layer_bf16_mfma_path(oracle, k, shared, C_, normalize, cg, res, gelu):
-    """bf16 layer on the MFMA path with gather-on-load: ragged T, binding capacity, drops."""
-    L = inputs.make_layer(T=700, d=128, F=256, E=4, dtype="bf16", seed=11 + k, biases=True, cg_rows=cg,
-                          w_scale=0.05)
+def test_layer_bf16_mfma_path(oracle, T, d, F, k, shared, C_, normalize, cg, res, gelu):
+    """bf16 layer with gather-on-load through both GEMM kernels: ragged T, binding capacity, drops."""
+    if C_ > 0:
+        assert tiled_chains(T, d, F, 4, k, C_, shared) == ((shared, True) if d == 512 else (False, False))
+    L = inputs.make_layer(T=T, d=d, F=F, E=4, dtype="bf16", seed=11 + k, biases=True, cg_rows=cg,
+                          w_scale=0.05 if d == 128 else 0.03)
     y, r, ref, rr = _layer_case(oracle, L, "bf16", 4, k, C_, shared, normalize, cg, gelu, res, two_streams=shared,
                                 pad_weights=(C_ == 200 or C_ == 300))
     if shared and cg == 0 and not res:
@@ -573,22 +585,23 @@ def test_layer_bf16_mfma_path(oracle, k, shared, C_, normalize, cg, res, gelu):
 
 
 @pytest.mark.parametrize("k,shared,C_,cg,res,two_streams", [
-    (1, True, 160, 0, False, False),      # routed second GEMM decodes (scatter, gate weight, add) in finish items
-    (1, True, 150, 2, True, False),       # ... and so does the shared expert's (its coefficient, the residual)
+    (1, True, 320, 0, False, False),      # routed second GEMM decodes (scatter, gate weight, add) in finish items
+    (1, True, 300, 2, True, False),       # ... and so does the shared expert's (its coefficient, the residual)
     (1, True, 100000, 1, False, True),    # two streams
-    (1, False, 150, 0, False, False),     # standard top-1 layer: decode with nothing below
-    (2, True, 300, 0, False, False)])     # two routed items per token: plain second GEMMs, combine kernel
+    (1, False, 300, 0, False, False),     # standard top-1 layer: decode with nothing below
+    (2, True, 600, 0, False, False)])     # two routed items per token: plain second GEMMs, combine kernel
 def test_layer_tiles_cut_along_k(oracle, k, shared, C_, cg, res, two_streams):
     """A layer whose second GEMMs have K = F = 2048 and only a handful of tiles, so that every
     tile is cut along K and written by finish items: the fused output decodes (scatter and gate
     weight of the routed rows, coefficient and residual of the shared expert's rows) in that
     path.  Every row compared with the oracle."""
-    L = inputs.make_layer(T=700, d=256, F=2048, E=4, dtype="bf16", seed=31 + k + cg, biases=True, cg_rows=cg,
+    assert tiled_chains(1400, 256, 2048, 4, k, C_, shared) == (shared, True)
+    L = inputs.make_layer(T=1400, d=256, F=2048, E=4, dtype="bf16", seed=31 + k + cg, biases=True, cg_rows=cg,
                           w_scale=0.03)
     y, r, ref, rr = _layer_case(oracle, L, "bf16", 4, k, C_, shared, 0 if k == 1 else 1, cg, 0, res,
                                 two_streams=two_streams)
     assert_close(y, ref, "bf16")
-    if C_ < 700:
+    if C_ < 1400:
         assert (r["dst_row"] < 0).any()
 
 
@@ -640,13 +653,15 @@ def test_shared_expert_moe_is_scmoe_with_equal_inputs(oracle):
     _layer_case(oracle, L, "bf16", 4, 1, 200, True)
 
 
-def test_layer_in_place_output(oracle):
+@pytest.mark.parametrize("T,d,F,C_", [(900, 128, 256, 300), (1400, 256, 2048, 400)])       # direct, tiled
+def test_layer_in_place_output(oracle, T, d, F, C_):
     """y may be the same buffer as x_cur: the layer then must not write y before it has read
     its inputs (the fused decode is skipped for overlapping buffers)."""
-    L = inputs.make_layer(T=900, d=128, F=256, E=4, dtype="bf16", seed=61, biases=True, w_scale=0.05)
+    assert tiled_chains(T, d, F, 4, 1, C_) == (d == 256,) * 2
+    L = inputs.make_layer(T=T, d=d, F=F, E=4, dtype="bf16", seed=61, biases=True, w_scale=0.05 if d == 128 else 0.03)
     D = DevLayer(L, "bf16")
-    ref, rr = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=300, shared=1)
-    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, 300, D.code)
+    ref, rr = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1)
+    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, C_, D.code)
     ws = torch.empty(B.scmoe_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
     y = D.x_cur.clone()
     B.scmoe_layer_forward(desc, D.x_prev, y, D.weights, y, ws)
@@ -659,15 +674,18 @@ def test_layer_in_place_output(oracle):
     assert relerr(to_host(y2), to_host(y)) <= 1e-2
 
 
+@pytest.mark.parametrize("T,d,F,C_", [(900, 128, 256, 300), (1400, 256, 2048, 400)])       # direct, tiled
 @pytest.mark.parametrize("cg", [0, 1, 2])
-def test_layer_output_in_place_of_the_residual(oracle, cg):
+def test_layer_output_in_place_of_the_residual(oracle, T, d, F, C_, cg):
     """y may be the residual's buffer (y = layer(x) + y): the fused decode of the residual and
     coefficient-gate forms is skipped then; with a buffer of its own it runs, same result."""
-    L = inputs.make_layer(T=900, d=128, F=256, E=4, dtype="bf16", seed=62 + cg, biases=True, cg_rows=cg, w_scale=0.05)
+    assert tiled_chains(T, d, F, 4, 1, C_) == (d == 256,) * 2
+    L = inputs.make_layer(T=T, d=d, F=F, E=4, dtype="bf16", seed=62 + cg, biases=True, cg_rows=cg,
+                          w_scale=0.05 if d == 128 else 0.03)
     D = DevLayer(L, "bf16")
-    ref, rr = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=300, shared=1, cg_mode=cg,
+    ref, rr = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1, cg_mode=cg,
                                    add_residual=1)
-    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, 300, D.code, 0, 0, cg)
+    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, C_, D.code, 0, 0, cg)
     ws = torch.empty(B.scmoe_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
     y = D.x_cur.clone()
     B.scmoe_layer_forward(desc, D.x_prev, D.x_cur, D.weights, y, ws, residual=y)
@@ -680,23 +698,29 @@ def test_layer_output_in_place_of_the_residual(oracle, cg):
     assert relerr(to_host(y2), to_host(y)) <= 1e-2
 
 
-@pytest.mark.parametrize("seed", range(24))
+@pytest.mark.parametrize("seed", range(40))
 def test_layer_random_configurations(oracle, seed):
-    """Seeded sweep over shapes and options: widths on and off the MFMA path (multiples of 64
-    or not), 1 to 12 experts, k up to 4, binding and loose capacities, both dtypes, both layer
-    kinds, every merge mode."""
+    """Seeded sweep over shapes and options: widths that are multiples of 64 or not, 1 to 12
+    experts, k up to 4, binding and loose capacities, both dtypes, both layer kinds, every merge
+    mode.  Up to seed 23 nearly all through the kernel without LDS tiles, from 24 on the tiled one."""
     rng = np.random.default_rng(7000 + seed)
-    dtype = "bf16" if seed % 3 else "f32"
-    mfma = dtype == "bf16" and seed % 2 == 0
+    tiled = seed >= 24
+    dtype = "bf16" if seed % 3 or tiled else "f32"
+    mfma = dtype == "bf16" and seed % 2 == 0 or tiled
     step = 64 if mfma else 8
     d = step * int(rng.integers(1, 7 if mfma else 20))
     F = step * int(rng.integers(1, 9 if mfma else 24))
     T = int(rng.integers(1, 900))
+    if tiled:
+        d, F, T = 64 * int(rng.integers(3, 11)), 64 * int(rng.integers(14, 40)), int(rng.integers(1700, 2600))
     E = int(rng.integers(1, 13))
     k = int(rng.integers(1, min(E, 4) + 1))
     shared = bool(rng.integers(0, 2))
     cg = int(rng.integers(0, 3)) if shared else 0
     C_ = int(rng.choice([0, 1, max(1, T * k // (2 * E)), -(-T * k // E), T * k]))
+    if tiled:
+        C_ = max(C_, -(-T * k // (2 * E)))
+        assert tiled_chains(T, d, F, E, k, C_, shared) == (shared, True)
     L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype=dtype, seed=7100 + seed, biases=bool(rng.integers(0, 2)),
                           cg_rows=cg, w_scale=0.05 if dtype == "bf16" else 0.1,
                           zipf=1.2 if seed % 5 == 0 else None)
@@ -707,9 +731,8 @@ def test_layer_random_configurations(oracle, seed):
 
 @pytest.mark.parametrize("seed", range(20))
 def test_layer_random_small_batches(oracle, seed):
-    """Seeded sweep over decode-size calls on the MFMA widths: 1 to 300 tokens, 1 to 64 experts,
-    k up to 4: the few-row GEMM in its three forms (32-row and 64-row blocks, cut along K or
-    not), the per-chain gate, the tiled GEMM with 128-row tiles and forced split-K."""
+    """Seeded sweep over decode-size calls at multiples of 64: 1 to 300 tokens, 1 to 64 experts,
+    k up to 4: the kernel without LDS tiles in its tile shapes, the per-chain gate."""
     rng = np.random.default_rng(8000 + seed)
     T = int(rng.choice([1, 2, 7, 16, 31, 32, 33, 48, 64, 65, 100, 129, 200, 300]))
     E = int(rng.choice([1, 2, 3, 8, 16, 40, 64]))
@@ -725,15 +748,17 @@ def test_layer_random_small_batches(oracle, seed):
                 two_streams=shared and bool(rng.integers(0, 2)), pad_weights=bool(rng.integers(0, 2)))
 
 
+@pytest.mark.parametrize("T,d,F,C_", [(700, 128, 256, 200), (1400, 256, 2048, 400)])       # direct; tiled, cut along K
 @pytest.mark.parametrize("two_streams", [False, True])
-def test_layer_in_a_hip_graph(oracle, two_streams):
+def test_layer_in_a_hip_graph(oracle, T, d, F, C_, two_streams):
     """The layer call makes no host synchronisation, allocates nothing and clears its
     counters with a kernel, so a caller can capture it in a HIP graph.  The graph is replayed
     on changing inputs with eager work and synchronisations in between; every replay must give
     the bits of the eager call on the same inputs."""
-    L = inputs.make_layer(T=700, d=128, F=256, E=4, dtype="bf16", seed=77, biases=True, w_scale=0.05)
+    assert tiled_chains(T, d, F, 4, 1, C_) == (d == 256,) * 2
+    L = inputs.make_layer(T=T, d=d, F=F, E=4, dtype="bf16", seed=77, biases=True, w_scale=0.05 if d == 128 else 0.03)
     D = DevLayer(L, "bf16")
-    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, 200, D.code)
+    desc = B.make_desc(D.T, D.d, D.F, D.E, 1, C_, D.code)
     ws = torch.empty(B.scmoe_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
     ws_eager = torch.empty_like(ws)
     xp, xc = D.x_prev.clone(), D.x_cur.clone()
@@ -745,7 +770,7 @@ def test_layer_in_a_hip_graph(oracle, two_streams):
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         B.scmoe_layer_forward(desc, xp, xc, D.weights, y, ws, stream_aux=aux)
-    ref, _ = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=200, shared=1)
+    ref, _ = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1)
     for rep in range(4):
         if rep:
             xp.copy_(torch.roll(D.x_prev, rep, 0))
@@ -760,11 +785,13 @@ def test_layer_in_a_hip_graph(oracle, two_streams):
             assert relerr(to_host(y), ref) <= TOL["bf16"]
 
 
-def test_layer_is_deterministic(oracle):
+@pytest.mark.parametrize("d,F", [(128, 256), (256, 2048)])       # direct; tiled, cut along K
+def test_layer_is_deterministic(oracle, d, F):
     """The same call gives the same bits every time.  One- and two-stream mode launch the
-    GEMMs differently (which tiles end up in a split-K tail differs), so across the modes the
-    routing is identical and the output equal up to that rounding."""
-    L = inputs.make_layer(T=3000, d=128, F=256, E=8, dtype="bf16", seed=41, w_scale=0.05)
+    GEMMs and merge differently (which tiles end up in a split-K tail, where an expert's row is
+    rounded), so across the modes the routing is identical and the output equal up to that rounding."""
+    assert tiled_chains(3000, d, F, 8, 1, 300) == (d == 256,) * 2
+    L = inputs.make_layer(T=3000, d=d, F=F, E=8, dtype="bf16", seed=41, w_scale=0.05 if d == 128 else 0.03)
     D = DevLayer(L, "bf16")
     outs = [run_layer(D, 1, 300, True, two_streams=(i % 2 == 1)) for i in range(4)]
     for i, (y, r) in enumerate(outs[1:], 1):
@@ -831,6 +858,7 @@ def _offload_case(oracle, T, E, k, C_, pool_experts, async_copy, seed, d=128, F=
 def test_offload_matches_resident_layer(oracle, async_copy):
     _offload_case(oracle, 700, 4, 1, 300, 4, async_copy, seed=71)
     _offload_case(oracle, 600, 8, 2, 200, 8, async_copy, seed=72)          # ScMoE-2 routing
+    _offload_case(oracle, 1400, 4, 1, 400, 4, async_copy, seed=77, d=256, F=2048)      # tiled, cut along K
     _offload_case(oracle, 300, 4, 1, 60, 4, async_copy, seed=75, d=64, dtype="f32")
     _offload_case(oracle, 300, 4, 2, 100, 4, async_copy, seed=76, d=72, F=200)
 

@@ -3,7 +3,9 @@ HIP runtime (in a child process), and the order that streams and events give the
 worked out from what it wrote down."""
 import ctypes as C
 import json
+import math
 import os
+import random
 import subprocess
 import sys
 
@@ -124,6 +126,26 @@ def test_small_products_take_the_direct_kernel_and_many_rows_the_tiled_one(recor
             kernels, _ = _order(lines)
             gemms = _at(kernels, "gemm_")
             assert st == 0 and gemms and _at(kernels, want) == gemms, c
+
+
+def test_tiled_chains_of_the_test_helper_is_the_library_s_rule(record):
+    """The rule as gpu_util states it for the GPU tests, against the kernels the library launches."""
+    from gpu_util import tiled_chains
+    rng = random.Random(3)
+    calls = []
+    for _ in range(300):
+        T, E = int(math.exp(rng.uniform(0, math.log(40000)))), rng.choice([1, 2, 4, 8, 16, 64])
+        d, F = (rng.choice([64, 64, 128, 256, 512, 1024, 2048]) for _ in range(2))
+        calls.append(_layer(T, d, F, E, rng.randint(1, min(E, 4))))
+        calls[-1]["capacity"] = rng.choice([10, max(1, T // E), T * calls[-1]["k"]])
+    seen = set()
+    for c, (st, lines) in zip(calls, record(calls)):
+        kernels, _ = _order(lines)
+        ran = {n for n in ("gemm_bf16_kernel", "gemm_direct_kernel") if _at(kernels, n)}
+        want = tiled_chains(c["T"], c["d"], c["F"], c["E"], c["k"], c["capacity"])
+        assert st == 0 and ran == {"gemm_bf16_kernel" if t else "gemm_direct_kernel" for t in want}, c
+        seen.add(want)
+    assert seen >= {(False, False), (True, True), (True, False)}
 
 
 def test_no_launch_passes_the_limit_on_work_items(record):
