@@ -339,8 +339,10 @@ int scmoe_workspace_bytes(const scmoe_desc* desc, size_t* out);
  * memory is allocated and no memset is enqueued, so the call can be captured in a HIP graph
  * (after one ordinary call on the device, which creates the events and sets kernel attributes).
  * Reproducibility: the routing is the same in every mode; y is the same bits for the same
- * call repeated, but one- and two-stream calls may differ in the last bit (the tiles of a
- * GEMM that are cut along K depend on what shares its launch).
+ * call repeated.  One- and two-stream calls agree up to the rounding of the stored type, not bit
+ * for bit: they may merge differently (fused decode, or the two FFN outputs stored and then
+ * combined: where an expert's row is rounded differs), and the tiles of a GEMM that are cut along
+ * K depend on what shares its launch.
  */
 int scmoe_layer_forward(const scmoe_desc* desc, const void* x_prev, int64_t ld_prev,
                         const void* x_cur, int64_t ld_cur, const scmoe_weights* w,

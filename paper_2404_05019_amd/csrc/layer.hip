@@ -419,8 +419,8 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // combine kernel (layer us, two launches / one):
   //  * both chains direct (few tiles each);
   //  * F < 2048 (tiles are not cut along K) and the 128 x 128 tiles of both fit two workgroups per
-  //    compute unit at once (8192 tokens, d = 384: 96 / 90.5; 4000, d = 256: 59 / 47; 2500, d = 640:
-  //    83 / 70; with more tiles 0.99 to 1.04);
+  //    compute unit at once (8192 tokens, d = 384: 97.7 / 90.8; 4000, d = 256: 57.9 / 47.2; 2500,
+  //    d = 640: 80.4 / 68.0; with more tiles 0.99 to 1.04);
   //  * 65 to 128 rows per segment (d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens
   //    501 / 496; at 500 tokens 328 / 342: the shared expert's tiles alone are cut along K).
   const size_t eb = elem_bytes(D->dtype);

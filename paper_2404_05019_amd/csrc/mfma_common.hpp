@@ -12,7 +12,6 @@ namespace scmoe {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 #define SCMOE_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -114,27 +113,16 @@ __device__ __forceinline__ void mfma_results_settle() {
 
 // 16-byte store / loads at device scope (sc1: past the caches that are not shared by the whole
 // device), for data handed from one workgroup to another inside a kernel.  The store is not
-// waited for here (follow it with a vmcnt(0) wait before publishing); the load reads four
-// pieces 1 KiB apart and returns when they have arrived.
+// waited for here (follow it with a vmcnt(0) wait before publishing); the loads return when they
+// have arrived.
 __device__ __forceinline__ void store16_device_scope(float* p, f32x4_t v) {
   // (the wait state after it: a store of more than 8 bytes per lane still reads its data
   // registers when the next instruction issues, and the compiler, which keeps that hazard for
   // its own stores, does not know that this is one)
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ void load4x16_device_scope(const float* p, f32x4_t& a, f32x4_t& b, f32x4_t& c, f32x4_t& d) {
-  asm volatile(
-      "global_load_dwordx4 %0, %4, off sc1\n\t"
-      "global_load_dwordx4 %1, %4, off offset:1024 sc1\n\t"
-      "global_load_dwordx4 %2, %4, off offset:2048 sc1\n\t"
-      "global_load_dwordx4 %3, %4, off offset:3072 sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-      : "v"(p)
-      : "memory");
-}
 
-// Sixteen such loads in flight at once: four pieces 1 KiB apart from each of four bases.  (The
+// Sixteen loads in flight at once: four pieces 1 KiB apart from each of four bases.  (The
 // reader of split-K partial sums has nothing to overlap a round trip to memory with: what
 // counts is how few round trips it makes.)
 __device__ __forceinline__ void load16x16_device_scope(const float* p0, const float* p1, const float* p2,
