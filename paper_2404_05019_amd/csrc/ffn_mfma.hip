@@ -753,7 +753,10 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // column tiles start their walk over K at different places (rotk): in step, with rows a power
   // of two apart, they would all be at the same few memory channels.  Measured, layer call at
   // d = 2048, F = 8192, E = 16: 500 tokens 0.383 -> 0.331 ms, 1000 tokens 0.451 -> 0.364; at 2000
-  // tokens (125 rows per expert) equal to the large tiles, above that those win.
+  // tokens (125 rows per expert) equal to the large tiles, above that those win.  At other widths and
+  // expert counts only against the smaller tiles before these: 500 tokens, d = 1024, F = 2048, E = 64
+  // 0.216 -> 0.191; 3000, d = 1024, F = 4096, E = 32 0.294 -> 0.257; between 129 and 320 rows per segment
+  // the two have not been compared.
   const bool few_rows = rows <= 128 * segs;
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;

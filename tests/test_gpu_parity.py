@@ -748,7 +748,8 @@ def test_layer_random_small_batches(oracle, seed):
                 two_streams=shared and bool(rng.integers(0, 2)), pad_weights=bool(rng.integers(0, 2)))
 
 
-@pytest.mark.parametrize("T,d,F,C_", [(700, 128, 256, 200), (1400, 256, 2048, 400)])       # direct; tiled, cut along K
+@pytest.mark.parametrize("T,d,F,C_", [(700, 128, 256, 200), (1400, 256, 2048, 400),        # direct; tiled, cut along K
+                                      (700, 128, 256, 0)])                                 # nothing kept
 @pytest.mark.parametrize("two_streams", [False, True])
 def test_layer_in_a_hip_graph(oracle, T, d, F, C_, two_streams):
     """The layer call makes no host synchronisation, allocates nothing and clears its
