@@ -3,7 +3,6 @@
  * process without a GPU, it shows the launches of a library call, their grids and their order. */
 #include <stdint.h>
 #include <stdio.h>
-#include <string.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
 
@@ -49,8 +48,8 @@ int hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** args, size_t lds, 
   return 0;
 }
 int hipMemcpyAsync(void* dst, const void* src, size_t bytes, int kind, void* stream) {
+  (void)kind;
   LOG("copy %p %p %p %zu\n", stream, dst, src, bytes);
-  if (kind == 2) memset(dst, 0, bytes);               /* device to host: a buffer of the caller */
   return 0;
 }
 int hipEventCreateWithFlags(void** e, unsigned flags) {
