@@ -75,6 +75,13 @@ struct ScanChores {
   int* zero_a = nullptr;
   int* zero_b = nullptr;
   int nzero = 0;
+  // For the joint second GEMM (one-launch dispatch, k = 1; token_of == nullptr: off): all tokens in
+  // the packed order, those without a row behind the others in ascending order; the gate weight
+  // of every packed row; and offsets with T as one more entry.
+  int32_t* token_of = nullptr;
+  float* row_gate = nullptr;
+  const float* gate_w = nullptr;
+  int32_t* joint_offsets = nullptr;
 };
 
 // ---- entry points implemented in one source and used by the layer orchestration --------
@@ -101,6 +108,10 @@ struct FfnArgs {
   // which the first is used, either pointer optional:
   //   y[r, :] = addend[r, :] + row_scale[2 r] * (W2 . hidden[r] + b2)
   const int32_t* scatter; const float* row_scale; const void* addend; int64_t ldadd;
+  // In the routed call of ffn_forward_pair: both second GEMMs as one product (GemmArgs::A2), over the
+  // E + 1 segments of joint_offsets; scatter: the tokens in packed order, which is also the gather
+  // array of the shared call; row_scale: per packed row.
+  const int32_t* joint_offsets;
   // Scratch of the tiled path (split-K of the last round of tiles); may be nullptr: no split.
   void* scratch; size_t scratch_bytes;
   bool scratch_zeroed;             // the arrival counters at the start of scratch are zero already
@@ -126,6 +137,7 @@ inline int64_t padded_ld(int64_t width, int dtype) {
   return ((width * eb) % 512 == 0) ? width + 128 / eb : width;
 }
 bool ffn_mfma_supported(int d, int F);
+bool ffn_joint_second_fits(int T, int d, int F, int E, int64_t ldh, int64_t ldw2);   // sizes that the joint second GEMM takes
 size_t ffn_mfma_scratch_bytes();   // scratch the tiled path can use (16-byte aligned)
 int ffn_mfma_counter_ints();       // ints at the start of that scratch that must be zero before a call
 

@@ -172,6 +172,8 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
   __shared__ int tot_s[64];        // items of expert e in the whole call
   __shared__ int seg[64];          // offsets[e]
   __shared__ int bef[64];          // items of expert e before this block
+  __shared__ int kept_s[2];        // joint second GEMM: rows kept in the whole call, and of items before this block
+  __shared__ int wdrop[NW];        // ... dropped items of each wave
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -321,6 +323,13 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
       }
       bef[lane] = bb;
     }
+    if (K == 1 && ch.token_of != nullptr) {
+      if constexpr (NIB) bb = lane < E ? bef[lane] : 0;
+      int kept = lane < E ? (bb < capacity ? bb : capacity) : 0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) kept += __shfl_xor(kept, off, 64);
+      if (lane == 0) kept_s[1] = kept;
+    }
     const int c = (lane < E) ? (tt < capacity ? tt : capacity) : 0;
     int incl = c;
 #pragma unroll
@@ -329,10 +338,18 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
       if (lane >= off) incl += up;
     }
     seg[lane] = incl - c;
+    if (lane == 63) kept_s[0] = incl;
     if (blockIdx.x == 0 && lane < E) {
       counts[lane] = c;
       offsets[lane] = incl - c;
       if (lane == E - 1) offsets[E] = incl;
+      if (K == 1 && ch.token_of != nullptr) {
+        ch.joint_offsets[lane] = incl - c;
+        if (lane == E - 1) {
+          ch.joint_offsets[E] = incl;
+          ch.joint_offsets[E + 1] = T;
+        }
+      }
     }
   } else if (wave == 1) {
     int run = 0;                                   // exclusive prefix of the own-vector counts over the waves
@@ -344,8 +361,8 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
     }
   }
   __syncthreads();
+  int out = -1;
   if (i < n) {
-    int out = -1;
     if (e >= 0) {
       const int slot = bef[e] + wown[wave][e] + rank;
       if (slot < capacity) {
@@ -354,6 +371,20 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
       }
     }
     dst_row[static_cast<int64_t>(t) * k + j] = out;
+  }
+  if (K == 1 && ch.token_of != nullptr) {          // (uniform over the launch)
+    const unsigned long long drop = __ballot(i < n && out < 0);
+    if (lane == 0) wdrop[wave] = __popcll(drop);
+    __syncthreads();
+    if (i < n) {
+      if (out >= 0) {
+        ch.row_gate[out] = ch.gate_w[i];
+      } else {
+        out = kept_s[0] + (i0 - kept_s[1]) + __popcll(drop & below);
+        for (int w = 0; w < wave; ++w) out += wdrop[w];
+      }
+      ch.token_of[out] = i;
+    }
   }
 }
 
@@ -394,6 +425,8 @@ static inline int disp_nblk(int T, int k) {
   return static_cast<int>((n + DISP_BLOCK - 1) / DISP_BLOCK);
 }
 
+bool dispatch_is_one_launch(int T, int k) { return static_cast<int64_t>(T) * k <= DISP1_MAX_ITEMS; }
+
 size_t dispatch_ws_bytes(int T, int E, int k) {
   // blockhist + blockbase, each [nblk, E] int32, rounded up to 256 bytes
   const size_t one = static_cast<size_t>(disp_nblk(T, k)) * static_cast<size_t>(E) * sizeof(int32_t);
@@ -419,6 +452,7 @@ int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, i
   if (T > 0 && !workspace) return SCMOE_ERR_NULL;
   const int nblk = disp_nblk(T, k);
   const int64_t items = static_cast<int64_t>(T) * k;
+  if (chores != nullptr && chores->token_of != nullptr && (items > DISP1_MAX_ITEMS || k != 1)) return SCMOE_ERR_ARG;
   if (items <= DISP1_MAX_ITEMS) {
     const int blocks = items > 0 ? static_cast<int>((items + DISP1_THREADS - 1) / DISP1_THREADS) : 1;
     const ScanChores sc = chores ? *chores : ScanChores{};

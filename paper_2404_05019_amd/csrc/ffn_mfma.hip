@@ -65,6 +65,8 @@ struct TileCfg {
 // (addend may be null: nothing is added).
 // 2: rows stay where they are: C[r] = addend[r] + row_scale[2 r] * row (row_scale: pairs of
 // coefficients per row, the first one is used; either pointer may be null).
+// 3: joint second GEMM of the shared and the routed expert of a token (see GemmArgs::A2); 4: the same with
+// addend rows.
 // XSEG: the launch may carry the dense extra segment (GemmArgs::xrows).
 template <class CFG, bool ACT, bool OFF32, int DEC, bool XSEG>
 __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void gemm_bf16_kernel(const GemmArgs p) {
@@ -75,8 +77,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   constexpr int HS = 2 * KS32;                                  // half-steps per k-tile
   constexpr int LPW = CFG::A_PER_WAVE + CFG::B_PER_WAVE;        // direct loads per wave and k-tile
   constexpr bool DECODE = DEC != 0;
-  constexpr bool ROTK = BM < 256;                               // (the large tiles are for calls it does not help)
-  static_assert(!(ACT && DEC != 0) && !(XSEG && DEC != 0) && DEC >= 0 && DEC <= 2, "the output decode belongs to second GEMMs without the extra segment");
+  constexpr bool CAT = DEC >= 3, ADD = DECODE && DEC != 3;
+  constexpr bool ROTK = BM < 256 && !CAT;                       // (the large tiles are for calls it does not help)
+  static_assert(!(ACT && DEC != 0) && !(XSEG && DEC != 0) && DEC >= 0 && DEC <= 4, "the output decode belongs to second GEMMs without the extra segment");
+  static_assert(!CAT || (OFF32 && NS == 2), "operands change at an even k-tile, by their scalar bases");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int tid = threadIdx.x;
@@ -84,13 +88,16 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // ---- tile schedule ------------------------------------------------------------------------
-  const int nk_all = p.Kd / BK;
-  TileSchedule<BM, BN, ACT ? CFG::GM_FIRST : CFG::GM_SECOND> sched(p, nk_all, p.splitk_part != nullptr && p.Kd >= SPLITK_MIN_K, CFG::WAVES);
+  const int nk1 = p.Kd / BK;               // k-tiles of one product
+  const int nk_all = CAT ? 2 * nk1 : nk1;
+  TileSchedule<BM, BN, ACT ? CFG::GM_FIRST : CFG::GM_SECOND, CAT> sched(p.nt, p.E, p.offsets, p.xrows, nk_all, p.splitk_part != nullptr && (CAT ? 2 : 1) * p.Kd >= SPLITK_MIN_K, CFG::WAVES,
+                                                                            blockIdx.x & 7, gridDim.x >> 3);
   const int nslots = sched.nslots;
   int it = blockIdx.x >> 3;                // work item: a tile, one K-part of a tile of the last round, or a finish item
   if (it >= sched.ngemm + sched.nfin) return;
   int nk = nk_all;                         // k-tiles of the current item
   int rot = 0;                             // the one it starts with (the walk wraps round)
+  int kmid = 0;                            // CAT: its k-tile at which the shared expert's operands begin
 
   // ---- per-lane source addresses of the direct-to-LDS loads -------------------------------
   // First row of the tile that this wave's A load i fills (RPL rows): the first half of the
@@ -110,16 +117,22 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   uint32_t aoff[OFF32 ? CFG::A_PER_WAVE : 1], boff[OFF32 ? CFG::B_PER_WAVE : 1];
   const unsigned char* abase = nullptr;     // OFF32: p.A / the expert's W, advanced to the item's first k-tile
   const unsigned char* wbase = nullptr;
+  const unsigned char* abase2 = nullptr;    // CAT: the same for the operands from k-tile kmid on
+  const unsigned char* wbase2 = nullptr;
   auto set_ptrs = [&](int e, int row0, int row_end, int n0, int kb) {   // kb: first k-tile of the item
     // The dense extra segment (operands of its own) and the fused output decode have
     // instantiations of their own: no kernel carries code it does not run (the register
     // allocation of the k loop feels every scalar that is live across it).
     const bool xs = XSEG && e == p.E;
     const int64_t lda = xs ? p.xlda : p.lda, ldw = xs ? p.xldw : p.ldw;
-    const int32_t* gather = xs ? nullptr : p.gather;
+    const int32_t* gather = xs ? p.xgather : p.gather;
     const unsigned char* We = (xs ? p.xW : p.W + static_cast<int64_t>(e) * p.N * ldw * 2) + static_cast<int64_t>(kb) * RB;
     abase = (xs ? p.xA : p.A) + static_cast<int64_t>(kb) * RB;
     wbase = We;
+    if constexpr (CAT) {
+      abase2 = p.A2 + static_cast<int64_t>(kb - nk1) * RB;
+      wbase2 = p.W2 + static_cast<int64_t>(kb - nk1) * RB;
+    }
 #pragma unroll
     for (int i = 0; i < CFG::A_PER_WAVE; ++i) {
       const int row = a_block(i) + lane / CPR;
@@ -146,7 +159,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   auto issue_a = [&](int kt, int stage, auto half_c) {
     constexpr int h = decltype(half_c)::value;
     if (ROTK && (kt += rot) >= nk) kt -= nk;
-    const unsigned char* ak = abase + static_cast<int64_t>(kt) * RB;
+    const unsigned char* ak = (CAT && kt >= kmid ? abase2 : abase) + static_cast<int64_t>(kt) * RB;
     if constexpr (OFF32) asm volatile("" : "+s"(ak));           // the scalar sum stays scalar
 #pragma unroll
     for (int i = h * A1_LPW; i < (h + 1) * A1_LPW; ++i) {
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   auto issue_w = [&](int kt, int stage) {
     if (ROTK && (kt += rot) >= nk) kt -= nk;
     unsigned char* sb = smem + stage * STAGE + A_BYTES + wave * CFG::B_PER_WAVE * 1024;
-    const unsigned char* wk = wbase + static_cast<int64_t>(kt) * RB;
+    const unsigned char* wk = (CAT && kt >= kmid ? wbase2 : wbase) + static_cast<int64_t>(kt) * RB;
     if constexpr (OFF32) asm volatile("" : "+s"(wk));
 #pragma unroll
     for (int i = 0; i < CFG::B_PER_WAVE; ++i) {
@@ -278,7 +291,16 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     sched.locate(l, e, row0, row_end, n0);
     int kb = 0;
     nk = nk_all;
-    if (part >= 0) {
+    if constexpr (CAT) {
+      if (part >= 0) {                                            // (cut at even k-tiles)
+        kb = part * nk1 / sched.S * 2;
+        nk = (part + 1) * nk1 / sched.S * 2 - kb;
+      } else if (e == p.E - 1) {                                  // dropped tokens: the shared expert alone
+        kb = nk1;
+        nk = nk1;
+      }
+      kmid = nk1 - kb;
+    } else if (part >= 0) {
       kb = part * nk_all / sched.S;
       nk = (part + 1) * nk_all / sched.S - kb;
     }
@@ -293,10 +315,33 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     // for a split-K item only in part 0).  Loading it here and not in the epilogue matters:
     // a load in the epilogue would wait behind the next tile's first k-tiles, which are
     // requested before the epilogue and complete in issue order.
+    // CAT: what the change of operands needs (the factors of the wave tile's rows, the shared
+    // expert's bias) waits in the wave's epilogue patch, where it takes no registers.
+    float* const mid_lds = reinterpret_cast<float*>(smem + NS * STAGE + wave * CFG::STG_BYTES);
+    if constexpr (CAT) {
+      asm volatile("" ::: "memory");      // (the patch was read as another type)
+      if (kmid > 0) {
+#pragma unroll
+        for (int q = 0; q < CFG::TM / 64; ++q) {
+          int r = row0 + wave_m * CFG::TM + q * 64 + lane;
+          if (r > row_end - 1) r = row_end - 1;
+          mid_lds[q * 64 + lane] = p.row_scale[r];
+        }
+        const int n = n0 + wave_n * CFG::TN + lane;
+        mid_lds[CFG::TM + lane] = (p.bias2 != nullptr && n < p.N) ? p.bias2[n] : 0.0f;
+      }
+    }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int n = n0 + wave_n * CFG::TN + j * 16 + 4 * lq;
       f32x4_t b = {0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (CAT) {
+        const float* bias = kmid > 0 ? (p.bias ? p.bias + static_cast<int64_t>(e) * p.N : nullptr) : p.bias2;
+        if (bias != nullptr && part <= 0 && n < p.N) b = *reinterpret_cast<const f32x4_t*>(bias + n);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) acc[i][j] = b;
+        continue;
+      }
       const bool xseg = XSEG && e == p.E;
       const float* bias = xseg ? p.xbias : p.bias + static_cast<int64_t>(e) * p.N;
       if ((xseg ? p.xbias : p.bias) != nullptr && part <= 0 && n < p.N)
@@ -364,13 +409,37 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     using std::integral_constant;
     using std::bool_constant;
     int kt = 0;
+    // CAT, all k-tiles of the routed product done: the rows times their gate weights, plus the shared
+    // expert's bias (a part of a cut tile may end before that point: then without the bias).
+    auto change_operands = [&](bool with_bias) {
+      f32x4_t b[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        b[j] = *reinterpret_cast<const f32x4_t*>(mid_lds + CFG::TM + j * 16 + 4 * lq);
+        if (!with_bias) b[j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const float f = mid_lds[i * 16 + l16];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[i][j][q] = fmaf(acc[i][j][q], f, b[j][q]);
+      }
+    };
     for (; kt + 2 * NS <= nk; kt += NS) {       // steady state: every load and read exists
+      if constexpr (CAT) {
+        if (kt == kmid && kt > 0) change_operands(true);
+      }
       k_tile(integral_constant<int, 0>{}, bool_constant<true>{}, kt);
       k_tile(integral_constant<int, 1>{}, bool_constant<true>{}, kt + 1);
       if constexpr (NS > 2) k_tile(integral_constant<int, 2>{}, bool_constant<true>{}, kt + 2);
       if constexpr (NS > 3) k_tile(integral_constant<int, 3>{}, bool_constant<true>{}, kt + 3);
     }
     for (; kt < nk; kt += NS) {                 // the last k-tiles (fewer than 2 NS), guarded
+      if constexpr (CAT) {
+        if (kt == kmid && kt > 0) change_operands(true);
+      }
       k_tile(integral_constant<int, 0>{}, bool_constant<false>{}, kt);
       if (kt + 1 < nk) k_tile(integral_constant<int, 1>{}, bool_constant<false>{}, kt + 1);
       if constexpr (NS > 2) {
@@ -381,8 +450,12 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       }
     }
 
+    if constexpr (CAT) {
+      if (kmid >= nk) change_operands(kmid == nk);
+    }
+
     // ---- next tile: its first k-tiles are requested before this tile's epilogue -----------
-    const int itn = it + nslots;
+    const int itn = sched.next(it);
     const bool more = itn < sched.ngemm;
     const int crow0 = row0, crow_end = row_end, cn0 = n0, cpart = part, cw = it;   // (a part is item cw < npart)
     unsigned char* const cC = (XSEG && e == p.E) ? p.xC : p.C;        // output of the current tile's segment
@@ -414,14 +487,14 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
         for (int q = 0; q < CFG::TM / 64; ++q) {
           int r = crow0 + wave_m * CFG::TM + q * 64 + lane;
           if (r > crow_end - 1) r = crow_end - 1;      // rows past the segment: its last row (never stored)
-          dtok[q] = (DEC == 1) ? p.scatter[r] : r;
+          dtok[q] = (DEC == 2) ? r : p.scatter[r];
         }
 #pragma unroll
         for (int q = 0; q < CFG::TM / 64; ++q) {
           if (DEC == 1) dscale[q] = p.row_scale[dtok[q]];
-          else dscale[q] = p.row_scale ? p.row_scale[2 * static_cast<int64_t>(dtok[q])] : 1.0f;
+          else if (DEC == 2) dscale[q] = p.row_scale ? p.row_scale[2 * static_cast<int64_t>(dtok[q])] : 1.0f;
         }
-        addend_loads(0);
+        if constexpr (ADD) addend_loads(0);
       }
     };
     constexpr bool dec = DECODE;
@@ -469,9 +542,11 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       if (dec) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) rscale[u] = __shfl(dscale[i >> 1], (i & 1) * 32 + u * 16 + l16);
+        if constexpr (ADD) {
 #pragma unroll
-        for (int g = 0; g < PIECES; ++g) add_cur[g] = dadd[g];
-        if (i + 1 < SLABS) addend_loads(i + 1);
+          for (int g = 0; g < PIECES; ++g) add_cur[g] = dadd[g];
+          if (i + 1 < SLABS) addend_loads(i + 1);
+        }
       }
 #pragma unroll
       for (int h = 0; h < 32 / CFG::STG_ROWS; ++h) {
@@ -489,7 +564,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
               for (int q = 0; q < 4; ++q)
                 v[q] = (p.gelu_mode == SCMOE_GELU_TANH) ? gelu_tanh_fast(v[q]) : gelu_erf_fast(v[q]);
             }
-            if (dec) {
+            if (dec && !CAT) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) v[q] *= rscale[u];
             }
@@ -513,7 +588,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
           int64_t orow = m;
           if (dec) orow = __shfl(dtok[i >> 1], (i & 1) * 32 + g * 8 + (lane >> 3));   // (all lanes take part)
           if (m < crow_end && n < p.N) {
-            if (dec) {
+            if constexpr (ADD) {
               // output decode: this packed row belongs to token orow; add the row already there
               const uint4 a = add_cur[g];
               o.x = add_bf16x2(o.x, a.x);
@@ -534,10 +609,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
         }
       }
     }
-    if (!more) break;
     it = itn;
+    if (!more) break;
   }
-  it += nslots;
   }
 
   // ---- finish items: one per wave tile of a tile that was cut along K ------------------------
@@ -581,6 +655,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       if constexpr (DEC == 1) {
         orow = p.scatter[mc];
         rscale = p.row_scale[orow];
+      } else if constexpr (CAT) {
+        orow = p.scatter[mc];
       } else if constexpr (DEC == 2) {
         if (p.row_scale != nullptr) rscale = p.row_scale[2 * static_cast<int64_t>(mc)];
       }
@@ -608,13 +684,13 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
         for (int c = 0; c < 4; ++c) {
           v[c] = a[j][c];
           if (ACT) v[c] = (p.gelu_mode == SCMOE_GELU_TANH) ? gelu_tanh_fast(v[c]) : gelu_erf_fast(v[c]);
-          if (DECODE) v[c] *= rscale;
+          if (DECODE && !CAT) v[c] *= rscale;
         }
         uint2 o;
         o.x = cvt_pk_bf16(v[0], v[1]);
         o.y = cvt_pk_bf16(v[2], v[3]);
         if (m < frow_end && n < p.N) {
-          if constexpr (DECODE) {
+          if constexpr (ADD) {
             if (p.addend != nullptr) {
               const uint2 ad = *reinterpret_cast<const uint2*>(p.addend + (orow * p.ldadd + n) * 2);
               o.x = add_bf16x2(o.x, ad.x);
@@ -658,7 +734,7 @@ bool ffn_mfma_supported(int d, int F) { return d > 0 && F > 0 && (d % 64) == 0 &
 
 // which output decode a launch asks for (see gemm_bf16_kernel)
 static int decode_kind(const GemmArgs& a) {
-  return a.scatter != nullptr ? 1 : (a.row_scale != nullptr || a.addend != nullptr) ? 2 : 0;
+  return a.A2 != nullptr ? (a.addend != nullptr ? 4 : 3) : a.scatter != nullptr ? 1 : (a.row_scale != nullptr || a.addend != nullptr) ? 2 : 0;
 }
 
 template <class CFG, bool ACT, bool OFF32, int DEC, bool XSEG>
@@ -675,7 +751,8 @@ static int launch_gemm_impl(GemmArgs a, int max_rows, hipStream_t stream) {
   }
   // only a second GEMM decodes, and not together with the dense extra segment
   if ((ACT && (a.scatter != nullptr || a.addend != nullptr)) || (!XSEG && a.xrows != 0)) return SCMOE_ERR_ARG;
-  if (DEC != decode_kind(a) || (DEC == 1 && a.row_scale == nullptr)) return SCMOE_ERR_ARG;
+  if (DEC != decode_kind(a) || (DEC != 0 && DEC != 2 && (a.scatter == nullptr || a.row_scale == nullptr))) return SCMOE_ERR_ARG;
+  if (DEC >= 3 && (a.W2 == nullptr || a.Kd % (2 * CFG::BK) != 0)) return SCMOE_ERR_ARG;
   // upper bound on row tiles: sum_e ceil(c_e / BM) <= max_rows / BM + E
   const int mtb = max_rows / CFG::BM + a.E + (a.xrows + CFG::BM - 1) / CFG::BM;
   a.nt = (a.N + CFG::BN - 1) / CFG::BN;
@@ -728,6 +805,8 @@ static int launch_gemm(const GemmArgs& a, int max_rows, int64_t a_rows, hipStrea
       case 2:
         return off32 ? launch_gemm_impl<CFG, false, true, 2, false>(a, max_rows, stream)
                      : launch_gemm_impl<CFG, false, false, 2, false>(a, max_rows, stream);
+      case 3:
+      case 4: return SCMOE_ERR_ARG;        // (launch_joint_second)
       default:
         return off32 ? launch_gemm_impl<CFG, false, true, 0, false>(a, max_rows, stream)
                      : launch_gemm_impl<CFG, false, false, 0, false>(a, max_rows, stream);
@@ -773,6 +852,12 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500
   // tokens, top-2, d = 768, E = 16: 86 -> 79; 3000 tokens, d = 1024, E = 32: 278 -> 245).
   return launch_gemm<CfgU, ACT>(g, max_rows, a_rows, stream);
+}
+
+// The joint second GEMM of a top-1 layer (GemmArgs::A2), rows: tokens.
+static int launch_joint_second(const GemmArgs& a, int rows, hipStream_t stream) {
+  return a.addend != nullptr ? launch_gemm_impl<CfgA, false, true, 4, false>(a, rows, stream)
+                             : launch_gemm_impl<CfgA, false, true, 3, false>(a, rows, stream);
 }
 
 __global__ void zero_ints(int* p, int n) {
@@ -869,6 +954,23 @@ bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_row
   return (d >= 128 || F >= 128) && static_cast<double>(all_rows) * (d + F) > 2.2e6;
 }
 
+// Where both second GEMMs of a top-1 layer run as one product.  What it saves: the shared expert's rows
+// written and read again, a launch, the decode's loads, an epilogue per row, and the idle end of one launch.
+// What it costs: the shared expert's product too now has a partly filled row tile per expert, half a tile of
+// F / 64 k-tiles for every expert and column tile, which is up to 16 k-tiles (21 us) for every CU
+// here.  Layer us, two launches / one (T, d, F, E):
+//   16384, 1024, 4096, 8 572.5 / 561.1 (4 k-tiles); 30000, 768, 3072, 8 659 / 588 (2); 16384, 1280, 5120, 4
+//   843 / 779 (3); 12000, 1536, 4096, 8 with a residual 629 / 606 (6); 6000, 2048, 5504, 8 642.2 / 641.3 (11);
+//   16384, 1024, 4096, 32 640.5 / 637.7 (16); 20000, 2048, 4096, 16 skewed 1000 / 977 (16); with 32 and
+//   F = 8192, E = 16 4096, 2048 681 / 673, but 8192, 2048 1021 / 1039; 16384, 2048 1900 / 1931; 32768, 2048
+//   3722 / 3752.
+// Below one 256 x 256 tile per CU the smaller tiles are faster, which have no such form.
+bool ffn_joint_second_fits(int T, int d, int F, int E, int64_t ldh, int64_t ldw2) {
+  const int64_t nt = (d + CfgA::BN - 1) / CfgA::BN, lim = int64_t(1) << 32;
+  return gemm_variant() == 0 && F % (2 * CfgA::BK) == 0 && T * ldh * 2 < lim && d * ldw2 * 2 < lim &&
+         (T / CfgA::BM + E) * nt >= num_cus() && E * nt * (F / CfgA::BK) <= 2 * 16 * static_cast<int64_t>(num_cus());
+}
+
 static bool is_tiled(const FfnArgs& a, int dtype) {
   if (a.path != FFN_AUTO) return a.path == FFN_TILED;
   return ffn_is_tiled(dtype, a.d, a.F, a.max_rows, a.E, a.max_rows, a.max_rows);
@@ -901,10 +1003,11 @@ int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
 }
 
 int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_t stream) {
-  if (se.d != rt.d || se.F != rt.F || se.E != 1 || se.gather != nullptr || se.gelu_mode != rt.gelu_mode) return SCMOE_ERR_ARG;
+  if (se.d != rt.d || se.F != rt.F || se.E != 1 || (se.gather != nullptr) != (rt.joint_offsets != nullptr) || se.gelu_mode != rt.gelu_mode) return SCMOE_ERR_ARG;
   if (se.max_rows <= 0) return ffn_forward(rt, dtype, stream);
   if (rt.max_rows <= 0) return ffn_forward(se, dtype, stream);
   const bool ts = is_tiled(se, dtype), tr = is_tiled(rt, dtype);
+  if (rt.joint_offsets != nullptr && (!ts || !tr || se.ldh != rt.ldh || se.ldw2 != rt.ldw2)) return SCMOE_ERR_ARG;
   if (!ts && !tr && rt.addend == nullptr) {
     const DirectJob first[2] = {direct_first(rt), direct_first(se)}, second[2] = {direct_second(rt), direct_second(se)};
     const int st = launch_gemm_direct(first, 2, dtype, stream);
@@ -926,6 +1029,7 @@ int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_
     g.xW = x.W;
     g.xldw = x.ldw;
     g.xbias = x.bias;
+    g.xgather = x.gather;
     g.xC = x.C;
     g.xldc = x.ldc;
     return g;
@@ -933,6 +1037,15 @@ int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_
   const GemmArgs s2 = second_gemm(se, sks), r2 = second_gemm(rt, skr);
   st = launch_variant<true>(with_shared(first_gemm(rt, skr), first_gemm(se, sks)), rt.max_rows, rt.gather ? rt.x_rows : rt.max_rows, stream);
   if (st != SCMOE_OK) return st;
+  if (rt.joint_offsets != nullptr) {
+    GemmArgs g = r2;
+    g.offsets = rt.joint_offsets;
+    g.E = rt.E + 1;
+    g.A2 = s2.A;
+    g.W2 = s2.W;
+    g.bias2 = s2.bias;
+    return launch_joint_second(g, se.max_rows, stream);
+  }
   // Neither decodes (more than one expert per token): one launch, whose tiles fill the chip better
   // (3001 tokens, top-2, d = 768, F = 3072, E = 12: 193 -> 167 us of layer time).
   if (decode_kind(s2) == 0 && decode_kind(r2) == 0) return launch_variant<false>(with_shared(r2, s2), rt.max_rows, rt.max_rows, stream);

@@ -13,6 +13,7 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
               int d, int E, int k, int normalize, int32_t* idx, float* gw, float* probs,
               hipStream_t stream);
 size_t dispatch_ws_bytes(int T, int E, int k);
+bool dispatch_is_one_launch(int T, int k);
 int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, int T, int d, int E,
              int k, int capacity, int32_t* counts, int32_t* offsets, int32_t* dst_row,
              int32_t* src_token, void* x_perm, int64_t ld_perm, void* workspace, size_t ws_bytes,
@@ -255,6 +256,14 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
   a.path = path;
   if (shared != nullptr) {
     FfnArgs se = *shared;
+    if (chores != nullptr && chores->token_of != nullptr) {      // both second GEMMs as one product
+      a.scatter = chores->token_of;
+      a.row_scale = chores->row_gate;
+      a.joint_offsets = chores->joint_offsets;
+      a.addend = se.addend; a.ldadd = se.ldadd;                  // (the residual)
+      se.addend = nullptr;
+      se.gather = chores->token_of; se.x_rows = D->T;
+    }
     se.scratch_zeroed = chores != nullptr && chores->nzero > 0 && chores->zero_b == se.scratch && se.scratch != nullptr;
     return ffn_forward_pair(se, a, D->dtype, stream);
   }
@@ -437,6 +446,20 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || one_round || (all_rows > 64 * segs && all_rows <= 128 * segs));
   const bool fused = D->k == 1 && !one_launch && !overlaps(y, ldy, x_prev, ld_prev) &&
                      !overlaps(y, ldy, x_cur, ld_cur) && (!residual || !overlaps(y, ldy, residual, ldres));
+  // Both second GEMMs as one product: y[t] = [g W2_e | W2s] . [h(t) ; hs(t)], a k loop twice as long over
+  // rows that both first GEMMs leave in the packed order.  The sum of both experts is rounded once.
+  const bool joint_second = joint && fused && tiled_s && tiled_r && D->cg_mode == SCMOE_CG_NONE && rows > 0 &&
+                            dispatch_is_one_launch(D->T, D->k) &&
+                            ffn_joint_second_fits(D->T, D->d, D->F, D->E, w.ldh, ld_or(W->ld_w2, D->F));
+  if (joint_second) {
+    // (the arrays lie where the shared expert's rows would go: d >= 64, so 128 bytes a token and more)
+    const size_t ints = align256(static_cast<size_t>(D->T) * 4);
+    unsigned char* p = static_cast<unsigned char*>(w.s);
+    chores.token_of = reinterpret_cast<int32_t*>(p);
+    chores.row_gate = reinterpret_cast<float*>(p + ints);
+    chores.joint_offsets = reinterpret_cast<int32_t*>(p + 2 * ints);
+    chores.gate_w = w.gate_w;
+  }
   FfnArgs se{};
   se.x = x_cur; se.ldx = ld_cur; se.gather = nullptr; se.offsets = tiled_s ? w.offsets_shared : nullptr;
   se.max_rows = D->T; se.E = 1; se.d = D->d; se.F = D->F;

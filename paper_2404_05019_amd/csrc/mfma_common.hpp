@@ -4,6 +4,7 @@
 #pragma once
 #include "common.hpp"
 #include "gelu.hpp"
+#include "tile_schedule.hpp"
 
 #include <type_traits>
 
@@ -66,8 +67,17 @@ struct GemmArgs {
   const unsigned char* xW;       // bf16 [N, Kd], row stride xldw
   int64_t xldw;
   const float* xbias;            // [N] or nullptr
+  const int32_t* xgather;        // row r reads xA[xgather[r]]; nullptr = identity
   unsigned char* xC;
   int64_t xldc;
+  // Joint second GEMM of a top-1 layer (optional; A2 == nullptr: off).  A row of the packed order is
+  // a token, and a tile's k loop runs over both its products: first A . W[e]^T + bias[e], Kd wide;
+  // the sum times row_scale[r] (r: packed row); then A2 . W2^T + bias2 is added, the same Kd, lda and
+  // ldw; row r goes to C[scatter[r], :], plus addend[scatter[r], :] if there is one.  The last of the E
+  // segments holds the tokens without a routed row, whose tiles run the second product alone.
+  const unsigned char* A2;
+  const unsigned char* W2;
+  const float* bias2;
 };
 
 // Scratch of the split-K tail: per XCD as many partial tiles as workgroups are resident
@@ -76,7 +86,6 @@ constexpr int SPLITK_PARTS = 8 * 64;
 constexpr size_t SPLITK_TILE_BYTES = 256 * 256 * 4;
 constexpr size_t SPLITK_COUNT_BYTES = SPLITK_PARTS * sizeof(int);
 constexpr size_t SPLITK_WS_BYTES = SPLITK_COUNT_BYTES + 8 * 32 * SPLITK_TILE_BYTES;
-constexpr int SPLITK_MAX = 8;    // most parts one tile is cut into
 // Tiles are cut along K only from this K on.  Writing a part's partial sums and reading them
 // back costs about as much as 20 k-tiles of 64, whatever K is (all workgroups do it at the same
 // time, so it is memory traffic, not latency); below K = 2048 a tile is done sooner than that.
@@ -168,144 +177,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
-
-// Persistent tile schedule.  Row tiles are counted from offsets[] on the device (no host
-// round trip).  Workgroup ids congruent mod 8 run on one XCD.  The tiles form up to two
-// ranges: the dense extra segment (if any) and the E segments of offsets[], segment after
-// segment, each segment in the raster order "a group of up to GM row tiles x all column
-// tiles" (so a group never mixes two experts' weights).  XCD x owns the x-th eighth of the
-// extra segment's range; the other range is dealt to the XCDs in chunks of RR tiles, XCD
-// after XCD, and only the rest that does not fill a round of chunks is cut into eighths (so
-// every XCD gets the same amount of both kinds of work, and at any time all XCDs read the
-// weights of the same one or two experts, which the memory-side cache then serves).  The
-// workgroups of an XCD take the tiles of its share round-robin, so the tiles in flight on one
-// XCD are neighbours and share A and W panels in its L2.
-template <int BM, int BN, int GM>
-struct TileSchedule {
-  int mt_seg, nt, E, xt, xrows;   // row tiles of the offsets[] segments / of the extra segment
-  const int32_t* offsets;
-  int nslots;
-  int a0, na, rr, b0;             // this XCD's share: tiles a0 .. a0+na-1 of the extra segment's
-                                  // range; of the other range rr tiles out of the dealt chunks,
-                                  // then tiles from b0 on of the undealt rest
-  static constexpr int RR = 32;
-  // Work items of this XCD.  Its `full` tiles fill whole rounds of nslots workgroups; the `rem`
-  // tiles of the last, partly filled round are each cut along K into S parts (S > 1 only with
-  // scratch for the partial sums), so that the round keeps (nearly) all workgroups busy.
-  // Item order: first the rem * S parts (part w % S of local tile full + w / S), then the full
-  // tiles (local tile = item - parts), then rem * FS finish items, one per FS-th of a cut tile,
-  // which add the parts up and write the result.  A workgroup takes items slot, slot + nslots,
-  // ...: a part is always the first item of its workgroup, a finish item the last, so the
-  // partial sums are long written when they are read (the kernel still checks the arrival count).
-  int full, rem, S, npart, ngemm, nfin, xcd;
-  int cur_e = 0, cur_base = 0;    // where the last search through offsets[] ended (see locate)
-
-  __device__ __forceinline__ TileSchedule(const GemmArgs& p, int nk, bool can_split, int FS)
-      : mt_seg(0), nt(p.nt), E(p.E), xt((p.xrows + BM - 1) / BM), xrows(p.xrows), offsets(p.offsets) {
-    for (int q = 0; q < E; ++q) mt_seg += (offsets[q + 1] - offsets[q] + BM - 1) / BM;
-    xcd = blockIdx.x & 7;
-    nslots = gridDim.x >> 3;
-    auto share = [&](int total, int& first) {
-      const int chunk = (total + 7) >> 3;
-      first = xcd * chunk;
-      const int last = (xcd + 1) * chunk < total ? (xcd + 1) * chunk : total;
-      return last > first ? last - first : 0;
-    };
-    na = share(xt * nt, a0);
-    const int routed = mt_seg * nt;
-    rr = (routed / (8 * RR)) * RR;
-    int n = share(routed - 8 * rr, b0);
-    b0 += 8 * rr;
-    n += na + rr;
-    full = (n / nslots) * nslots;
-    rem = n - full;
-    S = 1;
-    if (can_split && rem > 0) {
-      S = nslots / rem;
-      if (S > SPLITK_MAX) S = SPLITK_MAX;
-      if (S > nk) S = nk;
-      if (S < 1) S = 1;
-    }
-    npart = S > 1 ? rem * S : 0;
-    ngemm = S > 1 ? npart + full : n;
-    nfin = S > 1 ? rem * FS : 0;
-  }
-  // GEMM item (it < ngemm) -> local tile index and part (part < 0: the whole tile)
-  __device__ __forceinline__ void item(int it, int& l, int& part) const {
-    if (it < npart) {
-      l = full + it / S;
-      part = it - (it / S) * S;
-    } else {
-      l = it - npart;
-      part = -1;
-    }
-  }
-  // raster order inside a range of mt row tiles: tile l -> row tile, first column
-  // (the fewest groups of at most GM row tiles, of sizes that differ by one at most: the first
-  // `big` groups have one row tile more than the others)
-  __device__ __forceinline__ void raster(int l, int mt, int& m, int& n0) const {
-    const int ng = (mt + GM - 1) / GM;
-    const int base = mt / ng, big = mt - base * ng;
-    const int lbig = big * (base + 1) * nt;          // tiles in the larger groups
-    int grows, first, r;
-    if (l < lbig) {
-      grows = base + 1;
-      const int g = l / (grows * nt);
-      first = g * grows;
-      r = l - g * grows * nt;
-    } else {
-      grows = base;
-      const int g = (l - lbig) / (grows * nt);
-      first = big * (base + 1) + g * grows;
-      r = (l - lbig) - g * grows * nt;
-    }
-    m = first + r % grows;
-    n0 = (r / grows) * BN;
-  }
-  // local tile l -> expert e (E: the dense extra segment), packed rows [row0, row_end)
-  // (row0 + BM may exceed row_end), column n0
-  // The tiles of a workgroup come in ascending order, so the search through offsets[] goes on
-  // from the expert of the previous tile (cur_e, with cur_base tiles in the experts before
-  // it) instead of from expert 0: a dependent scalar load per expert passed, 2 us per tile
-  // at 16 experts when started from 0 every time.
-  __device__ __forceinline__ void locate(int l, int& e, int& row0, int& row_end, int& n0) {
-    int mt;
-    if (l < na) {
-      raster(a0 + l, xt, mt, n0);
-      e = E;
-      row0 = mt * BM;
-      row_end = xrows;
-      return;
-    }
-    // Segment after segment, each in its own raster order: a raster group never holds rows
-    // of two experts, so the workgroups that run side by side share one expert's weights.
-    int t = l - na;
-    t = (t < rr) ? ((t / RR) * 8 + xcd) * RR + t % RR : b0 + t - rr;
-    row0 = 0;
-    row_end = 1;
-    n0 = 0;
-    if (t < cur_base) {        // not expected; start over
-      cur_e = 0;
-      cur_base = 0;
-    }
-    int base = cur_base;
-    for (e = cur_e; e < E; ++e) {
-      const int s = offsets[e];
-      const int c = offsets[e + 1] - s;
-      const int ntile = (c + BM - 1) / BM;
-      if (t - base < ntile * nt) {
-        raster(t - base, ntile, mt, n0);
-        row0 = s + mt * BM;
-        row_end = s + c;
-        cur_e = e;
-        cur_base = base;
-        break;
-      }
-      base += ntile * nt;
-    }
-    if (e == E) e = E - 1;   // not reachable for a tile of this XCD's share
-  }
-};
 
 // One product of a launch of the direct grouped GEMM (ffn_direct.hip).  g.offsets == nullptr: one
 // dense segment of max_rows rows; otherwise max_rows bounds the packed rows.

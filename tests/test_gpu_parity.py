@@ -584,6 +584,20 @@ def test_layer_bf16_mfma_path(oracle, T, d, F, k, shared, C_, normalize, cg, res
         assert np.array_equal(y[dropped], s[dropped])
 
 
+@pytest.mark.parametrize("T,d,F,E,C_,res", [
+    (4200, 2048, 128, 16, 100000, False),   # no token dropped
+    (4200, 2048, 384, 16, 150, False),      # half of them dropped: short tiles beside the full ones
+    (4200, 2048, 1024, 16, 260, True),      # a few dropped, tiles cut along K, residual
+    (4099, 2048, 1152, 16, 1, False),       # hardly a routed row
+    (16400, 1024, 256, 4, 3000, True),      # more full tiles than one round
+    (3900, 2304, 2048, 14, 200, False)])    # (9 column tiles)
+def test_layer_joint_second_gemm(oracle, T, d, F, E, C_, res):
+    """Top-1 ScMoE on one stream at sizes whose second GEMMs run as one product: routed rows, then the
+    shared expert's, in one tile; tokens without a routed row in tiles of half the length."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, w_scale=0.03)
+    _layer_case(oracle, L, "bf16", E, 1, C_, True, residual=res, pad_weights=F == 384)
+
+
 @pytest.mark.parametrize("k,shared,C_,cg,res,two_streams", [
     (1, True, 320, 0, False, False),      # routed second GEMM decodes (scatter, gate weight, add) in finish items
     (1, True, 300, 2, True, False),       # ... and so does the shared expert's (its coefficient, the residual)

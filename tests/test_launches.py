@@ -148,6 +148,20 @@ def test_tiled_chains_of_the_test_helper_is_the_library_s_rule(record):
     assert seen >= {(False, False), (True, True), (True, False)}
 
 
+def test_joint_second_gemm_only_where_its_rule_and_its_forms_allow_it(record):
+    """Top-1 layers on one stream: two GEMM launches where the second products are one, else three."""
+    base = _layer(16384, 1024, 4096)
+    joint = [base, dict(base, res=True), dict(base, capacity=100), _layer(30000, 768, 3072), _layer(16384, 1024, 4096, 32),
+             _layer(4096, 2048, 128, 16)]
+    apart = [dict(base, two=True), dict(base, cg=1), dict(base, cg=2, res=True), _layer(32768, 2048, 8192, 16),    # k-tiles of padding
+             _layer(16384, 1024, 4096 + 64), _layer(140000, 256, 512), _layer(8192, 1024, 4096, 8)]   # odd, dispatch in three launches, few tiles
+    for want, calls in ((2, joint), (3, apart)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            gemms = _at(kernels, "gemm_")
+            assert st == 0 and len(gemms) == (4 if c["two"] else want) and gemms == _at(kernels, "gemm_bf16_kernel"), c
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
