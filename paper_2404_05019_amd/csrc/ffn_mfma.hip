@@ -108,10 +108,14 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     const int q = (wave * H + i % H) * CFG::RPL;                // row among the rows of that half
     return (q / HALF) * CFG::TM + (i / H) * HALF + q % HALF;
   };
-  // OFF32 (both operands span less than 4 GiB, checked on the host): an address is a
-  // wave-uniform 64-bit base plus a 32-bit per-lane offset, which the load takes as scalar
-  // base + vector offset: one register per load and no vector address arithmetic between
-  // the barrier of a k-tile and its next MFMA.  Otherwise full 64-bit per-lane pointers.
+  // OFF32 (both operands span less than BUFFER_SPAN, checked on the host): an address is a
+  // wave-uniform base plus a 32-bit per-lane offset that stays the same for a whole tile: one
+  // register per load and no vector address arithmetic between the barrier of a k-tile and its next
+  // MFMA.  A comes through a buffer descriptor, with the k-tile as its scalar offset: rows past the
+  // segment lie outside the buffer, read zeros and cost no memory traffic (as repeats of the last row
+  // 4096 tokens of 32 experts, d = 1024, F = 2048 190 us, so 186; W the same way took 24-46 scalar
+  // registers out of the k loop: 8192 tokens, d = 384 92.6 -> 93.6).  Otherwise full 64-bit per-lane
+  // pointers.
   const unsigned char* aptr[OFF32 ? 1 : CFG::A_PER_WAVE];
   const unsigned char* bptr[OFF32 ? 1 : CFG::B_PER_WAVE];
   uint32_t aoff[OFF32 ? CFG::A_PER_WAVE : 1], boff[OFF32 ? CFG::B_PER_WAVE : 1];
@@ -138,9 +142,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
       const int row = a_block(i) + lane / CPR;
       const int kc = (lane % CPR) ^ swz<CPR>(row);
       int m = row0 + row;
-      if (m > row_end - 1) m = row_end - 1;      // rows past the segment re-read its last row
+      const bool past = m > row_end - 1;
+      if (past) m = row_end - 1;                 // (64-bit pointers: rows past the segment re-read its last row)
       const int64_t src = gather ? gather[m] : m;
-      if constexpr (OFF32) aoff[i] = static_cast<uint32_t>(src * lda * 2 + kc * 16);
+      if constexpr (OFF32) aoff[i] = past ? BUFFER_NOWHERE : static_cast<uint32_t>(src * lda * 2 + kc * 16);
       else aptr[i] = abase + src * lda * 2 + kc * 16;
     }
 #pragma unroll
@@ -159,14 +164,12 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   auto issue_a = [&](int kt, int stage, auto half_c) {
     constexpr int h = decltype(half_c)::value;
     if (ROTK && (kt += rot) >= nk) kt -= nk;
-    const unsigned char* ak = (CAT && kt >= kmid ? abase2 : abase) + static_cast<int64_t>(kt) * RB;
-    if constexpr (OFF32) asm volatile("" : "+s"(ak));           // the scalar sum stays scalar
+    const unsigned char* ak = CAT && kt >= kmid ? abase2 : abase;
 #pragma unroll
     for (int i = h * A1_LPW; i < (h + 1) * A1_LPW; ++i) {
       unsigned char* sa = smem + stage * STAGE + a_block(i) * RB;
       if constexpr (OFF32) {
-        asm volatile("" : "+v"(aoff[i]));   // keeps the offset a 32-bit register of its own
-        __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(ak + aoff[i]), SCMOE_LDS_PTR(sa), 16, 0, 0);
+        buffer_to_lds16(ak, sa, aoff[i], static_cast<uint32_t>(kt) * RB);
       } else {
         __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(aptr[i] + static_cast<int64_t>(kt) * RB),
                                          SCMOE_LDS_PTR(sa), 16, 0, 0);
@@ -177,11 +180,11 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     if (ROTK && (kt += rot) >= nk) kt -= nk;
     unsigned char* sb = smem + stage * STAGE + A_BYTES + wave * CFG::B_PER_WAVE * 1024;
     const unsigned char* wk = (CAT && kt >= kmid ? wbase2 : wbase) + static_cast<int64_t>(kt) * RB;
-    if constexpr (OFF32) asm volatile("" : "+s"(wk));
+    if constexpr (OFF32) asm volatile("" : "+s"(wk));           // the scalar sum stays scalar
 #pragma unroll
     for (int i = 0; i < CFG::B_PER_WAVE; ++i) {
       if constexpr (OFF32) {
-        asm volatile("" : "+v"(boff[i]));
+        asm volatile("" : "+v"(boff[i]));   // keeps the offset a 32-bit register of its own
         __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(wk + boff[i]), SCMOE_LDS_PTR(sb + i * 1024), 16, 0, 0);
       } else {
         __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(bptr[i] + static_cast<int64_t>(kt) * RB),
@@ -269,9 +272,14 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 #pragma unroll
     for (int i = 0; i < MI / 2; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
+      for (int jj = 0; jj < NJ; ++jj) {
+        // there and back: only one operand changes from one instruction to the next, which the power limit
+        // turns into clock (layer of 32768 tokens, d = 2048, F = 8192, E = 16 3786 -> 3752 us; 16384, d = 1024,
+        // E = 8 563.5 -> 558.4)
+        const int j = (i & 1) ? NJ - 1 - jj : jj;
         acc[half * (MI / 2) + i][j] =
             __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[wbuf][j], xf[xbuf][i], acc[half * (MI / 2) + i][j], 0, 0, 0);
+      }
   };
   // issue order of one half-step: MFMA, ds_read, MFMA, ds_read, ... (the reads feed the NEXT one)
   auto interleave = [&](auto next_hs_c) {
@@ -788,8 +796,8 @@ static int launch_gemm_impl(GemmArgs a, int max_rows, hipStream_t stream) {
 // a_rows: rows of the activation matrix that can be addressed (through `gather` any of them).
 template <class CFG, bool ACT>
 static int launch_gemm(const GemmArgs& a, int max_rows, int64_t a_rows, hipStream_t stream) {
-  const int64_t lim = int64_t(1) << 32;
-  const bool off32 = a_rows * a.lda * 2 < lim && static_cast<int64_t>(a.N) * a.ldw * 2 < lim &&
+  const int64_t lim = BUFFER_SPAN;
+  const bool off32 = a.Kd < BUFFER_K && a_rows * a.lda * 2 < lim && static_cast<int64_t>(a.N) * a.ldw * 2 < lim &&
                      static_cast<int64_t>(a.xrows) * a.xlda * 2 < lim && static_cast<int64_t>(a.N) * a.xldw * 2 < lim;
   if constexpr (ACT) {
     return off32 ? launch_gemm_impl<CFG, true, true, 0, true>(a, max_rows, stream)
@@ -966,8 +974,8 @@ bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_row
 //   3722 / 3752.
 // Below one 256 x 256 tile per CU the smaller tiles are faster, which have no such form.
 bool ffn_joint_second_fits(int T, int d, int F, int E, int64_t ldh, int64_t ldw2) {
-  const int64_t nt = (d + CfgA::BN - 1) / CfgA::BN, lim = int64_t(1) << 32;
-  return gemm_variant() == 0 && F % (2 * CfgA::BK) == 0 && T * ldh * 2 < lim && d * ldw2 * 2 < lim &&
+  const int64_t nt = (d + CfgA::BN - 1) / CfgA::BN, lim = BUFFER_SPAN;
+  return gemm_variant() == 0 && F % (2 * CfgA::BK) == 0 && F < BUFFER_K && (T + 1) * ldh * 2 < lim && (d + 1) * ldw2 * 2 < lim &&
          (T / CfgA::BM + E) * nt >= num_cus() && E * nt * (F / CfgA::BK) <= 2 * 16 * static_cast<int64_t>(num_cus());
 }
 

@@ -160,6 +160,20 @@ __device__ __forceinline__ void load16x16_device_scope(const float* p0, const fl
       : "memory");
 }
 
+// Direct-to-LDS copy through a buffer descriptor: 16 bytes per lane from base + voff + soff to 1 KiB
+// of consecutive LDS.  An offset of BUFFER_SPAN or more is outside the buffer and reads zero;
+// BUFFER_NOWHERE is, whether or not the range check counts soff (at most two rows of BUFFER_K bf16).
+constexpr int64_t BUFFER_SPAN = 0xF0000000ll;
+constexpr int BUFFER_K = 1 << 24;
+constexpr uint32_t BUFFER_NOWHERE = 0xF8000000u;
+__device__ __forceinline__ void buffer_to_lds16(const unsigned char* base, unsigned char* lds, uint32_t voff, uint32_t soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, static_cast<uint32_t>(BUFFER_SPAN), 0x00020000),
+      SCMOE_LDS_PTR(lds), 16, voff, soff, 0, 0);
+#endif
+}
+
 // f(integral_constant<int, I>) for I = B .. N-1, unrolled at compile time.
 template <int B, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
