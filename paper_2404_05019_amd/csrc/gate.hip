@@ -5,7 +5,7 @@
 // rounded add of the bias.  Every kernel here keeps that chain intact per (token, expert) and
 // finds its parallelism elsewhere.  The chains run on the matrix cores (gate_mfma_kernel: the
 // fp32 matrix instruction is such a chain, four features at a time).  The two vector-ALU
-// kernels remain for a W_g that is not 16-byte aligned and for a few tokens with many experts.
+// kernels remain for a W_g that is not 16-byte aligned.
 // gate_kernel: a workgroup owns 64 tokens, lane = token, and each of
 // its eight waves (four for E <= 4) owns a contiguous group of EPL experts, so every lane
 // runs EPL independent FMA chains.  x is staged through LDS in [64 tokens x 256 bytes] tiles
@@ -322,9 +322,12 @@ __device__ __forceinline__ void lds_read_x(uint32_t& r, uint32_t addr) {
   if constexpr (BF16) asm volatile("ds_read_u16_d16_hi %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFF));
   else asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
 }
-// byte offset, inside a stage, of the x operand of step S (for the lane's row and feature)
+// the x operand of step S inside a stage: which 16-byte column of a 64-byte copy, and its byte offset
+// from there (for the lane's row and feature)
 template <bool BF16>
-constexpr int gm_x_off(int S) { return BF16 ? (S >> 1) * 256 + (S & 1) * 8 : S * 256; }
+constexpr int gm_x_col(int S) { return BF16 ? (S >> 1) & 3 : S & 3; }
+template <bool BF16>
+constexpr int gm_x_off(int S) { return BF16 ? (S >> 3) * 1024 + (S & 1) * 8 : (S >> 2) * 1024; }
 // until at most N of the LDS reads issued so far are outstanding; x and w are valid afterwards
 template <int N, int EG>
 __device__ __forceinline__ void lds_wait(uint32_t& x, uint32_t (&w)[EG]) {
@@ -377,11 +380,16 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
   unsigned char* const ring = gm + WB * GM_WBUF + wave * (XS * GM_STAGE);
 
   // ---- copies --------------------------------------------------------------------------------
-  // x: lane p of a copy fetches 16 bytes of row p % 16 at 16-byte column p / 16 of the 64 bytes
-  // the copy covers; they land at ring position p.  Columns past the row's end re-read its last
-  // 16 bytes (never consumed), and so do whole stages past the end, which keeps the number of
-  // copies per stage fixed for the waits below.
-  int trow = t0 + wave * 16 + c16;
+  // x: lane p of a copy fetches 16 bytes of row p / 4, at a 16-byte column of the 64 bytes the copy
+  // covers, and they land at ring position p.  Four lanes share the 64 bytes of a row: a copy whose
+  // neighbouring lanes read different rows takes the compute unit's address path up to four times as
+  // long (18 against 63 B/ns from the caches; four waves' copies would fill it at the rate the chain
+  // has now).  The column is p % 4
+  // XOR (row / 4) % 4, which spreads the operand reads over all banks.  Columns past the row's end
+  // re-read its last 16 bytes (never consumed), and so do whole stages past the end, which keeps
+  // the number of copies per stage fixed for the waits below.
+  const int crow = lane >> 2, ccol = (lane & 3) ^ ((lane >> 4) & 3);
+  int trow = t0 + wave * 16 + crow;
   if (trow > T - 1) trow = T - 1;
   const unsigned char* const xrow = x + static_cast<int64_t>(trow) * ldx * EB;
   const int row_last = d * EB - 16;
@@ -389,7 +397,7 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     unsigned char* dst = ring + slot * GM_STAGE;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      int off = i * 128 + h * 64 + kq * 16;
+      int off = i * 128 + h * 64 + ccol * 16;
       if (off > row_last) off = row_last;
       __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(xrow + off), SCMOE_LDS_PTR(dst + h * 1024), 16, 0, 0);
     }
@@ -421,13 +429,14 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
   using InFlightTileEnd = std::integral_constant<int, (XS - 2 < (WB - 1) * IPT) ? 2 * (XS - 2) : 2 * (WB - 1) * IPT>;
 
   // ---- operands ------------------------------------------------------------------------------
-  // x: token c16's 16 bytes of 16-byte column q sit at ring position 16 q + c16; W_g: feature
-  // row f of the tile starts at byte 4 E f.  Lanes past the last expert read expert E - 1 again
-  // (their rows of the product are never looked at).
-  const int xl = c16 * 16 + kq * EB;
-  int wl[EG];
+  // x: token c16's 16 bytes of 16-byte column q sit at ring position 4 c16 + (q ^ (c16 / 4)); W_g:
+  // feature row f of the tile starts at byte 4 E f.  Lanes past the last expert read what lies there
+  // (in bounds: the rings follow the tiles; their rows of the product are never looked at).
+  int xl[4], wl[SS];
 #pragma unroll
-  for (int g = 0; g < EG; ++g) wl[g] = (kq * E + (16 * g + c16 < E ? 16 * g + c16 : E - 1)) * 4;
+  for (int q = 0; q < 4; ++q) xl[q] = (c16 * 4 + (q ^ (c16 >> 2))) * 16 + kq * EB;
+#pragma unroll
+  for (int s = 0; s < SS; ++s) wl[s] = ((4 * s + kq) * E + c16) * 4;     // of step s of a stage
   // Operand registers hold what the matrix instruction takes: fp32 bits (a bf16 in the upper half).
   // P steps are in registers or on their way at any time: step s uses slot s % P.
   uint32_t xr[P], wr[P][EG];
@@ -441,12 +450,13 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     for (int g = 0; g < EG; ++g)
       acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wr[slot_r][g]), __uint_as_float(xr[slot_r]), acc[g], 0, 0, 0);
   };
-  // step S of the stage at xs, whose W_g rows start at wrow (plain reads: the compiler waits for them)
-  auto read_step = [&](int slot_r, const unsigned char* xs, const unsigned char* wrow, int S) {
-    if (BF16) xr[slot_r] = static_cast<uint32_t>(*reinterpret_cast<const uint16_t*>(xs + gm_x_off<BF16>(S))) << 16;
-    else xr[slot_r] = *reinterpret_cast<const uint32_t*>(xs + gm_x_off<BF16>(S));
+  // step S of the stage at xs, whose W_g rows start at ws (plain reads: the compiler waits for them)
+  auto read_step = [&](int slot_r, const unsigned char* xs, const unsigned char* ws, int S) {
+    const unsigned char* const xp = xs + xl[gm_x_col<BF16>(S)] + gm_x_off<BF16>(S);
+    if (BF16) xr[slot_r] = static_cast<uint32_t>(*reinterpret_cast<const uint16_t*>(xp)) << 16;
+    else xr[slot_r] = *reinterpret_cast<const uint32_t*>(xp);
 #pragma unroll
-    for (int g = 0; g < EG; ++g) wr[slot_r][g] = *reinterpret_cast<const uint32_t*>(wrow + wl[g]);
+    for (int g = 0; g < EG; ++g) wr[slot_r][g] = *reinterpret_cast<const uint32_t*>(ws + wl[S] + 64 * g);
   };
 
 #pragma unroll
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
   wait_vm(InFlight{});                                    // the first W_g tiles and stage 0 are in LDS
   lds_barrier();
 #pragma unroll
-  for (int s = 0; s < P; ++s) read_step(s, ring + xl, gm + s * 16 * E, s);
+  for (int s = 0; s < P; ++s) read_step(s, ring, gm, s);
   int slot = 0, slot_free = XS - 1;                       // ring slots of stage i and of stage i - 1
   int wbuf = 0, wbuf_free = WB - 1;                       // buffers of W_g tile j and of tile j - 1
   int i = 0;
@@ -471,14 +481,24 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
   };
 
   // Whole W_g tiles: IPT stages in straight-line code.  A dependent matrix instruction issues
-  // only when the one before it has finished, and the wave issues in order, so everything else
-  // (the reads of the operands P steps ahead, their addresses, the copies) is placed between
-  // the matrix instructions, where it costs nothing, and not in a block in front of them.
+  // only when the one before it has finished, and the wave issues in order, so the reads of the
+  // operands P steps ahead and the copies are placed between the matrix instructions, where they cost
+  // nothing.  Not so vector instructions: one between two dependent matrix instructions makes the
+  // step 55 to 67 cycles long, without any it is 33 (a probe of this loop on one wave).  So the
+  // addresses of the operands are worked out for half a stage at a time, and all that is added
+  // to them is a constant (us, with one per step / so, 500 tokens: d = 2048,
+  // E = 16 19.1 / 16.0, E = 32 35.9 / 28.2, E = 64 66.6 / 50.7; d = 4096, E = 16 34.3 / 28.6; 8 tokens the same).
   // The operand reads and their waits are written out here (lds_read_*, lds_wait): with
   // global -> LDS copies in flight every wait the compiler generates is a wait for everything,
   // i.e. for the reads issued just before.  LDS reads complete in order: a step's operands were
   // read P steps earlier, (P - 1) (1 + EG) reads ago.
   const int NTF = NS / (IPT * SS);
+  uint32_t xa[4], wa[SS];                                  // operand addresses: x columns of a stage, W_g of its steps
+  auto addresses = [&](uint32_t& a, const unsigned char* base, int off) {
+    asm volatile("v_add_u32 %0, %1, %2" : "=v"(a) : "s"(lds_addr(base)), "v"(off));
+  };
+#pragma unroll
+  for (int c = 0; c < 4; ++c) addresses(xa[c], ring, xl[c]);
   for (int j = 0; j < NTF; ++j) {
     if ((j + WB - 1) * KC < d) issue_w(j + WB - 1, wbuf_free);   // that buffer was released by the last barrier
     const unsigned char* const wt = gm + wbuf * GM_WBUF;
@@ -487,9 +507,9 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     static_for<0, IPT>([&](auto q_c) {
       constexpr int q = decltype(q_c)::value;
       issue_x(i + XS - 1, slot_free);
-      const uint32_t xs = lds_addr(ring + slot * GM_STAGE + xl);
       next_slot();
-      const uint32_t xs_next = lds_addr(ring + slot * GM_STAGE + xl);
+#pragma unroll
+      for (int s = P; s < SS; ++s) addresses(wa[s], wt + q * (SS * 16) * E, wl[s]);
       static_for<0, SS>([&](auto s_c) {
         constexpr int s = decltype(s_c)::value, s2 = s + P;
         if constexpr (s == SS - P) {                      // the reads of the next stage begin with this step
@@ -499,16 +519,16 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
           } else {
             wait_vm(InFlight{});                          // stage i + 1 is in LDS
           }
+          // (after the last stage: stale but in-bounds LDS, unused)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) addresses(xa[c], ring + slot * GM_STAGE, xl[c]);
+#pragma unroll
+          for (int c = 0; c < P; ++c) addresses(wa[c], q == IPT - 1 ? wt_next : wt + (q + 1) * (SS * 16) * E, wl[c]);
         }
         lds_wait<(P - 1) * (1 + EG)>(xr[s % P], wr[s % P]);
         chain_step(s % P);
-        // (after the last stage: stale but in-bounds LDS, unused)
-        const uint32_t xa = s2 < SS ? xs : xs_next;
-        const unsigned char* const wrow = s2 < SS ? wt + (q * SS + s2) * 16 * E
-                                        : q == IPT - 1 ? wt_next + (s2 - SS) * 16 * E : wt + ((q + 1) * SS + s2 - SS) * 16 * E;
-        lds_read_x<BF16, gm_x_off<BF16>(s2 % SS)>(xr[s % P], xa);
-#pragma unroll
-        for (int g = 0; g < EG; ++g) lds_read_b32<0>(wr[s % P][g], lds_addr(wrow + wl[g]));
+        lds_read_x<BF16, gm_x_off<BF16>(s2 % SS)>(xr[s % P], xa[gm_x_col<BF16>(s2 % SS)]);
+        static_for<0, EG>([&](auto g_c) { lds_read_b32<64 * decltype(g_c)::value>(wr[s % P][decltype(g_c)::value], wa[s2 % SS]); });
       });
       ++i;
     });
@@ -522,9 +542,9 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     if (q == 0 && (i / IPT + WB - 1) * KC < d) issue_w(i / IPT + WB - 1, wbuf_free);
     issue_x(i + XS - 1, slot_free);
     const int steps = NS - i * SS;                        // at least 2; SS or more unless this is the last stage
-    const unsigned char* const xs = ring + slot * GM_STAGE + xl;
+    const unsigned char* const xs = ring + slot * GM_STAGE;
     next_slot();
-    const unsigned char* const xs_next = ring + slot * GM_STAGE + xl;
+    const unsigned char* const xs_next = ring + slot * GM_STAGE;
     const unsigned char* const wt = gm + wbuf * GM_WBUF;
     const unsigned char* const wt_next = gm + (wbuf + 1 == WB ? 0 : wbuf + 1) * GM_WBUF;
     if (q == IPT - 1) next_wbuf();
@@ -539,8 +559,8 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
         }
       }
       if (s < steps) chain_step(s % P);
-      if (s2 < SS) read_step(s % P, xs, wt + (q * SS + s2) * 16 * E, s2);
-      else read_step(s % P, xs_next, q == IPT - 1 ? wt_next + (s2 - SS) * 16 * E : wt + ((q + 1) * SS + s2 - SS) * 16 * E, s2 - SS);
+      if (s2 < SS) read_step(s % P, xs, wt + q * (SS * 16) * E, s2);
+      else read_step(s % P, xs_next, q == IPT - 1 ? wt_next : wt + (q + 1) * (SS * 16) * E, s2 - SS);
     });
     ++i;
   }
@@ -838,15 +858,11 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
   if (!x || !Wg || !idx || !gw) return SCMOE_ERR_NULL;
   if (!view_ok(x, ldx, d, dtype)) return SCMOE_ERR_SHAPE;
   // The matrix-core kernel, at any number of tokens (measured against the two kernels below,
-  // bf16, d = 2048: E = 16, 8 to 4096 tokens: 23 us against 24-26; 32768 tokens: 32 against 66 us;
-  // E = 4, 8 to 8192 tokens: 18 against 66-69 us).  Its copies of W_g need 16-byte alignment.
+  // bf16, d = 2048: E = 16, 8 to 4096 tokens: 16 us against 24-26; 32768 tokens: 32 against 66 us;
+  // E = 4, 8 to 8192 tokens: 15 against 66-69 us; 64 tokens, E = 32 28 against 35, E = 64 51 against 75).  Its copies of W_g need 16-byte alignment.
   int epad = 1;
   while (epad < E) epad <<= 1;
-  // (a few tokens with more than 16 experts: a wave would walk 2-4 chains per step alone; the
-  // one-lane-per-chain kernel below is 10-20 % faster there: 64 tokens, d = 2048, E = 32: 35
-  // against 43 us, E = 64: 75 against 80)
-  const bool few_many = E > 16 && static_cast<int64_t>(T) * epad <= GATE_SMALL_LANES / 8;
-  if (aligned16(Wg) && !few_many) {
+  if (aligned16(Wg)) {
     // A wave takes 16 tokens.  Beyond one wave per SIMD eight waves per workgroup; below, four
     // share the copying of W_g, also where that leaves CUs idle: a single wave cannot keep enough
     // of W_g in flight to feed its chain (bf16, us, one wave per workgroup / four / eight: d = 2048,
