@@ -1,28 +1,30 @@
-// Grouped GEMM whose operands go straight from global memory into matrix-instruction
-// registers: the fp32 expert computation, bf16 layers whose widths the tiled kernel does not
+// Grouped GEMM without operand tiles that a workgroup shares: the fp32 expert computation, bf16 layers whose widths the tiled kernel does not
 // cover, and bf16 calls of a few rows per expert (decode steps), which are bound by streaming
 // the weights (ScMoE paper Eq. (1); experts are two-layer MLPs, Sec. 2.1; the memory-limited
 // inference setting is Sec. 5.3).
 //
 //   C[r, n] = act( sum_k A[row(r), k] * W[e, n, k] + bias[e, n] ),  r in segment e
 //
-// A workgroup owns 16 MI rows x 16 NJ columns of one segment and its waves split K among
+// A workgroup owns 16 MI rows x 16 NJ columns of one segment and its four waves split K among
 // themselves: every wave walks its own share of k for the whole tile, so no wave ever waits for
-// another one, there is no LDS and no barrier in the loop, and a call whose tiles are few still
-// has WK times as many waves in flight.  At the end the waves' sums meet in LDS, are added in
-// wave order (the result does not depend on timing), and every wave finishes a share of the tile.
+// another one, there is no barrier in the loop, and a call whose tiles are few still has four times as
+// many waves in flight.  At the end the waves' sums meet in LDS, are added in wave order (the
+// result does not depend on timing), and every wave finishes a share of the tile.
 //  * An operand fragment is 16 rows x 64 bytes, lane l holding 16-byte piece l / 16 of row
 //    l % 16: 32 k of bf16, one v_mfma_f32_16x16x32_bf16; or 16 k of fp32, four
 //    v_mfma_f32_16x16x4_f32, the c-th of which takes the c-th element of every piece (the k
 //    order inside a fragment is permuted alike for both operands, which a sum does not notice).
 //    fp32 products and sums are exact fused multiply-adds in fp32, like the vector ALU's.
-//  * The fragments of the next PF steps are in flight while one is multiplied (a ring of
-//    registers; loads complete in order, so the wait for a step leaves the others in flight).
-//  * fp32: 64 x 64 tiles need 16 bytes per clock and compute unit from the L1 at the full rate of
-//    the fp32 matrix instruction, a quarter of what it gives, so LDS tiles would not help.  Measured:
-//    94 of 153 TFLOP/s at 4096 tokens, d = 1024, F = 2048, E = 8 (the vector ALUs before: 20-30);
-//    what is missing are waves: 1.75 per SIMD, each with two or three steps of loads in flight.
-//  * Few rows: the weights arrive at 4.5 TB/s (8 tokens, 235 MB a launch) to 5.6 TB/s (64 tokens, 537
+//  * Small tiles: a wave's fragments come through a ring of its own in LDS, by copies whose lanes 4 r to
+//    4 r + 3 share the 64 bytes of row r.  Loaded as the instruction takes them, 16 neighbouring lanes
+//    read 16 rows, which takes the compute unit's address path up to four times as long: from the
+//    caches 18-38 B/ns a compute unit, so 63-125, and streaming weights asks for 25 of them and as much
+//    again of activations.  Layer us, registers / rings: 16 tokens, d = 1024, E = 16 75 / 70, 32 tokens,
+//    d = 2048 235 / 213, 300 tokens, d = 512 52 / 47; fp32, 200 tokens, d = 1024 223 / 202, 64 tokens, d = 2048,
+//    E = 8 340 / 308.  The copies of the next PF steps are in flight while a step is multiplied.
+//  * 64 x 64 tiles: fragments straight into registers, two or three steps ahead; fp32 94 of 153 TFLOP/s at
+//    4096 tokens, d = 1024, F = 2048, E = 8 (the vector ALUs: 20-30).
+//  * Few rows: the weights arrive at 4.7 TB/s (8 tokens, 235 MB a launch) to 5.7 TB/s (64 tokens, 537
 //    MB); a plain read of that size reaches 6.3.
 //  * A segment's last tile multiplies only the 16-row subtiles that hold rows (loop variants of
 //    1, 2 and 4 subtiles).
@@ -42,21 +44,28 @@ struct DirectArgs {
 constexpr int GRID_X = 1 << 16;   // workgroups per row of the grid (the runtime takes fewer than 2^32 work-items in x);
                                   // those past the last tile find no row and leave
 
-template <bool F32, int MI, int NJ, int WK>
+template <bool F32, int MI, int NJ>
 struct DirectCfg {
-  static constexpr int BM = 16 * MI, BN = 16 * NJ, THREADS = 64 * WK;
-  static constexpr int PARTS = WK > 4 ? 4 : WK;                 // sums that meet in LDS at the end
-  static constexpr int LDS = PARTS * MI * NJ * 1024;
-  static_assert(MI == 2 || MI == 4, "row subtiles");
-  static_assert(WK == 4 || WK == 8, "waves");
+  static constexpr int BM = 16 * MI, BN = 16 * NJ, WK = 4, THREADS = 64 * WK;
+  // Operands through rings in LDS, except for 64 x 64 tiles, whose rings would hold two steps only
+  // (fp32: 4096 tokens, d = 1024, E = 8 727 us of layer time through registers, 739 through LDS; 3000 tokens
+  // of 1000 columns, bf16, 355 / 394).
+  static constexpr bool RING = MI * NJ < 16;
+  static constexpr int STEP = (MI + NJ) * 1024;                 // bytes of a ring slot: one step's fragments
+  static constexpr int FIT = 64 / (WK * (MI + NJ));             // 64 KiB, so that two workgroups fit a compute unit
+  static constexpr int PF = FIT < 5 ? FIT : 5;                  // ring slots per wave
+  static constexpr int RED = WK * MI * NJ * 1024;               // sums (in the rings' place at the end)
+  static constexpr int LDS = RING && WK * PF * STEP > RED ? WK * PF * STEP : RED;
+  static_assert(MI == 1 || MI == 2 || MI == 4, "row subtiles");
   static_assert(LDS <= 64 * 1024, "static LDS");
 };
 
-template <bool F32, int MI, int NJ, int WK>
-__global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArgs args) {
-  using CFG = DirectCfg<F32, MI, NJ, WK>;
-  constexpr int EB = F32 ? 4 : 2;
-  __shared__ __attribute__((aligned(16))) f32x4_t red[CFG::PARTS][MI * NJ][64];
+template <bool F32, int MI, int NJ>
+__global__ __launch_bounds__(256, 2) void gemm_direct_kernel(const DirectArgs args) {
+  using CFG = DirectCfg<F32, MI, NJ>;
+  constexpr int EB = F32 ? 4 : 2, WK = CFG::WK;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[CFG::LDS];
+  auto& red = *reinterpret_cast<f32x4_t(*)[WK][MI * NJ][64]>(smem);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
@@ -105,20 +114,23 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   // ---- operand rows of this lane (rows past the segment or past N re-read the last one) --------
   const unsigned char* const abase = p.A;
   const unsigned char* const wbase = p.W + static_cast<int64_t>(e) * p.N * p.ldw * EB;
+  // RING: lane l of a copy fetches 16 bytes of row l / 4 of a fragment, so that four lanes share 64
+  // bytes; otherwise a lane loads what it multiplies.
+  const int crow = CFG::RING ? lane >> 2 : l16, cpiece = CFG::RING ? (lane & 3) ^ swz<4>(crow) : lq;
   int64_t ao[MI], wo[NJ];
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    int r = row0 + i * 16 + l16;
+  auto a_row = [&](int r) {                                     // byte offset of the packed row r
     if (r > row_end - 1) r = row_end - 1;
     const int64_t src = p.gather ? p.gather[r] : r;
-    ao[i] = src * p.lda * EB + lq * 16;
-  }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    int n = n0 + j * 16 + l16;
+    return src * p.lda * EB;
+  };
+  auto w_row = [&](int n) {
     if (n > p.N - 1) n = p.N - 1;
-    wo[j] = static_cast<int64_t>(n) * p.ldw * EB + lq * 16;
-  }
+    return static_cast<int64_t>(n) * p.ldw * EB;
+  };
+#pragma unroll
+  for (int i = 0; i < MI; ++i) ao[i] = a_row(row0 + i * 16 + crow) + cpiece * 16;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) wo[j] = w_row(n0 + j * 16 + crow) + cpiece * 16;
   // ---- what the epilogue needs of fragment (i, j) of the tile ------------------------------------
   struct Finish { f32x4_t bias; int orow; float rscale; };
   auto finish_loads = [&](int i, int jj) {
@@ -186,14 +198,122 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
   const int s1 = static_cast<int>(static_cast<int64_t>(wave + 1) * full / WK);
   const bool has_tail = tail != 0 && wave == WK - 1;
   const int subs = (row_end - row0 + 15) >> 4;                  // subtiles that hold rows
-  auto body = [&](auto ns_c) {
+  unsigned char* const ring = smem + wave * (CFG::PF * CFG::STEP);
+  uint32_t rbase = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(SCMOE_LDS_PTR(ring)));
+  asm volatile("" : "+s"(rbase));                               // (plain integers: see gemm_bf16_kernel's lds0)
+  const uint32_t rlane = rbase + (l16 * 4 + (lq ^ swz<4>(l16))) * 16;      // this lane's piece of a fragment
+  typedef const __attribute__((address_space(3))) u32x4_t* lds_piece_ptr;
+  auto sums_ring = [&](auto ns_c, auto& acc) {
+    constexpr int NS = decltype(ns_c)::value;
+    constexpr int PF = CFG::PF, LPS = NS + NJ;                  // copies per step
+    static_assert(PF * LPS < 64, "vmcnt field");
+    u32x4_t ra[2][NS], rb[2][NJ];
+    // A wave starts in the middle of its share (another place for each tile) and wraps round: with
+    // row strides of a power of two, tiles that walk k in step would all be at the same few memory
+    // channels.
+    // fp32: it starts at a multiple of 6 steps that depends on the columns and the segment alone, and
+    // the steps past the last such multiple come last: the order of a row's sum, and so its bits, do
+    // not depend on the other rows of the call or on the tile shape.  (Layer us with the place depending
+    // on the tile / so, before the rings: 2048 tokens, d = 384, E = 8 158.6 / 160.8; 200 tokens, d = 1024,
+    // E = 16 216 / 221; 64, d = 2048, E = 8 364 / 340; 8, d = 2048, E = 16 233 / 224; by the columns alone
+    // the first is 164.8, not at all 162.6.)
+    const int n = s1 - s0;
+    constexpr int UNIT = F32 ? 6 : 4;
+    const int starts = n / UNIT, round = starts * UNIT;           // steps that take part in the rotation
+    const int first = starts > 0 ? ((F32 ? n0 / 64 * 5 + e * p.rotk : b * 5) + wave) % starts * UNIT : 0;
+    int at = first, done = 0;                                     // the step to be requested next, and how many have been
+    auto issue = [&](int slot) {
+      const int step = s0 + (done < round ? at : done);
+      ++done;
+      at = at + 1 == round ? 0 : at + 1;
+      const unsigned char* a = abase + static_cast<int64_t>(step) * 64;
+      const unsigned char* w = wbase + static_cast<int64_t>(step) * 64;
+      unsigned char* dst = ring + slot * CFG::STEP;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(w + wo[j]), SCMOE_LDS_PTR(dst + j * 1024), 16, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NS; ++i) __builtin_amdgcn_global_load_lds(SCMOE_GLB_PTR(a + ao[i]), SCMOE_LDS_PTR(dst + (NJ + i) * 1024), 16, 0, 0);
+    };
+    auto read = [&](auto buf_c, int slot) {                       // the fragments of the step in `slot`
+      constexpr int buf = decltype(buf_c)::value;
+      const uint32_t at0 = rlane + slot * CFG::STEP;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) rb[buf][j] = *reinterpret_cast<lds_piece_ptr>(static_cast<uintptr_t>(at0 + j * 1024));
+#pragma unroll
+      for (int i = 0; i < NS; ++i) ra[buf][i] = *reinterpret_cast<lds_piece_ptr>(static_cast<uintptr_t>(at0 + (NJ + i) * 1024));
+    };
+    auto compute = [&](auto buf_c) {
+      constexpr int u = decltype(buf_c)::value;
+      // (fp32: element by element over all accumulators, so that no instruction waits for the
+      // one before it)
+#pragma unroll
+      for (int c = 0; c < (F32 ? 4 : 1); ++c)
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            if constexpr (F32)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(rb[u][j][c]), __uint_as_float(ra[u][i][c]), acc[i][j], 0, 0, 0);
+            else
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, rb[u][j]),
+                                                                  __builtin_bit_cast(bf16x8_t, ra[u][i]), acc[i][j], 0, 0, 0);
+          }
+    };
+    // until the oldest step in flight has landed (copies complete in issue order); `flying` steps are
+    auto landed = [&](int flying) {
+      static_for<0, PF>([&](auto f_c) {
+        constexpr int f = decltype(f_c)::value, c = f * LPS;      // f younger ones may still be on their way
+        if (flying == f + 1 || (f == PF - 1 && flying > f)) __builtin_amdgcn_s_waitcnt((c & 15) | ((c >> 4) << 14) | 0x0F70);
+      });
+      asm volatile("" ::: "memory");
+    };
+    using B0 = std::integral_constant<int, 0>;
+    using B1 = std::integral_constant<int, 1>;
+    for (int t = 0; t < PF; ++t)
+      if (t < n) issue(t);
+    if (n > 0) {
+      landed(done);
+      read(B0{}, 0);
+    }
+    int slot = 0;                                                 // of the step in the registers
+    // step t is in registers; step t + 1 is read while t is multiplied, then its slot's predecessor is refilled
+    auto turn = [&](auto cur, auto next, int t) {
+      const int after = slot + 1 == PF ? 0 : slot + 1;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // step t is in registers: its slot is free
+      if (done < n) issue(slot);
+      if (t + 1 < n) {
+        landed(done - (t + 1));
+        read(next, after);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      compute(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      slot = after;
+    };
+    for (int t = 0; t < n; t += 2) {
+      turn(B0{}, B1{}, t);
+      if (t + 1 < n) turn(B1{}, B0{}, t + 1);
+    }
+    if (has_tail) {                                             // pieces past the end of a row count as zeros
+      const bool in = lq < tail;
+      const u32x4_t zero = {0u, 0u, 0u, 0u};
+      const int64_t off = static_cast<int64_t>(full) * 64 + (in ? lq * 16 : 0);   // (else the step's first piece, unused)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(wbase + w_row(n0 + j * 16 + l16) + off);
+        rb[0][j] = in ? v : zero;
+      }
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(abase + a_row(row0 + i * 16 + l16) + off);
+        ra[0][i] = in ? v : zero;
+      }
+      compute(B0{});
+    }
+  };
+  auto sums_regs = [&](auto ns_c, auto& acc) {
     constexpr int NS = decltype(ns_c)::value;
     constexpr int PF = NS >= 4 ? 3 : NS == 2 ? (F32 ? 3 : 4) : 6;
-    f32x4_t acc[NS][NJ];
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     u32x4_t ra[PF][NS], rb[PF][NJ];
     // The PF steps of a block are read from where `seek` has put the bases.  A wave starts in
     // the middle of its share (another block for each tile) and wraps round: with row strides of
@@ -292,28 +412,28 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
       }
       compute(0);
     }
-    // more than four waves: the upper half hands its sums to the lower half first
-    constexpr int P = CFG::PARTS;
-    if (WK > P && wave >= P) {
-#pragma unroll
-      for (int i = 0; i < NS; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) red[wave - P][i * NJ + j][lane] = acc[i][j];
-    }
-    if (WK > P) __syncthreads();
-    if (wave < P) {
-#pragma unroll
-      for (int i = 0; i < NS; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {                          // (this lane's own slots)
-          if (WK > P) red[wave][i * NJ + j][lane] += acc[i][j];
-          else red[wave][i * NJ + j][lane] = acc[i][j];
-        }
-    }
   };
-  if (subs <= 1) body(std::integral_constant<int, 1>{});
+  auto body = [&](auto ns_c) {
+    constexpr int NS = decltype(ns_c)::value;
+    f32x4_t acc[NS][NJ];
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (CFG::RING) {
+      sums_ring(ns_c, acc);
+      __syncthreads();                                          // the rings have been read: the sums take their place
+    } else {
+      sums_regs(ns_c, acc);
+    }
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) red[wave][i * NJ + j][lane] = acc[i][j];
+  };
+  if (MI == 1 || subs <= 1) body(std::integral_constant<int, 1>{});
   else if (MI == 2 || subs == 2) body(std::integral_constant<int, 2>{});
-  else body(std::integral_constant<int, MI>{});
+  else body(std::integral_constant<int, MI < 2 ? 2 : MI>{});
   __syncthreads();
 #pragma unroll
   for (int f = 0; f < FPW; ++f) {
@@ -321,16 +441,16 @@ __global__ __launch_bounds__(64 * WK, 2) void gemm_direct_kernel(const DirectArg
     if (i >= subs || i >= MI) continue;                           // (wave-uniform)
     f32x4_t v = red[0][q][lane];
 #pragma unroll
-    for (int s = 1; s < CFG::PARTS; ++s) v += red[s][q][lane];
+    for (int s = 1; s < WK; ++s) v += red[s][q][lane];
     finish(i, jj, v, fin[f]);
   }
 }
 
 // ---- host side ----------------------------------------------------------------------------------
 
-template <bool F32, int MI, int NJ, int WK>
+template <bool F32, int MI, int NJ>
 static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
-  using CFG = DirectCfg<F32, MI, NJ, WK>;
+  using CFG = DirectCfg<F32, MI, NJ>;
   DirectArgs a{};
   int64_t blocks[2] = {0, 0};
   for (int q = 0; q < n; ++q) {
@@ -350,22 +470,23 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
   if (n == 1) a.j[1].nt = 1;                                    // (workgroups past the last tile: no rows there)
   const dim3 grid(static_cast<unsigned>(total < GRID_X ? total : GRID_X), static_cast<unsigned>((total + GRID_X - 1) / GRID_X)),
       block(CFG::THREADS);
-  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ, WK>), grid, block, 0, stream, a);
+  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ>), grid, block, 0, stream, a);
   return launch_status();
 }
 
 // Which tile, measured as a layer call's time (us) at d = 2048, F = 8192, E = 16 unless noted:
-//  * 64 x 64, four waves: when that gives every compute unit a tile and the segments average 32
-//    rows or more (fp32, 2048 tokens, d = 384: 165 against 190 with 32 x 32).
-//  * 32 x 32, four waves: everything smaller; weights are streamed (64 tokens: 251 against 261;
-//    fp32, 64 tokens, d = 1024: 126 against 155).
-//  * 32 x 16, eight waves: when those tiles would put fewer than 16 waves on a compute unit and K is
-//    long enough for eight (8 tokens, second GEMM alone: 48 against 64; d = 512: 33 against 29,
-//    hence the bound on K).  fp32: four waves like the others, so that K is always summed in the same
-//    four parts (8 tokens 224 against 232 with eight).
+//  * 64 x 64: when that gives every compute unit a tile and the segments average 32 rows or more
+//    (fp32, 2048 tokens, d = 384: 165 against 190 with 32 x 32).
+//  * 32 x 32: everything smaller; weights are streamed (64 tokens, shared expert on a second stream: 243
+//    against 252 with 32 x 16 where that fits and 250 with 16 x 32).
+//  * 16 x 16, bf16: when 32 x 32 tiles would put fewer than 16 waves on a compute unit, K is long and
+//    no segment has more than 16 rows (8 tokens 133.5 against 138 with 32 x 32 or 16 x 32; 16 tokens, d =
+//    1024 68 / 73); fp32 takes 32 x 16 there.
+//  * 16 x 32, bf16: other calls of 32 rows and fewer a product (32 tokens 213 against 229; top-2 of 8 tokens,
+//    d = 768 35.1 / 35.5).
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
-  int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0;
+  int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0, most = 0;   // most: rows of a product
   int steps = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = jobs[q].g;
@@ -374,12 +495,19 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     tiles32 += (r / 32 + s) * ((g.N + 31) / 32);
     rows += r;
     segs += s;
+    if (r > most) most = r;
     const int st = g.Kd * (F32 ? 4 : 2) / 64;
     if (st > steps) steps = st;
   }
-  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4, 4>(jobs, n, stream);
-  if (tiles32 * 4 < 16 * num_cus() && steps >= 128) return launch_direct_cfg<F32, 2, 1, F32 ? 4 : 8>(jobs, n, stream);
-  return launch_direct_cfg<F32, 2, 2, 4>(jobs, n, stream);
+  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4>(jobs, n, stream);
+  const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128;
+  if constexpr (F32) {
+    if (few_waves) return launch_direct_cfg<F32, 2, 1>(jobs, n, stream);
+  } else {
+    if (few_waves && most <= 16) return launch_direct_cfg<F32, 1, 1>(jobs, n, stream);
+    if (most <= 32) return launch_direct_cfg<F32, 1, 2>(jobs, n, stream);
+  }
+  return launch_direct_cfg<F32, 2, 2>(jobs, n, stream);
 }
 
 int launch_gemm_direct(const DirectJob* jobs, int n, int dtype, hipStream_t stream) {
