@@ -84,6 +84,16 @@ struct ScanChores {
   int32_t* joint_offsets = nullptr;
 };
 
+// What the input encode of a layer call writes (its inputs are the gate's choices).
+struct DispatchOut {
+  int32_t* counts = nullptr;
+  int32_t* offsets = nullptr;
+  int32_t* dst_row = nullptr;
+  int32_t* src_token = nullptr;
+  int capacity = 0;
+  ScanChores ch;
+};
+
 // ---- entry points implemented in one source and used by the layer orchestration --------
 enum { FFN_AUTO = 0, FFN_TILED = 1, FFN_DIRECT = 2 };
 // One expert-FFN call over packed segments.  All strides in elements.

@@ -346,7 +346,7 @@ struct GateMfmaCfg {
   static constexpr int KC = 256 / EG;                 // features per W_g tile: at most 16 KiB
   static constexpr int IPT = KC / SF;                 // stages per W_g tile
   static constexpr int WB = EG == 1 ? 2 : EG == 2 ? 3 : 4;             // W_g buffers: tile j + WB - 1 is requested when tile j begins
-  static constexpr int XS = EG == 1 ? (NW == 8 ? 7 : 8) : EG == 2 ? 6 : 5;   // x ring stages per wave
+  static constexpr int XS = NW == 16 ? 3 : EG == 1 ? (NW == 8 ? 7 : 8) : EG == 2 ? 6 : 5;   // x ring stages per wave
   static constexpr int P = EG == 1 ? SS / 2 : EG == 2 ? 4 : 2;         // steps the operand reads run ahead of their use
   static constexpr int LGS = 16 * EG + 1;             // row stride of the logit exchange buffer
   static constexpr int TOK = 16 * NW;
@@ -358,11 +358,75 @@ struct GateMfmaCfg {
   static_assert(LDS + 2 * TOK * 4 <= 160 * 1024, "LDS of a compute unit");
 };
 
-template <bool BF16, int NW, int EG>
+// The input encode of a call whose tokens all belong to this workgroup: thread i has item i = j T + t (the
+// order of dispatch_onepass, whose results these are), at most 64 NW of them.  lds: (NW + 1) * 64 ints.
+template <int NW>
+__device__ __forceinline__ void dispatch_own(const int32_t* expert_idx, int T, int k, int E, const DispatchOut& o, int* lds) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = threadIdx.x;
+  for (int z = i; z < o.ch.nzero; z += 64 * NW) {
+    if (o.ch.zero_a != nullptr) o.ch.zero_a[z] = 0;
+    if (o.ch.zero_b != nullptr) o.ch.zero_b[z] = 0;
+  }
+  if (o.ch.pair != nullptr && i == 0) {
+    o.ch.pair[0] = 0;
+    o.ch.pair[1] = o.ch.pair_hi;
+  }
+  const int n = T * k, j = i / T, t = i - j * T;
+  int e = -1;
+  if (i < n) e = expert_idx[t * k + j];
+  if (e >= E) e = -1;
+  // items of the wave whose expert is `lane`, and the lanes that hold this lane's expert
+  unsigned long long mine = __ballot(e >= 0), same = mine;
+  for (int b = 0; (1 << b) < E; ++b) {
+    const unsigned long long bal = __ballot(e >= 0 && ((e >> b) & 1));
+    mine &= ((lane >> b) & 1) ? bal : ~bal;
+    same &= ((e >> b) & 1) ? bal : ~bal;
+  }
+  const int rank = __popcll(same & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+  lds[wave * 64 + lane] = __popcll(mine);
+  __syncthreads();
+  if (wave == 0) {
+    int run = 0;                                          // items of expert `lane` in the waves before
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int c = lds[w * 64 + lane];
+      lds[w * 64 + lane] = run;
+      run += c;
+    }
+    const int c = lane < E ? (run < o.capacity ? run : o.capacity) : 0;
+    int incl = c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += up;
+    }
+    lds[NW * 64 + lane] = incl - c;
+    if (lane < E) {
+      o.counts[lane] = c;
+      o.offsets[lane] = incl - c;
+      if (lane == E - 1) o.offsets[E] = incl;
+    }
+  }
+  __syncthreads();
+  if (i < n) {
+    int out = -1;
+    if (e >= 0) {
+      const int slot = lds[wave * 64 + e] + rank;
+      if (slot < o.capacity) {
+        out = lds[NW * 64 + e] + slot;
+        o.src_token[out] = t;
+      }
+    }
+    o.dst_row[t * k + j] = out;
+  }
+}
+
+// ENC: the launch is one workgroup, which does the input encode as well (dispatch_own).
+template <bool BF16, int NW, int EG, bool ENC>
 __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     const unsigned char* __restrict__ x, int64_t ldx, const float* __restrict__ Wg,
     const float* __restrict__ bias, int T, int d, int E, int k, int normalize,
-    int32_t* __restrict__ expert_idx, float* __restrict__ gate_w, float* __restrict__ probs) {
+    int32_t* __restrict__ expert_idx, float* __restrict__ gate_w, float* __restrict__ probs, const DispatchOut enc) {
   using C = GateMfmaCfg<BF16, NW, EG>;
   constexpr int EB = C::EB, SS = C::SS, KC = C::KC, IPT = C::IPT, WB = C::WB, XS = C::XS, P = C::P;
   constexpr int TOK = C::TOK, LGS = C::LGS;
@@ -628,6 +692,10 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
       expert_idx[t] = bi;
       gate_w[t] = w;
     }
+    if constexpr (ENC) {
+      __syncthreads();                                    // the choices are written, the buffers free
+      dispatch_own<NW>(expert_idx, T, k, E, enc, reinterpret_cast<int*>(gm));
+    }
     return;
   }
   lds_barrier();                                          // the W_g buffers are free: reuse them for the logits
@@ -655,24 +723,30 @@ __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
       probs[static_cast<int64_t>(t0) * E + c] = expf(lg[tok * LGS + e] - row_max[tok]) / row_sum[tok];
     }
   }
+  if constexpr (ENC) {
+    __syncthreads();
+    dispatch_own<NW>(expert_idx, T, k, E, enc, reinterpret_cast<int*>(gm));
+  }
 }
 
-template <bool BF16, int NW, int EG>
+template <bool BF16, int NW, int EG, bool ENC = false>
 static int launch_gate_mfma(const void* x, int64_t ldx, const float* Wg, const float* bias, int T, int d, int E,
-                            int k, int normalize, int32_t* idx, float* gw, float* probs, hipStream_t stream) {
+                            int k, int normalize, int32_t* idx, float* gw, float* probs, hipStream_t stream,
+                            const DispatchOut& enc = DispatchOut{}) {
   constexpr int LDS = GateMfmaCfg<BF16, NW, EG>::LDS;
   static std::atomic<bool> attr_set[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
   if (dev < 0 || !attr_set[dev].load(std::memory_order_acquire)) {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_mfma_kernel<BF16, NW, EG>),
+    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_mfma_kernel<BF16, NW, EG, ENC>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (err != hipSuccess) return hip_fail(err);
     if (dev >= 0) attr_set[dev].store(true, std::memory_order_release);
   }
   dim3 grid((T + 16 * NW - 1) / (16 * NW)), block(64 * NW);
-  hipLaunchKernelGGL((gate_mfma_kernel<BF16, NW, EG>), grid, block, LDS, stream, static_cast<const unsigned char*>(x), ldx,
-                     Wg, bias, T, d, E, k, normalize, idx, gw, probs);
+  if (ENC && grid.x != 1) return SCMOE_ERR_ARG;
+  hipLaunchKernelGGL((gate_mfma_kernel<BF16, NW, EG, ENC>), grid, block, LDS, stream, static_cast<const unsigned char*>(x), ldx,
+                     Wg, bias, T, d, E, k, normalize, idx, gw, probs, enc);
   return launch_status();
 }
 
@@ -923,6 +997,32 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
   else SCMOE_GATE(8, 8, 1);                        // two tokens per lane would need more than 64 KiB of LDS
 #undef SCMOE_GATE
   return launch_status();
+}
+
+// Gate and input encode of a layer call in one launch of one workgroup: a launch less (4.7 us of host time
+// where a call is bound by its launches, 3-6 us of GPU time elsewhere).  Layer us, two launches / one: 8
+// tokens, d = 2048, E = 16 134.4 / 129.8; 1 token 52.8 / 48.4; 16, d = 1024 69.6 / 65.1; top-2 of 8, d = 768
+// 34.9 / 31.9; 60, d = 512, E = 64 67.2 / 65.2; 2, d = 256 23.3 / 19.4.  Up to 64 tokens that is one wave per SIMD, as
+// in the launch it replaces; with two or four on a SIMD the chain is slower, so more tokens only
+// where it is short: 256, d = 64, E = 4 24.5 / 20.7; 200, d = 128 23.4 / 20.9; 100, d = 1024 123.6 / 123.3; but 120, d =
+// 2048 129.0 / 133.0; 200, d = 256 24.7 / 25.6; 250, d = 256, E = 32 37.8 / 40.4.
+bool gate_dispatch_fits(const float* Wg, int T, int d, int E) {
+  return aligned16(Wg) && T >= 1 && (T <= 64 || (E <= 16 && ((T <= 128 && d <= 512) || (T <= 256 && d <= 128))));
+}
+
+int gate_dispatch(const void* x, int64_t ldx, int dtype, const float* Wg, const float* bias, int T, int d, int E, int k,
+                  int normalize, int32_t* idx, float* gw, const DispatchOut& enc, hipStream_t stream) {
+  if (!gate_dispatch_fits(Wg, T, d, E) || enc.ch.token_of != nullptr) return SCMOE_ERR_ARG;
+  const bool bf = dtype == SCMOE_BF16;
+#define SCMOE_GATE_ENC(NW, EG)                                                                                                \
+  return bf ? launch_gate_mfma<true, NW, EG, true>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, nullptr, stream, enc)    \
+            : launch_gate_mfma<false, NW, EG, true>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, nullptr, stream, enc)
+  if (T > 128) { SCMOE_GATE_ENC(16, 1); }
+  if (T > 64) { SCMOE_GATE_ENC(8, 1); }
+  if (E <= 16) { SCMOE_GATE_ENC(4, 1); }
+  if (E <= 32) { SCMOE_GATE_ENC(4, 2); }
+  SCMOE_GATE_ENC(4, 4);
+#undef SCMOE_GATE_ENC
 }
 
 }  // namespace scmoe

@@ -12,6 +12,9 @@ thread_local int g_last_hip_error = 0;
 int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const float* bias, int T,
               int d, int E, int k, int normalize, int32_t* idx, float* gw, float* probs,
               hipStream_t stream);
+bool gate_dispatch_fits(const float* Wg, int T, int d, int E);
+int gate_dispatch(const void* x, int64_t ldx, int dtype, const float* Wg, const float* bias, int T, int d, int E, int k,
+                  int normalize, int32_t* idx, float* gw, const DispatchOut& enc, hipStream_t stream);
 size_t dispatch_ws_bytes(int T, int E, int k);
 bool dispatch_is_one_launch(int T, int k);
 int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, int T, int d, int E,
@@ -212,11 +215,20 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
                         hipEvent_t before_ffn = nullptr, const FfnArgs* shared = nullptr,
                         const ScanChores* chores = nullptr, const float* row_coef = nullptr,
                         hipEvent_t coef_ready = nullptr, bool nothing_below = false, int path = FFN_AUTO) {
-  SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
-                      w.expert_idx, w.gate_w, nullptr, stream));
   // (no packed copy of the rows: the first GEMM gathers them on load)
-  SCMOE_TRY(dispatch(x, ldx, D->dtype, w.expert_idx, D->T, D->d, D->E, D->k, D->capacity, w.counts,
-                     w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, stream, chores));
+  if (gate_dispatch_fits(W->W_g, D->T, D->d, D->E) && (chores == nullptr || chores->token_of == nullptr)) {
+    DispatchOut enc;
+    enc.counts = w.counts; enc.offsets = w.offsets; enc.dst_row = w.dst_row; enc.src_token = w.src_token;
+    enc.capacity = D->capacity;
+    if (chores != nullptr) enc.ch = *chores;
+    SCMOE_TRY(gate_dispatch(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize, w.expert_idx,
+                            w.gate_w, enc, stream));
+  } else {
+    SCMOE_TRY(gate_topk(x, ldx, D->dtype, W->W_g, W->bias, D->T, D->d, D->E, D->k, D->normalize,
+                        w.expert_idx, w.gate_w, nullptr, stream));
+    SCMOE_TRY(dispatch(x, ldx, D->dtype, w.expert_idx, D->T, D->d, D->E, D->k, D->capacity, w.counts,
+                       w.offsets, w.dst_row, w.src_token, nullptr, D->d, w.disp_ws, w.disp_bytes, stream, chores));
+  }
   const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
   FfnArgs a{};
   a.x = x;

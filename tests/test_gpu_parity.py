@@ -584,6 +584,18 @@ def test_layer_bf16_mfma_path(oracle, T, d, F, k, shared, C_, normalize, cg, res
         assert np.array_equal(y[dropped], s[dropped])
 
 
+@pytest.mark.parametrize("T,d,E,k,C_,dtype", [
+    (1, 8, 1, 1, 5, "f32"), (16, 64, 5, 2, 4, "bf16"), (17, 200, 16, 1, 1, "bf16"), (63, 2048, 16, 4, 9, "bf16"),
+    (64, 72, 17, 3, 100000, "f32"), (64, 520, 64, 4, 3, "bf16"), (33, 256, 33, 2, 0, "bf16"),
+    (65, 512, 16, 1, 7, "bf16"), (128, 64, 3, 3, 50, "f32"), (128, 512, 7, 2, 100000, "bf16"),      # two waves on a SIMD
+    (129, 128, 16, 4, 20, "bf16"), (256, 64, 4, 1, 60, "f32"), (255, 8, 9, 2, 100000, "bf16"),      # four
+    (65, 520, 16, 1, 7, "bf16"), (129, 136, 4, 1, 30, "f32"), (257, 64, 4, 1, 80, "f32"), (65, 64, 17, 1, 4, "bf16")])   # two launches
+def test_layer_gate_and_encode_of_few_tokens(oracle, T, d, E, k, C_, dtype):
+    """The gate's workgroup does the input encode as well: routing against the oracle at the ends of its range."""
+    L = inputs.make_layer(T=T, d=d, F=64, E=E, dtype=dtype, seed=T + E, biases=False, w_scale=0.05)
+    _layer_case(oracle, L, dtype, E, k, C_, True)
+
+
 @pytest.mark.parametrize("T,d,F,E,C_,res", [
     (4200, 2048, 128, 16, 100000, False),   # no token dropped
     (4200, 2048, 384, 16, 150, False),      # half of them dropped: short tiles beside the full ones
