@@ -87,6 +87,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
+  // the arrival counters of the second GEMM's cut tiles (nothing is cut in this launch)
+  if (ACT && p.splitk_zero != nullptr && blockIdx.x == 0)
+    for (int i = tid; i < SPLITK_PARTS; i += CFG::THREADS) p.splitk_zero[i] = 0;
+
   // ---- tile schedule ------------------------------------------------------------------------
   const int nk1 = p.Kd / BK;               // k-tiles of one product
   const int nk_all = CAT ? 2 * nk1 : nk1;
@@ -842,15 +846,20 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // d = 2048, F = 8192, E = 16: 500 tokens 0.383 -> 0.331 ms, 1000 tokens 0.451 -> 0.364; at 2000
   // tokens (125 rows per expert) equal to the large tiles, above that those win.  At other widths and
   // expert counts only against the smaller tiles before these: 500 tokens, d = 1024, F = 2048, E = 64
-  // 0.216 -> 0.191; 3000, d = 1024, F = 4096, E = 32 0.294 -> 0.257; between 129 and 320 rows per segment
-  // the two have not been compared.
+  // 0.216 -> 0.191; 3000, d = 1024, F = 4096, E = 32 0.294 -> 0.257.
   const bool few_rows = rows <= 128 * segs;
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;
   // At N <= 128 half of a 256-column tile would be padding (layer call, us, large tiles / two
   // workgroups of 128 x 128: 32000 tokens, d = 64, F = 128, E = 8 50.7 / 39.5, E = 32 79 / 68; top-2 of
   // 16 experts, d = 128, F = 1024 161 / 148).
-  if (a.N > CfgU::BN && tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
+  // A first GEMM of one or two rounds of large tiles and up to 320 rows a segment: a segment's last 256-row
+  // tile is mostly padding, and smaller tiles fill the last round (layer us, large / small tiles: 4096 x 2
+  // rows, E = 32, d = 1024, F = 2048 179.8 / 175.0; 4096, E = 16, d = 1024, F = 4096 173.1 / 167.8; 6400, E = 32, d =
+  // 768 158.3 / 155.4; 10240, E = 32, d = 512 124.6 / 122.2; three rounds, 8192, E = 32, d = 1024, F = 4096 251.9 / 256.1;
+  // 400 rows a segment, 6400, E = 16 169.7 / 180.5).
+  const bool short_first = ACT && rows <= 320 * segs && (rows + 128 * segs) / 256 * ((a.N + 255) / 256) <= 2 * num_cus();
+  if (a.N > CfgU::BN && tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT) && !short_first) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
@@ -878,12 +887,19 @@ int ffn_mfma_counter_ints() { return SPLITK_PARTS; }
 // Split-K scratch of a call: arrival counters first (every launch leaves them at zero again),
 // then the partial tiles.  Without scratch the last round of tiles is not split.
 struct SplitK { float* parts = nullptr; int* counters = nullptr; };
-static int prepare_splitk(const FfnArgs& a, SplitK& sk, hipStream_t stream) {
+// clear: the counters that the first GEMM's launch has to clear (it cuts no tile itself: d is short), which
+// saves a launch of 4.7 us (top-2 of 32 experts, 4096 tokens, d = 1024, F = 2048 in four calls 180 -> 175).
+static int prepare_splitk(const FfnArgs& a, SplitK& sk, hipStream_t stream, int** clear = nullptr) {
+  if (clear != nullptr) *clear = nullptr;
   if (a.scratch == nullptr || a.scratch_bytes < SPLITK_WS_BYTES) return SCMOE_OK;
   if (a.d < SPLITK_MIN_K && a.F < SPLITK_MIN_K) return SCMOE_OK;      // no product long enough to be cut
   sk.counters = static_cast<int*>(a.scratch);
   sk.parts = reinterpret_cast<float*>(static_cast<unsigned char*>(a.scratch) + SPLITK_COUNT_BYTES);
   if (a.scratch_zeroed) return SCMOE_OK;
+  if (clear != nullptr && a.d < SPLITK_MIN_K) {
+    *clear = sk.counters;
+    return SCMOE_OK;
+  }
   hipLaunchKernelGGL(zero_ints, dim3(1), dim3(256), 0, stream, sk.counters, SPLITK_PARTS);
   return launch_status();
 }
@@ -1001,9 +1017,12 @@ int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream) {
     return st == SCMOE_OK ? launch_gemm_direct(&second, 1, dtype, stream) : st;
   }
   SplitK sk;
-  int st = prepare_splitk(a, sk, stream);
+  int* clear = nullptr;
+  int st = prepare_splitk(a, sk, stream, &clear);
   if (st != SCMOE_OK) return st;
-  st = launch_variant<true>(first_gemm(a, sk), a.max_rows, a.gather ? a.x_rows : a.max_rows, stream);
+  GemmArgs first = first_gemm(a, sk);
+  first.splitk_zero = clear;
+  st = launch_variant<true>(first, a.max_rows, a.gather ? a.x_rows : a.max_rows, stream);
   if (st != SCMOE_OK) return st;
   st = wait_before_second(a, stream);
   if (st != SCMOE_OK) return st;

@@ -57,6 +57,7 @@ struct GemmArgs {
   // Split-K of the last, partly filled round of tiles (optional; splitk_part == nullptr: off).
   float* splitk_part;            // SPLITK_PARTS partial tiles of BM x BN floats
   int* splitk_count;             // SPLITK_PARTS arrival counters, zero between launches
+  int* splitk_zero;              // first GEMM: SPLITK_PARTS counters to clear (nullptr: none)
   // Optional dense extra segment with operands of its own (xrows == 0: none): xC[r, :] =
   // act(xA[r, :] . xW^T + xbias) for r < xrows, same N and Kd.  Its tiles come first in the
   // tile order and it has the segment id E.  (The shared expert riding in the routed experts'
