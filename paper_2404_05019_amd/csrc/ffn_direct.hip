@@ -44,7 +44,7 @@ struct DirectArgs {
 constexpr int GRID_X = 1 << 16;   // workgroups per row of the grid (the runtime takes fewer than 2^32 work-items in x);
                                   // those past the last tile find no row and leave
 
-template <bool F32, int MI, int NJ>
+template <bool F32, int MI, int NJ, int SLOTS>
 struct DirectCfg {
   static constexpr int BM = 16 * MI, BN = 16 * NJ, WK = 4, THREADS = 64 * WK;
   // Operands through rings in LDS, except for 64 x 64 tiles, whose rings would hold two steps only
@@ -53,16 +53,16 @@ struct DirectCfg {
   static constexpr bool RING = MI * NJ < 16;
   static constexpr int STEP = (MI + NJ) * 1024;                 // bytes of a ring slot: one step's fragments
   static constexpr int FIT = 64 / (WK * (MI + NJ));             // 64 KiB, so that two workgroups fit a compute unit
-  static constexpr int PF = FIT < 5 ? FIT : 5;                  // ring slots per wave
+  static constexpr int PF = SLOTS ? SLOTS : FIT < 5 ? FIT : 5;  // ring slots per wave (SLOTS = 0: what fits)
   static constexpr int RED = WK * MI * NJ * 1024;               // sums (in the rings' place at the end)
   static constexpr int LDS = RING && WK * PF * STEP > RED ? WK * PF * STEP : RED;
   static_assert(MI == 1 || MI == 2 || MI == 4, "row subtiles");
   static_assert(LDS <= 64 * 1024, "static LDS");
 };
 
-template <bool F32, int MI, int NJ>
+template <bool F32, int MI, int NJ, int SLOTS>
 __global__ __launch_bounds__(256, 2) void gemm_direct_kernel(const DirectArgs args) {
-  using CFG = DirectCfg<F32, MI, NJ>;
+  using CFG = DirectCfg<F32, MI, NJ, SLOTS>;
   constexpr int EB = F32 ? 4 : 2, WK = CFG::WK;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[CFG::LDS];
   auto& red = *reinterpret_cast<f32x4_t(*)[WK][MI * NJ][64]>(smem);
@@ -448,9 +448,9 @@ __global__ __launch_bounds__(256, 2) void gemm_direct_kernel(const DirectArgs ar
 
 // ---- host side ----------------------------------------------------------------------------------
 
-template <bool F32, int MI, int NJ>
+template <bool F32, int MI, int NJ, int SLOTS>
 static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
-  using CFG = DirectCfg<F32, MI, NJ>;
+  using CFG = DirectCfg<F32, MI, NJ, SLOTS>;
   DirectArgs a{};
   int64_t blocks[2] = {0, 0};
   for (int q = 0; q < n; ++q) {
@@ -470,7 +470,7 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
   if (n == 1) a.j[1].nt = 1;                                    // (workgroups past the last tile: no rows there)
   const dim3 grid(static_cast<unsigned>(total < GRID_X ? total : GRID_X), static_cast<unsigned>((total + GRID_X - 1) / GRID_X)),
       block(CFG::THREADS);
-  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ>), grid, block, 0, stream, a);
+  hipLaunchKernelGGL((gemm_direct_kernel<F32, MI, NJ, SLOTS>), grid, block, 0, stream, a);
   return launch_status();
 }
 
@@ -484,6 +484,10 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 //    1024 68 / 73); fp32 takes 32 x 16 there.
 //  * 16 x 32, bf16: other calls of 32 rows and fewer a product (32 tokens 213 against 229; top-2 of 8 tokens,
 //    d = 768 35.1 / 35.5).
+//  * K of 32 steps and fewer (a wave has eight): two or three ring slots instead of four or five, so that more
+//    workgroups are resident, whose starts overlap, if there are more than those two per compute unit (16 tokens, d = 1024, E = 16 64.9 / 61.4; 60 tokens, top-2, d =
+//    512, E = 64 64.9 / 57.3; at 64 steps 64 tokens, d = 2048 237 / 258;
+//    160 tiles, fp32, 256 tokens, d = 64 20.2 / 21.3).
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
   int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0, most = 0;   // most: rows of a product
@@ -499,15 +503,15 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     const int st = g.Kd * (F32 ? 4 : 2) / 64;
     if (st > steps) steps = st;
   }
-  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4>(jobs, n, stream);
-  const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128;
+  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4, 0>(jobs, n, stream);
+  const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128, short_k = steps <= 32 && tiles32 > 2 * num_cus();
   if constexpr (F32) {
-    if (few_waves) return launch_direct_cfg<F32, 2, 1>(jobs, n, stream);
+    if (few_waves) return launch_direct_cfg<F32, 2, 1, 0>(jobs, n, stream);
   } else {
-    if (few_waves && most <= 16) return launch_direct_cfg<F32, 1, 1>(jobs, n, stream);
-    if (most <= 32) return launch_direct_cfg<F32, 1, 2>(jobs, n, stream);
+    if (few_waves && most <= 16) return launch_direct_cfg<F32, 1, 1, 0>(jobs, n, stream);
+    if (most <= 32) return short_k ? launch_direct_cfg<F32, 1, 2, 3>(jobs, n, stream) : launch_direct_cfg<F32, 1, 2, 0>(jobs, n, stream);
   }
-  return launch_direct_cfg<F32, 2, 2>(jobs, n, stream);
+  return short_k ? launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream) : launch_direct_cfg<F32, 2, 2, 0>(jobs, n, stream);
 }
 
 int launch_gemm_direct(const DirectJob* jobs, int n, int dtype, hipStream_t stream) {
