@@ -476,7 +476,13 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 
 // Which tile, measured as a layer call's time (us) at d = 2048, F = 8192, E = 16 unless noted:
 //  * 64 x 64: when that gives every compute unit a tile and the segments average 32 rows or more
-//    (fp32, 2048 tokens, d = 384: 165 against 190 with 32 x 32).
+//    (fp32, 4096 tokens, d = 1024, F = 2048, E = 8 727 against 763 with 32 x 32 in the first product and 830 in
+//    both; bf16, 3000 tokens of 1000 columns 354 against 609).
+//  * fp32, K of 40 steps and fewer: 32 x 32 with two ring slots, five workgroups on a compute unit, whose
+//    starts and ends overlap (2048 tokens, d = 384, E = 8 161.3 / 153.2; 700, d = 384, E = 4 86.0 / 77.4; 1000,
+//    top-2, d = 520 154.7 / 145.7; 8000, d = 128 95.1 / 88.1; 20000, d = 64 84.3 / 78.9; 6000, d = 512 557.6 / 560.3);
+//    up to 64 steps where 64 x 64 tiles are fewer than two per compute unit (2000 tokens, d = 256, F = 1024
+//    93.9 / 80.6).
 //  * 32 x 32: everything smaller; weights are streamed (64 tokens, shared expert on a second stream: 243
 //    against 252 with 32 x 16 where that fits and 250 with 16 x 32).
 //  * 16 x 16, bf16: when 32 x 32 tiles would put fewer than 16 waves on a compute unit, K is long and
@@ -503,7 +509,10 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     const int st = g.Kd * (F32 ? 4 : 2) / 64;
     if (st > steps) steps = st;
   }
-  if (tiles64 >= num_cus() && rows >= 32 * segs) return launch_direct_cfg<F32, 4, 4, 0>(jobs, n, stream);
+  if (tiles64 >= num_cus() && rows >= 32 * segs) {
+    if (F32 && (steps <= 40 || (steps <= 64 && tiles64 < 2 * num_cus()))) return launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream);
+    return launch_direct_cfg<F32, 4, 4, 0>(jobs, n, stream);
+  }
   const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128, short_k = steps <= 32 && tiles32 > 2 * num_cus();
   if constexpr (F32) {
     if (few_waves) return launch_direct_cfg<F32, 2, 1, 0>(jobs, n, stream);
