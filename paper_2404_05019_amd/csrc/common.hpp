@@ -147,7 +147,7 @@ inline int64_t padded_ld(int64_t width, int dtype) {
   return ((width * eb) % 512 == 0) ? width + 128 / eb : width;
 }
 bool ffn_mfma_supported(int d, int F);
-bool ffn_joint_second_fits(int T, int d, int F, int E, int64_t ldh, int64_t ldw2);   // sizes that the joint second GEMM takes
+bool ffn_joint_second_fits(int T, int rows, int d, int F, int E, int64_t ldh, int64_t ldw2);   // sizes that the joint second GEMM takes
 size_t ffn_mfma_scratch_bytes();   // scratch the tiled path can use (16-byte aligned)
 int ffn_mfma_counter_ints();       // ints at the start of that scratch that must be zero before a call
 

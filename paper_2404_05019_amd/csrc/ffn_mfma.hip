@@ -980,19 +980,29 @@ bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_row
 
 // Where both second GEMMs of a top-1 layer run as one product.  What it saves: the shared expert's rows
 // written and read again, a launch, the decode's loads, an epilogue per row, and the idle end of one launch.
-// What it costs: the shared expert's product too now has a partly filled row tile per expert, half a tile of
-// F / 64 k-tiles for every expert and column tile, which is up to 16 k-tiles (21 us) for every CU
-// here.  Layer us, two launches / one (T, d, F, E):
-//   16384, 1024, 4096, 8 572.5 / 561.1 (4 k-tiles); 30000, 768, 3072, 8 659 / 588 (2); 16384, 1280, 5120, 4
-//   843 / 779 (3); 12000, 1536, 4096, 8 with a residual 629 / 606 (6); 6000, 2048, 5504, 8 642.2 / 641.3 (11);
-//   16384, 1024, 4096, 32 640.5 / 637.7 (16); 20000, 2048, 4096, 16 skewed 1000 / 977 (16); with 32 and
-//   F = 8192, E = 16 4096, 2048 681 / 673, but 8192, 2048 1021 / 1039; 16384, 2048 1900 / 1931; 32768, 2048
-//   3722 / 3752.
+// What it costs: the shared expert's product too now has partly filled row tiles, at least one per expert.
+// rows: packed rows at most.  Layer us, two launches / one (T, d, F, E; balanced load unless noted):
+//  * Half a tile of F / 64 k-tiles for every expert and column tile, where the experts fill one: up to 16
+//    k-tiles (21 us) for every CU here.  16384, 1024, 4096, 8 572.5 / 561.1 (4 k-tiles); 30000, 768, 3072, 8
+//    659 / 588 (2); 16384, 1280, 5120, 4 843 / 779 (3); 12000, 1536, 4096, 8 with a residual 629 / 606 (6);
+//    6000, 2048, 5504, 8 642.2 / 641.3 (11); 16384, 1024, 4096, 32 640.5 / 637.7 (16); 20000, 2048, 4096, 16
+//    skewed 1000 / 977 (16); 16384, 1024, 2048, 64 463 / 456 (16); with 32 and F = 8192, E = 16 4096, 2048
+//    681 / 673, but 8192, 2048 1021 / 1039; 16384, 2048 1900 / 1931; 32768, 2048 3722 / 3752.
+//  * Experts of fewer than 256 rows have a tile each, so the shared expert's product gets E - rows / 256 row tiles
+//    more than it has alone: up to 0.4 tiles per CU.  d = 1024, F = 2048, E = 64: 1100 tokens 220 / 257, 4200 268 /
+//    297, 8192 309 / 326, 9600 351.6 / 352.9, 11520 (0.3 tiles per CU) 369 / 361, 12800 383 / 367; F = 1024 9600 208.3 /
+//    210.6; d = 2048, F = 2048, E = 32: 600 221 / 266, 4096 296 / 298, 5120 (0.375) 345 / 309, 6400 338 / 316; E =
+//    24: 2100 219 / 221, 4096 259 / 251; d = 1024, F = 1024, E = 48: 6000 164 / 159.  (0.45 pays at F = 1024, E = 48, 4800
+//    156 / 152; a skewed load the host does not know: 8192, 2048, 2048, 32 340 / 354.)
+// Not excluded: a capacity that drops three quarters of the tokens and more, where the shared expert's tiles fit
+// the chip at once and the routed launch alone would be short (16384, 1024, 4096, 8: 4096 rows 340 / 361; 8192 rows
+// 408 / 403; 8192, 2048, 2048, 8: 2048 rows 215 / 220, 4096 243 / 232).
 // Below one 256 x 256 tile per CU the smaller tiles are faster, which have no such form.
-bool ffn_joint_second_fits(int T, int d, int F, int E, int64_t ldh, int64_t ldw2) {
-  const int64_t nt = (d + CfgA::BN - 1) / CfgA::BN, lim = BUFFER_SPAN;
-  return gemm_variant() == 0 && F % (2 * CfgA::BK) == 0 && F < BUFFER_K && (T + 1) * ldh * 2 < lim && (d + 1) * ldw2 * 2 < lim &&
-         (T / CfgA::BM + E) * nt >= num_cus() && E * nt * (F / CfgA::BK) <= 2 * 16 * static_cast<int64_t>(num_cus());
+bool ffn_joint_second_fits(int T, int rows, int d, int F, int E, int64_t ldh, int64_t ldw2) {
+  const int64_t nt = (d + CfgA::BN - 1) / CfgA::BN, lim = BUFFER_SPAN, cus = num_cus();
+  if (gemm_variant() != 0 || F % (2 * CfgA::BK) != 0 || F >= BUFFER_K || (T + 1) * ldh * 2 >= lim || (d + 1) * ldw2 * 2 >= lim) return false;
+  if ((T / CfgA::BM + E) * nt < cus) return false;
+  return E * nt * (F / CfgA::BK) <= 2 * 16 * cus && 5 * nt * (CfgA::BM * static_cast<int64_t>(E) - rows) <= 2 * CfgA::BM * cus;
 }
 
 static bool is_tiled(const FfnArgs& a, int dtype) {

@@ -462,7 +462,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // rows that both first GEMMs leave in the packed order.  The sum of both experts is rounded once.
   const bool joint_second = joint && fused && tiled_s && tiled_r && D->cg_mode == SCMOE_CG_NONE && rows > 0 &&
                             dispatch_is_one_launch(D->T, D->k) &&
-                            ffn_joint_second_fits(D->T, D->d, D->F, D->E, w.ldh, ld_or(W->ld_w2, D->F));
+                            ffn_joint_second_fits(D->T, rows, D->d, D->F, D->E, w.ldh, ld_or(W->ld_w2, D->F));
   if (joint_second) {
     // (the arrays lie where the shared expert's rows would go: d >= 64, so 128 bytes a token and more)
     const size_t ints = align256(static_cast<size_t>(D->T) * 4);

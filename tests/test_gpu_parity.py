@@ -610,6 +610,15 @@ def test_layer_joint_second_gemm(oracle, T, d, F, E, C_, res):
     _layer_case(oracle, L, "bf16", E, 1, C_, True, residual=res, pad_weights=F == 384)
 
 
+@pytest.mark.parametrize("T,d,F,E,C_", [
+    (1100, 1024, 1024, 64, 100000), (600, 2048, 512, 32, 9),        # 17-19 rows per expert
+    (4096, 2048, 128, 32, 100000), (5120, 2048, 128, 32, 100000)])  # 128: two launches; 160: one product
+def test_layer_few_rows_per_expert_and_many_experts(oracle, T, d, F, E, C_):
+    """Top-1 ScMoE around the least rows per expert that the joint second GEMM takes."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, w_scale=0.03)
+    _layer_case(oracle, L, "bf16", E, 1, C_, True)
+
+
 @pytest.mark.parametrize("k,shared,C_,cg,res,two_streams", [
     (1, True, 320, 0, False, False),      # routed second GEMM decodes (scatter, gate weight, add) in finish items
     (1, True, 300, 2, True, False),       # ... and so does the shared expert's (its coefficient, the residual)

@@ -162,6 +162,20 @@ def test_joint_second_gemm_only_where_its_rule_and_its_forms_allow_it(record):
             assert st == 0 and len(gemms) == (4 if c["two"] else want) and gemms == _at(kernels, "gemm_bf16_kernel"), c
 
 
+def test_joint_second_gemm_needs_rows_for_its_tiles(record):
+    """Experts of fewer than 256 rows: the shared expert's product would get a tile per expert as well, which
+    pays up to 0.4 tiles of 256 x 256 per compute unit more than it has alone."""
+    apart = [_layer(T, 1024, 2048, 64) for T in (1100, 1500, 2000, 4200, 8192, 9800)] + [_layer(T, 2048, 2048, 32) for T in (600, 1000, 4096)]
+    apart += [dict(_layer(16384, 1024, 4096, 32), capacity=26), _layer(4200, 1024, 2048, 48), _layer(2100, 2048, 2048, 24)]
+    joint = [_layer(T, 1024, 2048, 64) for T in (10000, 16384)] + [_layer(T, 2048, 2048, 32) for T in (5120, 8192)]
+    joint += [dict(_layer(16384, 1024, 4096, 32), capacity=60), _layer(6000, 1024, 1024, 48), _layer(4096, 2048, 2048, 24)]
+    for want, calls in ((2, joint), (3, apart)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            gemms = _at(kernels, "gemm_bf16_kernel")
+            assert st == 0 and len(gemms) == want, (c, [k[0] for k in kernels])
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
