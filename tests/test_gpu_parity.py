@@ -318,7 +318,7 @@ def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, work
     (70, [0, 3] * 35, 40, 24, "f32", True, 0, False), (130, [0] * 64 + [1] * 2 + [0] * 63 + [20], 64, 64, "bf16", True, 0, False),
     # 64 x 64 tiles (every compute unit has one, 32 rows or more per segment), ragged in both directions
     (3, [1100, 0, 937], 72, 1000, "f32", True, 0, False), (2, [900, 1201], 136, 776, "bf16", True, 1, False),
-    # 32 x 16 tiles with eight waves: few rows, long K
+    # few rows and a long K: 16 x 32 tiles (18 rows and more in bf16), 32 x 16 in fp32
     (4, [3, 0, 8, 5], 64, 4160, "bf16", True, 0, False), (2, [7, 9], 72, 2120, "f32", True, 0, False),
     # small products at widths the tiled kernel has
     (3, [300, 0, 129], 256, 448, "bf16", True, 0, True),
@@ -327,6 +327,30 @@ def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, work
 def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad):
     """The kernel without LDS tiles: row subtiles and their remainders, K remainders, both types."""
     _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=2, pad=pad)
+
+
+@pytest.mark.parametrize("E,lens,d,F,pad", [
+    (4, [3, 0, 8, 5], 64, 4160, False),        # 130 steps: the waves' shares of K differ by a step
+    (1, [16], 128, 4096, True), (1, [1], 72, 4096, False),
+    (2, [7, 9], 200, 4104, False),             # a last step of one 16-byte piece, columns that end inside a tile
+    (16, [1] * 16, 1032, 4096, False),         # a segment per row, half of the last column tile
+    (3, [15, 0, 1], 4120, 72, False),          # the first GEMM has the long K (with GELU), a last step of three pieces
+    (2, [4, 4], 4160, 4096, False)])           # both
+def test_expert_ffn_16_rows_and_a_long_k(oracle, E, lens, d, F, pad):
+    """At most 16 rows and K of 128 steps or more in bf16: tiles of 16 x 16 (test_launches.py says that these calls
+    take them), element by element."""
+    g, ref = _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, pad=pad, w_scale=0.03)
+    assert_close(g, ref, "bf16")
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,res,two_streams", [
+    (8, 256, 4096, 16, 1, 8, False, False), (16, 136, 4104, 5, 1, 3, True, False), (1, 64, 8192, 4, 1, 1, False, False),
+    (8, 128, 4096, 8, 2, 16, False, False), (16, 256, 4096, 4, 1, 16, True, True)])
+def test_layer_16_rows_and_a_long_k(oracle, T, d, F, E, k, C_, res, two_streams):
+    """The same tiles in a layer: the routed and the shared expert's second product in one launch, or decoding."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, w_scale=0.03)
+    y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, True, residual=res, two_streams=two_streams)
+    assert_close(y, ref, "bf16")
 
 
 @pytest.mark.parametrize("d,F", [(520, 2120), (384, 1536), (1024, 2048)])
