@@ -750,9 +750,9 @@ static int launch_gate_mfma(const void* x, int64_t ldx, const float* Wg, const f
   return launch_status();
 }
 
-// Few tokens (decode steps, small batches: up to one workgroup of this kernel per CU;
+// W_g that is not 16-byte aligned and few tokens (up to one workgroup of this kernel per CU;
 // measured d = 2048, E = 16, bf16: 32 us against 59 us for 512 to 2048 tokens, 36 against 60 at
-// 4096): the kernel above would run few workgroups whose lanes each walk a serial chain over
+// 4096): gate_kernel would run few workgroups whose lanes each walk a serial chain over
 // 64 tokens' worth of LDS traffic.  Here a lane owns one (token,
 // expert) chain: EPAD = E rounded up to a power of two lanes per token, 256 / EPAD tokens per
 // workgroup.  W_g and the tokens' rows are staged through LDS in chunks of `kch` features
@@ -904,7 +904,7 @@ __global__ __launch_bounds__(256) void gate_small_kernel(
   }
 }
 
-constexpr int GATE_SMALL_LANES = 65536;   // T * EPAD up to which the kernel above is used (256 workgroups: one per CU)
+constexpr int GATE_SMALL_LANES = 65536;   // T * EPAD up to which gate_small_kernel is used (256 workgroups: one per CU)
 
 template <int EPL, int NW, int TPL>
 static void launch_gate(int dtype, const void* x, int64_t ldx, const float* Wg, const float* bias,

@@ -42,7 +42,7 @@ def _i32(n, fill=None):
     (3000, 640, 32, "bf16", 1, True), (40000, 264, 24, "f32", 2, False), (9000, 520, 64, "bf16", 1, False),
     (2000, 1032, 48, "f32", 1, True), (70000, 128, 17, "bf16", 2, False), (20000, 392, 64, "f32", 3, True),
     (5000, 2048, 64, "bf16", 1, False), (12000, 136, 33, "bf16", 4, True),
-    # a few tokens with many experts: the one-lane-per-chain kernel
+    # a few tokens with many experts
     (100, 72, 40, "f32", 2, True), (60, 520, 64, "bf16", 1, False), (250, 136, 24, "bf16", 3, True)])
 @pytest.mark.parametrize("normalize", [0, 1])
 def test_gate_parity(oracle, T, d, E, dtype, k, use_bias, normalize):
@@ -134,6 +134,29 @@ def test_gate_weights_not_16_byte_aligned(oracle, T, d, E, dtype):
     torch.cuda.synchronize()
     assert np.array_equal(gi.cpu().numpy().reshape(T, 2), idx)
     assert np.abs(gw.cpu().numpy().reshape(T, 2).astype(np.float64) - w).max() <= 1e-6
+
+
+@pytest.mark.parametrize("T,d,E,dtype,k", [
+    (40, 264, 5, "f32", 3), (100, 72, 40, "f32", 1), (300, 2048, 16, "f32", 4), (1, 8, 2, "f32", 1), (8192, 24, 8, "f32", 2),
+    (60, 520, 64, "bf16", 3), (100, 72, 40, "bf16", 4), (512, 1032, 17, "bf16", 1), (65, 136, 1, "bf16", 1),
+    (1024, 40, 64, "f32", 1), (1025, 40, 64, "f32", 1)])     # the last token count of the one-lane-per-chain kernel; one more
+@pytest.mark.parametrize("normalize", [0, 1])
+def test_gate_weights_not_16_byte_aligned_few_tokens(oracle, T, d, E, dtype, k, normalize):
+    """The one-lane-per-chain kernel, which only such calls take (test_launches.py): every k, with the probabilities."""
+    rng = np.random.default_rng(T + d + E)
+    x = inputs.quantize(rng.standard_normal((T, d)), dtype)
+    Wg = (0.02 * rng.standard_normal((d, E))).astype(np.float32)
+    bias = (0.3 * rng.standard_normal(E)).astype(np.float32)
+    idx, w, probs = oracle.gate(x, Wg, bias, k, normalize)
+    gW = torch.zeros(d * E + 1, dtype=torch.float32, device=DEV)[1:].view(d, E)
+    gW.copy_(torch.from_numpy(Wg))
+    gi, gw = _i32(T * k), torch.empty(T * k, dtype=torch.float32, device=DEV)
+    gp = torch.empty((T, E), dtype=torch.float32, device=DEV)
+    B.scmoe_gate_topk(to_dev(x, dtype), gW, to_dev(bias, "f32"), k, gi, gw, gp, normalize=normalize)
+    torch.cuda.synchronize()
+    assert np.array_equal(gi.cpu().numpy().reshape(T, k), idx)
+    assert np.abs(gw.cpu().numpy().reshape(T, k).astype(np.float64) - w).max() <= 1e-6
+    assert np.abs(gp.cpu().numpy().astype(np.float64) - probs).max() <= 1e-6
 
 
 def test_gate_nan_rule(oracle):
@@ -791,7 +814,7 @@ def test_layer_random_configurations(oracle, seed):
 @pytest.mark.parametrize("seed", range(20))
 def test_layer_random_small_batches(oracle, seed):
     """Seeded sweep over decode-size calls at multiples of 64: 1 to 300 tokens, 1 to 64 experts,
-    k up to 4: the kernel without LDS tiles in its tile shapes, the per-chain gate."""
+    k up to 4: the kernel without LDS tiles in its tile shapes, the gate that does the input encode."""
     rng = np.random.default_rng(8000 + seed)
     T = int(rng.choice([1, 2, 7, 16, 31, 32, 33, 48, 64, 65, 100, 129, 200, 300]))
     E = int(rng.choice([1, 2, 3, 8, 16, 40, 64]))

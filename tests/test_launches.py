@@ -37,6 +37,9 @@ def _child(recorder, library, calls):
             n, d, F, code = c["T"], c["d"], c["F"], c["dtype"]
             st = lib.scmoe_expert_ffn(P(1), C.c_int64(d), code, P(2), n, c["E"], d, F, P(3), C.c_int64(d), None, P(4), C.c_int64(F),
                                       None, P(5), C.c_int64(F), P(6), C.c_int64(d), 0, None, C.c_size_t(0), C.c_void_p(MAIN))
+        elif c["what"] == "gate":
+            st = lib.scmoe_gate_topk(P(1), C.c_int64(c["d"]), c["dtype"], C.c_void_p(P(2).value + c["off"]), None, c["T"], c["d"], c["E"],
+                                     c["k"], 0, P(3), P(4), P(5), C.c_void_p(MAIN))
         out.append([st, rec.recorder_text().decode()])
     print(json.dumps(out))
 
@@ -198,6 +201,17 @@ def test_tile_shapes_of_the_direct_kernel(record):
             (_layer(2048, 384, 1536, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, 0)])]
     got = [(c, _direct_shapes(lines)) for (c, _), (st, lines) in zip(want, record([c for c, _ in want]))]
     assert got == want, "\n".join(str(g) for g in got)
+
+
+def test_gate_kernels(record):
+    """The matrix-core kernel wherever W_g is 16-byte aligned; else one lane per chain up to 65536 lanes."""
+    gate = lambda T, d, E, off, dtype=F32, k=1: dict(what="gate", T=T, d=d, E=E, off=off, dtype=dtype, k=k)  # noqa: E731
+    want = [(gate(40, 264, 5, 4), "gate_small_kernel"), (gate(100, 72, 40, 4, BF16, 4), "gate_small_kernel"),
+            (gate(1024, 40, 64, 8), "gate_small_kernel"), (gate(1025, 40, 64, 12), "gate_kernel"), (gate(70000, 72, 8, 4), "gate_kernel")]
+    want += [(dict(c, off=0), "gate_mfma_kernel") for c, _ in want]
+    for (c, name), (st, lines) in zip(want, record([c for c, _ in want])):
+        kernels = [w[2] for w in lines if w[0] == "kernel"]
+        assert st == 0 and len(kernels) == 1 and "%d%s" % (len(name), name) in kernels[0], (c, kernels)
 
 
 def test_no_launch_passes_the_limit_on_work_items(record):
