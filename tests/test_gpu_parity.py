@@ -647,7 +647,8 @@ def test_layer_gate_and_encode_of_few_tokens(oracle, T, d, E, k, C_, dtype):
     (4200, 2048, 128, 16, 100000, False),   # no token dropped
     (4200, 2048, 384, 16, 150, False),      # half of them dropped: short tiles beside the full ones
     (4200, 2048, 1024, 16, 260, True),      # a few dropped, tiles cut along K, residual
-    (4099, 2048, 1152, 16, 1, False),       # hardly a routed row
+    (5200, 2048, 1152, 12, 1, False),       # hardly a routed row
+    (4099, 2048, 1152, 16, 1, False),       # ... of more experts: two launches
     (16400, 1024, 256, 4, 3000, True),      # more full tiles than one round
     (3900, 2304, 2048, 14, 200, False)])    # (9 column tiles)
 def test_layer_joint_second_gemm(oracle, T, d, F, E, C_, res):
@@ -655,6 +656,109 @@ def test_layer_joint_second_gemm(oracle, T, d, F, E, C_, res):
     shared expert's, in one tile; tokens without a routed row in tiles of half the length."""
     L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, w_scale=0.03)
     _layer_case(oracle, L, "bf16", E, 1, C_, True, residual=res, pad_weights=F == 384)
+
+
+@pytest.mark.parametrize("T,d,F,E,C_,without,gelu,normalize,zipf,res", [
+    (4200, 2048, 384, 16, 100000, ("b1", "b2", "b1s", "b2s"), 1, 0, None, False),
+    (4200, 2048, 1024, 16, 260, ("b2",), 0, 1, 1.2, True),          # skewed load: most experts far below a tile, many drops
+    (4200, 2048, 1024, 16, 100000, ("b2s",), 1, 0, 1.2, False),     # ... and none
+    (16400, 1024, 256, 4, 3000, ("b1", "b2s"), 1, 1, None, True)])
+def test_layer_joint_second_gemm_options(oracle, T, d, F, E, C_, without, gelu, normalize, zipf, res):
+    """The same with missing biases, the tanh GELU, normalised gate weights and a skewed load; rows of all
+    activations a stride apart (the padding holds huge values), and the output's padding left alone."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F + 1, biases=True, w_scale=0.03, zipf=zipf)
+    L.update({b: None for b in without})
+    D = DevLayer(L, "bf16")
+    ref, _ = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1, normalize=normalize,
+                                  gelu_mode=gelu, add_residual=int(res))
+    xp, xc, rs = to_dev(L["x_prev"], "bf16", d + 8), to_dev(L["x_cur"], "bf16", d + 64), to_dev(L["x_cur"], "bf16", d + 16)
+    desc = B.make_desc(T, d, F, E, 1, C_, B.BF16, gelu, normalize)
+    ws = torch.full((B.scmoe_workspace_bytes(desc),), 0xff, dtype=torch.uint8, device=DEV)
+    store = torch.full((T, d + 24), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.scmoe_layer_forward(desc, xp, xc, D.weights, store[:, :d], ws, residual=rs if res else None)
+    y2 = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+    B.scmoe_layer_forward(desc, xp, xc, D.weights, y2, ws, residual=rs if res else None, stream_aux=torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert_close(to_host(store[:, :d]), ref, "bf16")
+    assert (store[:, d:] == 7.0).all()
+    assert relerr(to_host(y2), to_host(store[:, :d])) <= 1e-2          # two streams: two products, the same up to rounding
+
+
+@pytest.mark.parametrize("C_", [260, 150])
+def test_layer_joint_second_gemm_keeps_non_finite_values_in_their_rows(C_):
+    """A NaN in a routed row, an infinity in a shared row and one in the residual reach their tokens and no
+    other, though all rows of a tile are multiplied by their factors between the two products."""
+    T, d, F, E = 4200, 2048, 1024, 16
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=9, biases=True, w_scale=0.03)
+    D = DevLayer(L, "bf16")
+    _, r = run_layer(D, 1, C_, True)
+    first = np.nonzero((r["idx"][:, 0] == 0) & (r["dst_row"][:, 0] >= 0))[0]        # (an all-NaN row of logits: expert 0)
+    dropped, kept = (np.nonzero((r["dst_row"][:, 0] < 0) == want)[0] for want in (True, False))
+    nan_routed, inf_shared, inf_dropped, inf_residual = int(first[3]), int(kept[-2]), int(dropped[5]), int(dropped[1])
+    desc = B.make_desc(T, d, F, E, 1, C_, B.BF16)
+    ws = torch.empty(B.scmoe_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
+    out = []
+    for bad in (False, True):
+        xp, xc, rs = D.x_prev.clone(), D.x_cur.clone(), D.x_cur.clone()
+        if bad:
+            xp[nan_routed, 7] = float("nan")
+            xc[inf_shared, 0], xc[inf_dropped, 2047], rs[inf_residual, 3] = (float("inf"),) * 3
+        y = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+        B.scmoe_layer_forward(desc, xp, xc, D.weights, y, ws, residual=rs)
+        torch.cuda.synchronize()
+        out.append(to_host(y))
+    assert np.isnan(out[1][nan_routed]).all()
+    for t in (inf_shared, inf_dropped):
+        assert not np.isfinite(out[1][t]).any()
+    assert out[1][inf_residual, 3] == np.inf
+    out[1][inf_residual, 3] = out[0][inf_residual, 3]
+    keep = np.ones(T, bool)
+    keep[[nan_routed, inf_shared, inf_dropped]] = False
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0][keep], out[1][keep])
+
+
+@pytest.mark.parametrize("C_,res", [(260, True), (150, False), (100000, False)])
+def test_layer_joint_second_gemm_again_and_in_a_graph(oracle, C_, res):
+    """Calls of different routing on one workspace that held garbage, then replays of a captured call on
+    changing inputs with eager work in between: the bits of a call on a workspace of its own."""
+    T, d, F, E = 4200, 2048, 1024, 16                  # (K = 2048 in all: tiles are cut along K)
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=78, biases=True, w_scale=0.03, zipf=0.5)
+    D = DevLayer(L, "bf16")
+    desc = B.make_desc(T, d, F, E, 1, C_, B.BF16)
+    size = B.scmoe_workspace_bytes(desc)
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+    xp, xc = D.x_prev.clone(), D.x_cur.clone()
+    y = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+    mean = D.Wg.mean(1)                                # a bent input: another load over the experts
+
+    def load(rep):
+        xp.copy_(torch.roll(D.x_prev, 37 * rep, 0) + (rep * D.Wg[:, rep] - rep * mean).bfloat16())
+        xc.copy_(torch.roll(D.x_cur, 5 * rep, 0))
+
+    def call(w):
+        y.fill_(3.0)
+        B.scmoe_layer_forward(desc, xp, xc, D.weights, y, w, residual=xc if res else None)
+        torch.cuda.synchronize()
+        return y.clone()
+
+    want = []
+    for rep in range(4):
+        load(rep)
+        want.append(call(torch.zeros(size, dtype=torch.uint8, device=DEV)))
+    ref, _ = oracle.layer_forward(L["x_prev"], L["x_cur"], L, k=1, capacity_=C_, shared=1, add_residual=int(res))
+    assert_close(to_host(want[0]), ref, "bf16")
+    for rep in (0, 1, 2, 3, 1, 0):
+        load(rep)
+        assert torch.equal(call(ws), want[rep]), rep
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.scmoe_layer_forward(desc, xp, xc, D.weights, y, ws, residual=xc if res else None)
+    for rep in (0, 3, 2, 1, 0):
+        load(rep)
+        y.fill_(3.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[rep]), "replay of input %d" % rep
 
 
 @pytest.mark.parametrize("T,d,F,E,C_", [

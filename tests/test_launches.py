@@ -172,6 +172,9 @@ def test_joint_second_gemm_needs_rows_for_its_tiles(record):
     apart = [_layer(T, 1024, 2048, 64) for T in (1100, 1500, 2000, 4200, 8192, 9800)] + [_layer(T, 2048, 2048, 32) for T in (600, 1000, 4096)]
     apart += [dict(_layer(16384, 1024, 4096, 32), capacity=26), _layer(4200, 1024, 2048, 48), _layer(2100, 2048, 2048, 24)]
     joint = [_layer(T, 1024, 2048, 64) for T in (10000, 16384)] + [_layer(T, 2048, 2048, 32) for T in (5120, 8192)]
+    joint += [dict(_layer(T, 2048, F, E), capacity=cap, res=cap == 260) for T, F, E, cap in              # (what the GPU tests rely on)
+              [(4200, 128, 16, 4200), (4200, 384, 16, 150), (4200, 1024, 16, 260), (5200, 1152, 12, 1)]]
+    joint += [dict(_layer(16400, 1024, 256, 4), capacity=3000), dict(_layer(3900, 2304, 2048, 14), capacity=200)]
     joint += [dict(_layer(16384, 1024, 4096, 32), capacity=60), _layer(6000, 1024, 1024, 48), _layer(4096, 2048, 2048, 24)]
     for want, calls in ((2, joint), (3, apart)):
         for c, (st, lines) in zip(calls, record(calls)):
