@@ -301,21 +301,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
     int l;
     sched.item(item, l, part);
     sched.locate(l, e, row0, row_end, n0);
-    int kb = 0;
-    nk = nk_all;
-    if constexpr (CAT) {
-      if (part >= 0) {                                            // (cut at even k-tiles)
-        kb = part * nk1 / sched.S * 2;
-        nk = (part + 1) * nk1 / sched.S * 2 - kb;
-      } else if (e == p.E - 1) {                                  // dropped tokens: the shared expert alone
-        kb = nk1;
-        nk = nk1;
-      }
-      kmid = nk1 - kb;
-    } else if (part >= 0) {
-      kb = part * nk_all / sched.S;
-      nk = (part + 1) * nk_all / sched.S - kb;
-    }
+    int kb;
+    sched.k_range(e, part, nk_all, kb, nk, kmid);
     if (ROTK) rot = p.rotk ? static_cast<int>(static_cast<unsigned>(n0 / BN) * p.rotk % static_cast<unsigned>(nk)) : 0;
     set_ptrs(e, row0, row_end, n0, kb);
   };

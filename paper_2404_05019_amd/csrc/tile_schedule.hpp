@@ -119,6 +119,29 @@ struct TileSchedule {
       part = -1;
     }
   }
+  // k-tiles kb .. kb + n - 1 of the nk of a tile are the item's (part of a tile of segment e; part < 0:
+  // the whole tile).  CAT: the second half of the nk belongs to the shared expert's product, which
+  // begins kmid k-tiles into the item; tiles of the last segment have that half alone, and tiles are cut at
+  // even k-tiles.
+  SCMOE_SCHED_FN void k_range(int e, int part, int nk, int& kb, int& n, int& kmid) const {
+    kb = 0;
+    n = nk;
+    kmid = 0;
+    if constexpr (CAT) {
+      const int half = nk / 2;
+      if (part >= 0) {
+        kb = part * half / S * 2;
+        n = (part + 1) * half / S * 2 - kb;
+      } else if (e == E) {
+        kb = half;
+        n = half;
+      }
+      kmid = half - kb;
+    } else if (part >= 0) {
+      kb = part * nk / S;
+      n = (part + 1) * nk / S - kb;
+    }
+  }
   // raster order inside a range of mt row tiles: tile l -> row tile, first column
   // (the fewest groups of at most GM row tiles, of sizes that differ by one at most: the first
   // `big` groups have one row tile more than the others)

@@ -43,6 +43,10 @@ def test_every_tile_once(walk, cat):
             calls.append([cat, bm, nt, 2 * rng.randrange(8, 70), split, 4 if bm == 128 else 8, slots, xrows, off])
     for call, line in zip(calls, walk(calls)):
         assert line.replace(" ", "").isdigit(), (call, line)
+        # the XCDs' shares differ by a tile of each of the two ranges at most, and the last round is one tile long
+        longest, total = map(int, line.split())
+        nk, slots = call[3], call[6]
+        assert longest <= total / (8 * slots) + nk * (1 + 2 / slots), (call, line)
 
 
 def test_short_tiles_fill_the_round_of_the_full_ones(walk):

@@ -26,17 +26,14 @@ static void walk(int nt, int nk, bool split, int fs, int slots, int xrows, int E
         int l, part, e, r0, r1, n0;
         s.item(it, l, part);
         s.locate(l, e, r0, r1, n0);
-        const bool last = CAT && e == E - 1;
-        int kb = 0, n = nk;
+        int kb, n, kmid;
+        s.k_range(e, part, nk, kb, n, kmid);
         if (part >= 0) {
-          if (it != slot || last) { printf("a part is not the first item\n"); return; }
-          kb = CAT ? part * (nk / 2) / s.S * 2 : part * nk / s.S;
-          n = (CAT ? (part + 1) * (nk / 2) / s.S * 2 : (part + 1) * nk / s.S) - kb;
+          if (it != slot || (CAT && e == E - 1)) { printf("a part is not the first item\n"); return; }
           ++parts[{e, r0, n0}];
-        } else if (last) {
-          kb = nk / 2;
-          n = nk - kb;
         }
+        if (CAT && (kmid != nk / 2 - kb || (part >= 0 && (kb % 2 || n % 2)))) { printf("operands change at the wrong k-tile\n"); return; }
+        if (kb < 0 || kb + n > nk) { printf("k-tiles out of range\n"); return; }
         const int lo = e < E ? off[e] : 0, hi = e < E ? off[e + 1] : xrows;
         if (r0 < lo || r0 >= hi || r1 != hi || (r0 - lo) % BM || n0 < 0 || n0 >= nt * BN || n0 % BN || n < 1) { printf("a tile that is none\n"); return; }
         auto& v = seen[{e, r0, n0}];
