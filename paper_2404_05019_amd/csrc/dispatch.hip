@@ -157,13 +157,16 @@ constexpr int DISP1_WAVES = DISP1_THREADS / 64;
 constexpr int DISP1_MAX_ITEMS = 131072;
 constexpr int DISP1_ROUND = 32;                 // 64-item vectors whose loads are in flight together
 
-template <bool NIB, int K>
+// JOINT: with the arrays of the joint second GEMM (ScanChores::token_of; an instantiation of its own: looking at the
+// pointer cost every other call 0.3 of 6.4 us).
+template <bool NIB, int K, bool JOINT>
 __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
     const int32_t* __restrict__ expert_idx, int T, int E, int capacity, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ dst_row, int32_t* __restrict__ src_token,
     const ScanChores ch) {
   constexpr int NW = DISP1_WAVES;
   constexpr int k = K;
+  static_assert(!JOINT || K == 1, "a token has one row");
   static_assert(DISP1_MAX_ITEMS / 64 / NW <= 255 && NW >= 16, "8-bit counters per lane; a wave per expert in the sum");
   // NIB: [0 = whole call, 1 = before this block][wave][lane] -> four words of 8-bit counters
   // (expert e: word (e & 1) * 2 + (e >> 3), byte (e >> 1) & 3); else [.][wave][lane = expert] counts.
@@ -323,7 +326,7 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
       }
       bef[lane] = bb;
     }
-    if (K == 1 && ch.token_of != nullptr) {
+    if constexpr (JOINT) {
       if constexpr (NIB) bb = lane < E ? bef[lane] : 0;
       int kept = lane < E ? (bb < capacity ? bb : capacity) : 0;
 #pragma unroll
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
       counts[lane] = c;
       offsets[lane] = incl - c;
       if (lane == E - 1) offsets[E] = incl;
-      if (K == 1 && ch.token_of != nullptr) {
+      if constexpr (JOINT) {
         ch.joint_offsets[lane] = incl - c;
         if (lane == E - 1) {
           ch.joint_offsets[E] = incl;
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(DISP1_THREADS) void dispatch_onepass(
     }
     dst_row[static_cast<int64_t>(t) * k + j] = out;
   }
-  if (K == 1 && ch.token_of != nullptr) {          // (uniform over the launch)
+  if constexpr (JOINT) {
     const unsigned long long drop = __ballot(i < n && out < 0);
     if (lane == 0) wdrop[wave] = __popcll(drop);
     __syncthreads();
@@ -456,22 +459,25 @@ int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, i
   if (items <= DISP1_MAX_ITEMS) {
     const int blocks = items > 0 ? static_cast<int>((items + DISP1_THREADS - 1) / DISP1_THREADS) : 1;
     const ScanChores sc = chores ? *chores : ScanChores{};
-#define SCMOE_ONEPASS(NIB, K)                                                                                    \
-  hipLaunchKernelGGL((dispatch_onepass<NIB, K>), dim3(blocks), dim3(DISP1_THREADS), 0, stream, expert_idx, T, E, \
+#define SCMOE_ONEPASS(NIB, ...)                                                                                            \
+  hipLaunchKernelGGL((dispatch_onepass<NIB, __VA_ARGS__>), dim3(blocks), dim3(DISP1_THREADS), 0, stream, expert_idx, T, E, \
                      capacity, counts, offsets, dst_row, src_token, sc)
-    if (E <= 16) {
+    if (sc.token_of != nullptr) {
+      if (E <= 16) SCMOE_ONEPASS(true, 1, true);
+      else SCMOE_ONEPASS(false, 1, true);
+    } else if (E <= 16) {
       switch (k) {
-        case 1: SCMOE_ONEPASS(true, 1); break;
-        case 2: SCMOE_ONEPASS(true, 2); break;
-        case 3: SCMOE_ONEPASS(true, 3); break;
-        default: SCMOE_ONEPASS(true, 4); break;
+        case 1: SCMOE_ONEPASS(true, 1, false); break;
+        case 2: SCMOE_ONEPASS(true, 2, false); break;
+        case 3: SCMOE_ONEPASS(true, 3, false); break;
+        default: SCMOE_ONEPASS(true, 4, false); break;
       }
     } else {
       switch (k) {
-        case 1: SCMOE_ONEPASS(false, 1); break;
-        case 2: SCMOE_ONEPASS(false, 2); break;
-        case 3: SCMOE_ONEPASS(false, 3); break;
-        default: SCMOE_ONEPASS(false, 4); break;
+        case 1: SCMOE_ONEPASS(false, 1, false); break;
+        case 2: SCMOE_ONEPASS(false, 2, false); break;
+        case 3: SCMOE_ONEPASS(false, 3, false); break;
+        default: SCMOE_ONEPASS(false, 4, false); break;
       }
     }
 #undef SCMOE_ONEPASS
