@@ -23,7 +23,9 @@
 //    d = 2048 235 / 213, 300 tokens, d = 512 52 / 47; fp32, 200 tokens, d = 1024 223 / 202, 64 tokens, d = 2048,
 //    E = 8 340 / 308.  The copies of the next PF steps are in flight while a step is multiplied.
 //  * 64 x 64 tiles: fragments straight into registers, two or three steps ahead; fp32 94 of 153 TFLOP/s at
-//    4096 tokens, d = 1024, F = 2048, E = 8 (the vector ALUs: 20-30).
+//    4096 tokens, d = 1024, F = 2048, E = 8 (the vector ALUs: 20-30).  Small tiles the same way where rows do not
+//    begin at 128-byte lines: the 64 bytes of a copy then lie in two lines, twice the requests, which a short
+//    fragment list pays for (see launch_direct_type).
 //  * Few rows: the weights arrive at 4.7 TB/s (8 tokens, 235 MB a launch) to 5.7 TB/s (64 tokens, 537
 //    MB); a plain read of that size reaches 6.3.
 //  * A segment's last tile multiplies only the 16-row subtiles that hold rows (loop variants of
@@ -44,16 +46,18 @@ struct DirectArgs {
 constexpr int GRID_X = 1 << 16;   // workgroups per row of the grid (the runtime takes fewer than 2^32 work-items in x);
                                   // those past the last tile find no row and leave
 
+constexpr int REGS = -1;          // SLOTS: no rings, operands straight into registers
+
 template <bool F32, int MI, int NJ, int SLOTS>
 struct DirectCfg {
   static constexpr int BM = 16 * MI, BN = 16 * NJ, WK = 4, THREADS = 64 * WK;
   // Operands through rings in LDS, except for 64 x 64 tiles, whose rings would hold two steps only
   // (fp32: 4096 tokens, d = 1024, E = 8 727 us of layer time through registers, 739 through LDS; 3000 tokens
   // of 1000 columns, bf16, 355 / 394).
-  static constexpr bool RING = MI * NJ < 16;
+  static constexpr bool RING = MI * NJ < 16 && SLOTS != REGS;
   static constexpr int STEP = (MI + NJ) * 1024;                 // bytes of a ring slot: one step's fragments
   static constexpr int FIT = 64 / (WK * (MI + NJ));             // 64 KiB, so that two workgroups fit a compute unit
-  static constexpr int PF = SLOTS ? SLOTS : FIT < 5 ? FIT : 5;  // ring slots per wave (SLOTS = 0: what fits)
+  static constexpr int PF = SLOTS > 0 ? SLOTS : FIT < 5 ? FIT : 5;  // ring slots per wave (SLOTS = 0: what fits)
   static constexpr int RED = WK * MI * NJ * 1024;               // sums (in the rings' place at the end)
   static constexpr int LDS = RING && WK * PF * STEP > RED ? WK * PF * STEP : RED;
   static_assert(MI == 1 || MI == 2 || MI == 4, "row subtiles");
@@ -494,10 +498,18 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 //    workgroups are resident, whose starts overlap, if there are more than those two per compute unit (16 tokens, d = 1024, E = 16 64.9 / 61.4; 60 tokens, top-2, d =
 //    512, E = 64 64.9 / 57.3; at 64 steps 64 tokens, d = 2048 237 / 258;
 //    160 tiles, fp32, 256 tokens, d = 64 20.2 / 21.3).
+//  * Rings only where both operands' rows begin at 128-byte lines, else registers (rings / registers; E = 8, 16 or 32,
+//    F = 8/3 d): bf16, one stream, 300 tokens of 32 experts, d = 776 106.5 / 94.0, d = 1424 269.8 / 252.8; 40, d = 1000 54.0 /
+//    49.9; 8, d = 1424 73.8 / 65.7; shared expert on a second stream, 100, d = 1424 123.0 / 112.8; 30 125.2 / 110.5; d = 544,
+//    rows at every other 64 bytes, 300 60.0 / 59.0.  fp32, 100, d = 1000 117.5 / 101.1; 20, d = 520 35.2 / 32.5; 500, d =
+//    520 (111 rows per segment) 87.8 / 81.7; but rings from 128 rows per segment on, where less of the time is streaming
+//    weights (second stream, 500, d = 1000 254.7 / 267.7; 1000, top-2, d = 520 147.8 / 151.0).
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
+  constexpr int EB = F32 ? 4 : 2;
   int64_t tiles64 = 0, tiles32 = 0, rows = 0, segs = 0, most = 0;   // most: rows of a product
   int steps = 0;
+  bool lines = true;                                               // rows begin at 128-byte lines
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = jobs[q].g;
     const int64_t r = jobs[q].max_rows, s = g.offsets == nullptr ? 1 : (g.E < r ? g.E : r);
@@ -506,20 +518,27 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     rows += r;
     segs += s;
     if (r > most) most = r;
-    const int st = g.Kd * (F32 ? 4 : 2) / 64;
+    const int st = g.Kd * EB / 64;
     if (st > steps) steps = st;
-  }
-  if (tiles64 >= num_cus() && rows >= 32 * segs) {
-    if (F32 && (steps <= 40 || (steps <= 64 && tiles64 < 2 * num_cus()))) return launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream);
-    return launch_direct_cfg<F32, 4, 4, 0>(jobs, n, stream);
+    lines = lines && (g.lda * EB) % 128 == 0 && (g.ldw * EB) % 128 == 0;
   }
   const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128, short_k = steps <= 32 && tiles32 > 2 * num_cus();
-  if constexpr (F32) {
-    if (few_waves) return launch_direct_cfg<F32, 2, 1, 0>(jobs, n, stream);
-  } else {
-    if (few_waves && most <= 16) return launch_direct_cfg<F32, 1, 1, 0>(jobs, n, stream);
-    if (most <= 32) return short_k ? launch_direct_cfg<F32, 1, 2, 3>(jobs, n, stream) : launch_direct_cfg<F32, 1, 2, 0>(jobs, n, stream);
+  const bool ring = lines || (F32 && rows >= 128 * segs);
+  if (tiles64 >= num_cus() && rows >= 32 * segs) {
+    if (F32 && (steps <= 40 || (steps <= 64 && tiles64 < 2 * num_cus())))
+      return ring ? launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream) : launch_direct_cfg<F32, 2, 2, REGS>(jobs, n, stream);
+    return launch_direct_cfg<F32, 4, 4, REGS>(jobs, n, stream);
   }
+  if constexpr (F32) {
+    if (few_waves) return ring ? launch_direct_cfg<F32, 2, 1, 0>(jobs, n, stream) : launch_direct_cfg<F32, 2, 1, REGS>(jobs, n, stream);
+  } else {
+    if (few_waves && most <= 16) return ring ? launch_direct_cfg<F32, 1, 1, 0>(jobs, n, stream) : launch_direct_cfg<F32, 1, 1, REGS>(jobs, n, stream);
+    if (most <= 32) {
+      if (!ring) return launch_direct_cfg<F32, 1, 2, REGS>(jobs, n, stream);
+      return short_k ? launch_direct_cfg<F32, 1, 2, 3>(jobs, n, stream) : launch_direct_cfg<F32, 1, 2, 0>(jobs, n, stream);
+    }
+  }
+  if (!ring) return launch_direct_cfg<F32, 2, 2, REGS>(jobs, n, stream);
   return short_k ? launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream) : launch_direct_cfg<F32, 2, 2, 0>(jobs, n, stream);
 }
 

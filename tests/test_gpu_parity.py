@@ -240,7 +240,7 @@ def test_dispatch_all_to_one_and_invalid(oracle):
 # ------------------------------------------------------------------------------- expert FFN
 
 def _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=5, w_scale=0.05, pad=False,
-              workspace=False):
+              workspace=False, lines=False):
     rng = np.random.default_rng(E * 100 + d + F)
     K = int(sum(lens))
     rows = K + extra_rows
@@ -255,6 +255,10 @@ def _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=5, w_s
     code = B.BF16 if dtype == "bf16" else B.F32
     # pad: weights and the hidden scratch at the row strides the library recommends
     ld1, ld2 = (B.scmoe_padded_ld(d, code), B.scmoe_padded_ld(F, code)) if pad else (d, F)
+    if lines:                                         # all rows at 128-byte lines, with padding
+        n = 64 if dtype == "bf16" else 32
+        ld1, ld2 = d + n - d % n, F + n - F % n
+        gx = to_dev(x, dtype, ld1)
     hidden = torch.zeros((rows, ld2), dtype=gx.dtype, device=DEV)[:, :F]
     y = torch.full((rows, d), 7.0, dtype=gx.dtype, device=DEV)
     ws = None
@@ -364,6 +368,21 @@ def test_expert_ffn_16_rows_and_a_long_k(oracle, E, lens, d, F, pad):
     take them), element by element."""
     g, ref = _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, pad=pad, w_scale=0.03)
     assert_close(g, ref, "bf16")
+
+
+@pytest.mark.parametrize("E,lens,d,F,dtype", [
+    (2, [15, 16], 8, 16, "bf16"), (3, [17, 0, 31], 24, 40, "bf16"), (4, [63, 64, 65, 1], 264, 200, "bf16"),
+    (2, [7, 9], 200, 4104, "bf16"), (3, [15, 0, 1], 4120, 72, "bf16"), (32, [9] * 32, 776, 2072, "bf16"),
+    (1, [1], 8, 8, "f32"), (3, [48, 49, 130], 136, 520, "f32"), (2, [7, 9], 72, 2120, "f32"), (3, [1100, 0, 937], 72, 1000, "f32")])
+def test_expert_ffn_odd_widths_in_rows_at_lines(oracle, E, lens, d, F, dtype):
+    """Widths with a K remainder in rows a multiple of 128 bytes apart take the LDS rings; dense, registers."""
+    g, ref = _ffn_case(oracle, E, lens, d, F, dtype, True, 0, extra_rows=0, w_scale=0.03, lines=True)
+    assert_close(g, ref, dtype)
+    g0, _ = _ffn_case(oracle, E, lens, d, F, dtype, True, 0, extra_rows=0, w_scale=0.03)
+    if dtype == "f32":
+        assert np.array_equal(g, g0)                   # the order of a row's sums is the same in both
+    else:
+        assert_close(g0, ref, dtype)
 
 
 @pytest.mark.parametrize("T,d,F,E,k,C_,res,two_streams", [

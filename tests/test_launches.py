@@ -184,24 +184,28 @@ def test_joint_second_gemm_needs_rows_for_its_tiles(record):
 
 
 def _direct_shapes(lines):
-    """(fp32, row subtiles, column subtiles, ring slots or 0) of the direct kernel's launches."""
+    """(fp32, row subtiles, column subtiles, ring slots; 0: what fits, -1: no ring) of the direct kernel's launches."""
     names = [w[2] for w in lines if w[0] == "kernel" and "gemm_direct_kernel" in w[2]]
-    return [tuple(int(v) for v in re.search(r"gemm_direct_kernelILb(\d)ELi(\d)ELi(\d)ELi(\d)E", n).groups()) for n in names]
+    return [tuple(int(v.replace("n", "-")) for v in re.search(r"gemm_direct_kernelILb(\d)ELi(\d)ELi(\d)ELi(n?\d)E", n).groups())
+            for n in names]
 
 
 def test_tile_shapes_of_the_direct_kernel(record):
     """Which calls take which tiles; the GPU tests of a shape rely on it (calls with 16 rows and a K of 128 steps: 16 x 16)."""
     ffn = lambda T, E, d, F, dtype=BF16: dict(what="ffn", T=T, E=E, d=d, F=F, dtype=dtype)  # noqa: E731
     short, long, few = (0, 1, 2, 3), (0, 1, 2, 0), (0, 1, 1, 0)      # 16 x 32 for a short and for a longer K; 16 x 16
-    want = [(ffn(16, 4, 64, 4160), [short, few]), (ffn(16, 1, 128, 4096), [long, few]), (ffn(1, 1, 72, 4096), [long, few]),
-            (ffn(16, 2, 200, 4104), [long, few]), (ffn(16, 16, 1032, 4096), [short, few]), (ffn(16, 3, 4120, 72), [few, long]),
-            (ffn(8, 2, 4160, 4096), [few, few]), (_layer(8, 256, 4096, 16), [short, few]), (_layer(16, 136, 4104, 5), [short, few]),
-            (_layer(1, 64, 8192, 4), [long, few]), (_layer(8, 2048, 8192, 16), [long, few]),
+    want = [(ffn(16, 4, 64, 4160), [short, few]), (ffn(16, 1, 128, 4096), [long, few]), (ffn(8, 2, 4160, 4096), [few, few]),
+            (_layer(8, 256, 4096, 16), [short, few]), (_layer(1, 64, 8192, 4), [long, few]), (_layer(8, 2048, 8192, 16), [long, few]),
             (ffn(18, 4, 64, 4160), [short, long]),                                 # two rows more
             (ffn(32, 32, 512, 1024), [short, short]), (ffn(64, 64, 512, 1024), [(0, 2, 2, 2)] * 2),
-            (ffn(2000, 2, 136, 776), [(0, 4, 4, 0), (0, 2, 2, 0)]),
-            (ffn(18, 2, 72, 2120, F32), [(1, 2, 2, 0), (1, 2, 1, 0)]), (ffn(2040, 3, 72, 1000, F32), [(1, 2, 2, 2), (1, 2, 2, 0)]),
-            (_layer(2048, 384, 1536, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, 0)])]
+            (_layer(2048, 384, 1536, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]), (_layer(64, 1024, 4096, dtype=F32), [(1, 2, 2, 0), (1, 2, 1, 0)]),
+            # rows that do not begin at 128-byte lines (72, 200, 1032, 4104, 4120 columns ...): no ring
+            (ffn(1, 1, 72, 4096), [(0, 1, 2, -1), few]), (ffn(16, 2, 200, 4104), [(0, 1, 2, -1), (0, 1, 1, -1)]),
+            (ffn(16, 16, 1032, 4096), [(0, 1, 2, -1), few]), (ffn(16, 3, 4120, 72), [(0, 1, 1, -1), (0, 1, 2, -1)]),
+            (_layer(16, 136, 4104, 5), [(0, 1, 2, -1), (0, 1, 1, -1)]), (_layer(300, 776, 2072, 32), [(0, 2, 2, -1)] * 2),
+            (ffn(2000, 2, 136, 776), [(0, 4, 4, -1), (0, 2, 2, -1)]), (ffn(18, 2, 72, 2120, F32), [(1, 2, 2, -1), (1, 2, 1, -1)]),
+            (_layer(100, 1000, 2664, dtype=F32), [(1, 2, 2, -1), (1, 2, 1, -1)]),
+            (ffn(2040, 3, 72, 1000, F32), [(1, 2, 2, 2), (1, 2, 2, 0)])]           # fp32, 128 rows per segment: rings all the same
     got = [(c, _direct_shapes(lines)) for (c, _), (st, lines) in zip(want, record([c for c, _ in want]))]
     assert got == want, "\n".join(str(g) for g in got)
 
