@@ -482,11 +482,13 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 //  * 64 x 64: when that gives every compute unit a tile and the segments average 32 rows or more
 //    (fp32, 4096 tokens, d = 1024, F = 2048, E = 8 727 against 763 with 32 x 32 in the first product and 830 in
 //    both; bf16, 3000 tokens of 1000 columns 354 against 609).
-//  * fp32, K of 40 steps and fewer: 32 x 32 with two ring slots, five workgroups on a compute unit, whose
-//    starts and ends overlap (2048 tokens, d = 384, E = 8 161.3 / 153.2; 700, d = 384, E = 4 86.0 / 77.4; 1000,
-//    top-2, d = 520 154.7 / 145.7; 8000, d = 128 95.1 / 88.1; 20000, d = 64 84.3 / 78.9; 6000, d = 512 557.6 / 560.3);
-//    up to 64 steps where 64 x 64 tiles are fewer than two per compute unit (2000 tokens, d = 256, F = 1024
-//    93.9 / 80.6).
+//  * fp32, short K: 32 x 32 with two ring slots, five workgroups on a compute unit, whose starts and ends
+//    overlap.  Up to 24 steps (64 x 64 / so: 2048 tokens, d = 384, E = 8 161.3 / 153.2; 700, d = 384, E = 4 86.0 / 77.4;
+//    8000, d = 128 95.1 / 88.1; 20000, d = 64 84.3 / 78.9, d = 384 552.7 / 552.2); up to 40 where 64 x 64 tiles are fewer than 14 per
+//    compute unit, whose rounds hide starts and ends by themselves (E = 8; tiles per unit: 1000, top-2, d = 520 154.7 /
+//    145.7; 3000, d = 640 (8) 257.0 / 256.0; 3000, d = 512, F = 2048 (13) 323.9 / 322.1; 3000, d = 640, F = 2560 (16) 461.6 / 465.2;
+//    8000, d = 640 (20) 587.4 / 595.0; 20000 (49) 1381 / 1411); up to 64 where they are fewer than two (2000, d =
+//    256, F = 1024 93.9 / 80.6).
 //  * 32 x 32: everything smaller; weights are streamed (64 tokens, shared expert on a second stream: 243
 //    against 252 with 32 x 16 where that fits and 250 with 16 x 32).
 //  * 16 x 16, bf16: when 32 x 32 tiles would put fewer than 16 waves on a compute unit, K is long and
@@ -525,7 +527,7 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
   const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128, short_k = steps <= 32 && tiles32 > 2 * num_cus();
   const bool ring = lines || (F32 && rows >= 128 * segs);
   if (tiles64 >= num_cus() && rows >= 32 * segs) {
-    if (F32 && (steps <= 40 || (steps <= 64 && tiles64 < 2 * num_cus())))
+    if (F32 && (steps <= 24 || tiles64 < (steps <= 40 ? 14 : steps <= 64 ? 2 : 0) * num_cus()))
       return ring ? launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream) : launch_direct_cfg<F32, 2, 2, REGS>(jobs, n, stream);
     return launch_direct_cfg<F32, 4, 4, REGS>(jobs, n, stream);
   }

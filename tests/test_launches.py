@@ -199,6 +199,9 @@ def test_tile_shapes_of_the_direct_kernel(record):
             (ffn(18, 4, 64, 4160), [short, long]),                                 # two rows more
             (ffn(32, 32, 512, 1024), [short, short]), (ffn(64, 64, 512, 1024), [(0, 2, 2, 2)] * 2),
             (_layer(2048, 384, 1536, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]), (_layer(64, 1024, 4096, dtype=F32), [(1, 2, 2, 0), (1, 2, 1, 0)]),
+            # fp32, K of 40 steps: 32 x 32 while 64 x 64 tiles are few (8 per compute unit; 20); of 24 always
+            (_layer(3000, 640, 1280, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]), (_layer(8000, 640, 1280, dtype=F32), [(1, 4, 4, -1)] * 2),
+            (_layer(20000, 384, 768, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]),
             # rows that do not begin at 128-byte lines (72, 200, 1032, 4104, 4120 columns ...): no ring
             (ffn(1, 1, 72, 4096), [(0, 1, 2, -1), few]), (ffn(16, 2, 200, 4104), [(0, 1, 2, -1), (0, 1, 1, -1)]),
             (ffn(16, 16, 1032, 4096), [(0, 1, 2, -1), few]), (ffn(16, 3, 4120, 72), [(0, 1, 1, -1), (0, 1, 2, -1)]),
