@@ -267,7 +267,7 @@ int scmoe_dispatch_static_max_bytes(size_t* out);
  * max_rows <= 64, or max_rows <= 16 E and max_rows <= 1024 (decode steps: bound by reading the
  * weights), small calls (at most 5e8 multiply-adds max_rows d F, and at most 2.2e6 outputs
  * max_rows (d + F) unless d and F are 64), fp32, and widths that are no multiples of 64 take a
- * kernel that feeds the matrix cores straight from global memory; it uses no workspace.
+ * kernel whose waves feed the matrix cores each on its own; it uses no workspace.
  * hidden with a row stride of scmoe_padded_ld(F) instead of F is worth about 15 % of the
  * first GEMM when F * 2 bytes is a large power of two.
  * With E = 1 and offsets = {0, T} this is the dense MLP used for the shared expert
@@ -327,7 +327,8 @@ int scmoe_workspace_bytes(const scmoe_desc* desc, size_t* out);
  * shared expert; otherwise the whole routed chain does and the join sits in front of the
  * combine kernel.  With stream_aux == NULL
  * everything runs in order on stream_main (and the first GEMMs of the shared and the routed
- * experts share one launch, and so do the second ones where that is faster).  The result is ready on stream_main.
+ * experts share one launch, and so do the second ones where that is faster, side by side or as one
+ * product).  The result is ready on stream_main.
  * (Measured on one MI355X: kernels of a few thousand tokens and more fill the chip and a second
  * stream gains nothing; up to about 4096 tokens it saves 5-13 % of the call.)
  * desc->k = 1 is ScMoE; desc->k = 2 routes two experts per token on x_prev (ScMoE-2,
@@ -340,9 +341,10 @@ int scmoe_workspace_bytes(const scmoe_desc* desc, size_t* out);
  * (after one ordinary call on the device, which creates the events and sets kernel attributes).
  * Reproducibility: the routing is the same in every mode; y is the same bits for the same
  * call repeated.  One- and two-stream calls agree up to the rounding of the stored type, not bit
- * for bit: they may merge differently (fused decode, or the two FFN outputs stored and then
- * combined: where an expert's row is rounded differs), and the tiles of a GEMM that are cut along
- * K depend on what shares its launch.
+ * for bit: they may merge differently (fused decode; the two FFN outputs stored and then
+ * combined; or, bf16 with k = 1 on one stream without a coefficient gate, both second GEMMs as one
+ * product over [hidden_routed ; hidden_shared], whose sum is rounded once: where an expert's row is
+ * rounded differs), and the tiles of a GEMM that are cut along K depend on what shares its launch.
  */
 int scmoe_layer_forward(const scmoe_desc* desc, const void* x_prev, int64_t ld_prev,
                         const void* x_cur, int64_t ld_cur, const scmoe_weights* w,

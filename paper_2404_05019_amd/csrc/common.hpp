@@ -135,9 +135,10 @@ bool ffn_is_tiled(int dtype, int d, int F, int max_rows, int E, int64_t mean_row
 // One expert-FFN call, whichever kernel it takes.
 int ffn_forward(const FfnArgs& a, int dtype, hipStream_t stream);
 // The shared expert `se` (one dense segment) and the routed experts `rt`.  Both tiled: their
-// first GEMMs share a launch; so do the second GEMMs unless one decodes: then the shared
-// expert's runs first (the routed one may decode into its rows).  Both direct: first GEMMs in
-// one launch, second GEMMs in one launch (no decode into the other's rows).
+// first GEMMs share a launch; the second GEMMs are one product with rt.joint_offsets, else one
+// launch if neither decodes, else two: the shared expert's first (the routed one may decode into
+// its rows).  Both direct: first GEMMs in one launch, second GEMMs in one launch (no decode into
+// the other's rows).
 int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_t stream);
 
 // Row stride the grouped GEMM likes for an operand of `width` columns: rows at a multiple

@@ -1,5 +1,5 @@
-// Grouped GEMM without operand tiles that a workgroup shares: the fp32 expert computation, bf16 layers whose widths the tiled kernel does not
-// cover, and bf16 calls of a few rows per expert (decode steps), which are bound by streaming
+// Grouped GEMM without operand tiles that a workgroup shares: the fp32 expert computation, bf16 layers whose
+// widths the tiled kernel does not cover, and bf16 calls of a few rows per expert (decode steps), which are bound by streaming
 // the weights (ScMoE paper Eq. (1); experts are two-layer MLPs, Sec. 2.1; the memory-limited
 // inference setting is Sec. 5.3).
 //
@@ -24,8 +24,8 @@
 //    E = 8 340 / 308.  The copies of the next PF steps are in flight while a step is multiplied.
 //  * 64 x 64 tiles: fragments straight into registers, two or three steps ahead; fp32 94 of 153 TFLOP/s at
 //    4096 tokens, d = 1024, F = 2048, E = 8 (the vector ALUs: 20-30).  Small tiles the same way where rows do not
-//    begin at 128-byte lines: the 64 bytes of a copy then lie in two lines, twice the requests, which a short
-//    fragment list pays for (see launch_direct_type).
+//    begin at 128-byte lines: the 64 bytes of a copy then mostly lie in two lines, and that costs more than the
+//    address path saves (figures at launch_direct_type).
 //  * Few rows: the weights arrive at 4.7 TB/s (8 tokens, 235 MB a launch) to 5.7 TB/s (64 tokens, 537
 //    MB); a plain read of that size reaches 6.3.
 //  * A segment's last tile multiplies only the 16-row subtiles that hold rows (loop variants of
@@ -51,7 +51,7 @@ constexpr int REGS = -1;          // SLOTS: no rings, operands straight into reg
 template <bool F32, int MI, int NJ, int SLOTS>
 struct DirectCfg {
   static constexpr int BM = 16 * MI, BN = 16 * NJ, WK = 4, THREADS = 64 * WK;
-  // Operands through rings in LDS, except for 64 x 64 tiles, whose rings would hold two steps only
+  // Operands through rings in LDS, except where REGS asks for registers and for 64 x 64 tiles, whose rings would hold two steps only
   // (fp32: 4096 tokens, d = 1024, E = 8 727 us of layer time through registers, 739 through LDS; 3000 tokens
   // of 1000 columns, bf16, 355 / 394).
   static constexpr bool RING = MI * NJ < 16 && SLOTS != REGS;

@@ -931,16 +931,18 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
   if (T == 0) return SCMOE_OK;
   if (!x || !Wg || !idx || !gw) return SCMOE_ERR_NULL;
   if (!view_ok(x, ldx, d, dtype)) return SCMOE_ERR_SHAPE;
-  // The matrix-core kernel, at any number of tokens (measured against the two kernels below,
-  // bf16, d = 2048: E = 16, 8 to 4096 tokens: 16 us against 24-26; 32768 tokens: 32 against 66 us;
-  // E = 4, 8 to 8192 tokens: 15 against 66-69 us; 64 tokens, E = 32 28 against 35, E = 64 51 against 75).  Its copies of W_g need 16-byte alignment.
+  // The matrix-core kernel, at any number of tokens (measured against the two kernels below, calls back
+  // to back on the host's clock; inside a layer, with cold caches, a trace shows 2-3 us more and 37 at 32768
+  // tokens; bf16, d = 2048: E = 16, 8 to 4096 tokens: 15-16 us against 24-26; 32768 tokens: 27 against 66;
+  // E = 4, 8 to 8192 tokens: 15 against 66-69; 64 tokens, E = 32 27 against 38, E = 64 50 against 86; the other way
+  // round by 1 us at 33 to 40 experts, d <= 256).  Its copies of W_g need 16-byte alignment.
   int epad = 1;
   while (epad < E) epad <<= 1;
   if (aligned16(Wg)) {
     // A wave takes 16 tokens.  Beyond one wave per SIMD eight waves per workgroup; below, four
     // share the copying of W_g, also where that leaves CUs idle: a single wave cannot keep enough
     // of W_g in flight to feed its chain (bf16, us, one wave per workgroup / four / eight: d = 2048,
-    // E = 16, 8 to 500 tokens 21 / 18 / 26; 4096 tokens, d = 1024, E = 32: 29.5 / 25.5 / 34).  Short
+    // E = 16, 8 to 500 tokens 18.4 / 15.6 / 23.8; 4096 tokens, d = 1024, E = 32, top-2: 23.0 / 19.3 / 26.5).  Short
     // rows have little of it: then as many waves as keep all CUs in use (d = 64: 3.1 / 3.8).
     const int64_t waves = (static_cast<int64_t>(T) + 15) / 16;
     const bool bf = dtype == SCMOE_BF16;

@@ -45,7 +45,7 @@ def assert_routing_equal(g, r, w_tol=1e-6):
 
 def tiled_chains(T, d, F, E, k, C_, shared=True, dtype="bf16"):
     """Which chains of a layer the tiled GEMM kernel runs: (shared expert, routed experts).  The
-    others take the kernel without LDS tiles.  Tests that are about one of them assert it."""
+    others take the kernel without shared operand tiles.  Tests that are about one of them assert it."""
     if dtype != "bf16" or d % 64 or F % 64:
         return (False, False)
     rows = min(T * k, E * C_)

@@ -331,7 +331,7 @@ def test_expert_ffn_many_tiles(oracle, E, lens, d, F, workspace):
 @pytest.mark.parametrize("workspace", [False, True])
 def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, workspace):
     """Calls of at most 64 rows, or of segments averaging at most 16 rows (decode steps), take
-    the kernel without LDS tiles, which uses no workspace: it may be there or not."""
+    the kernel without shared operand tiles, which uses no workspace: it may be there or not."""
     _ffn_case(oracle, E, lens, d, F, "bf16", biases, gelu_mode, extra_rows=0, pad=pad, workspace=workspace)
 
 
@@ -352,7 +352,7 @@ def test_expert_ffn_few_rows(oracle, E, lens, d, F, biases, gelu_mode, pad, work
     # more workgroups than one row of the grid holds
     (3, [21000, 0, 20010], 8, 6808, "bf16", True, 0, False)])
 def test_expert_ffn_direct(oracle, E, lens, d, F, dtype, biases, gelu_mode, pad):
-    """The kernel without LDS tiles: row subtiles and their remainders, K remainders, both types."""
+    """The kernel without shared operand tiles: row subtiles and their remainders, K remainders, both types."""
     _ffn_case(oracle, E, lens, d, F, dtype, biases, gelu_mode, extra_rows=2, pad=pad)
 
 
@@ -482,7 +482,7 @@ def test_non_finite_values_stay_in_their_rows(dtype, d, F):
     (12, 4, 2, 5, True, 2, False), (100, 8, 1, 100, True, 0, False), (64, 16, 2, 9, False, 0, False),
     (250, 16, 1, 250, True, 0, False), (48, 8, 1, 48, True, 0, False), (64, 4, 1, 20, True, 1, False)])
 def test_layer_decode_batches(oracle, T, E, k, C_, shared, cg, res):
-    """Layers of a few tokens (per-token decoding, Sec. 5.3): the kernel without LDS tiles."""
+    """Layers of a few tokens (per-token decoding, Sec. 5.3): the kernel without shared operand tiles."""
     assert not any(tiled_chains(T, 256, 512, E, k, C_, shared))
     L = inputs.make_layer(T=T, d=256, F=512, E=E, dtype="bf16", seed=300 + T, biases=True, cg_rows=cg,
                           w_scale=0.05)
@@ -907,7 +907,7 @@ def test_layer_output_in_place_of_the_residual(oracle, T, d, F, C_, cg):
 def test_layer_random_configurations(oracle, seed):
     """Seeded sweep over shapes and options: widths that are multiples of 64 or not, 1 to 12
     experts, k up to 4, binding and loose capacities, both dtypes, both layer kinds, every merge
-    mode.  Up to seed 23 nearly all through the kernel without LDS tiles, from 24 on the tiled one."""
+    mode.  Up to seed 23 nearly all through the kernel without shared operand tiles, from 24 on the tiled one."""
     rng = np.random.default_rng(7000 + seed)
     tiled = seed >= 24
     dtype = "bf16" if seed % 3 or tiled else "f32"
@@ -937,7 +937,7 @@ def test_layer_random_configurations(oracle, seed):
 @pytest.mark.parametrize("seed", range(20))
 def test_layer_random_small_batches(oracle, seed):
     """Seeded sweep over decode-size calls at multiples of 64: 1 to 300 tokens, 1 to 64 experts,
-    k up to 4: the kernel without LDS tiles in its tile shapes, the gate that does the input encode."""
+    k up to 4: the kernel without shared operand tiles in its tile shapes, the gate that does the input encode."""
     rng = np.random.default_rng(8000 + seed)
     T = int(rng.choice([1, 2, 7, 16, 31, 32, 33, 48, 64, 65, 100, 129, 200, 300]))
     E = int(rng.choice([1, 2, 3, 8, 16, 40, 64]))
