@@ -841,12 +841,18 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // At N <= 128 half of a 256-column tile would be padding (layer call, us, large tiles / two
   // workgroups of 128 x 128: 32000 tokens, d = 64, F = 128, E = 8 50.7 / 39.5, E = 32 79 / 68; top-2 of
   // 16 experts, d = 128, F = 1024 161 / 148).
-  // A first GEMM of one or two rounds of large tiles and up to 320 rows a segment: a segment's last 256-row
-  // tile is mostly padding, and smaller tiles fill the last round (layer us, large / small tiles: 4096 x 2
-  // rows, E = 32, d = 1024, F = 2048 179.8 / 175.0; 4096, E = 16, d = 1024, F = 4096 173.1 / 167.8; 6400, E = 32, d =
-  // 768 158.3 / 155.4; 10240, E = 32, d = 512 124.6 / 122.2; three rounds, 8192, E = 32, d = 1024, F = 4096 251.9 / 256.1;
-  // 400 rows a segment, 6400, E = 16 169.7 / 180.5).
-  const bool short_first = ACT && rows <= 320 * segs && (rows + 128 * segs) / 256 * ((a.N + 255) / 256) <= 2 * num_cus();
+  // A first GEMM whose large tiles leave the second of two rounds partly empty, at up to 320 rows a segment: a
+  // segment's last 256-row tile is mostly padding, and smaller tiles fill the last round.  From more than one round to
+  // 1.6, and up to two where segments just exceed a tile and pay for another one (layer us, large / small tiles, rounds:
+  // 4000, d = 640, F = 1728, E = 24 116.7 / 107.3 (1.1); 1302 x 4 rows, d = 512, F = 2048, E = 32 129.1 / 120.7 (1.2); 2500, d = 768,
+  // F = 3072, E = 16 143.5 / 134.9 (1.2); 4096 x 2, E = 32, d = 1024, F = 2048 179.8 / 175.0 and 4096, E = 16, F = 4096 173.1 / 167.8
+  // (1.5); 2000 x 4, d = 512, F = 2048, E = 32, 250 rows a segment 137.6 / 135.4 (1.7); but 2500, d = 2048, F = 2048, E = 16 168.8 /
+  // 180.6 (0.8), 1302 x 4, d = 512, F = 1344, E = 32 96.2 / 98.8 (0.9), 2500, d = 1024, F = 4096, E = 16, 156 rows 176.3 / 182.6 (1.6);
+  // three rounds, 8192, E = 32, d = 1024, F = 4096 251.9 / 256.1; 400 rows a segment, 6400, E = 16 169.7 / 180.5).
+  const int64_t own = max_rows <= 224 * static_cast<int64_t>(a.E) ? a.E : max_rows / CfgA::BM + a.E / 2;   // row tiles of the segments
+  const int64_t large = (own + (a.xrows + CfgA::BM - 1) / CfgA::BM) * ((a.N + CfgA::BN - 1) / CfgA::BN);
+  const bool short_first = ACT && rows <= 320 * segs && large > num_cus() &&
+                           (5 * large <= 8 * num_cus() || (max_rows >= 240 * static_cast<int64_t>(a.E) && large <= 2 * num_cus()));
   if (a.N > CfgU::BN && tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT) && !short_first) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4

@@ -224,6 +224,19 @@ def test_gate_kernels(record):
         assert st == 0 and len(kernels) == 1 and "%d%s" % (len(name), name) in kernels[0], (c, kernels)
 
 
+def test_first_gemm_of_small_tiles_where_the_large_ones_leave_a_round_partly_empty(record):
+    """128 x 128 tiles in a first GEMM of 129 to 320 rows per segment: not where the large tiles fit one round, nor
+    where they nearly fill the second."""
+    lay = lambda T, d, F, E, k=1: dict(_layer(T, d, F, E, k), capacity=-(-5 * k * T // (4 * E)))  # noqa: E731
+    small = [lay(4000, 640, 1728, 24), lay(1302, 512, 2048, 32, 4), lay(2500, 768, 3072, 16), lay(2000, 512, 2048, 32, 4)]
+    large = [lay(2500, 2048, 2048, 16), lay(1302, 512, 1344, 32, 4), lay(1700, 512, 1344, 32, 4), lay(1200, 1024, 4096, 8),
+             lay(2500, 1024, 4096, 16), lay(16384, 1024, 4096, 8), lay(6400, 768, 2048, 32)]
+    for edge, calls in ((128, small), (256, large)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            first = next(w[2] for w in lines if w[0] == "kernel" and "gemm_bf16_kernel" in w[2])
+            assert st == 0 and "TileCfgILi%dE" % edge in first, (c, first)
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
