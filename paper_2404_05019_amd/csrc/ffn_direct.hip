@@ -505,7 +505,11 @@ static int launch_direct_cfg(const DirectJob* jobs, int n, hipStream_t stream) {
 //    49.9; 8, d = 1424 73.8 / 65.7; shared expert on a second stream, 100, d = 1424 123.0 / 112.8; 30 125.2 / 110.5; d = 544,
 //    rows at every other 64 bytes, 300 60.0 / 59.0.  fp32, 100, d = 1000 117.5 / 101.1; 20, d = 520 35.2 / 32.5; 500, d =
 //    520 (111 rows per segment) 87.8 / 81.7; but rings from 128 rows per segment on, where less of the time is streaming
-//    weights (second stream, 500, d = 1000 254.7 / 267.7; 1000, top-2, d = 520 147.8 / 151.0).
+//    weights (second stream, 500, d = 1000 254.7 / 267.7; 1000, top-2, d = 520 147.8 / 151.0).  And registers in fp32 for one
+//    product alone of fewer than 10 rows per segment (four operator calls, weights new in every pass: 40 tokens of 16
+//    experts, d = 768 94.0 / 83.0; 3, top-4 of 12, d = 1536 106.4 / 95.1; 22 of 12, d = 960 100.1 / 95.1; but 200 of 16, d =
+//    1024 159.0 / 166.6; 120 of 8 100.8 / 104.3).  With the shared expert's product in the launch neither is the better one
+//    throughout (16 tokens of 8, d = 1024 76.8 / 83.2; 64, d = 2048 309 / 333; 64, d = 1024 120.7 / 112.1; 32 108.7 / 102.0): rings.
 template <bool F32>
 static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) {
   constexpr int EB = F32 ? 4 : 2;
@@ -525,7 +529,7 @@ static int launch_direct_type(const DirectJob* jobs, int n, hipStream_t stream) 
     lines = lines && (g.lda * EB) % 128 == 0 && (g.ldw * EB) % 128 == 0;
   }
   const bool few_waves = tiles32 * 4 < 16 * num_cus() && steps >= 128, short_k = steps <= 32 && tiles32 > 2 * num_cus();
-  const bool ring = lines || (F32 && rows >= 128 * segs);
+  const bool ring = (lines && !(F32 && n == 1 && rows < 10 * segs)) || (F32 && rows >= 128 * segs);
   if (tiles64 >= num_cus() && rows >= 32 * segs) {
     if (F32 && (steps <= 24 || tiles64 < (steps <= 40 ? 14 : steps <= 64 ? 2 : 0) * num_cus()))
       return ring ? launch_direct_cfg<F32, 2, 2, 2>(jobs, n, stream) : launch_direct_cfg<F32, 2, 2, REGS>(jobs, n, stream);

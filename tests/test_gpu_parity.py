@@ -373,7 +373,7 @@ def test_expert_ffn_16_rows_and_a_long_k(oracle, E, lens, d, F, pad):
 @pytest.mark.parametrize("E,lens,d,F,dtype", [
     (2, [15, 16], 8, 16, "bf16"), (3, [17, 0, 31], 24, 40, "bf16"), (4, [63, 64, 65, 1], 264, 200, "bf16"),
     (2, [7, 9], 200, 4104, "bf16"), (3, [15, 0, 1], 4120, 72, "bf16"), (32, [9] * 32, 776, 2072, "bf16"),
-    (1, [1], 8, 8, "f32"), (3, [48, 49, 130], 136, 520, "f32"), (2, [7, 9], 72, 2120, "f32"), (3, [1100, 0, 937], 72, 1000, "f32")])
+    (1, [11], 8, 8, "f32"), (3, [48, 49, 130], 136, 520, "f32"), (2, [12, 9], 72, 2120, "f32"), (3, [1100, 0, 937], 72, 1000, "f32")])
 def test_expert_ffn_odd_widths_in_rows_at_lines(oracle, E, lens, d, F, dtype):
     """Widths with a K remainder in rows a multiple of 128 bytes apart take the LDS rings; dense, registers."""
     g, ref = _ffn_case(oracle, E, lens, d, F, dtype, True, 0, extra_rows=0, w_scale=0.03, lines=True)

@@ -202,6 +202,9 @@ def test_tile_shapes_of_the_direct_kernel(record):
             # fp32, K of 40 steps: 32 x 32 while 64 x 64 tiles are few (8 per compute unit; 20); of 24 always
             (_layer(3000, 640, 1280, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]), (_layer(8000, 640, 1280, dtype=F32), [(1, 4, 4, -1)] * 2),
             (_layer(20000, 384, 768, dtype=F32), [(1, 2, 2, 2), (1, 4, 4, -1)]),
+            # fp32, one product alone: registers below 10 rows per segment
+            (ffn(40, 16, 768, 3072, F32), [(1, 2, 2, -1), (1, 2, 1, -1)]), (ffn(200, 16, 1024, 4096, F32), [(1, 2, 2, 0), (1, 2, 1, 0)]),
+            (ffn(120, 8, 1024, 4096, F32), [(1, 2, 2, 0), (1, 2, 1, 0)]),
             # rows that do not begin at 128-byte lines (72, 200, 1032, 4104, 4120 columns ...): no ring
             (ffn(1, 1, 72, 4096), [(0, 1, 2, -1), few]), (ffn(16, 2, 200, 4104), [(0, 1, 2, -1), (0, 1, 1, -1)]),
             (ffn(16, 16, 1032, 4096), [(0, 1, 2, -1), few]), (ffn(16, 3, 4120, 72), [(0, 1, 1, -1), (0, 1, 2, -1)]),
