@@ -149,6 +149,7 @@ inline int64_t padded_ld(int64_t width, int dtype) {
 }
 bool ffn_mfma_supported(int d, int F);
 bool ffn_joint_second_fits(int T, int rows, int d, int F, int E, int64_t ldh, int64_t ldw2);   // sizes that the joint second GEMM takes
+bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E);   // top-1 layer: both second GEMMs as one launch and the combine kernel
 size_t ffn_mfma_scratch_bytes();   // scratch the tiled path can use (16-byte aligned)
 int ffn_mfma_counter_ints();       // ints at the start of that scratch that must be zero before a call
 

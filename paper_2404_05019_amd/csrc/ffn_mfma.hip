@@ -46,7 +46,7 @@ struct TileCfg {
   static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
   static constexpr int A_PER_WAVE = BM / RPL / WAVES, B_PER_WAVE = BN / RPL / WAVES;
   static constexpr int STG_ROW = TN * 2;                  // bytes of one row of a wave's epilogue staging patch
-  static constexpr int STG_ROWS = (WAVES == 8) ? 32 : 16; // rows staged at a time (LDS budget)
+  static constexpr int STG_ROWS = (WAVES == 8 && NS * STAGE + 32 * WAVES * STG_ROW <= 160 * 1024) ? 32 : 16; // rows staged at a time (LDS budget)
   static constexpr int STG_BYTES = STG_ROWS * STG_ROW;
   static constexpr int LDS_BYTES = NS * STAGE + WAVES * STG_BYTES;
   // workgroups of this shape that fit one CU (512 VGPRs per SIMD lane, 160 KiB LDS)
@@ -622,8 +622,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   // their workgroups, which have lower ids and started earlier); the count is checked anyway,
   // with a bounded wait, so that no wave can be left waiting for good.
   for (; it < sched.ngemm + sched.nfin; it += nslots) {
-    constexpr int TILE = BM * BN, FRAGS = MI * NJ, FS = CFG::WAVES, RPW = MI / CFG::WAVES;
-    static_assert(MI % CFG::WAVES == 0 && NJ == 4, "row-subtiles of a wave tile are shared out among the waves");
+    constexpr int TILE = BM * BN, FRAGS = MI * NJ, FS = CFG::WAVES, RPW = MI > CFG::WAVES ? MI / CFG::WAVES : 1;
+    static_assert((MI % CFG::WAVES == 0 || MI < CFG::WAVES) && NJ == 4, "row-subtiles of a wave tile are shared out among the waves");
     const int f = it - sched.ngemm;
     const int lt = f / FS, region = f - lt * FS;                      // cut tile (0 .. rem-1), wave tile of it
     const int S = sched.S;
@@ -646,6 +646,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 #pragma unroll
     for (int u = 0; u < RPW; ++u) {
       const int i = wave * RPW + u;                                   // row-subtile of the wave tile
+      if (MI < CFG::WAVES && i >= MI) continue;                       // (wave-uniform) more waves than subtiles
       const int m = frow0 + rm * CFG::TM + i * 16 + l16;              // this lane's row
       if (frow0 + rm * CFG::TM + i * 16 >= frow_end) continue;        // (wave-uniform) subtile past the segment
       const int mc = m < frow_end ? m : frow_end - 1;
@@ -715,6 +716,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 using CfgA = TileCfg<256, 256, 64, 2, 4, 2>;   // 8 waves, 128 KiB LDS, one workgroup per CU
 using CfgB = TileCfg<256, 256, 32, 2, 4, 4>;   // 8 waves, 4 stages, 128 KiB LDS
 using CfgT = TileCfg<128, 128, 64, 2, 2, 3>;   // 4 waves of 64 x 64, 104 KiB LDS, one workgroup per CU: fewer 128 x 128 tiles than CUs
+using CfgV = TileCfg<256, 128, 64, 4, 2, 3>;   // 8 waves of 64 x 64, 160 KiB LDS, one workgroup per CU: second GEMMs of one round of such tiles
 using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
 // Tile configuration in use: 0 unless scmoe_set_gemm_variant has set another.  The one piece of
@@ -859,6 +861,15 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
   // of layer time with two workgroups per CU, whose free slots would cut the tiles along K).
   if (!ACT && tiles_of(CfgT::BM) <= num_cus()) return launch_gemm<CfgT, ACT>(g, max_rows, a_rows, stream);
+  // A second GEMM of more rows: 256 x 128 tiles, eight waves of 64 x 64 and three stages, one workgroup per CU: 0.82 us a
+  // k-tile of a full chip, where two workgroups of 128 x 128 take 0.7 to 1.0 for the same outputs (kernel us, 128 x 128 /
+  // 256 x 128: 3001 tokens, top-2, d = 768, F = 3072, E = 12 60.6 / 51.0; 4096, d = 2048, F = 8192 134.8 / 119.8; layer us 6000,
+  // d = 1024, F = 4096, E = 8 274 / 253; 1500, d = 1536 152 / 131; rounds of tiles: 1.6, top-2, 8192, d = 768, E = 8 232 / 220; 1.8,
+  // 6000, d = 768, E = 8 238 / 227).  Not for a little more than one round, where the smaller tiles fill the chip better (1.06,
+  // 16384, d = 512, F = 2048, E = 8 127.0 / 132.1; 1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9).
+  const int64_t wide = (own + (a.xrows + CfgV::BM - 1) / CfgV::BM) * ((a.N + CfgV::BN - 1) / CfgV::BN);
+  if (!ACT && !few_rows && a.N > CfgV::BN && (32 * wide <= 33 * num_cus() || 10 * wide >= 13 * num_cus()))
+    return launch_gemm<CfgV, ACT>(g, max_rows, a_rows, stream);
   // Otherwise two workgroups per CU, whose epilogues and waits fall on each other's arithmetic
   // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500
   // tokens, top-2, d = 768, E = 16: 86 -> 79; 3000 tokens, d = 1024, E = 32: 278 -> 245).
@@ -997,6 +1008,26 @@ bool ffn_joint_second_fits(int T, int rows, int d, int F, int E, int64_t ldh, in
   if (gemm_variant() != 0 || F % (2 * CfgA::BK) != 0 || F >= BUFFER_K || (T + 1) * ldh * 2 >= lim || (d + 1) * ldw2 * 2 >= lim) return false;
   if ((T / CfgA::BM + E) * nt < cus) return false;
   return E * nt * (F / CfgA::BK) <= 2 * 16 * cus && 5 * nt * (CfgA::BM * static_cast<int64_t>(E) - rows) <= 2 * CfgA::BM * cus;
+}
+
+// What a second GEMM of so many 256 x 128 tiles takes, in us: rounds of tiles, 0.82 us a k-tile and 4 us of epilogue and
+// tile change each, and from K = SPLITK_MIN_K on a last round of few tiles cut along K (18 us to sum the parts).
+// Measured / this: 256 tiles, K = 4096 63 / 61; 290 91 / 88; 200, K = 1536 28 / 29; 282, K = 2048 54 / 56; 306 65 / 60.
+static double second_gemm_us(int64_t tiles, int F) {
+  const int64_t slots = num_cus() / 8, n = (tiles + 7) / 8, full = n / slots, rem = n % slots;
+  const double tile = 0.82 * F / CfgV::BK + 4.0;
+  const int64_t parts = F >= SPLITK_MIN_K && rem > 0 ? (slots / rem < SPLITK_MAX ? slots / rem : SPLITK_MAX) : 1;
+  return 5.0 + full * tile + (rem == 0 ? 0.0 : parts > 1 ? 0.82 * F / CfgV::BK / parts + 18.0 : tile);
+}
+
+bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E) {
+  const int64_t nt = (d + CfgV::BN - 1) / CfgV::BN, shared = (T + CfgV::BM - 1) / CfgV::BM * nt;
+  const int64_t routed = (rows <= 224 * static_cast<int64_t>(E) ? E : rows / CfgV::BM + E / 2) * nt;
+  const double combine = 2.0 + 6.0 * T * d / 5.5e6;      // y_perm and s read, y written
+  // Not above two rounds (nothing gained at 8192 tokens, d = 1024, F = 4096, E = 8), and not for the fewest tiles: there
+  // either form cuts all of them into as many parts as it may, and one- and two-stream calls agree bit for bit.
+  if (shared + routed > 2 * num_cus() || 8 * (shared + routed) <= num_cus()) return false;
+  return second_gemm_us(shared + routed, F) + combine < second_gemm_us(shared, F) + second_gemm_us(routed, F);
 }
 
 static bool is_tiled(const FfnArgs& a, int dtype) {

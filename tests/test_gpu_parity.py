@@ -453,6 +453,30 @@ def test_layer_medium_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
         assert (r["dst_row"] < 0).any()
 
 
+# Calls of the second GEMM's 256 x 128 tiles (test_launches.py says that these take them): 9 column tiles, the last
+# one half empty; row tiles that are full, one row long and one row short of full.
+WIDE_FFN = [(4, [1023, 1, 1537, 640], 1088, 576), (4, [1023, 1, 1537, 640], 1088, 2112)]        # 9 k-tiles; 33, cut along K
+WIDE_LAYERS = [(1200, 1088, 576, 4, 2, 100000, 0, False, False, True),     # both chains in one launch
+               (1900, 1088, 2112, 5, 1, 300, 2, True, False, True),        # ... top-1, with drops, cut along K
+               (3700, 1088, 576, 3, 1, 1200, 2, True, True, True),         # fused decodes of both chains
+               (3700, 1088, 576, 3, 1, 1300, 0, False, False, False)]      # ... with nothing to add to
+
+
+@pytest.mark.parametrize("E,lens,d,F", WIDE_FFN)
+def test_expert_ffn_wide_tiles(oracle, E, lens, d, F):
+    """256 x 128 tiles, every element compared."""
+    _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, workspace=True)
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams,shared", WIDE_LAYERS)
+def test_layer_wide_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams, shared):
+    """The same tiles in a layer."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, cg_rows=cg, w_scale=0.03)
+    y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, shared, 0, cg, 0, res, two_streams=two_streams)
+    assert_close(y, ref, "bf16")
+    assert C_ * E >= T * k or (r["dst_row"] < 0).any()
+
+
 @pytest.mark.parametrize("dtype,d,F", [("f32", 72, 200), ("bf16", 128, 256), ("bf16", 512, 1024)])
 def test_non_finite_values_stay_in_their_rows(dtype, d, F):
     """A NaN or an infinity in one row of x reaches that row of the output and no other."""

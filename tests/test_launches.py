@@ -240,6 +240,25 @@ def test_first_gemm_of_small_tiles_where_the_large_ones_leave_a_round_partly_emp
             assert st == 0 and "TileCfgILi%dE" % edge in first, (c, first)
 
 
+def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
+    """256 x 128 tiles where they fill about a round or 1.3 and more; both second GEMMs of a top-1 layer in one launch
+    where that saves a partly filled round (what the GPU tests of those tiles rely on is among the calls)."""
+    from test_gpu_parity import WIDE_FFN, WIDE_LAYERS
+    ffn = [dict(what="ffn", E=E, T=sum(lens), d=d, F=F, dtype=BF16) for E, lens, d, F in WIDE_FFN]
+    lay = [dict(_layer(T, d, F, E, k, two=two), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res, two, shared in WIDE_LAYERS if shared]
+    wide = [(c, 1) for c in ffn + lay[:2]] + [(lay[2], 2), (_layer(3001, 768, 3072, 12, 2), 1), (_layer(6000, 512, 2048), 1), (_layer(9000, 768, 3072), 2),
+                                              (_layer(6000, 1024, 4096), 2), (_layer(8192, 1024, 4096), 1)]
+    other = [_layer(16384, 1024, 4096), _layer(32000, 128, 512), _layer(12000, 768, 2048), dict(what="ffn", E=16, T=8192, d=1024, F=4096, dtype=BF16),
+             _layer(500, 2048, 8192, 16)]
+    for c, (st, lines) in zip([c for c, _ in wide], record([c for c, _ in wide])):
+        kernels, _ = _order(lines)
+        n = sum("TileCfgILi256ELi128E" in k[0] for k in kernels)
+        assert st == 0 and n == dict((id(a), b) for a, b in wide)[id(c)], (c, [k[0] for k in kernels])
+    for c, (st, lines) in zip(other, record(other)):
+        kernels, _ = _order(lines)
+        assert st == 0 and not any("TileCfgILi256ELi128E" in k[0] for k in kernels), (c, [k[0] for k in kernels])
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
