@@ -94,6 +94,21 @@ struct DispatchOut {
   ScanChores ch;
 };
 
+// The gate of a layer call, its input encode and its coefficient gate, as work that the launch of the shared expert's
+// first GEMM does on the side (they do not depend on each other).
+struct GateWork {
+  const void* x; int64_t ldx;      // gate input [T, d]
+  const float* Wg; const float* bias;
+  int T, d, E, k, normalize;
+  int32_t* idx; float* gw;
+  DispatchOut enc;
+  unsigned long long* marks;       // 8 bytes of scratch for every 64 tokens, whatever they hold (all_arrived)
+  unsigned long long call;         // another number for every call
+  int workgroups;                  // set by the launch: of the gate, and of the coefficient gate
+  int coef_workgroups;
+  const void* xc; int64_t ldxc; const float* Wcg; int cg_mode; float* coef;   // (cg_mode SCMOE_CG_NONE: none)
+};
+
 // ---- entry points implemented in one source and used by the layer orchestration --------
 enum { FFN_AUTO = 0, FFN_TILED = 1, FFN_DIRECT = 2 };
 // One expert-FFN call over packed segments.  All strides in elements.
@@ -105,6 +120,7 @@ struct FfnArgs {
   const int32_t* offsets;          // [E + 1] segment starts, device (direct kernel: nullptr = one segment of max_rows rows)
   int max_rows, E, d, F;
   int path;                        // FFN_AUTO: by ffn_is_tiled; else the caller has decided
+  bool beside;                     // another chain runs beside this one on a second stream
   bool slots;                      // segments are pool slots: which expert has which depends on the other rows
   const void* W1; int64_t ldw1; const float* b1;   // [E, F, d]
   const void* W2; int64_t ldw2; const float* b2;   // [E, d, F]
@@ -122,6 +138,9 @@ struct FfnArgs {
   // E + 1 segments of joint_offsets; scatter: the tokens in packed order, which is also the gather
   // array of the shared call; row_scale: per packed row.
   const int32_t* joint_offsets;
+  // In the shared call of ffn_forward_pair: the first GEMM's launch does this on the side, ahead of everything else of
+  // the pair (nullptr: done already).
+  const GateWork* gate;
   // Scratch of the tiled path (split-K of the last round of tiles); may be nullptr: no split.
   void* scratch; size_t scratch_bytes;
   bool scratch_zeroed;             // the arrival counters at the start of scratch are zero already
@@ -150,6 +169,7 @@ inline int64_t padded_ld(int64_t width, int dtype) {
 bool ffn_mfma_supported(int d, int F);
 bool ffn_joint_second_fits(int T, int rows, int d, int F, int E, int64_t ldh, int64_t ldw2);   // sizes that the joint second GEMM takes
 bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E);   // top-1 layer: both second GEMMs as one launch and the combine kernel
+bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1);   // a call whose gate may be FfnArgs::gate
 size_t ffn_mfma_scratch_bytes();   // scratch the tiled path can use (16-byte aligned)
 int ffn_mfma_counter_ints();       // ints at the start of that scratch that must be zero before a call
 

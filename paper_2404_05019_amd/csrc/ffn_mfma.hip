@@ -30,7 +30,10 @@
 //    Sec. 2.2 "input encode"), and the second GEMM can scatter, scale and add on store
 //    ("output decode"), which lets the layer skip both permuted copies.
 #include "mfma_common.hpp"
+#include "coef_gate.hpp"
+#include "gate_mfma.hpp"
 #include <atomic>
+#include <math.h>
 
 namespace scmoe {
 
@@ -68,8 +71,10 @@ struct TileCfg {
 // 3: joint second GEMM of the shared and the routed expert of a token (see GemmArgs::A2); 4: the same with
 // addend rows.
 // XSEG: the launch may carry the dense extra segment (GemmArgs::xrows).
-template <class CFG, bool ACT, bool OFF32, int DEC, bool XSEG>
-__global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void gemm_bf16_kernel(const GemmArgs p) {
+// EG > 0: the last workgroups do a layer's gate (up to 16 EG experts), its encode and its coefficient gate first.
+struct GateGemmArgs : GemmArgs { GateWork w; };
+template <class CFG, bool ACT, bool OFF32, int DEC, bool XSEG, int EG = 0>
+__global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void gemm_bf16_kernel(const std::conditional_t<(EG > 0), GateGemmArgs, GemmArgs> p) {
   constexpr int BM = CFG::BM, BN = CFG::BN, BK = CFG::BK, RB = CFG::RB, CPR = CFG::CPR;
   constexpr int MI = CFG::MI, NJ = CFG::NJ, STAGE = CFG::STAGE, A_BYTES = CFG::A_BYTES;
   constexpr int NS = CFG::NS;
@@ -86,6 +91,20 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  if constexpr (EG > 0) {
+    const int g = gridDim.x - 1 - blockIdx.x;
+    if (g < p.w.workgroups) {
+      gate_mfma<true, CFG::WAVES, EG, GATE_ENC_LAST, CFG::LDS_BYTES>(smem, g, static_cast<const unsigned char*>(p.w.x), p.w.ldx, p.w.Wg, p.w.bias, p.w.T, p.w.d,
+                                                                     p.w.E, p.w.k, p.w.normalize, p.w.idx, p.w.gw, nullptr, p.w.enc, p.w.marks, p.w.call,
+                                                                     p.w.workgroups);
+      __syncthreads();                       // (the LDS becomes the stages of the tiles)
+    } else if (g - p.w.workgroups < p.w.coef_workgroups) {
+      coef_gate_rows<true, true>(reinterpret_cast<float*>(smem), g - p.w.workgroups, p.w.coef_workgroups, static_cast<const unsigned char*>(p.w.xc), p.w.ldxc * 2,
+                                 p.w.Wcg, p.w.cg_mode, p.w.T, p.w.d, p.w.coef);
+      __syncthreads();
+    }
+  }
 
   // ---- tile schedule ------------------------------------------------------------------------
   const int nk1 = p.Kd / BK;               // k-tiles of one product
@@ -816,6 +835,39 @@ static int launch_gemm(const GemmArgs& a, int max_rows, int64_t a_rows, hipStrea
   }
 }
 
+// Row tiles of that height of the segments of so many rows in all: as many as there are segments where those average less
+// than 7/8 of one.
+static int64_t row_tiles(int64_t rows, int64_t E, int edge) { return 8 * rows <= 7 * edge * E ? E : rows / edge + E / 2; }
+
+// Whether a launch takes the 256 x 256 tiles (variant 0): a first GEMM or not, no other chain beside it, rows in E segments
+// and in the extra one.
+static bool takes_large_tiles(bool first, bool alone, int64_t max_rows, int64_t E, int64_t xrows, int64_t N) {
+  const int64_t segs = E + (xrows > 0 ? 1 : 0), rows = max_rows + xrows, cus = num_cus();
+  const int64_t nt = (N + CfgA::BN - 1) / CfgA::BN, extra = (xrows + CfgA::BM - 1) / CfgA::BM;
+  // At N <= 128 half of a 256-column tile would be padding (layer call, us, large tiles / two
+  // workgroups of 128 x 128: 32000 tokens, d = 64, F = 128, E = 8 50.7 / 39.5, E = 32 79 / 68; top-2 of
+  // 16 experts, d = 128, F = 1024 161 / 148).
+  // A first GEMM whose large tiles leave the second of two rounds partly empty, at up to 320 rows a segment: a
+  // segment's last 256-row tile is mostly padding, and smaller tiles fill the last round.  From more than one round to
+  // 1.6, and up to two where segments just exceed a tile and pay for another one (layer us, large / small tiles, rounds:
+  // 4000, d = 640, F = 1728, E = 24 116.7 / 107.3 (1.1); 1302 x 4 rows, d = 512, F = 2048, E = 32 129.1 / 120.7 (1.2); 2500, d = 768,
+  // F = 3072, E = 16 143.5 / 134.9 (1.2); 4096 x 2, E = 32, d = 1024, F = 2048 179.8 / 175.0 and 4096, E = 16, F = 4096 173.1 / 167.8
+  // (1.5); 2000 x 4, d = 512, F = 2048, E = 32, 250 rows a segment 137.6 / 135.4 (1.7); but 2500, d = 2048, F = 2048, E = 16 168.8 /
+  // 180.6 (0.8), 1302 x 4, d = 512, F = 1344, E = 32 96.2 / 98.8 (0.9), 2500, d = 1024, F = 4096, E = 16, 156 rows 176.3 / 182.6 (1.6);
+  // three rounds, 8192, E = 32, d = 1024, F = 4096 251.9 / 256.1; 400 rows a segment, 6400, E = 16 169.7 / 180.5).
+  const int64_t large = (row_tiles(max_rows, E, CfgA::BM) + extra) * nt;
+  const bool few_rows = rows <= 128 * segs;
+  const bool short_first = first && rows <= 320 * segs && large > cus &&
+                           (5 * large <= 8 * cus || (max_rows >= 240 * E && large <= 2 * cus));
+  // A first GEMM of expert segments alone whose large tiles fill two thirds of the CUs or more, once, and are 85 % full (layer
+  // us, small / large tiles: top-1, 8192 tokens, d = 384, F = 1536, E = 8 62.5 / 58.6; 6000, d = 512, F = 2048 68.6 / 63.7; 78 % full,
+  // 5000, E = 12 65.6 / 66.4).  Not beside a chain on another stream, which could not share a CU with them (118 / 122).
+  if (first && alone && E > 1 && xrows == 0 && !few_rows && N > CfgU::BN && 3 * large >= 2 * cus && large <= cus &&
+      20 * max_rows >= 17 * CfgA::BM * row_tiles(max_rows, E, CfgA::BM))
+    return true;
+  return N > CfgU::BN && (max_rows / CfgA::BM + E + extra) * nt >= cus && !(few_rows && first) && !short_first;
+}
+
 template <bool ACT>
 static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipStream_t stream) {
   switch (gemm_variant()) {
@@ -840,22 +892,7 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   const bool few_rows = rows <= 128 * segs;
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;
-  // At N <= 128 half of a 256-column tile would be padding (layer call, us, large tiles / two
-  // workgroups of 128 x 128: 32000 tokens, d = 64, F = 128, E = 8 50.7 / 39.5, E = 32 79 / 68; top-2 of
-  // 16 experts, d = 128, F = 1024 161 / 148).
-  // A first GEMM whose large tiles leave the second of two rounds partly empty, at up to 320 rows a segment: a
-  // segment's last 256-row tile is mostly padding, and smaller tiles fill the last round.  From more than one round to
-  // 1.6, and up to two where segments just exceed a tile and pay for another one (layer us, large / small tiles, rounds:
-  // 4000, d = 640, F = 1728, E = 24 116.7 / 107.3 (1.1); 1302 x 4 rows, d = 512, F = 2048, E = 32 129.1 / 120.7 (1.2); 2500, d = 768,
-  // F = 3072, E = 16 143.5 / 134.9 (1.2); 4096 x 2, E = 32, d = 1024, F = 2048 179.8 / 175.0 and 4096, E = 16, F = 4096 173.1 / 167.8
-  // (1.5); 2000 x 4, d = 512, F = 2048, E = 32, 250 rows a segment 137.6 / 135.4 (1.7); but 2500, d = 2048, F = 2048, E = 16 168.8 /
-  // 180.6 (0.8), 1302 x 4, d = 512, F = 1344, E = 32 96.2 / 98.8 (0.9), 2500, d = 1024, F = 4096, E = 16, 156 rows 176.3 / 182.6 (1.6);
-  // three rounds, 8192, E = 32, d = 1024, F = 4096 251.9 / 256.1; 400 rows a segment, 6400, E = 16 169.7 / 180.5).
-  const int64_t own = max_rows <= 224 * static_cast<int64_t>(a.E) ? a.E : max_rows / CfgA::BM + a.E / 2;   // row tiles of the segments
-  const int64_t large = (own + (a.xrows + CfgA::BM - 1) / CfgA::BM) * ((a.N + CfgA::BN - 1) / CfgA::BN);
-  const bool short_first = ACT && rows <= 320 * segs && large > num_cus() &&
-                           (5 * large <= 8 * num_cus() || (max_rows >= 240 * static_cast<int64_t>(a.E) && large <= 2 * num_cus()));
-  if (a.N > CfgU::BN && tiles_of(CfgA::BM) >= num_cus() && !(few_rows && ACT) && !short_first) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
+  if (takes_large_tiles(ACT, !a.beside, max_rows, a.E, a.xrows, a.N)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
@@ -865,10 +902,13 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   // k-tile of a full chip, where two workgroups of 128 x 128 take 0.7 to 1.0 for the same outputs (kernel us, 128 x 128 /
   // 256 x 128: 3001 tokens, top-2, d = 768, F = 3072, E = 12 60.6 / 51.0; 4096, d = 2048, F = 8192 134.8 / 119.8; layer us 6000,
   // d = 1024, F = 4096, E = 8 274 / 253; 1500, d = 1536 152 / 131; rounds of tiles: 1.6, top-2, 8192, d = 768, E = 8 232 / 220; 1.8,
-  // 6000, d = 768, E = 8 238 / 227).  Not for a little more than one round, where the smaller tiles fill the chip better (1.06,
-  // 16384, d = 512, F = 2048, E = 8 127.0 / 132.1; 1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9).
-  const int64_t wide = (own + (a.xrows + CfgV::BM - 1) / CfgV::BM) * ((a.N + CfgV::BN - 1) / CfgV::BN);
-  if (!ACT && !few_rows && a.N > CfgV::BN && (32 * wide <= 33 * num_cus() || 10 * wide >= 13 * num_cus()))
+  // 6000, d = 768, E = 8 238 / 227).  Not for a little more than one round (an eighth of
+  // a row tile per segment more than the estimate counts), where the smaller tiles fill the chip better (1.06,
+  // 16384, d = 512, F = 2048, E = 8 127.0 / 132.1; 1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9), nor where there is no
+  // more than one of the smaller tiles per CU (8000, d = 192, E = 16, skewed 49.9 / 53.2; 3000 x 4 rows, d = 256 70.5 / 73.8).
+  const int64_t square = (max_rows / CfgU::BM + (a.xrows + CfgU::BM - 1) / CfgU::BM) * ((a.N + CfgU::BN - 1) / CfgU::BN);
+  const int64_t nt = (a.N + CfgV::BN - 1) / CfgV::BN, wide = (row_tiles(max_rows, a.E, CfgV::BM) + (a.xrows + CfgV::BM - 1) / CfgV::BM) * nt;
+  if (!ACT && !few_rows && a.N > CfgV::BN && square >= num_cus() && (32 * wide + 4 * a.E * nt <= 33 * num_cus() || 10 * wide >= 13 * num_cus()))
     return launch_gemm<CfgV, ACT>(g, max_rows, a_rows, stream);
   // Otherwise two workgroups per CU, whose epilogues and waits fall on each other's arithmetic
   // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500
@@ -925,6 +965,7 @@ static GemmArgs first_gemm(const FfnArgs& a, const SplitK& sk) {
   g.N = a.F;
   g.Kd = a.d;
   g.gelu_mode = a.gelu_mode;
+  g.beside = a.beside;
   g.splitk_part = sk.parts;
   g.splitk_count = sk.counters;
   return g;
@@ -1022,12 +1063,74 @@ static double second_gemm_us(int64_t tiles, int F) {
 
 bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E) {
   const int64_t nt = (d + CfgV::BN - 1) / CfgV::BN, shared = (T + CfgV::BM - 1) / CfgV::BM * nt;
-  const int64_t routed = (rows <= 224 * static_cast<int64_t>(E) ? E : rows / CfgV::BM + E / 2) * nt;
+  const int64_t routed = row_tiles(rows, E, CfgV::BM) * nt;
   const double combine = 2.0 + 6.0 * T * d / 5.5e6;      // y_perm and s read, y written
   // Not above two rounds (nothing gained at 8192 tokens, d = 1024, F = 4096, E = 8), and not for the fewest tiles: there
   // either form cuts all of them into as many parts as it may, and one- and two-stream calls agree bit for bit.
   if (shared + routed > 2 * num_cus() || 8 * (shared + routed) <= num_cus()) return false;
   return second_gemm_us(shared + routed, F) + combine < second_gemm_us(shared, F) + second_gemm_us(routed, F);
+}
+
+// The shared expert's first GEMM with a layer's gate, encode and coefficient gate on the side: the tiles go to the first
+// workgroups of every XCD, the gate's tokens to the last ones of the launch.
+template <class CFG, int EG>
+static int launch_first_with_gate(GemmArgs a, GateWork w, hipStream_t stream) {
+  static std::atomic<bool> attr_set[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+  if (dev < 0 || !attr_set[dev].load(std::memory_order_acquire)) {
+    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<CFG, true, true, 0, true, EG>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, CFG::LDS_BYTES);
+    if (err != hipSuccess) return hip_fail(err);
+    if (dev >= 0) attr_set[dev].store(true, std::memory_order_release);
+  }
+  a.nt = (a.N + CFG::BN - 1) / CFG::BN;
+  a.stream_out = static_cast<int64_t>(a.xrows) * a.N * 2 >= (int64_t(256) << 20);
+  const int64_t tiles = (a.xrows + CFG::BM - 1) / CFG::BM * static_cast<int64_t>(a.nt);
+  const int resident = num_cus() * CFG::WG_PER_CU;
+  w.workgroups = (w.T + 16 * CFG::WAVES - 1) / (16 * CFG::WAVES);
+  w.coef_workgroups = 0;
+  if (w.cg_mode != SCMOE_CG_NONE) {
+    w.coef_workgroups = (w.T + 4 * CFG::WAVES - 1) / (4 * CFG::WAVES);      // four tokens a wave, where there is room
+    const int room = resident - w.workgroups;
+    if (w.coef_workgroups > room) w.coef_workgroups = room;
+    if (w.coef_workgroups < 1) return SCMOE_ERR_ARG;
+  }
+  const int64_t all = tiles + w.workgroups + w.coef_workgroups;
+  const int grid = all < resident ? static_cast<int>((all + 7) / 8 * 8) : resident;
+  if (w.workgroups + w.coef_workgroups > grid) return SCMOE_ERR_ARG;
+  GateGemmArgs g;
+  static_cast<GemmArgs&>(g) = a;
+  g.w = w;
+  hipLaunchKernelGGL((gemm_bf16_kernel<CFG, true, true, 0, true, EG>), dim3(grid), dim3(CFG::THREADS), CFG::LDS_BYTES, stream, g);
+  return launch_status();
+}
+
+// Whether a layer's gate and encode go on the side of the shared expert's first GEMM, which then is a launch of its own
+// ahead of the routed experts'.  What that saves are the launches of gate and encode (14 to 30 us, in which the matrix cores
+// idle); what it costs is a partly filled round of tiles more, so only where both launches together have no more rounds
+// (tiles per CU, rounded up) than the joint one.  Layer us, joint / on the side: 500 tokens, d = 2048, F = 8192, E = 16
+// 325 / 297; 600, d = 1024, F = 4096, E = 16 109 / 100; 1000, d = 1024, F = 2048, E = 8 with a coefficient gate 74 / 65;
+// 8192, d = 384, F = 1536, E = 8 90 / 85; but 1500, d = 1536, F = 4096, E = 8 (a round
+// more) 132 / 135, 3001, top-2, d = 768, F = 3072, E = 12 147 / 154.  Not at widths whose tiles are done before the encode
+// is (16000, d = 128 57.2 / 61.0; 8000, d = 192 53 / 54; 7777, d = 320 with large tiles 75.4 / 79.9), and up to 16 experts: above them the gate is two
+// or four times as long (4096, d = 768, F = 2048, E = 24 123 / 115, but 1200, d = 640, E = 64 174 / 175; 4096, d = 512, E = 32 127 / 130).
+bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
+  const int64_t lim = BUFFER_SPAN, cus = num_cus();
+  if (gemm_variant() != 0 || !aligned16(g.Wg) || g.d < 256 || g.d >= 4096 || g.E > 16 || static_cast<int64_t>(g.T) * g.k > 32768) return false;
+  if (static_cast<int64_t>(g.T) * g.ldxc * 2 >= lim || static_cast<int64_t>(F) * ldw1 * 2 >= lim) return false;
+  const int edge = takes_large_tiles(true, true, rows, g.E, g.T, F) ? 256 : 128;
+  const int64_t nt = (F + edge - 1) / edge, shared = (g.T + edge - 1) / edge * nt, gate = (g.T + edge / 2 - 1) / (edge / 2);
+  // (the segments' tiles, from above and, where a balanced load is clear of the next tile, from below)
+  const double mean = static_cast<double>(rows) / g.E;
+  const int64_t most = row_tiles(rows, g.E, edge), clear = g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge));
+  const int64_t routed = most * nt, joint = shared + (most < clear ? most : clear) * nt;
+  if (shared + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;
+  return (shared + cus - 1) / cus + (routed + cus - 1) / cus <= (joint + cus - 1) / cus;
+}
+
+static int launch_first_with_gate(const GemmArgs& a, int max_rows, int E, const GateWork& w, hipStream_t stream) {
+  return takes_large_tiles(true, true, max_rows, E, a.xrows, a.N) ? launch_first_with_gate<CfgA, 1>(a, w, stream) : launch_first_with_gate<CfgU, 1>(a, w, stream);
 }
 
 static bool is_tiled(const FfnArgs& a, int dtype) {
@@ -1097,7 +1200,14 @@ int ffn_forward_pair(const FfnArgs& se, const FfnArgs& rt, int dtype, hipStream_
     return g;
   };
   const GemmArgs s2 = second_gemm(se, sks), r2 = second_gemm(rt, skr);
-  st = launch_variant<true>(with_shared(first_gemm(rt, skr), first_gemm(se, sks)), rt.max_rows, rt.gather ? rt.x_rows : rt.max_rows, stream);
+  if (se.gate != nullptr) {
+    GemmArgs none = first_gemm(rt, SplitK{});      // (no routed tiles)
+    none.E = 0;
+    st = launch_first_with_gate(with_shared(none, first_gemm(se, SplitK{})), rt.max_rows, rt.E, *se.gate, stream);
+    if (st == SCMOE_OK) st = launch_variant<true>(first_gemm(rt, skr), rt.max_rows, rt.gather ? rt.x_rows : rt.max_rows, stream);
+  } else {
+    st = launch_variant<true>(with_shared(first_gemm(rt, skr), first_gemm(se, sks)), rt.max_rows, rt.gather ? rt.x_rows : rt.max_rows, stream);
+  }
   if (st != SCMOE_OK) return st;
   if (rt.joint_offsets != nullptr) {
     GemmArgs g = r2;

@@ -5,6 +5,8 @@
 
 #include <math.h>
 
+#include <chrono>
+
 namespace scmoe {
 
 thread_local int g_last_hip_error = 0;
@@ -97,6 +99,16 @@ static LayerWs carve(const scmoe_desc* D, void* base, bool shared) {
   }
   w.total = off;
   return w;
+}
+
+// Another number for every call that uses one (a permutation of a running count, never zero; not the bits of small
+// numbers, of pointers or of bf16 activations).
+static unsigned long long next_call() {
+  static std::atomic<unsigned long long> n{static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count())};
+  unsigned long long v = n.fetch_add(1, std::memory_order_relaxed);
+  v = (v ^ (v >> 30)) * 0xbf58476d1ce4e5b9ull;
+  v = (v ^ (v >> 27)) * 0x94d049bb133111ebull;
+  return (v ^ (v >> 31)) | 1ull;
 }
 
 // out[t] = gate_w[t] * coef[2 t + 1]: the factor of a token's routed row under a coefficient gate (top-1)
@@ -214,9 +226,11 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
                         const LayerWs& w, hipStream_t stream, void* fused_y = nullptr, int64_t ld_fused = 0,
                         hipEvent_t before_ffn = nullptr, const FfnArgs* shared = nullptr,
                         const ScanChores* chores = nullptr, const float* row_coef = nullptr,
-                        hipEvent_t coef_ready = nullptr, bool nothing_below = false, int path = FFN_AUTO) {
+                        hipEvent_t coef_ready = nullptr, bool nothing_below = false, int path = FFN_AUTO, bool beside = false) {
   // (no packed copy of the rows: the first GEMM gathers them on load)
-  if (gate_dispatch_fits(W->W_g, D->T, D->d, D->E) && (chores == nullptr || chores->token_of == nullptr)) {
+  if (shared != nullptr && shared->gate != nullptr) {
+    // (gate and encode run on the side of the shared expert's first GEMM)
+  } else if (gate_dispatch_fits(W->W_g, D->T, D->d, D->E) && (chores == nullptr || chores->token_of == nullptr)) {
     DispatchOut enc;
     enc.counts = w.counts; enc.offsets = w.offsets; enc.dst_row = w.dst_row; enc.src_token = w.src_token;
     enc.capacity = D->capacity;
@@ -266,6 +280,7 @@ static int routed_chain(const scmoe_desc* D, const void* x, int64_t ldx, const s
     }
   }
   a.path = path;
+  a.beside = beside;
   if (shared != nullptr) {
     FfnArgs se = *shared;
     if (chores != nullptr && chores->token_of != nullptr) {      // both second GEMMs as one product
@@ -493,7 +508,21 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     se.addend = residual;
     se.ldadd = ldres;
   }
-  if (coef != nullptr) {
+  GateWork gate{};
+  if (joint && tiled_s && tiled_r && rows > 0 && !joint_second && !(fused && coef != nullptr) && !gate_dispatch_fits(W->W_g, D->T, D->d, D->E)) {
+    gate.x = x_prev; gate.ldx = ld_prev; gate.Wg = W->W_g; gate.bias = W->bias;
+    gate.T = D->T; gate.d = D->d; gate.E = D->E; gate.k = D->k; gate.normalize = D->normalize;
+    gate.idx = w.expert_idx; gate.gw = w.gate_w;
+    gate.enc.counts = w.counts; gate.enc.offsets = w.offsets; gate.enc.dst_row = w.dst_row; gate.enc.src_token = w.src_token;
+    gate.enc.capacity = D->capacity; gate.enc.ch = chores;
+    gate.marks = static_cast<unsigned long long*>(w.hidden);      // (not in use before the routed experts' first GEMM)
+    gate.xc = x_cur; gate.ldxc = ld_cur; gate.Wcg = W->W_cg; gate.cg_mode = D->cg_mode; gate.coef = w.coef;
+    if (rows * w.ldh * 2 >= (D->T + 63) / 64 * 8 && ffn_gate_on_the_side(gate, rows, D->F, ld_or(W->ld_w1, D->d))) {
+      gate.call = next_call();
+      se.gate = &gate;
+    }
+  }
+  if (coef != nullptr && se.gate == nullptr) {
     SCMOE_TRY(coef_gate(x_cur, ld_cur, D->dtype, W->W_cg, D->cg_mode, D->T, D->d, w.coef, s_shared));
     if (two && fused) {
       // the fused decode reads the coefficients on the main stream, ahead of the join
@@ -509,11 +538,11 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   // routed experts on the preceding-layer representation
   if (fused) {
     SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, y, ldy, two ? ev->join : nullptr, joint ? &se : nullptr,
-                           joint ? &chores : nullptr, coef, two ? ev->coef : nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
+                           joint ? &chores : nullptr, coef, two ? ev->coef : nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT, two));
     return copy_routing(D, w, routing, sm);
   }
   SCMOE_TRY(routed_chain(D, x_prev, ld_prev, W, w, sm, nullptr, 0, nullptr, joint ? &se : nullptr,
-                         joint ? &chores : nullptr, nullptr, nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT));
+                         joint ? &chores : nullptr, nullptr, nullptr, false, tiled_r ? FFN_TILED : FFN_DIRECT, two));
   if (two) {
     hipError_t e = hipStreamWaitEvent(sm, ev->join, 0);
     if (e != hipSuccess) return hip_fail(e);

@@ -47,6 +47,7 @@ struct GemmArgs {
   int gelu_mode;
   int rotk;                 // tiled: column tile c starts its walk over K at k-tile rotk * c (mod the k-tiles); 0: at the first.
                             // direct, fp32: what the segment index adds to the place of the first step
+  bool beside;              // (host) another chain runs beside this launch on a second stream
   int stream_out;           // store C with the streaming (non-temporal) hint
   // Fused output decode (optional; scatter == nullptr stores C[r, :] as is).  Packed row r
   // is written to row t = scatter[r] of C as  addend[t, :] + row_scale[t] * (sum + bias).

@@ -455,11 +455,11 @@ def test_layer_medium_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
 
 # Calls of the second GEMM's 256 x 128 tiles (test_launches.py says that these take them): 9 column tiles, the last
 # one half empty; row tiles that are full, one row long and one row short of full.
-WIDE_FFN = [(4, [1023, 1, 1537, 640], 1088, 576), (4, [1023, 1, 1537, 640], 1088, 2112)]        # 9 k-tiles; 33, cut along K
-WIDE_LAYERS = [(1200, 1088, 576, 4, 2, 100000, 0, False, False, True),     # both chains in one launch
-               (1900, 1088, 2112, 5, 1, 300, 2, True, False, True),        # ... top-1, with drops, cut along K
-               (3700, 1088, 576, 3, 1, 1200, 2, True, True, True),         # fused decodes of both chains
-               (3700, 1088, 576, 3, 1, 1300, 0, False, False, False)]      # ... with nothing to add to
+WIDE_FFN = [(4, [1023, 1, 2049, 768], 1088, 576), (4, [1023, 1, 2049, 768], 1088, 2112)]        # 9 k-tiles; 33, cut along K
+WIDE_LAYERS = [(1300, 1088, 576, 4, 2, 100000, 0, False, False, True),     # both chains in one launch
+               (2200, 1088, 2112, 5, 1, 350, 2, True, False, True),        # ... top-1, with drops, cut along K
+               (3800, 1088, 576, 3, 1, 1260, 2, True, True, True),         # fused decodes of both chains
+               (3800, 1088, 576, 3, 1, 1300, 0, False, False, False)]      # ... with nothing to add to
 
 
 @pytest.mark.parametrize("E,lens,d,F", WIDE_FFN)
@@ -802,6 +802,66 @@ def test_layer_joint_second_gemm_again_and_in_a_graph(oracle, C_, res):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want[rep]), "replay of input %d" % rep
+
+
+# Layers whose gate, encode and coefficient gate run on the side of the shared expert's first GEMM (test_launches.py says
+# that these do): T, d, F, E, k, C_, cg, res.
+SIDE_LAYERS = [(500, 256, 4096, 4, 1, 100000, 0, False),     # 128 x 128 tiles, the gate's last workgroup 52 tokens
+               (449, 320, 4096, 5, 1, 100, 0, True),         # ... one token, drops
+               (448, 256, 4096, 5, 2, 120, 2, True),         # two choices, coefficient gates
+               (430, 1024, 4096, 16, 1, 20, 0, False),       # 16 experts
+               (400, 512, 4096, 16, 4, 25, 1, False),        # four choices
+               (2100, 384, 4096, 4, 1, 100000, 0, True),     # 256 x 256 tiles
+               (2177, 384, 4096, 4, 2, 540, 1, False)]       # ... two choices, a last gate workgroup of one token
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res", SIDE_LAYERS)
+def test_layer_gate_on_the_side(oracle, T, d, F, E, k, C_, cg, res):
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + k, biases=True, cg_rows=cg, w_scale=0.03, zipf=0.7 if E == 4 else None)
+    y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, True, int(k > 1), cg, 0, res)
+    assert_close(y, ref, "bf16")
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_", [(500, 256, 4096, 4, 1, 100), (2100, 384, 4096, 4, 1, 100000)])
+def test_layer_gate_on_the_side_again_and_in_a_graph(T, d, F, E, k, C_):
+    """Calls of different routing on one workspace that held garbage, then replays of a captured call on changing inputs
+    with eager calls on the same workspace in between: the bits of a call on a workspace of its own."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=79, biases=True, w_scale=0.03)
+    D = DevLayer(L, "bf16")
+    desc = B.make_desc(T, d, F, E, k, C_, B.BF16)
+    size = B.scmoe_workspace_bytes(desc)
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+    xp, y = D.x_prev.clone(), torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+
+    def load(rep):
+        xp.copy_(torch.roll(D.x_prev, 37 * rep, 0) + (rep * D.Wg[:, rep % E] - rep * D.Wg.mean(1)).bfloat16())
+
+    def call(w):
+        y.fill_(3.0)
+        B.scmoe_layer_forward(desc, xp, D.x_cur, D.weights, y, w)
+        torch.cuda.synchronize()
+        return y.clone()
+
+    want = []
+    for rep in range(4):
+        load(rep)
+        want.append(call(torch.zeros(size, dtype=torch.uint8, device=DEV)))
+    assert not torch.equal(want[0], want[3])
+    for rep in (0, 1, 2, 3, 1, 0):
+        load(rep)
+        assert torch.equal(call(ws), want[rep]), rep
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.scmoe_layer_forward(desc, xp, D.x_cur, D.weights, y, ws)
+    for rep in (0, 3, 2, 1, 0):
+        load(rep)
+        y.fill_(3.0)
+        g.replay()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[rep]), "replay of input %d" % rep
+        load(3 - rep)
+        assert torch.equal(call(ws), want[3 - rep]), rep
 
 
 @pytest.mark.parametrize("T,d,F,E,C_", [

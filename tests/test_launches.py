@@ -259,6 +259,22 @@ def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
         assert st == 0 and not any("TileCfgILi256ELi128E" in k[0] for k in kernels), (c, [k[0] for k in kernels])
 
 
+def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
+    """No launch of gate, encode and coefficient gate where the first of three products' launches does them, which is where the
+    shared expert's tiles apart from the routed ones take no round more (the GPU tests rely on the first ones)."""
+    from test_gpu_parity import SIDE_LAYERS
+    side = [dict(_layer(T, d, F, E, k), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res in SIDE_LAYERS]
+    side += [_layer(500, 2048, 8192, 16), dict(_layer(8192, 384, 1536), capacity=1280), _layer(6000, 512, 2048)]
+    apart = [_layer(500, 2048, 8192, 16, two=True), _layer(500, 2048, 8192, 24), _layer(16384, 1024, 4096), _layer(1500, 1536, 4096),
+             _layer(3001, 768, 3072, 12, 2), _layer(8000, 192, 768), _layer(8, 2048, 8192, 16), _layer(20000, 512, 2048, k=2)]
+    for want, calls in ((True, side), (False, apart)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            first = next(k[0] for k in kernels if "gemm_" in k[0])
+            assert st == 0 and ("ELb1ELi1EEE" in first) == want, (c, [k[0] for k in kernels])
+            assert (not any(n in k[0] for k in kernels for n in ("gate_mfma_kernel", "dispatch_", "coef_gate_kernel"))) == want, c
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
