@@ -736,6 +736,7 @@ using CfgA = TileCfg<256, 256, 64, 2, 4, 2>;   // 8 waves, 128 KiB LDS, one work
 using CfgB = TileCfg<256, 256, 32, 2, 4, 4>;   // 8 waves, 4 stages, 128 KiB LDS
 using CfgT = TileCfg<128, 128, 64, 2, 2, 3>;   // 4 waves of 64 x 64, 104 KiB LDS, one workgroup per CU: fewer 128 x 128 tiles than CUs
 using CfgV = TileCfg<256, 128, 64, 4, 2, 3>;   // 8 waves of 64 x 64, 160 KiB LDS, one workgroup per CU: second GEMMs of one round of such tiles
+using CfgS = TileCfg<64, 128, 64, 1, 2, 3>;    // 2 waves of 64 x 64, 76 KiB LDS, two workgroups per CU: second GEMMs of up to 64 rows per segment
 using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
 // Tile configuration in use: 0 unless scmoe_set_gemm_variant has set another.  The one piece of
@@ -893,6 +894,11 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;
   if (takes_large_tiles(ACT, !a.beside, max_rows, a.E, a.xrows, a.N)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
+  // A second GEMM of up to 64 rows per expert: half of a 128-row stage would be padding, and three stages of 64 rows keep half
+  // as much again of the weights in flight (layer us, d = 2048, F = 8192, E = 16: 500 tokens 294 / 278, 800 tokens 327 / 318;
+  // 300, d = 1024, F = 4096 108.6 / 90.4; top-1 without shared expert, 500, d = 1024 92.1 / 90.0; a first GEMM, with its many
+  // column tiles, gains nothing: 500 tokens 296 / 297, 800 tokens 327 / 341).
+  if (!ACT && max_rows <= 64 * static_cast<int64_t>(a.E) && rows <= 96 * segs) return launch_gemm<CfgS, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
@@ -1062,6 +1068,10 @@ static double second_gemm_us(int64_t tiles, int F) {
 }
 
 bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E) {
+  const int64_t all = static_cast<int64_t>(T) + rows, segs = static_cast<int64_t>(E) + 1;
+  if (all <= 64 * segs) return ((T + CfgS::BM - 1) / CfgS::BM + static_cast<int64_t>(E)) * ((d + CfgS::BN - 1) / CfgS::BN) <= 2 * num_cus();
+  if (all <= 128 * segs) return true;
+  if (d <= CfgV::BN) return false;
   const int64_t nt = (d + CfgV::BN - 1) / CfgV::BN, shared = (T + CfgV::BM - 1) / CfgV::BM * nt;
   const int64_t routed = row_tiles(rows, E, CfgV::BM) * nt;
   const double combine = 2.0 + 6.0 * T * d / 5.5e6;      // y_perm and s read, y written

@@ -461,8 +461,9 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   //    combine kernel included (ffn_second_in_one_launch; 1500 tokens, d = 1536, F = 4096, E = 8 152 / 131; 2048, d = 512,
   //    F = 2048 77 / 59; 1024, d = 1024, F = 2048 85 / 69; 3300, d = 1280 288 / 247; 8192, d = 512 142 / 133; two launches stay
   //    at 6000, d = 1024, F = 4096 259 / 266 and 16384, d = 384, F = 1536 153 / 175; up to two rounds of tiles);
-  //  * 65 to 128 rows per segment (d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens
-  //    501 / 496; at 500 tokens 328 / 342: the shared expert's tiles alone are cut along K).
+  //  * 65 to 128 rows per segment (d = 2048, F = 8192, E = 16: 1000 tokens 366 / 336, 2000 tokens 501 / 496);
+  //  * fewer, with at most two of the 64 x 128 tiles per compute unit (500 tokens 299 / 278; 300, d = 1024, F = 4096, E = 16 107 / 90;
+  //    400, d = 1024, F = 2048, E = 24 99 / 80).
   const size_t eb = elem_bytes(D->dtype);
   auto overlaps = [&](const void* a, int64_t lda_, const void* b, int64_t ldb_) {
     const unsigned char* a0 = static_cast<const unsigned char*>(a);
@@ -476,8 +477,7 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
   const bool one_round = D->F < 2048 && tiles <= 2 * num_cus();
   const bool joint_fits = joint && D->k == 1 && tiled_s && tiled_r && D->cg_mode == SCMOE_CG_NONE && rows > 0 && dispatch_is_one_launch(D->T, D->k) &&
                           ffn_joint_second_fits(D->T, rows, D->d, D->F, D->E, w.ldh, ld_or(W->ld_w2, D->F));
-  const bool one_rows = all_rows > 128 * segs && D->d > 128 && !joint_fits && ffn_second_in_one_launch(D->T, rows, D->d, D->F, D->E);
-  const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || one_round || one_rows || (all_rows > 64 * segs && all_rows <= 128 * segs));
+  const bool one_launch = joint && tiled_s == tiled_r && (!tiled_s || one_round || (!joint_fits && ffn_second_in_one_launch(D->T, rows, D->d, D->F, D->E)));
   const bool fused = D->k == 1 && !one_launch && !overlaps(y, ldy, x_prev, ld_prev) &&
                      !overlaps(y, ldy, x_cur, ld_cur) && (!residual || !overlaps(y, ldy, residual, ldres));
   // Both second GEMMs as one product: y[t] = [g W2_e | W2s] . [h(t) ; hs(t)], a k loop twice as long over

@@ -462,6 +462,27 @@ WIDE_LAYERS = [(1300, 1088, 576, 4, 2, 100000, 0, False, False, True),     # bot
                (3800, 1088, 576, 3, 1, 1300, 0, False, False, False)]      # ... with nothing to add to
 
 
+# Calls of its 64 x 128 tiles: up to 64 rows per segment on average, and row tiles of one row to a full one.
+SHORT_FFN = [(12, [64, 65, 0, 1, 63, 128, 40, 17, 64, 50, 100, 33], 1088, 832), (12, [64, 65, 0, 1, 63, 128, 40, 17, 64, 50, 100, 33], 1088, 2112)]
+SHORT_LAYERS = [(300, 1088, 2112, 16, 1, 100000, 1, True, False), (300, 1088, 1728, 16, 1, 17, 0, False, False),     # both chains in one launch
+                (300, 1088, 1728, 16, 2, 100000, 2, True, False), (600, 1088, 1728, 16, 1, 30, 2, True, True)]    # (fused decode)
+
+
+@pytest.mark.parametrize("E,lens,d,F", SHORT_FFN)
+@pytest.mark.parametrize("workspace", [False, True])
+def test_expert_ffn_short_tiles(oracle, E, lens, d, F, workspace):
+    """64 x 128 tiles, every element compared."""
+    _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, workspace=workspace)
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams", SHORT_LAYERS)
+def test_layer_short_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
+    """The same tiles in a layer."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F + k, biases=True, cg_rows=cg, w_scale=0.03, zipf=0.5)
+    y, r, ref, rr = _layer_case(oracle, L, "bf16", E, k, C_, True, 0, cg, 0, res, two_streams=two_streams)
+    assert_close(y, ref, "bf16")
+
+
 @pytest.mark.parametrize("E,lens,d,F", WIDE_FFN)
 def test_expert_ffn_wide_tiles(oracle, E, lens, d, F):
     """256 x 128 tiles, every element compared."""

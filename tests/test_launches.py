@@ -259,6 +259,20 @@ def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
         assert st == 0 and not any("TileCfgILi256ELi128E" in k[0] for k in kernels), (c, [k[0] for k in kernels])
 
 
+def test_second_gemm_of_short_tiles(record):
+    """64 x 128 tiles up to 64 rows per segment; both second GEMMs of a top-1 layer in one launch of at most two tiles per CU."""
+    from test_gpu_parity import SHORT_FFN, SHORT_LAYERS
+    calls = [dict(what="ffn", E=E, T=sum(lens), d=d, F=F, dtype=BF16) for E, lens, d, F in SHORT_FFN]
+    calls += [dict(_layer(T, d, F, E, k, two=two), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res, two in SHORT_LAYERS]
+    calls += [_layer(500, 2048, 8192, 16), _layer(400, 1024, 2048, 24)]
+    for c, (st, lines) in zip(calls, record(calls)):
+        kernels, _ = _order(lines)
+        n = sum("TileCfgILi64ELi128E" in k[0] for k in kernels)
+        assert st == 0 and n == 1 and len(_at(kernels, "combine_kernel")) == (c["what"] == "layer" and not c["two"]), (c, [k[0] for k in kernels])
+    for c, (st, lines) in zip([_layer(1500, 1024, 4096, 16), _layer(8, 2048, 8192, 16)], record([_layer(1500, 1024, 4096, 16), _layer(8, 2048, 8192, 16)])):
+        assert st == 0 and not any("TileCfgILi64ELi128E" in k[0] for k in _order(lines)[0]), c
+
+
 def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
     """No launch of gate, encode and coefficient gate where the first of three products' launches does them, which is where the
     shared expert's tiles apart from the routed ones take no round more (the GPU tests rely on the first ones)."""
