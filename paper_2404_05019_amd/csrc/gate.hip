@@ -210,32 +210,33 @@ __global__ __launch_bounds__(64 * NW) void gate_kernel(
 }
 
 // The matrix-core kernel (gate_mfma.hpp).  ENC: the launch is one workgroup, which does the input encode as well.
-template <bool BF16, int NW, int EG, bool ENC>
+template <bool BF16, int NW, int EG, bool ENC, int GW = 1>
 __global__ __launch_bounds__(64 * NW) void gate_mfma_kernel(
     const unsigned char* __restrict__ x, int64_t ldx, const float* __restrict__ Wg,
     const float* __restrict__ bias, int T, int d, int E, int k, int normalize,
     int32_t* __restrict__ expert_idx, float* __restrict__ gate_w, float* __restrict__ probs, const DispatchOut enc) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char gm[];
-  gate_mfma<BF16, NW, EG, ENC ? GATE_ENC_OWN : GATE_ONLY>(gm, blockIdx.x, x, ldx, Wg, bias, T, d, E, k, normalize, expert_idx, gate_w, probs, enc, nullptr, 0, 0);
+  gate_mfma<BF16, NW, EG, ENC ? GATE_ENC_OWN : GATE_ONLY, 160 * 1024, GW>(gm, blockIdx.x, x, ldx, Wg, bias, T, d, E, k, normalize, expert_idx, gate_w, probs, enc, nullptr, 0, 0);
 }
 
-template <bool BF16, int NW, int EG, bool ENC = false>
+template <bool BF16, int NW, int EG, bool ENC = false, int GW = 1>
 static int launch_gate_mfma(const void* x, int64_t ldx, const float* Wg, const float* bias, int T, int d, int E,
                             int k, int normalize, int32_t* idx, float* gw, float* probs, hipStream_t stream,
                             const DispatchOut& enc = DispatchOut{}) {
-  constexpr int LDS = GateMfmaCfg<BF16, NW, EG>::LDS;
+  using C = GateMfmaCfg<BF16, NW, EG, 160 * 1024, GW>;
+  constexpr int LDS = C::LDS;
   static std::atomic<bool> attr_set[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
   if (dev < 0 || !attr_set[dev].load(std::memory_order_acquire)) {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_mfma_kernel<BF16, NW, EG, ENC>),
+    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_mfma_kernel<BF16, NW, EG, ENC, GW>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (err != hipSuccess) return hip_fail(err);
     if (dev >= 0) attr_set[dev].store(true, std::memory_order_release);
   }
-  dim3 grid((T + 16 * NW - 1) / (16 * NW)), block(64 * NW);
+  dim3 grid((T + C::TOK - 1) / C::TOK), block(64 * NW);
   if (ENC && grid.x != 1) return SCMOE_ERR_ARG;
-  hipLaunchKernelGGL((gate_mfma_kernel<BF16, NW, EG, ENC>), grid, block, LDS, stream, static_cast<const unsigned char*>(x), ldx,
+  hipLaunchKernelGGL((gate_mfma_kernel<BF16, NW, EG, ENC, GW>), grid, block, LDS, stream, static_cast<const unsigned char*>(x), ldx,
                      Wg, bias, T, d, E, k, normalize, idx, gw, probs, enc);
   return launch_status();
 }
@@ -447,6 +448,19 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
     case 2: SCMOE_GATE_MFMA(2, EG);                                                                                \
     default: SCMOE_GATE_MFMA(1, EG);                                                                               \
   }
+    // More than 16 experts and no more than a wave per SIMD: a wave for every 16 tokens and 16 experts, whose chain is not
+    // longer than with 16 experts (call us, two or four groups per wave / so: four operator calls, 4096 tokens, top-2, d =
+    // 1024, F = 2048, E = 32 172.8 / 168.5, E = 64 236.6 / 225.4; top-1, 500 tokens, E = 64 145.4 / 135.8; top-2, 2000, d = 256, E = 64
+    // 82.2 / 77.6).  Not in the launch that does the encode as well, one workgroup, which four or more waves a SIMD slow
+    // down (20 tokens, d = 2048, E = 32 148.3 / 149.0; 60, d = 1024, E = 24 78.9 / 79.8).
+    if (E > 16 && waves * (E <= 32 ? 2 : 4) <= 4 * num_cus()) {
+#define SCMOE_GATE_MFMA_GW(GW)                                                                                                       \
+  return bf ? launch_gate_mfma<true, 4, 1, false, GW>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)               \
+            : launch_gate_mfma<false, 4, 1, false, GW>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)
+      if (E <= 32) SCMOE_GATE_MFMA_GW(2);
+      SCMOE_GATE_MFMA_GW(4);
+#undef SCMOE_GATE_MFMA_GW
+    }
     if (E <= 16) { SCMOE_GATE_MFMA_NW(1) }
     else if (E <= 32) { SCMOE_GATE_MFMA_NW(2) }
     else { SCMOE_GATE_MFMA_NW(4) }
@@ -506,7 +520,7 @@ int gate_dispatch(const void* x, int64_t ldx, int dtype, const float* Wg, const 
                   int normalize, int32_t* idx, float* gw, const DispatchOut& enc, hipStream_t stream) {
   if (!gate_dispatch_fits(Wg, T, d, E) || enc.ch.token_of != nullptr) return SCMOE_ERR_ARG;
   const bool bf = dtype == SCMOE_BF16;
-#define SCMOE_GATE_ENC(NW, EG)                                                                                                \
+#define SCMOE_GATE_ENC(NW, EG)                                                                                                  \
   return bf ? launch_gate_mfma<true, NW, EG, true>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, nullptr, stream, enc)    \
             : launch_gate_mfma<false, NW, EG, true>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, nullptr, stream, enc)
   if (T > 128) { SCMOE_GATE_ENC(16, 1); }

@@ -100,7 +100,8 @@ __device__ __forceinline__ void route_token(const float* l, int E, int k, int no
 // advances the 16 x 16 chains of 16 tokens and 16 experts by four features: the same bits as
 // the kernels below at a quarter of a dependent instruction per feature and chain.  With more
 // than 16 experts a wave keeps EG = 2 or 4 accumulators, one per group of 16 experts, and
-// every step issues EG independent instructions on the same x operand.
+// every step issues EG independent instructions on the same x operand; where there are fewer waves than SIMDs, GW = 2 or
+// 4 waves share 16 tokens instead, each with a group of its own, and the chain is as short as with 16 experts.
 // A wave owns 16 tokens.  Nothing passes through registers on the way in: x rows and W_g are
 // copied global -> LDS directly (so the compiler never waits for a register load, which with
 // such copies in flight would drain all of them), x into a ring of XS stages per wave (a
@@ -142,21 +143,24 @@ __device__ __forceinline__ void lds_wait(uint32_t& x, uint32_t (&w)[EG]) {
   else asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(x), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : "n"(N));
 }
 
-// Shape of the kernel for EG groups of 16 experts (E <= 16 EG), NW waves per workgroup and ROOM bytes of LDS.
-template <bool BF16, int NW, int EG, int ROOM = 160 * 1024>
+// Shape of the kernel for EG groups of 16 experts per wave, GW waves that share 16 tokens (E <= 16 EG GW; one of EG and
+// GW is 1), NW waves per workgroup and ROOM bytes of LDS.
+template <bool BF16, int NW, int EG, int ROOM = 160 * 1024, int GW = 1>
 struct GateMfmaCfg {
+  static constexpr int G = EG * GW;                   // groups in all
   static constexpr int EB = BF16 ? 2 : 4;
   static constexpr int SF = 128 / EB;                 // features per stage of x
   static constexpr int SS = SF / 4;                   // steps (of four features) per stage
-  static constexpr int KC = 256 / EG;                 // features per W_g tile: at most 16 KiB
+  static constexpr int KC = 256 / G;                  // features per W_g tile: at most 16 KiB
   static constexpr int IPT = KC / SF;                 // stages per W_g tile
-  static constexpr int WB0 = EG == 1 ? 2 : EG == 2 ? 3 : 4;
+  static constexpr int WB0 = G == 1 ? 2 : G == 2 ? 3 : 4;
   static constexpr int WB = ROOM - WB0 * GM_WBUF >= 3 * NW * GM_STAGE ? WB0 : WB0 - 1;   // W_g buffers: tile j + WB - 1 is requested when tile j begins
   static constexpr int XS0 = NW == 16 ? 3 : EG == 1 ? (NW == 8 ? 7 : 8) : EG == 2 ? 6 : 5, XS1 = (ROOM - WB * GM_WBUF) / (NW * GM_STAGE);
   static constexpr int XS = XS0 < XS1 ? XS0 : XS1;                     // x ring stages per wave
   static constexpr int P = EG == 1 ? SS / 2 : EG == 2 ? 4 : 2;         // steps the operand reads run ahead of their use
-  static constexpr int LGS = 16 * EG + 1;             // row stride of the logit exchange buffer
-  static constexpr int TOK = 16 * NW;
+  static constexpr int LGS = 16 * G + 1;              // row stride of the logit exchange buffer
+  static constexpr int TOK = 16 * NW / GW;
+  static_assert((EG == 1 || GW == 1) && NW % GW == 0, "groups");
   static constexpr int LDS = WB * GM_WBUF + NW * XS * GM_STAGE;
   static_assert(IPT >= 1 && SS % P == 0 && P <= SS / 2, "steps per stage and per tile");
   static_assert((P - 1) * (1 + EG) < 15, "LDS reads a wait can count");
@@ -349,14 +353,14 @@ __device__ __forceinline__ bool all_arrived(unsigned long long* marks, unsigned 
 // its own (dispatch_own); count itself in, and the last of the launch's gate workgroups does the encode (dispatch_all).
 enum { GATE_ONLY = 0, GATE_ENC_OWN = 1, GATE_ENC_LAST = 2 };
 
-// The workgroup's part of the gate: tokens 16 NW block and on.  gm: ROOM bytes of LDS, 1024-byte aligned.
-template <bool BF16, int NW, int EG, int MODE, int ROOM = 160 * 1024>
+// The workgroup's part of the gate: tokens 16 NW / GW block and on.  gm: ROOM bytes of LDS, 1024-byte aligned.
+template <bool BF16, int NW, int EG, int MODE, int ROOM = 160 * 1024, int GW = 1>
 __device__ __forceinline__ void gate_mfma(
     unsigned char* gm, int block, const unsigned char* __restrict__ x, int64_t ldx, const float* __restrict__ Wg,
     const float* __restrict__ bias, int T, int d, int E, int k, int normalize,
     int32_t* __restrict__ expert_idx, float* __restrict__ gate_w, float* __restrict__ probs, const DispatchOut& enc,
     unsigned long long* marks, unsigned long long call, int workgroups) {
-  using C = GateMfmaCfg<BF16, NW, EG, ROOM>;
+  using C = GateMfmaCfg<BF16, NW, EG, ROOM, GW>;
   constexpr int EB = C::EB, SS = C::SS, KC = C::KC, IPT = C::IPT, WB = C::WB, XS = C::XS, P = C::P;
   constexpr int TOK = C::TOK, LGS = C::LGS;
   constexpr bool AGENT = MODE == GATE_ENC_LAST;           // the choices are read by another workgroup of this launch
@@ -383,7 +387,8 @@ __device__ __forceinline__ void gate_mfma(
   // re-read its last 16 bytes (never consumed), and so do whole stages past the end, which keeps
   // the number of copies per stage fixed for the waits below.
   const int crow = lane >> 2, ccol = (lane & 3) ^ ((lane >> 4) & 3);
-  int trow = t0 + wave * 16 + crow;
+  const int tgroup = wave / GW, egroup = wave % GW;       // 16 tokens; 16 experts (GW > 1)
+  int trow = t0 + tgroup * 16 + crow;
   if (trow > T - 1) trow = T - 1;
   const unsigned char* const xrow = x + static_cast<int64_t>(trow) * ldx * EB;
   const int row_last = d * EB - 16;
@@ -401,7 +406,7 @@ __device__ __forceinline__ void gate_mfma(
   // the end of the matrix a copy re-reads its last 16 bytes (never consumed).
   const unsigned char* const wg = reinterpret_cast<const unsigned char*>(Wg);
   const int64_t w_last = static_cast<int64_t>(d) * E * 4 - 16;
-  const int w_copies = (E + EG - 1) / EG;                 // = ceil(4 KC E / 1024)
+  const int w_copies = (E + C::G - 1) / C::G;                 // = ceil(4 KC E / 1024)
   auto issue_w = [&](int j, int buf) {
     unsigned char* dst = gm + buf * GM_WBUF;
     for (int u = wave; u < w_copies; u += NW) {
@@ -430,7 +435,7 @@ __device__ __forceinline__ void gate_mfma(
 #pragma unroll
   for (int q = 0; q < 4; ++q) xl[q] = (c16 * 4 + (q ^ (c16 >> 2))) * 16 + kq * EB;
 #pragma unroll
-  for (int s = 0; s < SS; ++s) wl[s] = ((4 * s + kq) * E + c16) * 4;     // of step s of a stage
+  for (int s = 0; s < SS; ++s) wl[s] = ((4 * s + kq) * E + c16) * 4 + 64 * egroup;     // of step s of a stage
   // Operand registers hold what the matrix instruction takes: fp32 bits (a bf16 in the upper half).
   // P steps are in registers or on their way at any time: step s uses slot s % P.
   uint32_t xr[P], wr[P][EG];
@@ -578,7 +583,7 @@ __device__ __forceinline__ void gate_mfma(
       }
     }
   };
-  if (EG == 1 && k == 1 && probs == nullptr) {
+  if (EG == 1 && GW == 1 && k == 1 && probs == nullptr) {
     // Top-1 without the probability output is routed in registers: a lane folds its four logits,
     // then the four lanes of a token (16 lanes apart, in ascending expert order) fold theirs.
     // Same rule and same operations in the same order as route_token, hence the same bits: the
@@ -650,17 +655,17 @@ __device__ __forceinline__ void gate_mfma(
   for (int g = 0; g < EG; ++g) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int e = 16 * g + 4 * kq + r;
+      const int e = 16 * (g + egroup) + 4 * kq + r;
       if (e < E) {
         float v = acc[g][r];
         if (bias != nullptr) v = __fadd_rn(v, bias[e]);
-        lg[(wave * 16 + c16) * LGS + e] = v;
+        lg[(tgroup * 16 + c16) * LGS + e] = v;
       }
     }
   }
   __syncthreads();
   if (tid < TOK)
-    route_token<16 * EG, AGENT>(lg + tid * LGS, E, k, normalize, t0 + tid < T, t0 + tid, expert_idx, gate_w, row_max[tid], row_sum[tid]);
+    route_token<16 * C::G, AGENT>(lg + tid * LGS, E, k, normalize, t0 + tid < T, t0 + tid, expert_idx, gate_w, row_max[tid], row_sum[tid]);
   if (probs != nullptr) {
     __syncthreads();
     const int ntok = (T - t0 < TOK) ? T - t0 : TOK;

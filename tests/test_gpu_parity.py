@@ -69,6 +69,14 @@ def test_gate_parity(oracle, T, d, E, dtype, k, use_bias, normalize):
     assert np.abs(gp.cpu().numpy().astype(np.float64) - probs).max() <= 1e-6
 
 
+@pytest.mark.parametrize("T,d,E,dtype,k,use_bias", [
+    (4096, 136, 64, "bf16", 2, True), (4097, 136, 64, "bf16", 2, True), (8192, 72, 32, "f32", 1, False), (8193, 72, 32, "bf16", 1, False),
+    (15, 2056, 17, "bf16", 3, False), (33, 264, 49, "f32", 4, True), (16, 8, 33, "bf16", 1, True)])
+def test_gate_a_wave_for_16_tokens_and_16_experts(oracle, T, d, E, dtype, k, use_bias):
+    """17 to 64 experts up to one wave per SIMD (and just above), ragged in tokens, experts and features."""
+    test_gate_parity(oracle, T, d, E, dtype, k, use_bias, 0)
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_gate_random_shapes(oracle, seed):
     """Seeded sweep of the gate: token counts of every workgroup shape, feature counts that end
