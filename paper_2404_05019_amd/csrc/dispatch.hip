@@ -461,7 +461,8 @@ int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, i
     const int blocks = items > 0 ? static_cast<int>((items + DISP1_THREADS - 1) / DISP1_THREADS) : 1;
     const ScanChores sc = chores ? *chores : ScanChores{};
 #define SCMOE_ONEPASS(NIB, K, JOINT)                                                                                       \
-  if (NIB) SCMOE_ONEPASS_NB(true, K, JOINT, 4);                                                                            \
+  if (NIB && E <= 8) SCMOE_ONEPASS_NB(true, K, JOINT, 3);                                                                  \
+  else if (NIB) SCMOE_ONEPASS_NB(true, K, JOINT, 4);                                                                       \
   else if (E <= 32) SCMOE_ONEPASS_NB(false, K, JOINT, 5);                                                                  \
   else SCMOE_ONEPASS_NB(false, K, JOINT, 6)
 #define SCMOE_ONEPASS_NB(NIB, ...)                                                                                         \
