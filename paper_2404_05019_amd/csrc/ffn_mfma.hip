@@ -1135,7 +1135,7 @@ bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
   const double mean = static_cast<double>(rows) / g.E;
   const int64_t most = row_tiles(rows, g.E, edge), clear = g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge));
   const int64_t routed = most * nt, joint = shared + (most < clear ? most : clear) * nt;
-  if (shared + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;
+  if (gate > cus || shared + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;     // (and room for the coefficient gate)
   return (shared + cus - 1) / cus + (routed + cus - 1) / cus <= (joint + cus - 1) / cus;
 }
 

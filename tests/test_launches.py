@@ -281,6 +281,7 @@ def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
     side += [_layer(500, 2048, 8192, 16), dict(_layer(8192, 384, 1536), capacity=1280), _layer(6000, 512, 2048)]
     apart = [_layer(500, 2048, 8192, 16, two=True), _layer(500, 2048, 8192, 24), _layer(16384, 1024, 4096), _layer(1500, 1536, 4096),
              _layer(3001, 768, 3072, 12, 2), _layer(8000, 192, 768), _layer(8, 2048, 8192, 16), _layer(20000, 512, 2048, k=2)]
+    apart += [dict(_layer(T, 256, F), cg=cg) for T in (16385, 32768) for F in (128, 256) for cg in (0, 2)]      # (more gate workgroups than CUs)
     for want, calls in ((True, side), (False, apart)):
         for c, (st, lines) in zip(calls, record(calls)):
             kernels, _ = _order(lines)
