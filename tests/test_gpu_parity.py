@@ -506,6 +506,19 @@ def test_layer_wide_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams, share
     assert C_ * E >= T * k or (r["dst_row"] < 0).any()
 
 
+@pytest.mark.parametrize("T,d,F,E,C_,cg", [(2364, 1152, 2304, 8, 370, 1), (300, 1088, 2112, 16, 18, 2)])
+def test_dropped_rows_under_a_coefficient_gate_are_rounded_once(T, d, F, E, C_, cg):
+    """y of a token without a routed row is c0 times the fp32 sums of the shared expert, rounded once: what the decode of the
+    two-stream call stores, up to sums in another order (where tiles are cut along K), which flip about one rounding in a
+    thousand.  Rounded before the scaling as well, a quarter of the values differ."""
+    D = DevLayer(inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T, biases=True, cg_rows=cg, w_scale=0.03, zipf=1.0), "bf16")
+    one, r = run_layer(D, 1, C_, True, 0, cg)
+    two, _ = run_layer(D, 1, C_, True, 0, cg, two_streams=True)
+    dropped = r["dst_row"][:, 0] < 0
+    assert dropped.sum() > 60
+    assert np.mean(one[dropped] != two[dropped]) < 0.01
+
+
 @pytest.mark.parametrize("dtype,d,F", [("f32", 72, 200), ("bf16", 128, 256), ("bf16", 512, 1024)])
 def test_non_finite_values_stay_in_their_rows(dtype, d, F):
     """A NaN or an infinity in one row of x reaches that row of the output and no other."""

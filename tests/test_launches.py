@@ -273,6 +273,18 @@ def test_second_gemm_of_short_tiles(record):
         assert st == 0 and not any("TileCfgILi64ELi128E" in k[0] for k in _order(lines)[0]), c
 
 
+def test_dropped_rows_under_a_coefficient_gate_are_not_left_to_the_combine_kernel(record):
+    """It would scale the shared expert's rounded rows and round a second time; with a residual, without drops or without
+    the gate it rounds as often as the two decodes do."""
+    base = dict(_layer(2364, 1152, 2304), cg=1, capacity=370)
+    few = dict(_layer(300, 1088, 2112, 16), cg=1, capacity=25)
+    for want, calls in ((0, [base, dict(base, cg=2), few]),
+                        (1, [dict(base, cg=0), dict(base, res=True), dict(base, capacity=2364), dict(few, cg=0), dict(few, res=True), dict(few, capacity=300)])):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            assert st == 0 and len(_at(kernels, "combine_kernel")) == want, (c, [k[0] for k in kernels])
+
+
 def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
     """No launch of gate, encode and coefficient gate where the first of three products' launches does them, which is where the
     shared expert's tiles apart from the routed ones take no round more (the GPU tests rely on the first ones)."""
