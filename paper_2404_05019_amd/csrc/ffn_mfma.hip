@@ -1106,7 +1106,10 @@ static int launch_first_with_gate(GemmArgs a, GateWork w, hipStream_t stream) {
     if (w.coef_workgroups > room) w.coef_workgroups = room;
     if (w.coef_workgroups < 1) return SCMOE_ERR_ARG;
   }
-  const int64_t all = tiles + w.workgroups + w.coef_workgroups;
+  // An XCD's tiles go to as many of its first workgroups, and the gate's workgroups follow: the slowest of those encodes, and
+  // with a tile behind that the launch takes 44 us instead of 26 (7883 tokens, d = 512, F = 1344, E = 8, 186 tiles: on 248
+  // workgroups the layer took 112 us, so 97).
+  const int64_t all = (tiles + 7) / 8 * 8 + w.workgroups + w.coef_workgroups;
   const int grid = all < resident ? static_cast<int>((all + 7) / 8 * 8) : resident;
   if (w.workgroups + w.coef_workgroups > grid) return SCMOE_ERR_ARG;
   GateGemmArgs g;
@@ -1130,7 +1133,7 @@ bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
   if (gemm_variant() != 0 || !aligned16(g.Wg) || g.d < 256 || g.d >= 4096 || g.E > 16 || static_cast<int64_t>(g.T) * g.k > 32768) return false;
   if (static_cast<int64_t>(g.T) * g.ldxc * 2 >= lim || static_cast<int64_t>(F) * ldw1 * 2 >= lim) return false;
   const int edge = takes_large_tiles(true, true, rows, g.E, g.T, F) ? 256 : 128;
-  const int64_t nt = (F + edge - 1) / edge, shared = (g.T + edge - 1) / edge * nt, gate = (g.T + edge / 2 - 1) / (edge / 2);
+  const int64_t nt = (F + edge - 1) / edge, shared = ((g.T + edge - 1) / edge * nt + 7) / 8 * 8, gate = (g.T + edge / 2 - 1) / (edge / 2);
   // (the segments' tiles, from above and, where a balanced load is clear of the next tile, from below)
   const double mean = static_cast<double>(rows) / g.E;
   const int64_t most = row_tiles(rows, g.E, edge), clear = g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge));

@@ -302,6 +302,26 @@ def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
             assert (not any(n in k[0] for k in kernels for n in ("gate_mfma_kernel", "dispatch_", "coef_gate_kernel"))) == want, c
 
 
+def test_gate_workgroups_on_the_side_have_no_tile(record):
+    """Every XCD's tiles go to its first workgroups and the gate's are the launch's last ones: room for both, whatever the
+    remainders of the tiles and of the gate's workgroups by eight are."""
+    rng = random.Random(7)
+    calls = [_layer(7883, 512, 1344), _layer(3712, 1344, 3584), dict(_layer(1480, 1920, 7680), cg=1)]
+    calls += [dict(_layer(int(math.exp(rng.uniform(math.log(300), math.log(9000)))), 64 * rng.randint(4, 32), 64 * rng.randint(10, 128),
+                          rng.choice([2, 4, 8, 12, 16]), rng.choice([1, 1, 2])), cg=rng.choice([0, 1])) for _ in range(400)]
+    seen = set()
+    for c, (st, lines) in zip(calls, record(calls)):
+        assert st == 0
+        first = next((w for w in lines if w[0] == "kernel" and "gemm_bf16_kernel" in w[2]), None)
+        if first is None or "ELb1ELi1EEE" not in first[2]:
+            continue
+        edge = int(re.search(r"TileCfgILi(\d+)E", first[2]).group(1))
+        tiles, gate = -(-c["T"] // edge) * -(-c["F"] // edge), -(-c["T"] // (edge // 2))
+        assert int(first[3]) >= -(-tiles // 8) * 8 + gate, (c, first[2:5])
+        seen.add((edge, tiles % 8 > 0))
+    assert len(seen) == 4
+
+
 def test_no_launch_passes_the_limit_on_work_items(record):
     """2^32 work-items in x is what the runtime takes; 1.1 million rows of 65544 columns need more
     workgroups than that (144 GB of hidden rows in bf16: they fit the card)."""
