@@ -32,6 +32,7 @@
 #include "mfma_common.hpp"
 #include "coef_gate.hpp"
 #include "gate_mfma.hpp"
+#include <algorithm>
 #include <atomic>
 #include <math.h>
 
@@ -1121,25 +1122,38 @@ static int launch_first_with_gate(GemmArgs a, GateWork w, hipStream_t stream) {
 
 // Whether a layer's gate and encode go on the side of the shared expert's first GEMM, which then is a launch of its own
 // ahead of the routed experts'.  What that saves are the launches of gate and encode (14 to 30 us, in which the matrix cores
-// idle); what it costs is a partly filled round of tiles more, so only where both launches together have no more rounds
-// (tiles per CU, rounded up) than the joint one.  Layer us, joint / on the side: 500 tokens, d = 2048, F = 8192, E = 16
-// 325 / 297; 600, d = 1024, F = 4096, E = 16 109 / 100; 1000, d = 1024, F = 2048, E = 8 with a coefficient gate 74 / 65;
-// 8192, d = 384, F = 1536, E = 8 90 / 85; but 1500, d = 1536, F = 4096, E = 8 (a round
-// more) 132 / 135, 3001, top-2, d = 768, F = 3072, E = 12 147 / 154.  Not at widths whose tiles are done before the encode
-// is (16000, d = 128 57.2 / 61.0; 8000, d = 192 53 / 54; 7777, d = 320 with large tiles 75.4 / 79.9), and up to 16 experts: above them the gate is two
-// or four times as long (4096, d = 768, F = 2048, E = 24 123 / 115, but 1200, d = 640, E = 64 174 / 175; 4096, d = 512, E = 32 127 / 130).
+// idle) and of the coefficient gate; what it costs is
+//  * the encode by one workgroup where that ends after the tiles do: a wave walks its share of the choices, 64 a turn, and
+//    has as many turns as the tiles have k-tiles, or three times as many with 256-row tiles, whose k-tile is that much
+//    longer (layer us, apart / on the side: top-2, 5161 tokens, d = 256, F = 704, E = 8, 41 turns 51 / 68; top-4, 2304, d = 384,
+//    F = 768, E = 4, 36 turns 57 / 67; 7809, d = 384, F = 1024, E = 8, 62 turns 145 / 162);
+//  * a partly filled round of tiles more, so only where both launches together have no more rounds (tiles per CU, rounded up)
+//    than the joint one.  The routed launch is counted from above: a balanced load with the mean half a standard deviation
+//    higher, and at 256 rows a tile a skewed one, with a last tile of their own for three quarters of the experts; the joint
+//    one from below, where a capacity may drop a quarter of the rows (1500, d = 1536, F = 4096, E = 8 130 / 142; 3001, top-2, d = 768,
+//    F = 3072, E = 12 144 / 153; skewed 2733, d = 1920, F = 3840, E = 16 270 / 305; skewed with drops 8205, d = 384, F = 1024, E = 4
+//    58 / 63; but taken: 500, d = 2048, F = 8192, E = 16 307 / 279; 600, d = 1024, F = 4096, E = 16 106 / 96; 8192, d = 384, F = 1536, E = 8
+//    81 / 77; 6000, d = 512, F = 2048 91 / 84; with a coefficient gate top-2, 456, d = 768, F = 2048, E = 16 61 / 52).
+// Of 1800 drawn layers that fit, 1082 are taken; six of those are slower than apart by more than 1.5 %, skewed loads whose rounds
+// the host cannot count (top-3, 825 tokens, d = 1536, F = 4096, E = 16 184 / 206; 1980, d = 1856, F = 7424, E = 2 236 / 267).
+// Not at widths whose tiles are done before the encode is (16000, d = 128 59 / 66; 8000, d = 192, E = 8 and 16 52 / 52 and 56 / 56),
+// with 256-row tiles not below d = 384, and only up to 16 experts, for which alone the launch is built.
 bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
-  const int64_t lim = BUFFER_SPAN, cus = num_cus();
-  if (gemm_variant() != 0 || !aligned16(g.Wg) || g.d < 256 || g.d >= 4096 || g.E > 16 || static_cast<int64_t>(g.T) * g.k > 32768) return false;
+  const int64_t lim = BUFFER_SPAN, cus = num_cus(), items = static_cast<int64_t>(g.T) * g.k;
+  if (gemm_variant() != 0 || !aligned16(g.Wg) || g.d < 256 || g.d >= 4096 || g.E > 16 || items > 32768) return false;
   if (static_cast<int64_t>(g.T) * g.ldxc * 2 >= lim || static_cast<int64_t>(F) * ldw1 * 2 >= lim) return false;
   const int edge = takes_large_tiles(true, true, rows, g.E, g.T, F) ? 256 : 128;
-  const int64_t nt = (F + edge - 1) / edge, shared = ((g.T + edge - 1) / edge * nt + 7) / 8 * 8, gate = (g.T + edge / 2 - 1) / (edge / 2);
-  // (the segments' tiles, from above and, where a balanced load is clear of the next tile, from below)
+  const int64_t nt = (F + edge - 1) / edge, shared = (g.T + edge - 1) / edge * nt, gate = (g.T + edge / 2 - 1) / (edge / 2);
+  if (gate > cus || (shared + 7) / 8 * 8 + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;     // (and room for the coefficient gate)
+  const int64_t turns = ((items + 63) / 64 + edge / 32 - 1) / (edge / 32);
+  if (64 * turns > (edge == 256 ? 3 : 1) * g.d) return false;
   const double mean = static_cast<double>(rows) / g.E;
-  const int64_t most = row_tiles(rows, g.E, edge), clear = g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge));
-  const int64_t routed = most * nt, joint = shared + (most < clear ? most : clear) * nt;
-  if (gate > cus || shared + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;     // (and room for the coefficient gate)
-  return (shared + cus - 1) / cus + (routed + cus - 1) / cus <= (joint + cus - 1) / cus;
+  int64_t least = row_tiles(rows, g.E, edge), most = std::max(least, g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge)));
+  if (edge == 256) {
+    most = std::max(most, static_cast<int64_t>(rows / 256 + 3 * g.E / 4));
+    if (g.enc.capacity < g.T) least = std::min(least, static_cast<int64_t>(rows * int64_t(3) / 1024 + g.E / 2));
+  }
+  return (shared + cus - 1) / cus + (most * nt + cus - 1) / cus <= (shared + least * nt + cus - 1) / cus;
 }
 
 static int launch_first_with_gate(const GemmArgs& a, int max_rows, int E, const GateWork& w, hipStream_t stream) {
