@@ -841,6 +841,12 @@ static int launch_gemm(const GemmArgs& a, int max_rows, int64_t a_rows, hipStrea
 // than 7/8 of one.
 static int64_t row_tiles(int64_t rows, int64_t E, int edge) { return 8 * rows <= 7 * edge * E ? E : rows / edge + E / 2; }
 
+// ... and from above for a balanced load: with its mean half a standard deviation higher.
+static int64_t most_row_tiles(int64_t rows, int64_t E, int edge) {
+  const double mean = static_cast<double>(rows) / E;
+  return std::max(row_tiles(rows, E, edge), E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge)));
+}
+
 // Whether a launch takes the 256 x 256 tiles (variant 0): a first GEMM or not, no other chain beside it, rows in E segments
 // and in the extra one.
 static bool takes_large_tiles(bool first, bool alone, int64_t max_rows, int64_t E, int64_t xrows, int64_t N) {
@@ -1074,11 +1080,15 @@ bool ffn_second_in_one_launch(int T, int rows, int d, int F, int E) {
   if (all <= 128 * segs) return true;
   if (d <= CfgV::BN) return false;
   const int64_t nt = (d + CfgV::BN - 1) / CfgV::BN, shared = (T + CfgV::BM - 1) / CfgV::BM * nt;
-  const int64_t routed = row_tiles(rows, E, CfgV::BM) * nt;
+  const int64_t routed = most_row_tiles(rows, E, CfgV::BM) * nt;
   const double combine = 2.0 + 6.0 * T * d / 5.5e6;      // y_perm and s read, y written
-  // Not above two rounds (nothing gained at 8192 tokens, d = 1024, F = 4096, E = 8), and not for the fewest tiles: there
-  // either form cuts all of them into as many parts as it may, and one- and two-stream calls agree bit for bit.
-  if (shared + routed > 2 * num_cus() || 8 * (shared + routed) <= num_cus()) return false;
+  // Up to 15/8 rounds, counted from above: with a third one the single launch loses (two / one, layer us, tiles per CU by the
+  // average: 20387 tokens, d = 320, F = 1280, E = 16 151 / 170 (1.96); 14602, d = 512, F = 1344, E = 24 176 / 191 (1.98); 10491, d = 640,
+  // F = 2560, E = 32 258 / 278 (1.89); 2117, d = 2048, F = 4096, E = 8 232 / 238 (1.31, from above 1.56); nothing gained at 8192,
+  // d = 1024, F = 4096, E = 8).  Of 271 drawn layers 251 are taken, four of them slower by more than 1.5 %, at most 6 (skewed).
+  // And not for the fewest tiles: there either form cuts all of them into as many parts as it may, and one- and two-stream
+  // calls agree bit for bit.
+  if (8 * (shared + routed) > 15 * num_cus() || 8 * (shared + routed) <= num_cus()) return false;
   return second_gemm_us(shared + routed, F) + combine < second_gemm_us(shared, F) + second_gemm_us(routed, F);
 }
 
@@ -1147,8 +1157,7 @@ bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
   if (gate > cus || (shared + 7) / 8 * 8 + (edge == 256 ? gate : 0) > cus || (edge == 256 && g.d < 384)) return false;     // (and room for the coefficient gate)
   const int64_t turns = ((items + 63) / 64 + edge / 32 - 1) / (edge / 32);
   if (64 * turns > (edge == 256 ? 3 : 1) * g.d) return false;
-  const double mean = static_cast<double>(rows) / g.E;
-  int64_t least = row_tiles(rows, g.E, edge), most = std::max(least, g.E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge)));
+  int64_t least = row_tiles(rows, g.E, edge), most = most_row_tiles(rows, g.E, edge);
   if (edge == 256) {
     most = std::max(most, static_cast<int64_t>(rows / 256 + 3 * g.E / 4));
     if (g.enc.capacity < g.T) least = std::min(least, static_cast<int64_t>(rows * int64_t(3) / 1024 + g.E / 2));

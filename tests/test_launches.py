@@ -315,6 +315,17 @@ def test_gate_on_the_side_not_where_it_ends_later_or_a_round_is_lost(record):
             assert st == 0 and any("ELb1ELi1EEE" in k[0] for k in kernels) == want, (c, [k[0] for k in kernels])
 
 
+def test_second_gemms_of_a_layer_in_one_launch_up_to_two_rounds_from_above(record):
+    """Not where both would need a third round of 256 x 128 tiles, with the experts' last row tiles counted from above."""
+    one = [_layer(1500, 1536, 4096), _layer(2048, 512, 2048), _layer(3300, 1280, 4096), _layer(1024, 1024, 2048)]
+    two = [_layer(20387, 320, 1280, 16), _layer(14602, 512, 1344, 24), _layer(10491, 640, 2560, 32), _layer(2117, 2048, 4096), _layer(2421, 1856, 4928)]
+    for want, calls in ((1, one), (2, two)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            kernels, _ = _order(lines)
+            assert st == 0 and len([k for k in kernels if "gemm_bf16" in k[0] and "EEELb0E" in k[0]]) == want, (c, [k[0] for k in kernels])
+            assert len(_at(kernels, "combine_kernel")) == (want == 1), c
+
+
 def test_gate_workgroups_on_the_side_have_no_tile(record):
     """Every XCD's tiles go to its first workgroups and the gate's are the launch's last ones: room for both, whatever the
     remainders of the tiles and of the gate's workgroups by eight are."""
