@@ -901,11 +901,25 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   GemmArgs g = a;
   g.rotk = few_rows ? 5 : 0;
   if (takes_large_tiles(ACT, !a.beside, max_rows, a.E, a.xrows, a.N)) return launch_gemm<CfgA, ACT>(g, max_rows, a_rows, stream);
-  // A second GEMM of up to 64 rows per expert: half of a 128-row stage would be padding, and three stages of 64 rows keep half
-  // as much again of the weights in flight (layer us, d = 2048, F = 8192, E = 16: 500 tokens 294 / 278, 800 tokens 327 / 318;
-  // 300, d = 1024, F = 4096 108.6 / 90.4; top-1 without shared expert, 500, d = 1024 92.1 / 90.0; a first GEMM, with its many
-  // column tiles, gains nothing: 500 tokens 296 / 297, 800 tokens 327 / 341).
-  if (!ACT && max_rows <= 64 * static_cast<int64_t>(a.E) && rows <= 96 * segs) return launch_gemm<CfgS, ACT>(g, max_rows, a_rows, stream);
+  // A second GEMM of up to 53 rows per expert (above, more and more experts pass 64): half of a 128-row stage would be padding,
+  // and three stages of 64 rows keep half as much again of the weights in flight (layer us, d = 2048, F = 8192, E = 16: 500 tokens
+  // 294 / 278, 800 tokens 327 / 318; 300, d = 1024, F = 4096 108.6 / 90.4; top-1 without shared expert, 500, d = 1024 92.1 / 90.0; a
+  // first GEMM, with its many column tiles, gains nothing: 500 tokens 296 / 297, 800 tokens 327 / 341).  With an expert in each:
+  //  * more than 3/8 of a tile per CU (fewer are better off with four waves a workgroup: top-4, 64 tokens, d = 1280, F = 2560,
+  //    E = 8 83 / 91; top-1, 126, d = 1472, F = 3904, E = 4 54 / 57), or few enough to be cut along a long K where the 128-row
+  //    tiles are not, a quarter of one per CU being their limit (top-4, 43, d = 1600, F = 6400, E = 4 102 / 84; top-1, 181,
+  //    d = 1664, F = 4416 77 / 70; with the shared expert 182, d = 1536, F = 6144 100 / 86, but 39, top-4, d = 1472, F = 3904 85 / 87);
+  //  * up to one, with two tiles for some experts, or from 5/4 to 2: between, some CUs have a second tile (224 tokens, top-2,
+  //    d = 1728, F = 4608, E = 16 150 / 166; skewed, 265, d = 1344, F = 3584 103 / 116; 600, d = 1536, F = 4096, E = 12 124 / 126);
+  //  * no other chain's second GEMM beside it (top-3, 99 tokens, d = 1600, F = 6400, E = 8 on two streams 141 / 172).
+  // Of 450 drawn calls of up to 64 rows about 220 are taken, four of them slower by more than 1.5 %, at most 7.  The 256-row tiles
+  // above come first, whatever the segments: from (rows / 256 + experts) x column tiles of one per CU on (600 tokens, d = 2048, E = 32).
+  const int64_t cus = num_cus(), s_nt = (a.N + CfgS::BN - 1) / CfgS::BN, s_segs = a.E + (a.xrows + CfgS::BM - 1) / CfgS::BM;
+  const int64_t s_tiles = s_segs * s_nt, s_more = (s_segs + max_rows / (2 * CfgS::BM)) * s_nt, s_most = (s_segs + max_rows / CfgS::BM) * s_nt;
+  const bool s_rows = 6 * static_cast<int64_t>(max_rows) <= 5 * CfgS::BM * static_cast<int64_t>(a.E) && rows <= 96 * segs;
+  const bool s_fit = 8 * s_tiles > 3 * cus && s_tiles <= 2 * cus && (s_more <= cus || 4 * s_tiles > 5 * cus);
+  const bool s_cut = a.splitk_part != nullptr && 2 * a.Kd >= (a.xrows > 0 ? 4 : 3) * SPLITK_MIN_K && 4 * tiles_of(CfgT::BM) > cus && 2 * s_most <= cus;
+  if (!ACT && s_rows && (s_fit || s_cut) && !(a.beside && a.scatter == nullptr)) return launch_gemm<CfgS, ACT>(g, max_rows, a_rows, stream);
   // Not even one 128 x 128 tile per CU, and a second GEMM (long K, short epilogue): every
   // workgroup is alone on its CU, and three LDS stages keep more in flight (small workload: 18.4
   // against 27.8 us with two waves and 32-deep k-tiles; 2000 tokens, d = 512: 79.6 against 95.9 us
@@ -1004,6 +1018,7 @@ static GemmArgs second_gemm(const FfnArgs& a, const SplitK& sk) {
   g.row_scale = a.row_scale;
   g.addend = static_cast<const unsigned char*>(a.addend);
   g.ldadd = a.ldadd;
+  g.beside = a.beside;
   g.splitk_part = sk.parts;
   g.splitk_count = sk.counters;
   return g;

@@ -260,16 +260,23 @@ def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
 
 
 def test_second_gemm_of_short_tiles(record):
-    """64 x 128 tiles up to 64 rows per segment; both second GEMMs of a top-1 layer in one launch of at most two tiles per CU."""
+    """64 x 128 tiles up to 53 rows per expert, 3/8 to 1 or 5/4 to 2 of them per CU, and no other second GEMM beside them; both
+    second GEMMs of a top-1 layer in one launch of at most two tiles per CU."""
     from test_gpu_parity import SHORT_FFN, SHORT_LAYERS
     calls = [dict(what="ffn", E=E, T=sum(lens), d=d, F=F, dtype=BF16) for E, lens, d, F in SHORT_FFN]
     calls += [dict(_layer(T, d, F, E, k, two=two), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res, two in SHORT_LAYERS]
-    calls += [_layer(500, 2048, 8192, 16), _layer(400, 1024, 2048, 24)]
+    calls += [_layer(500, 2048, 8192, 16), _layer(400, 1024, 2048, 17)]
     for c, (st, lines) in zip(calls, record(calls)):
         kernels, _ = _order(lines)
         n = sum("TileCfgILi64ELi128E" in k[0] for k in kernels)
         assert st == 0 and n == 1 and len(_at(kernels, "combine_kernel")) == (c["what"] == "layer" and not c["two"]), (c, [k[0] for k in kernels])
-    for c, (st, lines) in zip([_layer(1500, 1024, 4096, 16), _layer(8, 2048, 8192, 16)], record([_layer(1500, 1024, 4096, 16), _layer(8, 2048, 8192, 16)])):
+    cut = [_layer(86, 2048, 5440, 4, 2), _layer(182, 1536, 6144, 4)]       # a long K, 128-row tiles too many to be cut
+    for c, (st, lines) in zip(cut, record(cut)):
+        assert st == 0 and sum("TileCfgILi64ELi128E" in k[0] for k in _order(lines)[0]) == 1, c
+    other = [_layer(39, 1472, 3904, 4, 4), _layer(1500, 1024, 4096, 16), _layer(8, 2048, 8192, 16), _layer(600, 1536, 4096, 12), _layer(224, 1728, 4608, 16, 2), _layer(400, 1024, 2048, 24),
+             _layer(64, 1280, 2560, 8, 4), _layer(99, 1600, 6400, 8, 3, two=True), _layer(265, 1344, 3584, 16, 2), _layer(600, 2048, 2048, 32),
+             dict(what="ffn", E=16, T=940, d=1984, F=5312, dtype=BF16), dict(what="ffn", E=4, T=126, d=1472, F=3904, dtype=BF16)]
+    for c, (st, lines) in zip(other, record(other)):
         assert st == 0 and not any("TileCfgILi64ELi128E" in k[0] for k in _order(lines)[0]), c
 
 
