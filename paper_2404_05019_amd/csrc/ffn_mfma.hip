@@ -736,7 +736,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
 using CfgA = TileCfg<256, 256, 64, 2, 4, 2>;   // 8 waves, 128 KiB LDS, one workgroup per CU
 using CfgB = TileCfg<256, 256, 32, 2, 4, 4>;   // 8 waves, 4 stages, 128 KiB LDS
 using CfgT = TileCfg<128, 128, 64, 2, 2, 3>;   // 4 waves of 64 x 64, 104 KiB LDS, one workgroup per CU: fewer 128 x 128 tiles than CUs
-using CfgV = TileCfg<256, 128, 64, 4, 2, 3>;   // 8 waves of 64 x 64, 160 KiB LDS, one workgroup per CU: second GEMMs of one round of such tiles
+using CfgV = TileCfg<256, 128, 64, 4, 2, 3>;   // 8 waves of 64 x 64, 160 KiB LDS, one workgroup per CU: second GEMMs of one round of such tiles, of most of a second, or with a long K
 using CfgS = TileCfg<64, 128, 64, 1, 2, 3>;    // 2 waves of 64 x 64, 76 KiB LDS, two workgroups per CU: second GEMMs of up to 64 rows per segment
 using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
@@ -843,6 +843,7 @@ static int64_t row_tiles(int64_t rows, int64_t E, int edge) { return 8 * rows <=
 
 // ... and from above for a balanced load: with its mean half a standard deviation higher.
 static int64_t most_row_tiles(int64_t rows, int64_t E, int edge) {
+  if (E == 1) return (rows + edge - 1) / edge;
   const double mean = static_cast<double>(rows) / E;
   return std::max(row_tiles(rows, E, edge), E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge)));
 }
@@ -927,15 +928,22 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   if (!ACT && tiles_of(CfgT::BM) <= num_cus()) return launch_gemm<CfgT, ACT>(g, max_rows, a_rows, stream);
   // A second GEMM of more rows: 256 x 128 tiles, eight waves of 64 x 64 and three stages, one workgroup per CU: 0.82 us a
   // k-tile of a full chip, where two workgroups of 128 x 128 take 0.7 to 1.0 for the same outputs (kernel us, 128 x 128 /
-  // 256 x 128: 3001 tokens, top-2, d = 768, F = 3072, E = 12 60.6 / 51.0; 4096, d = 2048, F = 8192 134.8 / 119.8; layer us 6000,
-  // d = 1024, F = 4096, E = 8 274 / 253; 1500, d = 1536 152 / 131; rounds of tiles: 1.6, top-2, 8192, d = 768, E = 8 232 / 220; 1.8,
-  // 6000, d = 768, E = 8 238 / 227).  Not for a little more than one round (an eighth of
-  // a row tile per segment more than the estimate counts), where the smaller tiles fill the chip better (1.06,
-  // 16384, d = 512, F = 2048, E = 8 127.0 / 132.1; 1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9), nor where there is no
-  // more than one of the smaller tiles per CU (8000, d = 192, E = 16, skewed 49.9 / 53.2; 3000 x 4 rows, d = 256 70.5 / 73.8).
-  const int64_t square = (max_rows / CfgU::BM + (a.xrows + CfgU::BM - 1) / CfgU::BM) * ((a.N + CfgU::BN - 1) / CfgU::BN);
-  const int64_t nt = (a.N + CfgV::BN - 1) / CfgV::BN, wide = (row_tiles(max_rows, a.E, CfgV::BM) + (a.xrows + CfgV::BM - 1) / CfgV::BM) * nt;
-  if (!ACT && !few_rows && a.N > CfgV::BN && square >= num_cus() && (32 * wide + 4 * a.E * nt <= 33 * num_cus() || 10 * wide >= 13 * num_cus()))
+  // 256 x 128: 3001 tokens, top-2, d = 768, F = 3072, E = 12 60.6 / 51.0; layer us 6000, d = 1024, F = 4096, E = 8 274 / 253; 1500,
+  // d = 1536 152 / 131).  Where they were measured to gain (layer or call us in the same order):
+  //  * 16 k-tiles and more (below, three stages are hardly filled: 6780, d = 320, F = 640, E = 2 50 / 59);
+  //  * more of the smaller tiles than CUs, by a tenth below 44 k-tiles (those have a CU each up to there: 8000, d = 192, E = 16,
+  //    skewed 49.9 / 53.2; 17279, d = 192, F = 768, E = 16, skewed 53 / 56; but 1525, top-2, d = 1024, F = 4096, E = 8 159 / 132);
+  //  * not with the second round of them partly empty: more than one, counted from above, up to 1.75 (1.06, 16384, d = 512, F = 2048,
+  //    E = 8 127.0 / 132.1; 1.5, 10708, d = 768, F = 2048, E = 32 162 / 175; 1.64, skewed, 18538, d = 576, F = 1536, E = 12 200 / 221), or
+  //    from 44 k-tiles on, which gain more, by the average up to 1.3 (1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9; but
+  //    1.6, 7007, d = 1792, F = 4800, E = 12 619 / 596; 7522, top-1 without shared expert, d = 896, F = 3584, E = 4 271 / 253).
+  // Of 600 drawn calls that the average alone takes 100 are slower by more than 1.5 %, up to 19 %; of the 300 left 17, up to 6 %.
+  const int64_t v_extra = (a.xrows + CfgV::BM - 1) / CfgV::BM, v_nt = (a.N + CfgV::BN - 1) / CfgV::BN;
+  const int64_t square = (max_rows / CfgU::BM + (a.xrows + CfgU::BM - 1) / CfgU::BM) * static_cast<int64_t>((a.N + CfgU::BN - 1) / CfgU::BN);
+  const int64_t wide = (row_tiles(max_rows, a.E, CfgV::BM) + v_extra) * v_nt, v_most = (most_row_tiles(max_rows, a.E, CfgV::BM) + v_extra) * v_nt;
+  const bool v_long = a.Kd >= 44 * CfgV::BK;
+  if (!ACT && !few_rows && a.N > CfgV::BN && a.Kd >= 16 * CfgV::BK && 10 * square >= (v_long ? 10 : 11) * cus &&
+      (32 * wide + 4 * a.E * v_nt <= 33 * cus || 10 * wide >= 13 * cus) && (v_long || v_most <= cus || 4 * v_most > 7 * cus))
     return launch_gemm<CfgV, ACT>(g, max_rows, a_rows, stream);
   // Otherwise two workgroups per CU, whose epilogues and waits fall on each other's arithmetic
   // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500

@@ -463,11 +463,16 @@ def test_layer_medium_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
 
 # Calls of the second GEMM's 256 x 128 tiles (test_launches.py says that these take them): 9 column tiles, the last
 # one half empty; row tiles that are full, one row long and one row short of full.
-WIDE_FFN = [(4, [1023, 1, 2049, 768], 1088, 576), (4, [1023, 1, 2049, 768], 1088, 2112)]        # 9 k-tiles; 33, cut along K
-WIDE_LAYERS = [(1300, 1088, 576, 4, 2, 100000, 0, False, False, True),     # both chains in one launch
-               (2200, 1088, 2112, 5, 1, 350, 2, True, False, True),        # ... top-1, with drops, cut along K
-               (3800, 1088, 576, 3, 1, 1260, 2, True, True, True),         # fused decodes of both chains
-               (3800, 1088, 576, 3, 1, 1300, 0, False, False, False)]      # ... with nothing to add to
+WIDE_FFN = [(4, [1023, 1, 2561, 1280], 1088, 1088, 0),
+            (4, [767, 1, 1281, 100], 1088, 2112, 2716)]       # as few as are cut along K, in buffers for more
+WIDE_LAYERS = [(1540, 1088, 1088, 4, 2, 100000, 0, False, False, True),    # both chains in one launch
+               (2600, 1088, 2112, 5, 1, 420, 2, True, False, True),        # ... top-1, with drops
+               (4700, 1088, 1088, 3, 1, 1560, 2, True, True, True),        # fused decodes of both chains
+               (4700, 1088, 1088, 3, 1, 1600, 0, False, False, False)]     # ... with nothing to add to
+# ... and calls of the same forms below their range, which take the 128 x 128 tiles
+SQUARE_FFN = [(4, [1023, 1, 2049, 768], 1088, 576, 0), (4, [1023, 1, 2049, 768], 1088, 2112, 0)]
+SQUARE_LAYERS = [(1300, 1088, 576, 4, 2, 100000, 0, False, False, True), (2200, 1088, 2112, 5, 1, 350, 2, True, False, True),
+                 (3800, 1088, 576, 3, 1, 1260, 2, True, True, True), (3800, 1088, 576, 3, 1, 1300, 0, False, False, False)]
 
 
 # Calls of its 64 x 128 tiles: up to 64 rows per segment on average, and row tiles of one row to a full one.
@@ -491,13 +496,13 @@ def test_layer_short_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams):
     assert_close(y, ref, "bf16")
 
 
-@pytest.mark.parametrize("E,lens,d,F", WIDE_FFN)
-def test_expert_ffn_wide_tiles(oracle, E, lens, d, F):
+@pytest.mark.parametrize("E,lens,d,F,extra", WIDE_FFN + SQUARE_FFN)
+def test_expert_ffn_wide_tiles(oracle, E, lens, d, F, extra):
     """256 x 128 tiles, every element compared."""
-    _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=0, workspace=True)
+    _ffn_case(oracle, E, lens, d, F, "bf16", True, 0, extra_rows=extra, workspace=True)
 
 
-@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams,shared", WIDE_LAYERS)
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res,two_streams,shared", WIDE_LAYERS + SQUARE_LAYERS)
 def test_layer_wide_tiles(oracle, T, d, F, E, k, C_, cg, res, two_streams, shared):
     """The same tiles in a layer."""
     L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + F, biases=True, cg_rows=cg, w_scale=0.03)
