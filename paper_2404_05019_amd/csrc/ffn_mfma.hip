@@ -868,11 +868,15 @@ static bool takes_large_tiles(bool first, bool alone, int64_t max_rows, int64_t 
   const bool few_rows = rows <= 128 * segs;
   const bool short_first = first && rows <= 320 * segs && large > cus &&
                            (5 * large <= 8 * cus || (max_rows >= 240 * E && large <= 2 * cus));
-  // A first GEMM of expert segments alone whose large tiles fill two thirds of the CUs or more, once, and are 85 % full (layer
-  // us, small / large tiles: top-1, 8192 tokens, d = 384, F = 1536, E = 8 62.5 / 58.6; 6000, d = 512, F = 2048 68.6 / 63.7; 78 % full,
-  // 5000, E = 12 65.6 / 66.4).  Not beside a chain on another stream, which could not share a CU with them (118 / 122).
-  if (first && alone && E > 1 && xrows == 0 && !few_rows && N > CfgU::BN && 3 * large >= 2 * cus && large <= cus &&
-      20 * max_rows >= 17 * CfgA::BM * row_tiles(max_rows, E, CfgA::BM))
+  // A first GEMM of expert segments alone whose large tiles fill four fifths of the CUs or more, once, and are 85 % full in rows and
+  // columns (layer us, small / large tiles: top-1, 8192 tokens, d = 384, F = 1536, E = 8 62.5 / 58.6; 6000, d = 512, F = 2048 68.6 / 63.7;
+  // fewer, at 0.75 of the CUs, top-1, 15212, d = 320, F = 640, E = 8 47 / 53 and 7567, top-2, d = 384, F = 768, E = 8 94 / 98; half a last
+  // column tile, 10613, d = 128, F = 320 47 / 52; 78 % full, 5000, E = 12 65.6 / 66.4).  Of 315 drawn calls of two thirds of the CUs,
+  // 85 % full in rows, 32 are slower by more than 1.5 %, up to 16 %, of the 116 left three, up to 4 %.
+  // Not beside a chain on another stream, which could not share a CU with them (118 / 122).
+  const int64_t most = most_row_tiles(max_rows, E, CfgA::BM) * nt;
+  if (first && alone && E > 1 && xrows == 0 && !few_rows && N > CfgU::BN && 5 * most >= 4 * cus && most <= cus &&
+      20 * max_rows * N >= 17 * CfgA::BM * row_tiles(max_rows, E, CfgA::BM) * CfgA::BN * nt)
     return true;
   return N > CfgU::BN && (max_rows / CfgA::BM + E + extra) * nt >= cus && !(few_rows && first) && !short_first;
 }

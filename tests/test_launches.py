@@ -240,6 +240,17 @@ def test_first_gemm_of_small_tiles_where_the_large_ones_leave_a_round_partly_emp
             assert st == 0 and "TileCfgILi%dE" % edge in first, (c, first)
 
 
+def test_first_gemm_alone_of_large_tiles_that_fill_a_round(record):
+    """256 x 256 tiles in a first GEMM without the shared expert: four fifths of a round and more, 85 % full in both directions."""
+    ffn = lambda T, d, F, E: dict(what="ffn", T=T, d=d, F=F, E=E, dtype=BF16)  # noqa: E731
+    large = [ffn(8192, 384, 1536, 8), ffn(6000, 512, 2048, 8), ffn(16451, 192, 768, 12)]
+    small = [ffn(15212, 320, 640, 8), ffn(15134, 384, 768, 8), ffn(21226, 128, 320, 8), ffn(23447, 128, 320, 4), ffn(5000, 512, 2048, 12)]
+    for edge, calls in ((256, large), (128, small)):
+        for c, (st, lines) in zip(calls, record(calls)):
+            first = next(w[2] for w in lines if w[0] == "kernel" and "gemm_bf16_kernel" in w[2])
+            assert st == 0 and "TileCfgILi%dE" % edge in first, (c, first)
+
+
 def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
     """256 x 128 tiles of 16 k-tiles and more in up to a round or from 1.75 on; both second GEMMs of a top-1 layer in one launch
     where that saves a partly filled round (what the GPU tests of those tiles rely on is among the calls)."""
