@@ -325,9 +325,10 @@ def test_gate_on_the_side_not_where_it_ends_later_or_a_round_is_lost(record):
     """The encode by one workgroup has as many turns as the tiles have k-tiles (three times as many at 256 rows), and the routed
     experts' launch has no round more, also at a skewed load; capacities that drop rows leave the joint launch with fewer."""
     lay = lambda T, d, F, E, k=1, cap=None, cg=0: dict(_layer(T, d, F, E, k), capacity=T if cap is None else cap, cg=cg)  # noqa: E731
-    side = [lay(512, 256, 4096, 5, 2, 120), lay(8192, 384, 1536, 8, 1, 1280), lay(7883, 512, 1344, 8, 1, 1232), lay(4018, 576, 2304, 8)]
+    side = [lay(512, 256, 4096, 5, 2, 120), lay(8192, 384, 1536, 8, 1, 1280), lay(7883, 512, 1344, 8, 1, 1232), lay(4018, 576, 2304, 8), lay(3418, 512, 1344, 16, 2, 535, 2)]
     apart = [lay(513, 256, 4096, 5, 2, 120), lay(5161, 256, 704, 8, 2), lay(3305, 256, 704, 8, 4, 2066, 1), lay(2304, 384, 768, 4, 4, 2880),
-             lay(7809, 384, 1024, 8, 4, 3905, 1), lay(2733, 1920, 3840, 16), lay(8205, 384, 1024, 4, 1, 2565), lay(1500, 1536, 4096, 8)]
+             lay(7809, 384, 1024, 8, 4, 3905, 1), lay(2733, 1920, 3840, 16), lay(8205, 384, 1024, 4, 1, 2565), lay(1500, 1536, 4096, 8),
+             lay(3418, 512, 1344, 16, 2, 535)]
     for want, calls in ((True, side), (False, apart)):
         for c, (st, lines) in zip(calls, record(calls)):
             kernels, _ = _order(lines)
