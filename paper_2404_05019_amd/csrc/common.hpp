@@ -103,7 +103,7 @@ struct GateWork {
   int32_t* idx; float* gw;
   DispatchOut enc;
   unsigned long long* marks;       // 8 bytes of scratch for every 64 tokens, whatever they hold (all_arrived)
-  unsigned long long call;         // another number for every call
+  unsigned long long call;         // another number for every call, not zero (call_number)
   int workgroups;                  // set by the launch: of the gate, and of the coefficient gate
   int coef_workgroups;
   const void* xc; int64_t ldxc; const float* Wcg; int cg_mode; float* coef;   // (cg_mode SCMOE_CG_NONE: none)

@@ -337,9 +337,10 @@ __device__ __forceinline__ void dispatch_all(const int32_t* expert_idx, int T, i
 }
 
 // Marks workgroup `mine` of `all` as done and says whether all are (called by one whole wave; its earlier stores have been
-// performed).  The last one to be marked sees all marks; others may as well.  A mark is the number of the call, another one
-// for every call: the memory is the caller's and not cleared, and whoever saw all of them clears them (a replayed graph has
-// the same number again).
+// performed).  The last one to be marked sees all marks; others may as well.  A mark is the number of the call (call_number),
+// another one for every call, because the memory is the caller's and not cleared: whatever lies there counts as a mark only if
+// it is that number, which for other data has a probability of 2^-64 a mark and which no other call of the process has.
+// A replayed graph has the same number again, so whoever saw all marks clears them.
 __device__ __forceinline__ bool all_arrived(unsigned long long* marks, unsigned long long call, int mine, int all) {
   const int lane = threadIdx.x & 63;
   if (lane == 0) __hip_atomic_store(marks + mine, call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

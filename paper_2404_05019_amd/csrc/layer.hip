@@ -1,6 +1,7 @@
 // C-ABI entry points that are not a single kernel: status text, capacity, workspace sizes,
 // the expert FFN dispatcher, and the layer orchestration of ScMoE (paper Eq. (7), Sec. 3.2)
 // and of the standard top-k MoE layer (Eq. (1)-(4)).
+#include "call_number.hpp"
 #include "common.hpp"
 
 #include <math.h>
@@ -101,14 +102,11 @@ static LayerWs carve(const scmoe_desc* D, void* base, bool shared) {
   return w;
 }
 
-// Another number for every call that uses one (a permutation of a running count, never zero; not the bits of small
-// numbers, of pointers or of bf16 activations).
+// Another number, never zero, for every call that uses one: of a count that starts at the clock, kept by the process.
 static unsigned long long next_call() {
   static std::atomic<unsigned long long> n{static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count())};
-  unsigned long long v = n.fetch_add(1, std::memory_order_relaxed);
-  v = (v ^ (v >> 30)) * 0xbf58476d1ce4e5b9ull;
-  v = (v ^ (v >> 27)) * 0x94d049bb133111ebull;
-  return (v ^ (v >> 31)) | 1ull;
+  for (;;)
+    if (const unsigned long long v = call_number(n.fetch_add(1, std::memory_order_relaxed))) return v;
 }
 
 // out[t] = gate_w[t] * coef[2 t + 1]: the factor of a token's routed row under a coefficient gate (top-1)
