@@ -118,13 +118,18 @@ const char* scmoe_status_string(int status);
 /* hipError_t (as int) of the most recent SCMOE_ERR_HIP on the calling thread. */
 int scmoe_last_hip_error(void);
 
-/* Tuning knob, process-wide and the only state the library keeps between calls (one atomic
- * integer, read once per launch; no environment variable is consulted): tile configuration of
+/* Tuning knob, process-wide and the only setting the library keeps between calls (one atomic
+ * integer, read once per launch; no environment variable is consulted.  What else outlives a call: a
+ * count of the calls of scmoe_layer_forward that need a number of their own, which reaches no result
+ * and which the replays of a captured call share (the call clears what it marked with it);
+ * per thread the last HIP error and, per device, the events of two-stream calls; per device the number
+ * of compute units and which kernels have their LDS limit raised): tile configuration of
  * the bf16 grouped GEMM behind scmoe_expert_ffn and the layer calls.  Meant for benchmarks and
  * tests; a call that races with a change of the knob uses the old or the new value.
  * 0 (default) = chosen per launch: 256x256x64 tiles, 8 waves, 2 LDS stages; 128x128x64 tiles,
  * 4 waves, for few rows per expert and for problems that the larger tiles would not spread over
- * all compute units; small products take a kernel without tiles in LDS.  1 = always 256x256x32,
+ * all compute units; second GEMMs between those sizes 256x128x64 or 64x128x64 tiles, 3 stages;
+ * small products take a kernel without tiles in LDS.  1 = always 256x256x32,
  * 8 waves, 4 stages; 2 = always 128x128x64, 2 stages, two workgroups per compute unit; 3 = always
  * 128x128x64 with 3 stages (where the tiled kernel is used at all: not in fp32, at widths that are
  * no multiples of 64, for at most 64 rows, or for at most 16 rows per expert and 1024 in all).
@@ -327,7 +332,8 @@ int scmoe_workspace_bytes(const scmoe_desc* desc, size_t* out);
  * shared expert; otherwise the whole routed chain does and the join sits in front of the
  * combine kernel.  With stream_aux == NULL
  * everything runs in order on stream_main (and the first GEMMs of the shared and the routed
- * experts share one launch, and so do the second ones where that is faster, side by side or as one
+ * experts share one launch, or the shared one's does the gate and the encode on the side, ahead of the
+ * routed one's; the second ones share a launch where that is faster, side by side or as one
  * product).  The result is ready on stream_main.
  * (Measured on one MI355X: kernels of a few thousand tokens and more fill the chip and a second
  * stream gains nothing; up to about 4096 tokens it saves 5-13 % of the call.)

@@ -66,8 +66,8 @@ __device__ __forceinline__ float gelu_f32(float v, int mode) {
   return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
 }
 
-// Small chores that a layer call would otherwise launch kernels of their own for; the single
-// workgroup of the dispatch scan does them on the side: pair[0..1] = {0, pair_hi} (the segment
+// Small chores that a layer call would otherwise launch kernels of their own for; the input encode
+// (one workgroup of its launch, or the gate workgroup that encodes) does them on the side: pair[0..1] = {0, pair_hi} (the segment
 // bounds of the shared expert) and nzero zeros at each of zero_a, zero_b.  All optional.
 struct ScanChores {
   int32_t* pair = nullptr;

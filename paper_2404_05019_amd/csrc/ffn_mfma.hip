@@ -740,8 +740,8 @@ using CfgV = TileCfg<256, 128, 64, 4, 2, 3>;   // 8 waves of 64 x 64, 160 KiB LD
 using CfgS = TileCfg<64, 128, 64, 1, 2, 3>;    // 2 waves of 64 x 64, 76 KiB LDS, two workgroups per CU: second GEMMs of up to 64 rows per segment
 using CfgU = TileCfg<128, 128, 64, 2, 2, 2>;   // 4 waves of 64 x 64, 72 KiB LDS, two workgroups per CU: few rows per expert, small problems
 
-// Tile configuration in use: 0 unless scmoe_set_gemm_variant has set another.  The one piece of
-// process-wide state of the library: an atomic, read once per launch.
+// Tile configuration in use: 0 unless scmoe_set_gemm_variant has set another.  The one
+// process-wide setting of the library: an atomic, read once per launch.
 static std::atomic<int> g_variant{0};
 constexpr int NUM_VARIANTS = 4;
 

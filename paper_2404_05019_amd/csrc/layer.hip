@@ -423,9 +423,10 @@ extern "C" int scmoe_layer_forward(const scmoe_desc* D, const void* x_prev, int6
     if (e != hipSuccess) return hip_fail(e);
   }
   // One stream: the shared expert's first GEMM joins the routed experts' (one launch over E + 1
-  // segments, or one launch of two jobs of the direct kernel), and on the tiled path the
-  // dispatch scan also writes the shared expert's segment bounds and clears the split-K counters
-  // of both chains.  Two streams: the shared expert runs on its own, ahead of the routing.
+  // segments, or one launch of two jobs of the direct kernel), or it goes ahead of theirs with gate, encode and
+  // coefficient gate on the side (GateWork).  On the tiled path the encode, wherever it runs, also writes the shared
+  // expert's segment bounds and clears the split-K counters of both chains.
+  // Two streams: the shared expert runs on its own, ahead of the routing.
   const int rows = static_cast<int>(packed_rows(D->T, D->E, D->k, D->capacity));
   const int64_t all_rows = static_cast<int64_t>(D->T) + rows, mean_rows = (all_rows + 1) / 2;
   const bool tiled_s = ffn_is_tiled(D->dtype, D->d, D->F, D->T, 1, mean_rows, all_rows);
