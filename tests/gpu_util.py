@@ -62,8 +62,9 @@ def stratified_tokens(rr, T, E, seed, block=128):
     `block` consecutive packed rows of every expert segment (the routed experts' row tiles,
     counted from the segment start as the kernels do), plus the first and the last packed row
     of every segment (the ragged last tile) and some dropped tokens.  A compared row spans all
-    column tiles, so the tiles of the split-K tail are among them whichever they are; 128 is
-    the smallest row tile any kernel variant uses."""
+    column tiles, so the tiles of the split-K tail are among them whichever they are.  128 is
+    the smallest row tile of the calls whose rows are sampled so; calls of the second GEMM's 64-row
+    tiles have every element compared instead."""
     rng = np.random.default_rng(seed)
     toks = [0, T - 1]
     for b0 in range(0, T, block):

@@ -547,6 +547,27 @@ def test_non_finite_values_stay_in_their_rows(dtype, d, F):
     assert np.array_equal(out[0][keep], out[1][keep])
 
 
+@pytest.mark.parametrize("E,lens,d,F", [SHORT_FFN[0], WIDE_FFN[0][:4]])
+def test_non_finite_values_stay_in_their_rows_of_short_and_wide_tiles(E, lens, d, F):
+    """The same with the second GEMM's 64 x 128 and 256 x 128 tiles, in the middle, the last and the first row of a segment."""
+    rng = np.random.default_rng(6)
+    rows, off = int(sum(lens)), np.concatenate([[0], np.cumsum(lens)])
+    bad = [(int(off[0]) + 40, float("nan")), (int(off[1]) - 1, float("inf")), (int(off[-2]), float("inf"))]
+    gx = to_dev(inputs.quantize(rng.standard_normal((rows, d)), "bf16"), "bf16")
+    W1, W2 = (to_dev(inputs.quantize(0.05 * rng.standard_normal(s), "bf16"), "bf16") for s in ((E, F, d), (E, d, F)))
+    out = []
+    for values in ([], bad):
+        for row, v in values:
+            gx[row, 5] = v
+        hidden, y = torch.zeros((rows, F), dtype=gx.dtype, device=DEV), torch.zeros((rows, d), dtype=gx.dtype, device=DEV)
+        B.scmoe_expert_ffn(gx, torch.tensor(off, dtype=torch.int32, device=DEV), rows, W1, None, W2, None, hidden, y)
+        torch.cuda.synchronize()
+        out.append(to_host(y))
+    keep = ~np.isin(np.arange(rows), [row for row, _ in bad])
+    assert np.isnan(out[1][bad[0][0]]).all() and not any(np.isfinite(out[1][row]).any() for row, _ in bad)
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0][keep], out[1][keep])
+
+
 @pytest.mark.parametrize("T,E,k,C_,shared,cg,res", [
     (8, 4, 1, 8, True, 0, False), (20, 8, 1, 3, True, 0, False), (1, 2, 1, 1, True, 0, False),
     (16, 4, 2, 32, False, 0, False), (10, 8, 3, 30, False, 0, False), (32, 16, 1, 32, True, 1, True),
@@ -869,7 +890,59 @@ def test_layer_gate_on_the_side(oracle, T, d, F, E, k, C_, cg, res):
     assert_close(y, ref, "bf16")
 
 
-@pytest.mark.parametrize("T,d,F,E,k,C_", [(500, 256, 4096, 4, 1, 100), (2100, 384, 4096, 4, 1, 100000)])
+# ... and with about as many choices as one workgroup encodes, 128 x 128 and 256 x 256 tiles
+LONG_SIDE_LAYERS = [(4095, 2048, 832, 8, 2, 768, 0, False), (16383, 1536, 320, 16, 2, 1535, 0, False)]
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg,res", LONG_SIDE_LAYERS)
+def test_layer_gate_on_the_side_long_encode(oracle, T, d, F, E, k, C_, cg, res):
+    """Routing of every token, and a row of every row tile."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T, w_scale=0.03)
+    y, r = run_layer(DevLayer(L, "bf16"), k, C_, True)
+    rr = oracle.route(L["x_prev"], L, E, k, C_, 0)
+    assert_routing_equal(r, rr)
+    assert (r["dst_row"] < 0).any()
+    tokens = stratified_tokens(rr, T, E, seed=4)
+    assert_close(y[tokens], oracle.layer_rows(L["x_prev"], L["x_cur"], L, rr, tokens, k=k, shared=1), "bf16")
+
+
+@pytest.mark.parametrize("T,d,F,E,k,C_,cg", [(448, 256, 4096, 5, 2, 120, 2), (2177, 384, 4096, 4, 2, 540, 1)])
+def test_layer_gate_on_the_side_strided_rows(T, d, F, E, k, C_, cg):
+    """Activations whose rows lie further apart than d, with 3e38 in between: the bits of the dense ones."""
+    L = inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + 1, biases=True, cg_rows=cg, w_scale=0.03)
+    D = DevLayer(L, "bf16")
+    dense, r = run_layer(D, k, C_, True, 1, cg)
+    D.x_prev, D.x_cur = to_dev(L["x_prev"], "bf16", d + 8), to_dev(L["x_cur"], "bf16", d + 72)
+    y, rs = run_layer(D, k, C_, True, 1, cg)
+    assert all(np.array_equal(r[n], rs[n]) for n in r) and np.isfinite(y).all()
+    assert np.array_equal(y, dense)
+
+
+@pytest.mark.parametrize("T,d,F,E,C_", [(449, 320, 4096, 5, 100), (2100, 384, 4096, 4, 100000)])
+def test_layer_gate_on_the_side_keeps_non_finite_values_in_their_rows(T, d, F, E, C_):
+    """A NaN in a routed row (an all-NaN row of logits: expert 0) and infinities in a routed and in a shared row, without a
+    change of the routing: no other row changes a bit."""
+    D = DevLayer(inputs.make_layer(T=T, d=d, F=F, E=E, dtype="bf16", seed=T + 2, biases=True, w_scale=0.03), "bf16")
+    clean, r = run_layer(D, 1, C_, True)
+    kept = r["dst_row"][:, 0] >= 0
+    # (an infinity times a column of W_g: the first expert with a weight of its sign there has the first infinite logit)
+    to = int(np.argmax(D.Wg[5].cpu().numpy() > 0))
+    nan_routed = int(np.nonzero(kept & (r["idx"][:, 0] == 0))[0][3])
+    inf_routed = int(np.nonzero(kept & (r["idx"][:, 0] == to))[0][4])
+    inf_shared = int(np.nonzero(kept)[0][-2])
+    bad = [nan_routed, inf_routed, inf_shared]
+    D.x_prev[nan_routed, 7] = float("nan")
+    D.x_prev[inf_routed, 5] = float("inf")
+    D.x_cur[inf_shared, 0] = float("inf")
+    y, rs = run_layer(D, 1, C_, True)
+    assert all(np.array_equal(r[n], rs[n]) for n in ("idx", "counts", "offsets", "dst_row", "src_token"))
+    assert np.isnan(y[nan_routed]).all() and not any(np.isfinite(y[t]).any() for t in bad)
+    keep = ~np.isin(np.arange(T), bad)
+    assert np.isfinite(clean).all() and np.array_equal(clean[keep], y[keep])
+
+
+# (the first of these has its gate in a launch of its own: its routed experts' tiles fit the shared one's round)
+@pytest.mark.parametrize("T,d,F,E,k,C_", [(500, 256, 4096, 4, 1, 100), (449, 320, 4096, 5, 1, 100), (2100, 384, 4096, 4, 1, 100000)])
 def test_layer_gate_on_the_side_again_and_in_a_graph(T, d, F, E, k, C_):
     """Calls of different routing on one workspace that held garbage, then replays of a captured call on changing inputs
     with eager calls on the same workspace in between: the bits of a call on a workspace of its own."""

@@ -307,8 +307,8 @@ def test_dropped_rows_under_a_coefficient_gate_are_not_left_to_the_combine_kerne
 def test_gate_on_the_side_of_the_shared_expert_s_first_gemm(record):
     """No launch of gate, encode and coefficient gate where the first of three products' launches does them, which is where the
     shared expert's tiles apart from the routed ones take no round more (the GPU tests rely on the first ones)."""
-    from test_gpu_parity import SIDE_LAYERS
-    side = [dict(_layer(T, d, F, E, k), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res in SIDE_LAYERS]
+    from test_gpu_parity import LONG_SIDE_LAYERS, SIDE_LAYERS
+    side = [dict(_layer(T, d, F, E, k), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res in SIDE_LAYERS + LONG_SIDE_LAYERS]
     side += [_layer(500, 2048, 8192, 16), dict(_layer(8192, 384, 1536), capacity=1280), _layer(6000, 512, 2048)]
     apart = [_layer(500, 2048, 8192, 16, two=True), _layer(500, 2048, 8192, 24), _layer(16384, 1024, 4096), _layer(1500, 1536, 4096),
              _layer(3001, 768, 3072, 12, 2), _layer(8000, 192, 768), _layer(8, 2048, 8192, 16), _layer(20000, 512, 2048, k=2)]

@@ -34,13 +34,15 @@ def _offsets(rng, E, most):
 def test_every_tile_once(walk, cat):
     rng = random.Random(5)
     calls = []
-    for bm, nt, split, slots in itertools.product([128, 256], [1, 2, 3, 8], [0, 1], [1, 5, 32, 64]):
+    for bm, nt, split, slots in itertools.product([128, 256] if cat else [64, 128, 256], [1, 2, 3, 8], [0, 1], [1, 5, 32, 64]):
         for _ in range(6):
             off = _offsets(rng, rng.choice([1, 2, 8, 17, 64]) + cat, rng.choice([40, 600, 3000]))
             if off[-1] == 0:
                 off[-1] = 1
             xrows = 0 if cat else rng.choice([0, 1, 700, 4096])
-            calls.append([cat, bm, nt, 2 * rng.randrange(8, 70), split, 4 if bm == 128 else 8, slots, xrows, off])
+            calls.append([cat, bm, nt, 2 * rng.randrange(8, 70), split, {64: 2, 128: 4, 256: 8}[bm], slots, xrows, off])
+        if not cat:                                  # the extra segment alone: the launch that has the gate on the side
+            calls.append([0, bm, nt, 2 * rng.randrange(2, 70), 0, bm // 32, slots, rng.choice([1, bm, bm + 1, 3001]), [0]])
     for call, line in zip(calls, walk(calls)):
         assert line.replace(" ", "").isdigit(), (call, line)
         # the XCDs' shares differ by a tile of each of the two ranges at most, and the last round is one tile long

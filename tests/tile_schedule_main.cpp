@@ -1,5 +1,5 @@
 // Walks the grouped GEMM's tile schedule as its workgroups do and checks that every tile is done
-// exactly once: input lines "CAT BM nt nk split fs slots xrows E offsets[0..E]" (CAT: joint second GEMM, whose
+// exactly once: input lines "CAT BM nt nk split fs slots xrows E offsets[0..E]" (E = 0: no segment but the extra one; CAT: joint second GEMM, whose
 // offsets hold the tokens without a routed row as the last of the E segments); for each a line "LONGEST
 // TOTAL", the k-tiles of the workgroup with the most and of all, or what is wrong.
 #include <stdio.h>
@@ -70,7 +70,8 @@ int main() {
     std::vector<int32_t> off(E + 1);
     for (auto& o : off)
       if (scanf("%d", &o) != 1) return 1;
-    auto f = cat ? (bm == 256 ? walk<256, true> : walk<128, true>) : (bm == 256 ? walk<256, false> : walk<128, false>);
+    auto f = cat ? (bm == 256 ? walk<256, true> : walk<128, true>) : bm == 256 ? walk<256, false> : bm == 128 ? walk<128, false> : walk<64, false>;
+    if (bm != 256 && bm != 128 && (cat || bm != 64)) return 1;
     f(nt, nk, split != 0, fs, slots, xrows, E, off);
   }
   return 0;
