@@ -1133,8 +1133,7 @@ static int launch_first_with_gate(GemmArgs a, GateWork w, hipStream_t stream) {
     if (dev >= 0) attr_set[dev].store(true, std::memory_order_release);
   }
   a.nt = (a.N + CFG::BN - 1) / CFG::BN;
-  a.stream_out = static_cast<int64_t>(a.xrows) * a.N * 2 >= (int64_t(256) << 20);
-  const int64_t tiles = (a.xrows + CFG::BM - 1) / CFG::BM * static_cast<int64_t>(a.nt);
+  const int64_t tiles = (a.xrows + CFG::BM - 1) / CFG::BM * static_cast<int64_t>(a.nt);     // (no more than CUs: too little to be stored with the streaming hint)
   const int resident = num_cus() * CFG::WG_PER_CU;
   w.workgroups = (w.T + 16 * CFG::WAVES - 1) / (16 * CFG::WAVES);
   w.coef_workgroups = 0;

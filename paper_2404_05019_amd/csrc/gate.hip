@@ -441,13 +441,6 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
 #define SCMOE_GATE_MFMA(NW, EG)                                                                                    \
   return bf ? launch_gate_mfma<true, NW, EG>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)      \
             : launch_gate_mfma<false, NW, EG>(x, ldx, Wg, bias, T, d, E, k, normalize, idx, gw, probs, stream)
-#define SCMOE_GATE_MFMA_NW(EG)                                                                                     \
-  switch (nw) {                                                                                                    \
-    case 8: SCMOE_GATE_MFMA(8, EG);                                                                                \
-    case 4: SCMOE_GATE_MFMA(4, EG);                                                                                \
-    case 2: SCMOE_GATE_MFMA(2, EG);                                                                                \
-    default: SCMOE_GATE_MFMA(1, EG);                                                                               \
-  }
     // More than 16 experts and no more than a wave per SIMD: a wave for every 16 tokens and 16 experts, whose chain is not
     // longer than with 16 experts (call us, two or four groups per wave / so: four operator calls, 4096 tokens, top-2, d =
     // 1024, F = 2048, E = 32 172.8 / 168.5, E = 64 236.6 / 225.4; top-1, 500 tokens, E = 64 145.4 / 135.8; top-2, 2000, d = 256, E = 64
@@ -461,10 +454,20 @@ int gate_topk(const void* x, int64_t ldx, int dtype, const float* Wg, const floa
       SCMOE_GATE_MFMA_GW(4);
 #undef SCMOE_GATE_MFMA_GW
     }
-    if (E <= 16) { SCMOE_GATE_MFMA_NW(1) }
-    else if (E <= 32) { SCMOE_GATE_MFMA_NW(2) }
-    else { SCMOE_GATE_MFMA_NW(4) }
-#undef SCMOE_GATE_MFMA_NW
+    // (left of 17 to 32 experts are more than two waves a CU, of more experts more than one)
+    if (E <= 16) {
+      if (nw == 8) SCMOE_GATE_MFMA(8, 1);
+      if (nw == 4) SCMOE_GATE_MFMA(4, 1);
+      if (nw == 2) SCMOE_GATE_MFMA(2, 1);
+      SCMOE_GATE_MFMA(1, 1);
+    }
+    if (E <= 32) {
+      if (nw == 8) SCMOE_GATE_MFMA(8, 2);
+      SCMOE_GATE_MFMA(4, 2);
+    }
+    if (nw == 8) SCMOE_GATE_MFMA(8, 4);
+    if (nw == 4) SCMOE_GATE_MFMA(4, 4);
+    SCMOE_GATE_MFMA(2, 4);
 #undef SCMOE_GATE_MFMA
   }
   if (static_cast<int64_t>(T) * epad <= GATE_SMALL_LANES) {

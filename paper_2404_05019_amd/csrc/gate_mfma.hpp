@@ -153,8 +153,7 @@ struct GateMfmaCfg {
   static constexpr int SS = SF / 4;                   // steps (of four features) per stage
   static constexpr int KC = 256 / G;                  // features per W_g tile: at most 16 KiB
   static constexpr int IPT = KC / SF;                 // stages per W_g tile
-  static constexpr int WB0 = G == 1 ? 2 : G == 2 ? 3 : 4;
-  static constexpr int WB = ROOM - WB0 * GM_WBUF >= 3 * NW * GM_STAGE ? WB0 : WB0 - 1;   // W_g buffers: tile j + WB - 1 is requested when tile j begins
+  static constexpr int WB = G == 1 ? 2 : G == 2 ? 3 : 4;               // W_g buffers: tile j + WB - 1 is requested when tile j begins
   static constexpr int XS0 = NW == 16 ? 3 : EG == 1 ? (NW == 8 ? 7 : 8) : EG == 2 ? 6 : 5, XS1 = (ROOM - WB * GM_WBUF) / (NW * GM_STAGE);
   static constexpr int XS = XS0 < XS1 ? XS0 : XS1;                     // x ring stages per wave
   static constexpr int P = EG == 1 ? SS / 2 : EG == 2 ? 4 : 2;         // steps the operand reads run ahead of their use
@@ -235,10 +234,18 @@ __device__ __forceinline__ void dispatch_own(const int32_t* expert_idx, int T, i
 // The input encode of a whole call by one workgroup: the items in order, an equal share of consecutive 64-item vectors
 // to every wave, counted and ranked inside their vectors on one walk, placed on a second one, with the results of
 // dispatch_onepass.  The choices come from other workgroups of this launch and are read at device scope.
-// E <= 2^NB.  lds: (NW + 1) * 64 ints, then two bytes an item, in whole vectors.
-template <int NW, int NB>
-__device__ __forceinline__ void dispatch_all_n(const int32_t* expert_idx, int T, int k, int E, const DispatchOut& o, int* lds) {
-  constexpr int ROUND = 8;                                // vectors whose loads are in flight together
+// Up to 16 experts.  lds: (NW + 1) * 64 ints, then two bytes an item, in whole vectors.
+template <int NW>
+__device__ __forceinline__ void dispatch_all(const int32_t* expert_idx, int T, int k, int E, const DispatchOut& o, int* lds) {
+  constexpr int ROUND = 8, NB = 4;                        // vectors whose loads are in flight together; bits of an expert index
+  for (int z = threadIdx.x; z < o.ch.nzero; z += 64 * NW) {
+    if (o.ch.zero_a != nullptr) o.ch.zero_a[z] = 0;
+    if (o.ch.zero_b != nullptr) o.ch.zero_b[z] = 0;
+  }
+  if (o.ch.pair != nullptr && threadIdx.x == 0) {
+    o.ch.pair[0] = 0;
+    o.ch.pair[1] = o.ch.pair_hi;
+  }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = T * k, nvec = (n + 63) >> 6, per = (nvec + NW - 1) / NW;
   const int va = wave * per, vz = va + per < nvec ? va + per : nvec;
@@ -321,19 +328,6 @@ __device__ __forceinline__ void dispatch_all_n(const int32_t* expert_idx, int T,
       o.dst_row[t * k + j] = out;
     }
   }
-}
-
-template <int NW>   // (up to 16 experts)
-__device__ __forceinline__ void dispatch_all(const int32_t* expert_idx, int T, int k, int E, const DispatchOut& o, int* lds) {
-  for (int z = threadIdx.x; z < o.ch.nzero; z += 64 * NW) {
-    if (o.ch.zero_a != nullptr) o.ch.zero_a[z] = 0;
-    if (o.ch.zero_b != nullptr) o.ch.zero_b[z] = 0;
-  }
-  if (o.ch.pair != nullptr && threadIdx.x == 0) {
-    o.ch.pair[0] = 0;
-    o.ch.pair[1] = o.ch.pair_hi;
-  }
-  dispatch_all_n<NW, 4>(expert_idx, T, k, E, o, lds);
 }
 
 // Marks workgroup `mine` of `all` as done and says whether all are (called by one whole wave; its earlier stores have been
