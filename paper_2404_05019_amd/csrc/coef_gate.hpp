@@ -29,20 +29,20 @@ __device__ __forceinline__ void load8(const unsigned char* p, float* v) {
 // the bytes of the token's row in cache traffic); otherwise they are read in place (rows too
 // long for the LDS).
 // Workgroup `block` of `blocks` that share the tokens.  cg_w: 4 d bytes of LDS, 8 d with mode SCMOE_CG_2.
-template <bool BF16, bool LDS_W>
+// WAVES: of the workgroup (asked for at run time, its size is a dependent load from memory ahead of the first weights).
+template <bool BF16, bool LDS_W, int WAVES>
 __device__ __forceinline__ void coef_gate_rows(float* cg_w, int block, int blocks, const unsigned char* __restrict__ x,
                                                int64_t ldx_bytes, const float* __restrict__ Wcg, int mode, int T, int d,
                                                float* __restrict__ coef) {
   constexpr int NV = BF16 ? 8 : 4;
   if (LDS_W) {
     const int n = (mode == SCMOE_CG_2 ? 2 : 1) * d;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) cg_w[i] = Wcg[i];
+    for (int i = threadIdx.x; i < n; i += 64 * WAVES) cg_w[i] = Wcg[i];
     __syncthreads();
   }
   auto w = [&](int i) { return LDS_W ? cg_w[i] : Wcg[i]; };
   const int lane = threadIdx.x & 63;
-  const int waves = blockDim.x >> 6;
-  for (int t = block * waves + (threadIdx.x >> 6); t < T; t += blocks * waves) {
+  for (int t = block * WAVES + (threadIdx.x >> 6); t < T; t += blocks * WAVES) {
     const unsigned char* row = x + static_cast<int64_t>(t) * ldx_bytes;
     float a = 0.0f, b = 0.0f;
     for (int i0 = lane * NV; i0 < d; i0 += 64 * NV) {

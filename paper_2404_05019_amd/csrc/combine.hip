@@ -121,12 +121,13 @@ int combine(const void* y_perm, int64_t ldyp, int dtype, const int32_t* dst_row,
 }
 
 // The coefficient gate (coef_gate.hpp).  LDS_W: its weight rows fit the LDS.
+constexpr int COEF_WAVES = 4;
 template <bool BF16, bool LDS_W>
-__global__ __launch_bounds__(256) void coef_gate_kernel(const unsigned char* __restrict__ x, int64_t ldx_bytes,
-                                                        const float* __restrict__ Wcg, int mode, int T,
-                                                        int d, float* __restrict__ coef) {
+__global__ __launch_bounds__(64 * COEF_WAVES) void coef_gate_kernel(const unsigned char* __restrict__ x, int64_t ldx_bytes,
+                                                                     const float* __restrict__ Wcg, int mode, int T,
+                                                                     int d, float* __restrict__ coef) {
   extern __shared__ __attribute__((aligned(16))) float cg_w[];
-  coef_gate_rows<BF16, LDS_W>(cg_w, blockIdx.x, gridDim.x, x, ldx_bytes, Wcg, mode, T, d, coef);
+  coef_gate_rows<BF16, LDS_W, COEF_WAVES>(cg_w, blockIdx.x, gridDim.x, x, ldx_bytes, Wcg, mode, T, d, coef);
 }
 
 int coef_gate(const void* x, int64_t ldx, int dtype, const float* Wcg, int mode, int T, int d,
@@ -139,17 +140,17 @@ int coef_gate(const void* x, int64_t ldx, int dtype, const float* Wcg, int mode,
   if (!view_ok(x, ldx, d, dtype)) return SCMOE_ERR_SHAPE;
   const unsigned char* xb = static_cast<const unsigned char*>(x);
   const size_t lds = static_cast<size_t>(mode == SCMOE_CG_2 ? 2 : 1) * d * sizeof(float);
-  const int wgs = (T + 3) / 4;
+  const int wgs = (T + COEF_WAVES - 1) / COEF_WAVES;
   if (lds <= 48 * 1024) {
     // weight rows in LDS: a few workgroups per CU, each over many tokens
     const int cap = 8 * num_cus();
-    dim3 grid(wgs < cap ? wgs : cap), block(256);
+    dim3 grid(wgs < cap ? wgs : cap), block(64 * COEF_WAVES);
     if (dtype == SCMOE_BF16)
       hipLaunchKernelGGL((coef_gate_kernel<true, true>), grid, block, lds, stream, xb, ldx * 2, Wcg, mode, T, d, coef);
     else
       hipLaunchKernelGGL((coef_gate_kernel<false, true>), grid, block, lds, stream, xb, ldx * 4, Wcg, mode, T, d, coef);
   } else {
-    dim3 grid(wgs), block(256);
+    dim3 grid(wgs), block(64 * COEF_WAVES);
     if (dtype == SCMOE_BF16)
       hipLaunchKernelGGL((coef_gate_kernel<true, false>), grid, block, 0, stream, xb, ldx * 2, Wcg, mode, T, d, coef);
     else

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::WG_PER_CU * CFG::WAVES / 4) void
                                                                      p.w.workgroups);
       __syncthreads();                       // (the LDS becomes the stages of the tiles)
     } else if (g - p.w.workgroups < p.w.coef_workgroups) {
-      coef_gate_rows<true, true>(reinterpret_cast<float*>(smem), g - p.w.workgroups, p.w.coef_workgroups, static_cast<const unsigned char*>(p.w.xc), p.w.ldxc * 2,
+      coef_gate_rows<true, true, CFG::WAVES>(reinterpret_cast<float*>(smem), g - p.w.workgroups, p.w.coef_workgroups, static_cast<const unsigned char*>(p.w.xc), p.w.ldxc * 2,
                                  p.w.Wcg, p.w.cg_mode, p.w.T, p.w.d, p.w.coef);
       __syncthreads();
     }
