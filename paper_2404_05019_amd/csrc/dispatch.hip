@@ -151,6 +151,9 @@ __global__ __launch_bounds__(DISP_BLOCK) void dispatch_rank(
 //    added up once at the end (wave e sums expert e).
 //  * E > 16: one ballot per bit of the expert index per vector; lane L keeps the count of expert L (the bits unrolled: four
 //    operator calls, 4096 tokens, top-2, E = 32 176.2 -> 172.8 us, E = 64 241.4 -> 236.6).
+// Every thread's own item is ranked by one ballot per bit in either form: three up to 8 experts and one for two, where the
+// four of up to 16 cost 1 to 5 % of the call (us, replayed back to back, four / three ballots: top-2, 543 tokens, E = 8 6.29 / 6.19;
+// top-3, 876 6.69 / 6.57; three / one: 956 tokens, E = 2 5.28 / 5.07; top-2, 2146 6.29 / 5.90).
 // Integer counts only, so the permutation is the same bit for bit as the three kernels'.  No
 // scratch memory, no atomics, no waiting.
 constexpr int DISP1_THREADS = 1024;
@@ -461,7 +464,8 @@ int dispatch(const void* x, int64_t ldx, int dtype, const int32_t* expert_idx, i
     const int blocks = items > 0 ? static_cast<int>((items + DISP1_THREADS - 1) / DISP1_THREADS) : 1;
     const ScanChores sc = chores ? *chores : ScanChores{};
 #define SCMOE_ONEPASS(NIB, K, JOINT)                                                                                       \
-  if (NIB && E <= 8) SCMOE_ONEPASS_NB(true, K, JOINT, 3);                                                                  \
+  if (NIB && E <= 2) SCMOE_ONEPASS_NB(true, K, JOINT, 1);                                                                  \
+  else if (NIB && E <= 8) SCMOE_ONEPASS_NB(true, K, JOINT, 3);                                                             \
   else if (NIB) SCMOE_ONEPASS_NB(true, K, JOINT, 4);                                                                       \
   else if (E <= 32) SCMOE_ONEPASS_NB(false, K, JOINT, 5);                                                                  \
   else SCMOE_ONEPASS_NB(false, K, JOINT, 6)
