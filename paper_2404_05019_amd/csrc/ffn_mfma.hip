@@ -841,11 +841,15 @@ static int launch_gemm(const GemmArgs& a, int max_rows, int64_t a_rows, hipStrea
 // than 7/8 of one.
 static int64_t row_tiles(int64_t rows, int64_t E, int edge) { return 8 * rows <= 7 * edge * E ? E : rows / edge + E / 2; }
 
-// ... and from above for a balanced load: with its mean half a standard deviation higher.
-static int64_t most_row_tiles(int64_t rows, int64_t E, int edge) {
-  if (E == 1) return (rows + edge - 1) / edge;
+// ... of a balanced load: with its mean half a standard deviation higher in every segment.
+static int64_t balanced_row_tiles(int64_t rows, int64_t E, int edge) {
   const double mean = static_cast<double>(rows) / E;
-  return std::max(row_tiles(rows, E, edge), E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge)));
+  return E * static_cast<int64_t>(ceil((mean + 0.5 * sqrt(mean)) / edge));
+}
+
+// ... and from above, where the load is balanced or is not.
+static int64_t most_row_tiles(int64_t rows, int64_t E, int edge) {
+  return E == 1 ? (rows + edge - 1) / edge : std::max(row_tiles(rows, E, edge), balanced_row_tiles(rows, E, edge));
 }
 
 // Whether a launch takes the 256 x 256 tiles (variant 0): a first GEMM or not, no other chain beside it, rows in E segments
@@ -1166,12 +1170,14 @@ static int launch_first_with_gate(GemmArgs a, GateWork w, hipStream_t stream) {
 //  * a partly filled round of tiles more, so only where both launches together have no more rounds (tiles per CU, rounded up)
 //    than the joint one.  The routed launch is counted from above: a balanced load with the mean half a standard deviation
 //    higher, and at 256 rows a tile a skewed one, with a last tile of their own for three quarters of the experts; the joint
-//    one from below, where a capacity may drop a quarter of the rows, unless a coefficient gate's launch is saved as well, which
-//    is worth as much as the round (1500, d = 1536, F = 4096, E = 8 130 / 142; 3001, top-2, d = 768,
+//    one from below at 256 rows a tile: balanced (the round cost 12 of 14 such layers 2 to 12 %: 1828, d = 960, F = 3840, E = 8 90 / 94;
+//    top-2, 6950, d = 768, F = 1536 with a coefficient gate 140 / 150; top-4, 2003, d = 512, F = 1344, E = 8 70 / 78), and with a
+//    quarter of the rows dropped where a capacity may, unless a coefficient gate's launch is saved as well, which is worth as much
+//    as the round (1500, d = 1536, F = 4096, E = 8 130 / 142; 3001, top-2, d = 768,
 //    F = 3072, E = 12 144 / 153; skewed 2733, d = 1920, F = 3840, E = 16 270 / 305; skewed with drops 8205, d = 384, F = 1024, E = 4
 //    58 / 63; but taken: 500, d = 2048, F = 8192, E = 16 307 / 279; 600, d = 1024, F = 4096, E = 16 106 / 96; 8192, d = 384, F = 1536, E = 8
 //    81 / 77; 6000, d = 512, F = 2048 91 / 84; with a coefficient gate top-2, 456, d = 768, F = 2048, E = 16 61 / 52).
-// Of 1800 drawn layers that fit, about 1130 are taken; ten of those are slower than apart by more than 1.5 %, skewed loads whose
+// Of 1800 drawn layers that fit, about 1100 are taken; ten of those are slower than apart by more than 1.5 %, skewed loads whose
 // rounds the host cannot count (top-3, 825 tokens, d = 1536, F = 4096, E = 16 184 / 206; 1980, d = 1856, F = 7424, E = 2 236 / 267).
 // Not at widths whose tiles are done before the encode is (16000, d = 128 59 / 66; 8000, d = 192, E = 8 and 16 52 / 52 and 56 / 56),
 // with 256-row tiles not below d = 384, and only up to 16 experts, for which alone the launch is built.
@@ -1187,6 +1193,7 @@ bool ffn_gate_on_the_side(const GateWork& g, int rows, int F, int64_t ldw1) {
   int64_t least = row_tiles(rows, g.E, edge), most = most_row_tiles(rows, g.E, edge);
   if (edge == 256) {
     most = std::max(most, static_cast<int64_t>(rows / 256 + 3 * g.E / 4));
+    least = std::min(least, balanced_row_tiles(rows, g.E, edge));
     if (g.enc.capacity < g.T && g.cg_mode == SCMOE_CG_NONE) least = std::min(least, static_cast<int64_t>(rows * int64_t(3) / 1024 + g.E / 2));
   }
   return (shared + cus - 1) / cus + (most * nt + cus - 1) / cus <= (shared + least * nt + cus - 1) / cus;

@@ -328,7 +328,7 @@ def test_gate_on_the_side_not_where_it_ends_later_or_a_round_is_lost(record):
     side = [lay(512, 256, 4096, 5, 2, 120), lay(8192, 384, 1536, 8, 1, 1280), lay(7883, 512, 1344, 8, 1, 1232), lay(4018, 576, 2304, 8), lay(3418, 512, 1344, 16, 2, 535, 2)]
     apart = [lay(513, 256, 4096, 5, 2, 120), lay(5161, 256, 704, 8, 2), lay(3305, 256, 704, 8, 4, 2066, 1), lay(2304, 384, 768, 4, 4, 2880),
              lay(7809, 384, 1024, 8, 4, 3905, 1), lay(2733, 1920, 3840, 16), lay(8205, 384, 1024, 4, 1, 2565), lay(1500, 1536, 4096, 8),
-             lay(3418, 512, 1344, 16, 2, 535)]
+             lay(3418, 512, 1344, 16, 2, 535), lay(1828, 960, 3840, 8), lay(6950, 768, 1536, 8, 2, 2172, 1), lay(2622, 1984, 3968, 16, 3)]
     for want, calls in ((True, side), (False, apart)):
         for c, (st, lines) in zip(calls, record(calls)):
             kernels, _ = _order(lines)
