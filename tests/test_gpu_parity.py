@@ -205,6 +205,8 @@ def _run_dispatch(x, idx, E, k, C_, dtype, copy=True):
     (1000, 6, 4, 500, 8, "f32"), (257, 3, 3, 300, 8, "f32"),
     # block boundaries of the one-launch form (blocks of 1024 items): one block, one item past it, two full blocks
     (1024, 8, 1, 100, 8, "f32"), (1025, 5, 1, 300, 8, "f32"), (1024, 16, 2, 90, 8, "bf16"), (683, 9, 3, 200, 8, "f32"),
+    # one, three and four ballots a vector: two, eight and nine experts
+    (1025, 2, 1, 500, 8, "bf16"), (700, 2, 2, 600, 8, "f32"), (1300, 8, 4, 100000, 8, "f32"), (1300, 9, 4, 500, 8, "f32"),
     # fewer tokens than a wave has lanes with several choices (an item vector spans choices), 64 experts, 33 experts
     (5, 4, 4, 3, 8, "f32"), (40, 6, 3, 100, 8, "bf16"), (4097, 64, 4, 200, 8, "f32"), (9000, 33, 1, 250, 8, "bf16"),
     # the one-launch form's limit of 131072 items: at it, just past it (three kernels with scratch), far past it
@@ -761,6 +763,7 @@ def test_layer_gate_and_encode_of_few_tokens(oracle, T, d, E, k, C_, dtype):
     (5200, 2048, 1152, 12, 1, False),       # hardly a routed row
     (4099, 2048, 1152, 16, 1, False),       # ... of more experts: two launches
     (16400, 1024, 256, 4, 3000, True),      # more full tiles than one round
+    (16400, 1024, 128, 2, 6560, False),     # two experts
     (3900, 2304, 2048, 14, 200, False)])    # (9 column tiles)
 def test_layer_joint_second_gemm(oracle, T, d, F, E, C_, res):
     """Top-1 ScMoE on one stream at sizes whose second GEMMs run as one product: routed rows, then the
