@@ -944,14 +944,16 @@ static int launch_variant(const GemmArgs& a, int max_rows, int64_t a_rows, hipSt
   //  * not with the second round of them partly empty: more than one, counted from above, up to 1.75 (1.06, 16384, d = 512, F = 2048,
   //    E = 8 127.0 / 132.1; 1.5, 10708, d = 768, F = 2048, E = 32 162 / 175; 1.64, skewed, 18538, d = 576, F = 1536, E = 12 200 / 221), or
   //    from 44 k-tiles on, which gain more, by the average up to 1.3 (1.25, 8192, d = 1024, F = 4096, E = 16 216.9 / 220.9; but
-  //    1.6, 7007, d = 1792, F = 4800, E = 12 619 / 596; 7522, top-1 without shared expert, d = 896, F = 3584, E = 4 271 / 253).
+  //    1.6, 7007, d = 1792, F = 4800, E = 12 619 / 596; 7522, top-1 without shared expert, d = 896, F = 3584, E = 4 271 / 253), unless
+  //    experts fit one of the smaller row tiles: half of the wide ones is padding then (1204, d = 1984, F = 3968, E = 16 196 / 213;
+  //    top-2, 1641, d = 1088, F = 4352, E = 32 250 / 271; of 48 such calls the 40 beyond one round lose 3 to 20 %, the eight within gain 3 to 9 %).
   // Of 600 drawn calls that the average alone takes 100 are slower by more than 1.5 %, up to 19 %; of the 300 left 17, up to 6 %.
   const int64_t v_extra = (a.xrows + CfgV::BM - 1) / CfgV::BM, v_nt = (a.N + CfgV::BN - 1) / CfgV::BN;
   const int64_t square = (max_rows / CfgU::BM + (a.xrows + CfgU::BM - 1) / CfgU::BM) * static_cast<int64_t>((a.N + CfgU::BN - 1) / CfgU::BN);
   const int64_t wide = (row_tiles(max_rows, a.E, CfgV::BM) + v_extra) * v_nt, v_most = (most_row_tiles(max_rows, a.E, CfgV::BM) + v_extra) * v_nt;
-  const bool v_long = a.Kd >= 44 * CfgV::BK;
+  const bool v_long = a.Kd >= 44 * CfgV::BK, v_full = 8 * static_cast<int64_t>(max_rows) > 7 * CfgU::BM * static_cast<int64_t>(a.E);
   if (!ACT && !few_rows && a.N > CfgV::BN && a.Kd >= 16 * CfgV::BK && 10 * square >= (v_long ? 10 : 11) * cus &&
-      (32 * wide + 4 * a.E * v_nt <= 33 * cus || 10 * wide >= 13 * cus) && (v_long || v_most <= cus || 4 * v_most > 7 * cus))
+      (32 * wide + 4 * a.E * v_nt <= 33 * cus || 10 * wide >= 13 * cus) && ((v_long && v_full) || v_most <= cus || 4 * v_most > 7 * cus))
     return launch_gemm<CfgV, ACT>(g, max_rows, a_rows, stream);
   // Otherwise two workgroups per CU, whose epilogues and waits fall on each other's arithmetic
   // (layer time, us, against two waves and 32-deep k-tiles: 700 tokens, d = 768: 97 -> 90; 1500

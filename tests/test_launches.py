@@ -258,10 +258,11 @@ def test_second_gemm_of_wide_tiles_and_second_gemms_in_one_launch(record):
     ffn = [dict(what="ffn", E=E, T=sum(lens) + extra, d=d, F=F, dtype=BF16) for E, lens, d, F, extra in WIDE_FFN]
     lay = [dict(_layer(T, d, F, E, k, two=two), capacity=C_, cg=cg, res=res) for T, d, F, E, k, C_, cg, res, two, shared in WIDE_LAYERS if shared]
     wide = [(c, 1) for c in ffn + lay[:2]] + [(lay[2], 2), (_layer(3001, 768, 3072, 12, 2), 1), (_layer(6000, 512, 2048), 1), (_layer(9000, 768, 3072), 2),
-                                              (_layer(6000, 1024, 4096), 2), (_layer(8192, 1024, 4096), 1)]
+                                              (_layer(6000, 1024, 4096), 2), (_layer(8192, 1024, 4096), 1), (_layer(1664, 1216, 4864, 16), 1), (_layer(654, 1984, 3968, 12, 2), 1)]
     other = [_layer(16384, 1024, 4096), _layer(32000, 128, 512), _layer(12000, 768, 2048), dict(what="ffn", E=16, T=8192, d=1024, F=4096, dtype=BF16),
              _layer(500, 2048, 8192, 16), _layer(18538, 576, 1536, 12), _layer(17279, 192, 768, 16), _layer(6780, 320, 640, 2), _layer(4999, 768, 2048, 8),
-             dict(what="ffn", E=32, T=10708, d=768, F=2048, dtype=BF16), dict(what="ffn", E=8, T=21385, d=320, F=1280, dtype=BF16)]
+             dict(what="ffn", E=32, T=10708, d=768, F=2048, dtype=BF16), dict(what="ffn", E=8, T=21385, d=320, F=1280, dtype=BF16),
+             _layer(1204, 1984, 3968, 16), _layer(1641, 1088, 4352, 32, 2)]
     for c, (st, lines) in zip([c for c, _ in wide], record([c for c, _ in wide])):
         kernels, _ = _order(lines)
         n = sum("TileCfgILi256ELi128E" in k[0] for k in kernels)
