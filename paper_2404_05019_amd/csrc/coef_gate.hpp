@@ -29,7 +29,8 @@ __device__ __forceinline__ void load8(const unsigned char* p, float* v) {
 // the bytes of the token's row in cache traffic); otherwise they are read in place (rows too
 // long for the LDS).
 // Workgroup `block` of `blocks` that share the tokens.  cg_w: 4 d bytes of LDS, 8 d with mode SCMOE_CG_2.
-// WAVES: of the workgroup (asked for at run time, its size is a dependent load from memory ahead of the first weights).
+// WAVES: of the workgroup (asked for at run time, its size is a dependent load from memory ahead of the first weights: 50 drawn
+// calls took 3 % longer, 7208 tokens, d = 120 4.72 us against 4.45).
 template <bool BF16, bool LDS_W, int WAVES>
 __device__ __forceinline__ void coef_gate_rows(float* cg_w, int block, int blocks, const unsigned char* __restrict__ x,
                                                int64_t ldx_bytes, const float* __restrict__ Wcg, int mode, int T, int d,
